@@ -206,44 +206,30 @@ __device__ __forceinline__ double wave_sum64(double v) {
 
 // targets in passes of TG, each pass unrolled (static accumulator indices);
 // the sources are read once per pass
-template <int LS, bool NODE, int RS, int TG>
+template <int LS, bool NODE, int TG>
 __global__ __launch_bounds__(64) void k_p2p_leaf32(NearArgs a, const float4* __restrict__ pf,
                                                    const float2* __restrict__ phh) {
+  const int RS = a.rec_stride;
   const int lane = threadIdx.x;
   const uint32_t item = blockIdx.x;
   if (item >= a.item_off[a.nleaves]) return;  // the grid is an upper bound
-  const int l = a.item_leaf[item];
-  const uint32_t kitem = a.item_k[item];
-  const int node = a.leaf_node[l];
-  const NodeInfo ti = a.info[node];
-  const int nt = ti.cnt;
+  const P2PItem it0 = a.item[item];
+  const int node = it0.node(), tlo = it0.lo, nt = it0.cnt();
   const double* rt = a.rec + (int64_t)node * RS;
   const double ct0 = rt[0], ct1 = rt[1], ct2 = rt[2];
   __shared__ float tg[LS][5];  // offset x, y, z, 1/h, h
   if (lane < nt) {
-    const float4 o = pf[ti.lo + lane];
-    const float2 hh = phh[ti.lo + lane];
+    const float4 o = pf[tlo + lane];
+    const float2 hh = phh[tlo + lane];
     tg[lane][0] = o.x; tg[lane][1] = o.y; tg[lane][2] = o.z;
     tg[lane][3] = hh.y; tg[lane][4] = hh.x;
   }
   __syncthreads();
-  uint64_t e0, e1;
-  const int32_t* list;
-  if (NODE) {
-    e0 = a.node_p2p_off[node];
-    e1 = e0 + a.node_p2p_cnt[node];
-    list = reinterpret_cast<const int32_t*>(a.node_p2p_pool);
-  } else {
-    e0 = a.p2p_off[l];
-    e1 = a.p2p_off[l + 1];
-    list = a.p2p_list;
-  }
-  // this item's run [f_lo, f_hi) of the leaf's flattened sources
-  const uint32_t f_lo = kitem * kP2PItem;
-  const uint32_t ftot = a.src_total[l];
-  const uint32_t f_hi = f_lo + kP2PItem < ftot ? f_lo + kP2PItem : ftot;
-  uint32_t carry0 = 0;  // from the list entry that holds the run's first source
-  if (kitem > 0) { e0 = a.item_e0[item]; carry0 = a.item_c0[item]; }
+  // this item's run [f_lo, f_hi) of the leaf's flattened sources, from the
+  // list entry that holds its first source
+  const uint64_t e0 = it0.e0, e1 = e0 + it0.ne;
+  const int32_t* list = NODE ? reinterpret_cast<const int32_t*>(a.node_p2p_pool) : a.p2p_list;
+  const uint32_t f_lo = it0.f0, f_hi = it0.f1, carry0 = it0.c0;
   uint32_t nsoft = 0;  // pairs inside a kernel (complete on lane 0)
   for (int t0 = 0; t0 < nt; t0 += TG) {
     double fx[TG], fy[TG], fz[TG], ph[TG];
@@ -303,7 +289,7 @@ __global__ __launch_bounds__(64) void k_p2p_leaf32(NearArgs a, const float4* __r
         for (int ii = 0; ii < TG; ++ii) {
           const int i = t0 + ii;
           if (i >= nt) continue;
-          const float w = (j == ti.lo + i) ? 0.f : oj.w;
+          const float w = (j == tlo + i) ? 0.f : oj.w;
           const float thi = tg[i][3];
           const float dx = cx + (tg[i][0] - oj.x);
           const float dy = cy + (tg[i][1] - oj.y);
@@ -344,7 +330,7 @@ __global__ __launch_bounds__(64) void k_p2p_leaf32(NearArgs a, const float4* __r
       }
     }
   }
-  if (lane == 0 && nsoft) atomicAdd(a.soft_pairs, (unsigned long long)nsoft);
+  if (lane == 0) a.soft_pairs[item] = nsoft;
 }
 
 // ---- P2P, wave per item with the targets in scalar registers -------------------
@@ -391,10 +377,11 @@ struct AccT {
   __device__ __forceinline__ void keep() { asm volatile("" ::"v"(hi), "v"(lo)); }
 };
 
-template <int K, int LS, int RS, typename Acc>
+template <int K, int LS, typename Acc>
 __device__ __forceinline__ void p2p_wave32_pass(const NearArgs& a, const float4* __restrict__ pf,
                                                 const float2* __restrict__ phh, const Wave32Item& w,
                                                 int t0, int* qj, float* qc, uint32_t& nsoft) {
+  const int RS = a.rec_stride;
   const int lane = threadIdx.x;
   const int tlo = w.tlo;
   float tx[K], ty[K], tz[K], t4[K];
@@ -561,49 +548,38 @@ __device__ __forceinline__ void p2p_wave32_pass(const NearArgs& a, const float4*
   }
 }
 
-template <int LS, bool NODE, int RS, int TG, int WPE, typename Acc>
+template <int LS, bool NODE, int TG, int WPE, typename Acc>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE))) void k_p2p_wave32(
     NearArgs a, const float4* __restrict__ pf, const float2* __restrict__ phh) {
   const int lane = threadIdx.x;
   const uint32_t item = xcd_block(blockIdx.x, gridDim.x);
   if (item >= a.item_off[a.nleaves]) return;  // the grid is an upper bound
-  const int l = a.item_leaf[item];
-  const uint32_t kitem = a.item_k[item];
-  const int node = a.leaf_node[l];
-  const NodeInfo ti = a.info[node];
+  const P2PItem it0 = a.item[item];
   Wave32Item w;
-  w.tlo = ti.lo;
-  w.nt = ti.cnt;
+  w.tlo = it0.lo;
+  w.nt = it0.cnt();
   w.item = item;
-  const double* rt = a.rec + (int64_t)node * RS;
+  const double* rt = a.rec + (int64_t)it0.node() * a.rec_stride;
   w.ct0 = rt[0]; w.ct1 = rt[1]; w.ct2 = rt[2];
-  if (NODE) {
-    w.e0 = a.node_p2p_off[node];
-    w.e1 = w.e0 + a.node_p2p_cnt[node];
-    w.list = reinterpret_cast<const int32_t*>(a.node_p2p_pool);
-  } else {
-    w.e0 = a.p2p_off[l];
-    w.e1 = a.p2p_off[l + 1];
-    w.list = a.p2p_list;
-  }
-  w.f_lo = kitem * kP2PItem;
-  const uint32_t ftot = a.src_total[l];
-  w.f_hi = w.f_lo + kP2PItem < ftot ? w.f_lo + kP2PItem : ftot;
-  w.carry0 = 0;
-  if (kitem > 0) { w.e0 = a.item_e0[item]; w.carry0 = a.item_c0[item]; }
+  w.e0 = it0.e0;
+  w.e1 = it0.e0 + it0.ne;
+  w.list = NODE ? reinterpret_cast<const int32_t*>(a.node_p2p_pool) : a.p2p_list;
+  w.f_lo = it0.f0;
+  w.f_hi = it0.f1;
+  w.carry0 = it0.c0;
   __shared__ int qj[TG * kTQ32];
   __shared__ float qc[TG * kTQ32 * 3];
   uint32_t nsoft = 0;
   int t0 = 0;
   for (; t0 + TG <= w.nt; t0 += TG)
-    p2p_wave32_pass<TG, LS, RS, Acc>(a, pf, phh, w, t0, qj, qc, nsoft);
+    p2p_wave32_pass<TG, LS, Acc>(a, pf, phh, w, t0, qj, qc, nsoft);
   // the remainder, a pass with a fixed target count (uniform branches)
   static_for<TG>([&](auto rc) {
     constexpr int r = decltype(rc)::value;
     if (r > 0 && w.nt - t0 == r)
-      p2p_wave32_pass<(r > 0 ? r : 1), LS, RS, Acc>(a, pf, phh, w, t0, qj, qc, nsoft);
+      p2p_wave32_pass<(r > 0 ? r : 1), LS, Acc>(a, pf, phh, w, t0, qj, qc, nsoft);
   });
-  if (lane == 0 && nsoft) atomicAdd(a.soft_pairs, (unsigned long long)nsoft);
+  if (lane == 0) a.soft_pairs[item] = nsoft;
 }
 
 constexpr int kFarSplit32 = 2;
@@ -626,21 +602,21 @@ void prep_particles(int nleaves, const int32_t* leaf_node, const NodeInfo* info,
 // variant 0: the wave kernel with scalar-register targets; 7: the same with
 // TwoSum-compensated FP32 sums instead of FP64 ones; 6: the earlier shape
 // (targets in LDS, the softened branch taken in the pass)
-template <int LS, int RS>
+template <int LS>
 void p2p32(bool node_lists, int variant, const NearArgs& a, const float4* pf, const float2* ph,
            int64_t items, hipStream_t s, KernelMarks km) {
   constexpr int TG = LS <= 10 ? 5 : 8;
   const unsigned nb = (unsigned)items;
   record_mark(km.begin, s);
   if (variant == 6) {
-    if (node_lists) k_p2p_leaf32<LS, true, RS, TG><<<nb, 64, 0, s>>>(a, pf, ph);
-    else k_p2p_leaf32<LS, false, RS, TG><<<nb, 64, 0, s>>>(a, pf, ph);
+    if (node_lists) k_p2p_leaf32<LS, true, TG><<<nb, 64, 0, s>>>(a, pf, ph);
+    else k_p2p_leaf32<LS, false, TG><<<nb, 64, 0, s>>>(a, pf, ph);
   } else if (variant == 7) {
-    if (node_lists) k_p2p_wave32<LS, true, RS, TG, 4, AccT><<<nb, 64, 0, s>>>(a, pf, ph);
-    else k_p2p_wave32<LS, false, RS, TG, 4, AccT><<<nb, 64, 0, s>>>(a, pf, ph);
+    if (node_lists) k_p2p_wave32<LS, true, TG, 4, AccT><<<nb, 64, 0, s>>>(a, pf, ph);
+    else k_p2p_wave32<LS, false, TG, 4, AccT><<<nb, 64, 0, s>>>(a, pf, ph);
   } else {
-    if (node_lists) k_p2p_wave32<LS, true, RS, TG, 4, AccD><<<nb, 64, 0, s>>>(a, pf, ph);
-    else k_p2p_wave32<LS, false, RS, TG, 4, AccD><<<nb, 64, 0, s>>>(a, pf, ph);
+    if (node_lists) k_p2p_wave32<LS, true, TG, 4, AccD><<<nb, 64, 0, s>>>(a, pf, ph);
+    else k_p2p_wave32<LS, false, TG, 4, AccD><<<nb, 64, 0, s>>>(a, pf, ph);
   }
   record_mark(km.end, s);
   if (!km.skip_reduce) launch_p2p_reduce(a, LS, s);
@@ -684,17 +660,10 @@ bool launch_near32(int order, bool node_lists, int leaf_size, int variant, const
                    const float4* pf, const float2* ph, int64_t items, hipStream_t s,
                    KernelMarks km) {
   if (a.n <= 0) return true;
-  const int RS = rec_stride(order);
   if (leaf_size > 16) return false;
-#define SFMM_P2P32(LS)                                                   \
-  switch (RS) {                                                          \
-    case 16: p2p32<LS, 16>(node_lists, variant, a, pf, ph, items, s, km); break;      \
-    case 24: p2p32<LS, 24>(node_lists, variant, a, pf, ph, items, s, km); break;      \
-    case 32: p2p32<LS, 32>(node_lists, variant, a, pf, ph, items, s, km); break;      \
-    case 48: p2p32<LS, 48>(node_lists, variant, a, pf, ph, items, s, km); break;      \
-  }
-  if (leaf_size <= 10) { SFMM_P2P32(10) } else { SFMM_P2P32(16) }
-#undef SFMM_P2P32
+  (void)order;
+  if (leaf_size <= 10) p2p32<10>(node_lists, variant, a, pf, ph, items, s, km);
+  else p2p32<16>(node_lists, variant, a, pf, ph, items, s, km);
   return true;
 }
 

@@ -89,6 +89,12 @@ __global__ __launch_bounds__(256) void k_near(NearArgs a) {
   a.pot[o] = -G * (fr[3] + ph);
 }
 
+// the pool that the items' list entries lie in
+template <bool NODE>
+__device__ __forceinline__ const int32_t* p2p_list(const NearArgs& a) {
+  return NODE ? reinterpret_cast<const int32_t*>(a.node_p2p_pool) : a.p2p_list;
+}
+
 // ---- wave per target leaf ----------------------------------------------------
 // The leaf's particles (at most LS) are wave-uniform and held in registers;
 // the lanes walk the flattened list of source particles of the leaf's P2P
@@ -101,6 +107,21 @@ __device__ __forceinline__ int wave_incl_scan(int v) {
     const int t = __shfl_up(v, o, 64);
     if (lane >= o) v += t;
   }
+  return v;
+}
+
+// inclusive sum over the wave's lanes (data-parallel moves, no LDS)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t add_dpp(uint32_t v) {
+  return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
+}
+__device__ __forceinline__ uint32_t wave_incl_sum(uint32_t v) {
+  v = add_dpp<0x111, 0xf>(v);  // rows of 16: shifted by 1, 2, 4, 8
+  v = add_dpp<0x112, 0xf>(v);
+  v = add_dpp<0x114, 0xf>(v);
+  v = add_dpp<0x118, 0xf>(v);
+  v = add_dpp<0x142, 0xa>(v);  // lane 15 (47) to row 1 (3)
+  v = add_dpp<0x143, 0xc>(v);  // lane 31 to rows 2 and 3
   return v;
 }
 
@@ -123,37 +144,21 @@ __global__ __launch_bounds__(64) void k_p2p_leaf(NearArgs a) {
   const int lane = threadIdx.x;
   const uint32_t item = blockIdx.x;
   if (item >= a.item_off[a.nleaves]) return;  // the grid is an upper bound
-  const int l = a.item_leaf[item];
-  const uint32_t kitem = a.item_k[item];
-  const int node = a.leaf_node[l];
-  const NodeInfo ti = a.info[node];
-  const int nt = ti.cnt;
+  const P2PItem it0 = a.item[item];
+  const int tlo = it0.lo, nt = it0.cnt();
   // targets in LDS (read back as broadcasts): x, y, z, 1/h, h
   __shared__ double tg[LS][5];
   if (lane < nt) {
-    const int j = ti.lo + lane;
+    const int j = tlo + lane;
     tg[lane][0] = a.xs[j]; tg[lane][1] = a.ys[j]; tg[lane][2] = a.zs[j];
     tg[lane][3] = a.his[j]; tg[lane][4] = a.hs[j];
   }
   __syncthreads();
-  uint64_t e0, e1;
-  const int32_t* list;
-  if (NODE) {
-    e0 = a.node_p2p_off[node];
-    e1 = e0 + a.node_p2p_cnt[node];
-    list = reinterpret_cast<const int32_t*>(a.node_p2p_pool);
-  } else {
-    e0 = a.p2p_off[l];
-    e1 = a.p2p_off[l + 1];
-    list = a.p2p_list;
-  }
   // this item's run [f_lo, f_hi) of the leaf's flattened sources, from the
   // list entry that holds its first source
-  const uint32_t f_lo = kitem * kP2PItem;
-  const uint32_t ftot = a.src_total[l];
-  const uint32_t f_hi = f_lo + kP2PItem < ftot ? f_lo + kP2PItem : ftot;
-  uint32_t carry0 = 0;
-  if (kitem > 0) { e0 = a.item_e0[item]; carry0 = a.item_c0[item]; }
+  const uint64_t e0 = it0.e0, e1 = e0 + it0.ne;
+  const int32_t* list = p2p_list<NODE>(a);
+  const uint32_t f_lo = it0.f0, f_hi = it0.f1, carry0 = it0.c0;
   __shared__ int qj[128];
   __shared__ int qi[128];
   uint32_t qn = 0;     // queued softened pairs (the same on every lane)
@@ -167,7 +172,7 @@ __global__ __launch_bounds__(64) void k_p2p_leaf(NearArgs a) {
     auto flush = [&](uint32_t count) {
       __syncthreads();
       const bool act = (uint32_t)lane < count;
-      const int j2 = act ? qj[lane] : ti.lo;
+      const int j2 = act ? qj[lane] : tlo;
       const int i2 = act ? qi[lane] : 0;
       const double thi = tg[i2][3];
       const double dx = tg[i2][0] - a.xs[j2], dy = tg[i2][1] - a.ys[j2], dz = tg[i2][2] - a.zs[j2];
@@ -230,7 +235,7 @@ __global__ __launch_bounds__(64) void k_p2p_leaf(NearArgs a) {
         // lanes past the window's end stay in step with the others (the queue
         // count and its barriers are per wave) and contribute nothing
         const bool fv = f < total;
-        const int j = fv ? jj : ti.lo;
+        const int j = fv ? jj : tlo;
         const double xj = a.xs[j], yj = a.ys[j], zj = a.zs[j], mj = a.ms[j];
         const double hjinv = a.his[j];
         const double hj2inv = hjinv * hjinv;
@@ -238,7 +243,7 @@ __global__ __launch_bounds__(64) void k_p2p_leaf(NearArgs a) {
         for (int ii = 0; ii < NA; ++ii) {
           const int i = t0 + ii;
           if (i >= nt) continue;
-          const double w = (!fv || j == ti.lo + i) ? 0.0 : mj;  // the pair (i, i) is skipped
+          const double w = (!fv || j == tlo + i) ? 0.0 : mj;  // the pair (i, i) is skipped
           const double thi = tg[i][3];
           const double dx = tg[i][0] - xj, dy = tg[i][1] - yj, dz = tg[i][2] - zj;
           const double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
@@ -278,238 +283,382 @@ __global__ __launch_bounds__(64) void k_p2p_leaf(NearArgs a) {
       }
     }
   }
-  if (lane == 0 && nsoft) atomicAdd(a.soft_pairs, (unsigned long long)nsoft);
+  if (lane == 0) a.soft_pairs[item] = nsoft;
 }
 
 // Wave per item, targets held in scalar registers.  The same sums as
 // k_p2p_leaf with less work per pair: the loop control is wave-uniform
 // (scalar), the targets of a pass are wave-uniform values, a pair is inside
-// a kernel when r^2 < max(4 h_i^2, 4 h_j^2), and the field of a pair beyond
-// both kernels is m/r^3 (dx, dy, dz) and m/r, with the refined 1/r replaced
-// by 0 for pairs inside a kernel (the self pair and coincident particles
-// included: r^2 = 0 is always inside).  Pairs inside a kernel, other than
-// the self pair, go to a queue per target in LDS and are evaluated 64 at a
-// time, each batch for one target (so its data stay wave-uniform), after
-// each group of 64 sources has met the pass's targets.  A leaf's targets
-// are taken in passes of TG and one pass of the remainder, each with a fixed
-// target count (no per-target exits inside the unrolled loop).
+// a kernel when r^2 < 4 h_i^2 or r^2 < 4 h_j^2, and the field of a pair
+// beyond both kernels is m/r^3 (dx, dy, dz) and m/r, with the refined 1/r
+// replaced by 0 for pairs inside a kernel (the self pair and coincident
+// particles included: r^2 = 0 is always inside).  Pairs inside a kernel,
+// other than the self pair, go to a queue per target in LDS and are
+// evaluated 64 at a time, each batch for one target (so its data stay
+// wave-uniform), after each group of 64 sources has met the pass's targets.
+// A leaf's targets are taken in as few passes of at most TG as they need, of
+// equal size within one, each with a fixed target count (no per-target exits
+// inside the unrolled loop).
+//
+// The item's sources (at most kP2PItem) are flattened once into LDS, as byte
+// offsets into the 16-byte particle arrays (so n < 2^28), padded to whole
+// groups of 64; every pass then only streams over them.  The records of the
+// next group load while the current one is evaluated.
+//
+// Bound: FP64 issue.  A pair takes 21 FP64-rate instructions of 4 cycles a
+// wave and one v_rsq_f64 of 16 (100 cycles for 64 pairs), so 1.76e9 pairs need
+// 1.3 ms at the 2.05 GHz the chip holds under this load.  Measured (Plummer
+// sphere of 1e6, 1.76e9 pairs, 3.5 % softened): 2.83 ms, before 3.84 ms; of
+// 9.95e8 VALU instructions (40 per 64 pairs) 23 are the pair's, the others the
+// queues, the softened pairs, list scans and reductions, and the VALU is busy
+// 77 % of the time.  Polytrope of 1e6 at leaf size 16: 1.95 ms, before 2.50.
 struct WaveItem {
   int tlo, nt;
-  uint64_t e0, e1;
-  const int32_t* list;
-  uint32_t f_lo, f_hi;
-  uint32_t carry0;  // the flattened start of entry e0
+  int total;  // flattened sources of the item
   int64_t item;
 };
 
-constexpr uint32_t kTQ = 192;  // queue slots per target (63 + 64 U, U <= 2)
+// One piece of the cubic spline of softening.h: with q = r / h
+//   g   = (c0 + q (c1 + q (c2 + q c3)) - cr / q^3) / h^3
+//   psi = (d0 + q^2 (d2 + q (d3 + q (d4 + q d5))) - dr / q) / h
+// for q < 1, 1 <= q < 2 and q >= 2 (outside: 1/r^3 and 1/r).  A lane reads
+// its piece from LDS, which takes 24 instructions a kernel where evaluating
+// the pieces and selecting takes 38.
+struct alignas(16) SoftCoef {
+  double c0, c1, c2, c3, cr, d0, d2, d3, d4, d5, dr, pad;
+};
+__constant__ const SoftCoef kSoftCoef[3] = {
+    {4.0 / 3.0, 0.0, -1.2, 0.5, 0.0, 1.4, -2.0 / 3.0, 0.0, 0.3, -0.1, 0.0, 0.0},
+    {8.0 / 3.0, -3.0, 1.2, -1.0 / 6.0, 1.0 / 15.0, 1.6, -4.0 / 3.0, 1.0, -0.3, 1.0 / 30.0,
+     1.0 / 15.0, 0.0},
+    {0.0, 0.0, 0.0, 0.0, -1.0, 0.0, 0.0, 0.0, 0.0, 0.0, -1.0, 0.0}};
 
-// U groups of 64 sources per step: their index searches and loads are
-// independent, so a wave keeps U chains of latency in flight
-template <int K, int LS, int U>
-__device__ __forceinline__ void p2p_wave_pass(const NearArgs& a, const WaveItem& w, int t0,
-                                              int* q, uint32_t& nsoft) {
-  const int lane = threadIdx.x;
-  const int tlo = w.tlo;
-  double tx[K], ty[K], tz[K], t4[K];
-  double fx[K], fy[K], fz[K], ph[K];
-  uint32_t qh[K], qn[K];  // per-target ring queue head and length (wave-uniform)
-#pragma unroll
-  for (int ii = 0; ii < K; ++ii) {
-    const int it = tlo + t0 + ii;
-    tx[ii] = wave_uniform(a.xs[it]);
-    ty[ii] = wave_uniform(a.ys[it]);
-    tz[ii] = wave_uniform(a.zs[it]);
-    const double hu = wave_uniform(a.hs[it]);
-    t4[ii] = 4.0 * hu * hu;
-    fx[ii] = 0.0; fy[ii] = 0.0; fz[ii] = 0.0; ph[ii] = 0.0;
-    qh[ii] = 0; qn[ii] = 0;
-  }
-  // the first `count` queued sources of target ii, one per lane
-  auto flush = [&](auto iic, uint32_t count) {
-    constexpr int ii = decltype(iic)::value;
-    __syncthreads();
-    const bool act = (uint32_t)lane < count;
-    uint32_t slot = qh[ii] + (uint32_t)lane;
-    if (slot >= kTQ) slot -= kTQ;
-    const int j2 = act ? q[ii * kTQ + slot] : tlo;
-    const int it = tlo + t0 + ii;  // wave-uniform
-    const double hi = wave_uniform(a.hs[it]), hiinv = wave_uniform(a.his[it]);
-    const double2* rj = reinterpret_cast<const double2*>(a.p4 + 4 * (int64_t)j2);
-    const double2 sxy = rj[0], szm = rj[1];
-    const double dx = tx[ii] - sxy.x, dy = ty[ii] - sxy.y, dz = tz[ii] - szm.x;
-    const double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
-    const double rinv = rsqrt_pair(r2);
-    const double rinv3 = rinv * rinv * rinv;
-    const double r = r2 * rinv;
-    const double hj = a.hs[j2], hjinv = a.his[j2];
-    double g1, p1, g2, p2;
-    soft_sel(r * hiinv, hiinv, hi * rinv, rinv, rinv3, g1, p1);
-    soft_sel(r * hjinv, hjinv, hj * rinv, rinv, rinv3, g2, p2);
-    const double wm = act ? szm.y : 0.0;
-    const double mg = wm * (0.5 * (g1 + g2));
-    fx[ii] = fma(mg, dx, fx[ii]);
-    fy[ii] = fma(mg, dy, fy[ii]);
-    fz[ii] = fma(mg, dz, fz[ii]);
-    ph[ii] = fma(wm, 0.5 * (p1 + p2), ph[ii]);
-    qh[ii] += count;
-    if (qh[ii] >= kTQ) qh[ii] -= kTQ;
-    qn[ii] -= count;
-  };
-  uint32_t carry = w.carry0;  // sources of the list entries before c0 (wave-uniform)
-  for (uint64_t c0 = w.e0; c0 < w.e1; c0 += 64) {
-    // 64 list entries: their particle ranges [fb, fe) in the flattened
-    // order, then clipped to the run
-    int cnt = 0, lo = 0;
-    uint32_t fb = 0xffffffffu;
-    NodeInfo si{};
-    const bool in = c0 + lane < w.e1;
-    if (in) si = a.info[w.list[c0 + lane]];
-    const int sincl = wave_incl_scan(in ? si.cnt : 0);
-    if (in) {
-      const uint32_t fe = carry + (uint32_t)sincl;
-      fb = fe - (uint32_t)si.cnt;
-      const uint32_t b = fb > w.f_lo ? fb : w.f_lo;
-      const uint32_t en = fe < w.f_hi ? fe : w.f_hi;
-      if (en > b) { cnt = (int)(en - b); lo = si.lo + (int)(b - fb); }
-    }
-    carry += (uint32_t)__builtin_amdgcn_readlane(sincl, 63);
-    // lane 0 always holds an entry (c0 < e1)
-    if ((uint32_t)__builtin_amdgcn_readfirstlane(fb) >= w.f_hi) break;  // the run is done
-    const int incl = wave_incl_scan(cnt);
-    const int pre = incl - cnt;
-    const int total = __builtin_amdgcn_readlane(incl, 63);
-    for (int f0 = 0; f0 < total; f0 += 64 * U) {
-      int j[U];
-      bool fv[U];
-      double xj[U], yj[U], zj[U], mj[U], h4j[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int f = f0 + 64 * u + lane;
-        // owner lane k: the last lane with pre <= f (binary search over lanes)
-        int k = 0;
-#pragma unroll
-        for (int step = 32; step > 0; step >>= 1) {
-          const int pk = __shfl(pre, k + step, 64);
-          if (pk <= f) k += step;
-        }
-        const int jj = __shfl(lo, k, 64) + (f - __shfl(pre, k, 64));
-        fv[u] = f < total;
-        j[u] = fv[u] ? jj : tlo;  // a valid index; contributes nothing
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const double2* rj = reinterpret_cast<const double2*>(a.p4 + 4 * (int64_t)j[u]);
-        const double2 sxy = rj[0], szm = rj[1];
-        const double hj = a.hs[j[u]];
-        xj[u] = sxy.x;
-        yj[u] = sxy.y;
-        zj[u] = szm.x;
-        mj[u] = fv[u] ? szm.y : 0.0;
-        h4j[u] = 4.0 * hj * hj;
-      }
-#pragma unroll
-      for (int ii = 0; ii < K; ++ii) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const double dx = tx[ii] - xj[u], dy = ty[ii] - yj[u], dz = tz[ii] - zj[u];
-          const double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
-          const bool inside = r2 < fmax(t4[ii], h4j[u]);
-          const double rinv = inside ? 0.0 : rsqrt_refined(r2);
-          const double mr = mj[u] * rinv;
-          const double mg = mr * (rinv * rinv);
-          fx[ii] = fma(mg, dx, fx[ii]);
-          fy[ii] = fma(mg, dy, fy[ii]);
-          fz[ii] = fma(mg, dz, fz[ii]);
-          ph[ii] += mr;
-          // (an empty statement that reads the sums: keeps this target's
-          // arithmetic ahead of the queue branch below, so that the compiler
-          // does not move it past the branches of the later targets and hold
-          // every target's separation vector at once)
-          asm volatile("" ::"v"(fx[ii]), "v"(fy[ii]), "v"(fz[ii]), "v"(ph[ii]));
-          const bool push = inside && fv[u] && j[u] != tlo + t0 + ii;
-          const uint64_t bal = __builtin_amdgcn_ballot_w64(push);
-          if (bal) {
-            if (push) {
-              const uint32_t below = __builtin_amdgcn_mbcnt_hi(
-                  (uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
-              uint32_t sl = qh[ii] + qn[ii] + below;
-              if (sl >= kTQ) sl -= kTQ;
-              q[ii * kTQ + sl] = j[u];
-            }
-            const uint32_t c = (uint32_t)__popcll(bal);
-            qn[ii] += c;
-            nsoft += c;
-          }
-        }
-      }
-      // a queue holds at most 63 + 64 U entries here
-      static_for<K>([&](auto iic) {
-        constexpr int ii = decltype(iic)::value;
-        while (qn[ii] >= 64) flush(iic, 64);
-      });
-    }
-  }
-  static_for<K>([&](auto iic) {
-    constexpr int ii = decltype(iic)::value;
-    if (qn[ii] > 0) flush(iic, qn[ii]);
-  });
-#pragma unroll
-  for (int ii = 0; ii < K; ++ii) {
-    const double sx = wave_sum(fx[ii]), sy = wave_sum(fy[ii]), sz = wave_sum(fz[ii]);
-    const double sp = wave_sum(ph[ii]);
-    if (lane == t0 + ii) {
-      double* o = a.part + (w.item * LS + t0 + ii) * 4;
-      o[0] = sx; o[1] = sy; o[2] = sz; o[3] = sp;
-    }
-  }
+// g = f(q) / (q h^3) and psi(q) / h at q = r hinv, qi = h / r
+__device__ __forceinline__ void soft_piece(const SoftCoef* coef, double q, double qi, double hinv,
+                                           double& g, double& psi) {
+  const SoftCoef& k = coef[q < 1.0 ? 0 : q < 2.0 ? 1 : 2];
+  const double qr = q < 1.0 ? 0.0 : qi;  // (1/q^3 may overflow there; its coefficient is 0)
+  const double q2 = q * q;
+  const double gp = fma(q, fma(q, fma(q, k.c3, k.c2), k.c1), k.c0);
+  const double pp = fma(q2, fma(q, fma(q, fma(q, k.d5, k.d4), k.d3), k.d2), k.d0);
+  g = hinv * hinv * hinv * fma(-k.cr, qr * qr * qr, gp);
+  psi = hinv * fma(-k.dr, qr, pp);
 }
 
-template <int LS, bool NODE, int TG, int WPE, int U>
+constexpr int kTQ = 256;  // queue slots per target
+
+template <int TG>
+struct alignas(16) WaveLds {
+  uint32_t off[kP2PItem];  // 16 x particle index of each source
+  union {
+    uint16_t q[TG * kTQ];  // queued sources (places in off)
+    double red[4][64];     // a soft pass's sums by component (x, z, y, p) and lane
+  };
+  SoftCoef coef[3];        // the spline pieces (kSoftCoef)
+};
+
+__device__ __forceinline__ double make_double(uint32_t lo, uint32_t hi) {
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+__device__ __forceinline__ uint32_t lo32(double v) { return (uint32_t)__double_as_longlong(v); }
+__device__ __forceinline__ uint32_t hi32(double v) {
+  return (uint32_t)((unsigned long long)__double_as_longlong(v) >> 32);
+}
+
+// lanes 0..31: a summed over the wave's two halves, lanes 32..63: b
+__device__ __forceinline__ double fold32(double a, double b) {
+  auto l = __builtin_amdgcn_permlane32_swap(lo32(a), lo32(b), false, false);
+  auto h = __builtin_amdgcn_permlane32_swap(hi32(a), hi32(b), false, false);
+  return make_double(l[0], h[0]) + make_double(l[1], h[1]);
+}
+// within each half: its even row of 16 lanes gets a summed over the half's
+// two rows, its odd row b
+__device__ __forceinline__ double fold16(double a, double b) {
+  auto l = __builtin_amdgcn_permlane16_swap(lo32(a), lo32(b), false, false);
+  auto h = __builtin_amdgcn_permlane16_swap(hi32(a), hi32(b), false, false);
+  return make_double(l[0], h[0]) + make_double(l[1], h[1]);
+}
+// v plus v of the lane N places on in the row of 16 (rotated)
+template <int N>
+__device__ __forceinline__ double add_ror(double v) {
+  const int l = __builtin_amdgcn_mov_dpp((int)lo32(v), 0x120 + N, 0xf, 0xf, true);
+  const int h = __builtin_amdgcn_mov_dpp((int)hi32(v), 0x120 + N, 0xf, 0xf, true);
+  return v + make_double((uint32_t)l, (uint32_t)h);
+}
+// the wave's sums of four values, one per row of 16 lanes: x, z, y, p
+__device__ __forceinline__ double wave_sum4(double x, double y, double z, double p) {
+  double v = fold16(fold32(x, y), fold32(z, p));
+  v = add_ror<8>(v);
+  v = add_ror<4>(v);
+  v = add_ror<2>(v);
+  return add_ror<1>(v);
+}
+
+// The queued pairs of a pass of K targets (lane t of lens: the length of
+// target t's queue, total their sum).  A lane takes `run` consecutive entries
+// of one target, each target as many lanes as its queue needs:
+// sum_t ceil(len_t / run) <= total / run + K <= 64 for run >= total / (64 - K).
+// The lanes' sums are added per target in lane order, into the component that
+// lane (row, t) holds (rows of 16 lanes: x, z, y, p).
+template <int K, int TG>
+__device__ __forceinline__ double p2p_wave_soft(const NearArgs& a, int t0p, WaveLds<TG>& sh,
+                                                uint32_t lens, uint32_t total) {
+  const int lane = threadIdx.x;
+  const uint32_t run = (total + (64 - K) - 1) / (64 - K);
+  const uint32_t len = lane < K ? lens : 0u;
+  // (small whole numbers: the quotient's floor is exact)
+  const uint32_t nl = (uint32_t)(((float)(len + run - 1) + 0.5f) / (float)run);
+  const uint32_t end = wave_incl_sum(lane < K ? nl : 0u);  // (lanes K.. repeat the last end)
+  int t = 0;
+  uint32_t first = 0;
+#pragma unroll
+  for (int k = 0; k + 1 < K; ++k) {
+    const uint32_t e = (uint32_t)__builtin_amdgcn_readlane((int)end, k);
+    const bool past = (uint32_t)lane >= e;
+    t = past ? k + 1 : t;
+    first = past ? e : first;
+  }
+  const uint32_t at = ((uint32_t)lane - first) * run;  // this lane's first entry
+  const uint32_t mylen = (uint32_t)__shfl((int)len, t, 64);
+  const int it = t0p + t;
+  const double2 txy = a.pxy[it], tzm = a.pzm[it];
+  const double hi = a.hs[it], hiinv = a.his[it];
+  const uint16_t* qt = sh.q + t * kTQ;
+  double sx = 0.0, sy = 0.0, sz = 0.0, sp = 0.0;
+  // (the next source's record loads while the current pair is evaluated)
+  struct Src {
+    double2 xy, zm;
+    double h, hinv;
+  };
+  auto load = [&](uint32_t b) {
+    const int j = at + b < mylen ? (int)(sh.off[qt[at + b]] >> 4) : it;
+    return Src{a.pxy[j], a.pzm[j], a.hs[j], a.his[j]};
+  };
+  Src next = load(0);
+  for (uint32_t b = 0; b < run; ++b) {
+    const bool act = at + b < mylen;
+    const double2 sxy = next.xy, szm = next.zm;
+    const double hj = next.h, hjinv = next.hinv;
+    if (b + 1 < run) next = load(b + 1);
+    const double dx = txy.x - sxy.x, dy = txy.y - sxy.y, dz = tzm.x - szm.x;
+    const double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
+    const double rinv = rsqrt_pair(r2);
+    const double r = r2 * rinv;
+    double g1, p1, g2, p2;
+    soft_piece(sh.coef, r * hiinv, hi * rinv, hiinv, g1, p1);
+    soft_piece(sh.coef, r * hjinv, hj * rinv, hjinv, g2, p2);
+    const double wm = act ? 0.5 * szm.y : 0.0;
+    const double mg = wm * (g1 + g2);
+    sx = fma(mg, dx, sx);
+    sy = fma(mg, dy, sy);
+    sz = fma(mg, dz, sz);
+    sp = fma(wm, p1 + p2, sp);
+  }
+  __syncthreads();  // (the sums take the place of the queues)
+  sh.red[0][lane] = sx;
+  sh.red[1][lane] = sz;
+  sh.red[2][lane] = sy;
+  sh.red[3][lane] = sp;
+  __syncthreads();
+  const int tk = lane & 15;
+  const uint32_t e1 = (uint32_t)__shfl((int)end, tk, 64);
+  uint32_t e0 = (uint32_t)__shfl((int)end, tk > 0 ? tk - 1 : 0, 64);
+  if (tk == 0) e0 = 0;
+  double sum = 0.0;
+  if (tk < K)
+    for (uint32_t e = e0; e < e1; ++e) sum += sh.red[lane >> 4][e];
+  return sum;
+}
+
+template <int K, int LS, int TG>
+__device__ __forceinline__ void p2p_wave_pass(const NearArgs& a, const WaveItem& w, int t0,
+                                              WaveLds<TG>& sh, uint32_t& nsoft) {
+  const int lane = threadIdx.x;
+  const int t0p = w.tlo + t0;
+  double tx[K], ty[K], tz[K], t4[K];
+  double fx[K], fy[K], fz[K], ph[K];
+  uint32_t qn[K];  // per-target queue length (wave-uniform)
+#pragma unroll
+  for (int ii = 0; ii < K; ++ii) {
+    const double2 xy = a.pxy[t0p + ii], zm = a.pzm[t0p + ii];
+    tx[ii] = wave_uniform(xy.x);
+    ty[ii] = wave_uniform(xy.y);
+    tz[ii] = wave_uniform(zm.x);
+    t4[ii] = wave_uniform(a.h4[t0p + ii]);
+    fx[ii] = 0.0; fy[ii] = 0.0; fz[ii] = 0.0; ph[ii] = 0.0;
+    qn[ii] = 0;
+  }
+  double soft = 0.0;  // sums over queued pairs, by lane as p2p_wave_soft returns them
+  const char* bxy = reinterpret_cast<const char*>(a.pxy);
+  const char* bzm = reinterpret_cast<const char*>(a.pzm);
+  const char* bh4 = reinterpret_cast<const char*>(a.h4);
+  auto load_src = [&](int u0, uint32_t& off, double2& xy, double2& zm, double& h4) {
+    off = sh.off[u0 + lane];
+    xy = *reinterpret_cast<const double2*>(bxy + off);
+    zm = *reinterpret_cast<const double2*>(bzm + off);
+    h4 = *reinterpret_cast<const double*>(bh4 + (off >> 1));
+  };
+  uint32_t off;
+  double2 xy, zm;
+  double h4;
+  load_src(0, off, xy, zm, h4);
+  for (int u0 = 0; u0 < w.total; u0 += 64) {
+    const uint32_t offc = off;
+    const double xj = xy.x, yj = xy.y, zj = zm.x;
+    double mj = zm.y;
+    const uint64_t h4b = (uint64_t)__double_as_longlong(h4);
+    const bool end = u0 + 64 >= w.total;
+    uint64_t valid = ~0ull;
+    if (!end) {
+      load_src(u0 + 64, off, xy, zm, h4);
+    } else if (w.total - u0 < 64) {
+      // lanes past the end contribute nothing
+      valid = (1ull << (w.total - u0)) - 1ull;
+      mj = __builtin_amdgcn_inverse_ballot_w64(valid) ? mj : 0.0;
+    }
+    uint64_t im[K], met = 0;  // the lanes whose pair lies inside a kernel
+#pragma unroll
+    for (int ii = 0; ii < K; ++ii) {
+      const double dx = tx[ii] - xj, dy = ty[ii] - yj, dz = tz[ii] - zj;
+      const double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
+      // (r^2 >= 0 orders like its bits: with one compare of each kind the
+      // compiler keeps two of them, where it would fold two of a kind into
+      // one against the larger bound, whose maximum costs three more)
+      im[ii] = __builtin_amdgcn_ballot_w64(r2 < t4[ii]) |
+               __builtin_amdgcn_ballot_w64((uint64_t)__double_as_longlong(r2) < h4b);
+      const bool inside = __builtin_amdgcn_inverse_ballot_w64(im[ii]);
+      // (inside: the high word alone is cleared, which leaves a number below
+      // 2^-1022, 0 to every sum that holds a softened pair)
+      const double ri = rsqrt_refined(r2);
+      const double rinv = make_double(lo32(ri), inside ? 0u : hi32(ri));
+      const double mr = mj * rinv;
+      const double mg = mr * (rinv * rinv);
+      fx[ii] = fma(mg, dx, fx[ii]);
+      fy[ii] = fma(mg, dy, fy[ii]);
+      fz[ii] = fma(mg, dz, fz[ii]);
+      ph[ii] += mr;
+      met |= im[ii];
+      // (an empty statement that reads the sums: keeps this arithmetic ahead
+      // of the queue branch below, so that the compiler does not move it past
+      // that branch and hold every target's separation vector at once)
+      asm volatile("" ::"v"(fx[ii]), "v"(fy[ii]), "v"(fz[ii]), "v"(ph[ii]));
+    }
+    if (__builtin_expect_with_probability((met & valid) != 0 || end, 1, 0.1)) {
+      uint32_t lens = 0, most = 0, sum = 0;
+#pragma unroll
+      for (int ii = 0; ii < K; ++ii) {
+        // (the self pair has r^2 = 0 and is always inside)
+        const uint64_t bal =
+            im[ii] & valid & ~__builtin_amdgcn_ballot_w64(offc == 16u * (uint32_t)(t0p + ii));
+        if (__builtin_amdgcn_inverse_ballot_w64(bal)) {
+          const uint32_t below = __builtin_amdgcn_mbcnt_hi(
+              (uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
+          sh.q[ii * kTQ + (int)(qn[ii] + below)] = (uint16_t)(u0 + lane);
+        }
+        qn[ii] = __builtin_amdgcn_readfirstlane(qn[ii] + (uint32_t)__popcll(bal));
+        most = qn[ii] > most ? qn[ii] : most;
+        sum += qn[ii];
+        lens = lane == ii ? qn[ii] : lens;
+      }
+      // queues that might overflow in the next group, at the end all of them
+      if (__builtin_expect_with_probability(most > (end ? 0u : (uint32_t)(kTQ - 64)), 1, 0.05)) {
+        nsoft += sum;
+        __syncthreads();
+        soft += p2p_wave_soft<K, TG>(a, t0p, sh, lens, sum);
+        __syncthreads();
+#pragma unroll
+        for (int ii = 0; ii < K; ++ii) qn[ii] = 0;
+      }
+    }
+  }
+  // the sums over the wave: row r of 16 lanes gets component {x, z, y, p}[r];
+  // lane ii of the row keeps target ii's
+  double mine = 0.0;
+#pragma unroll
+  for (int ii = 0; ii < K; ++ii) {
+    const double v = wave_sum4(fx[ii], fy[ii], fz[ii], ph[ii]);
+    mine = (lane & 15) == ii ? v : mine;
+  }
+  const int row = lane >> 4, tk = lane & 15;
+  if (tk < K) {
+    const int comp = row == 1 ? 2 : row == 2 ? 1 : row;
+    a.part[(w.item * LS + t0 + tk) * 4 + comp] = mine + soft;
+  }
+  __syncthreads();  // (the queues are reused by the next pass)
+}
+
+template <int LS, bool NODE, int TG, int WPE>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE))) void k_p2p_wave(
     NearArgs a) {
   const int lane = threadIdx.x;
   const uint32_t item = xcd_block(blockIdx.x, gridDim.x);
   if (item >= a.item_off[a.nleaves]) return;  // the grid is an upper bound
-  const int l = a.item_leaf[item];
-  const uint32_t kitem = a.item_k[item];
-  const int node = a.leaf_node[l];
-  const NodeInfo ti = a.info[node];
-  WaveItem w;
-  w.tlo = ti.lo;
-  w.nt = ti.cnt;
-  w.item = item;
-  if (NODE) {
-    w.e0 = a.node_p2p_off[node];
-    w.e1 = w.e0 + a.node_p2p_cnt[node];
-    w.list = reinterpret_cast<const int32_t*>(a.node_p2p_pool);
-  } else {
-    w.e0 = a.p2p_off[l];
-    w.e1 = a.p2p_off[l + 1];
-    w.list = a.p2p_list;
-  }
+  const P2PItem it0 = a.item[item];
   // this item's run [f_lo, f_hi) of the leaf's flattened sources, from the
   // list entry that holds its first source
-  w.f_lo = kitem * kP2PItem;
-  const uint32_t ftot = a.src_total[l];
-  w.f_hi = w.f_lo + kP2PItem < ftot ? w.f_lo + kP2PItem : ftot;
-  w.carry0 = 0;
-  if (kitem > 0) { w.e0 = a.item_e0[item]; w.carry0 = a.item_c0[item]; }
-  __shared__ int q[TG * kTQ];
+  const uint64_t e0 = it0.e0, e1 = e0 + it0.ne;
+  const int32_t* list = p2p_list<NODE>(a);
+  const uint32_t f_lo = it0.f0, f_hi = it0.f1;
+  uint32_t carry = it0.c0;  // the flattened start of the entries of a step
+  __shared__ WaveLds<TG> sh;
+  if (lane < (int)(sizeof(kSoftCoef) / sizeof(double)))
+    reinterpret_cast<double*>(sh.coef)[lane] = reinterpret_cast<const double*>(kSoftCoef)[lane];
+  // 64 list entries per step: entry [fb, fe) of the flattened order, clipped
+  // to the run, goes to its place in LDS; entries of at most 16 sources one
+  // source per iteration, larger ones by the whole wave
+  for (uint64_t c0 = e0; c0 < e1 && carry < f_hi; c0 += 64) {
+    NodeInfo si{};
+    if (c0 + lane < e1) si = a.info[list[c0 + lane]];
+    const uint32_t fe = carry + wave_incl_sum((uint32_t)si.cnt);
+    const uint32_t fb = fe - (uint32_t)si.cnt;
+    carry = (uint32_t)__builtin_amdgcn_readlane((int)fe, 63);
+    const uint32_t b = fb > f_lo ? fb : f_lo, en = fe < f_hi ? fe : f_hi;
+    const int nw = en > b ? (int)(en - b) : 0;
+    const int at = (int)(b - f_lo);
+    const uint32_t from = 16u * (uint32_t)(si.lo + (int)(b - fb));
+    const bool big = nw > 16;
+    const int nsm = big ? 0 : nw;
+    for (int k = 0; k < 16; ++k) {
+      if (!__builtin_amdgcn_ballot_w64(k < nsm)) break;
+      if (k < nsm) sh.off[at + k] = from + 16u * (uint32_t)k;
+    }
+    uint64_t bigm = __builtin_amdgcn_ballot_w64(big);
+    while (bigm) {
+      const int k = __builtin_ctzll(bigm);
+      bigm &= bigm - 1;
+      const int kat = __builtin_amdgcn_readlane(at, k), kn = __builtin_amdgcn_readlane(nw, k);
+      const uint32_t kfrom = (uint32_t)__builtin_amdgcn_readlane((int)from, k);
+      for (int q = lane; q < kn; q += 64) sh.off[kat + q] = kfrom + 16u * (uint32_t)q;
+    }
+  }
+  WaveItem w;
+  w.tlo = __builtin_amdgcn_readfirstlane(it0.lo);
+  w.nt = __builtin_amdgcn_readfirstlane(it0.cnt());
+  const uint32_t f_end = carry < f_hi ? carry : f_hi;
+  w.total = __builtin_amdgcn_readfirstlane(f_end > f_lo ? (int)(f_end - f_lo) : 0);
+  w.item = item;
+  // (lanes past the last source read a valid record)
+  if (w.total == 0 || w.total + lane < (w.total + 63) / 64 * 64)
+    sh.off[w.total + lane] = 16u * (uint32_t)w.tlo;
+  __syncthreads();
   uint32_t nsoft = 0;
+  const int npass = (w.nt + TG - 1) / TG;
   int t0 = 0;
-  for (; t0 + TG <= w.nt; t0 += TG) p2p_wave_pass<TG, LS, U>(a, w, t0, q, nsoft);
-  // the remainder, a pass with a fixed target count (uniform branches)
-  static_for<TG>([&](auto rc) {
-    constexpr int r = decltype(rc)::value;
-    if (r > 0 && w.nt - t0 == r) p2p_wave_pass<(r > 0 ? r : 1), LS, U>(a, w, t0, q, nsoft);
-  });
-  if (lane == 0 && nsoft) atomicAdd(a.soft_pairs, (unsigned long long)nsoft);
+  for (int p = 0; p < npass; ++p) {
+    const int k = (w.nt - t0 + (npass - p) - 1) / (npass - p);
+    // a pass with a fixed target count (uniform branches)
+    static_for<TG>([&](auto rc) {
+      constexpr int r = decltype(rc)::value + 1;
+      if (k == r) p2p_wave_pass<r, LS, TG>(a, w, t0, sh, nsoft);
+    });
+    t0 += k;
+  }
+  if (lane == 0) a.soft_pairs[item] = nsoft;
 }
 
 // per leaf, the particles over its P2P list entries and its work items:
-// max(1, ceil(sources / kP2PItem)).  One wave per leaf.  (The level walk
-// computes both in its leaf pass.)
+// max(1, ceil(sources / the rule's run length)).  One wave per leaf.  (The
+// level walk computes both in its leaf pass.)
 template <bool NODE>
 __global__ __launch_bounds__(64) void k_p2p_items_count(NearArgs a, uint32_t* __restrict__ src_total,
                                                         uint32_t* __restrict__ cnt) {
@@ -536,53 +685,51 @@ __global__ __launch_bounds__(64) void k_p2p_items_count(NearArgs a, uint32_t* __
   }
   if (lane == 0) {
     src_total[l] = carry;
-    const uint32_t k = (carry + kP2PItem - 1) / kP2PItem;
+    const uint32_t len = a.rule.len(a.info[a.leaf_node[l]].lo);
+    const uint32_t k = (carry + len - 1) / len;
     cnt[l] = k > 0 ? k : 1u;
   }
 }
 
-// item_leaf / item_k of every item, and for each item after a leaf's first
-// the list entry holding its first source and that entry's start in the
-// flattened order (item k starts at source k * kP2PItem).  One wave per
-// kFillLeaves leaves: a lane per leaf for the first two, then the whole wave
-// scans the list of each of its leaves with more than one item (a few in a
-// hundred, so a wave meets about one).
+// the work items.  A block of kFillLeaves waves per kFillLeaves leaves, a wave
+// per leaf: it writes the leaf's items and, when there are several, scans the
+// leaf's list for the entries that hold their first sources.  (One wave for
+// all 16 leaves took 441 us on a Plummer sphere of 1e6, whose halo leaves all
+// have lists of thousands of entries and sit together in the leaf order.)
 constexpr int kFillLeaves = 16;
 constexpr int kFillGroups = 8;
 template <bool NODE>
-__global__ __launch_bounds__(64) void k_p2p_items_fill(NearArgs a, int32_t* __restrict__ item_leaf,
-                                                       uint32_t* __restrict__ item_k,
-                                                       uint32_t* __restrict__ item_e0,
-                                                       uint32_t* __restrict__ item_c0) {
-  const int lane = threadIdx.x;
-  const int lme = blockIdx.x * kFillLeaves + lane;
-  uint32_t nb = 0, ne = 0;
-  if (lane < kFillLeaves && lme < a.nleaves) {
-    nb = a.item_off[lme];
-    ne = a.item_off[lme + 1];
-    for (uint32_t t = nb; t < ne; ++t) {
-      item_leaf[t] = lme;
-      item_k[t] = t - nb;
-    }
-  }
-  uint64_t multi = __ballot(ne - nb > 1);
-  while (multi) {
-    const int q = __builtin_ctzll(multi);
-    multi &= multi - 1;
-    const int l = blockIdx.x * kFillLeaves + q;
-    const uint32_t b = (uint32_t)__shfl((int)nb, q, 64), e = (uint32_t)__shfl((int)ne, q, 64);
+__global__ __launch_bounds__(64 * kFillLeaves) void k_p2p_items_fill(NearArgs a,
+                                                                     P2PItem* __restrict__ item) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  {
+    const int l = blockIdx.x * kFillLeaves + wv;
+    if (l >= a.nleaves) return;
+    const uint32_t b = a.item_off[l], e = a.item_off[l + 1];
+    const int node = a.leaf_node[l];
+    const NodeInfo ti = a.info[node];
     uint64_t e0, e1;
-    const int32_t* list;
     if (NODE) {
-      const int node = a.leaf_node[l];
       e0 = a.node_p2p_off[node];
       e1 = e0 + a.node_p2p_cnt[node];
-      list = reinterpret_cast<const int32_t*>(a.node_p2p_pool);
     } else {
       e0 = a.p2p_off[l];
       e1 = a.p2p_off[l + 1];
-      list = a.p2p_list;
     }
+    const uint32_t len = a.rule.len(ti.lo), ftot = a.src_total[l];
+    P2PItem q{};
+    q.e0 = e0;
+    q.ne = (uint32_t)(e1 - e0);
+    q.lo = ti.lo;
+    q.nd = (uint32_t)node | ((uint32_t)ti.cnt << kSrcBits);
+    for (uint32_t t = b + lane; t < e; t += 64) {
+      q.f0 = (t - b) * len;
+      q.f1 = q.f0 + len < ftot ? q.f0 + len : ftot;
+      if (t == b) item[t] = q;
+      else { item[t].f0 = q.f0; item[t].f1 = q.f1; item[t].lo = q.lo; item[t].nd = q.nd; }
+    }
+    if (e - b <= 1) return;
+    const int32_t* list = p2p_list<NODE>(a);
     // kFillGroups groups of 64 entries per step, their loads issued together
     // (the longest lists, a few thousand entries, set this kernel's time)
     uint32_t carry = 0;
@@ -602,16 +749,33 @@ __global__ __launch_bounds__(64) void k_p2p_items_fill(NearArgs a, int32_t* __re
         const int incl = wave_incl_scan((int)c);
         const uint32_t fe = carry + (uint32_t)incl, fb = fe - c;
         if (in && c > 0) {
-          uint32_t k = (fb + kP2PItem - 1) / kP2PItem;
+          uint32_t k = (fb + len - 1) / len;
           if (k == 0) k = 1;
-          for (; k * kP2PItem < fe && b + k < e; ++k) {
-            item_e0[b + k] = (uint32_t)(g0 + lane);
-            item_c0[b + k] = fb;
+          for (; k * len < fe && b + k < e; ++k) {
+            item[b + k].e0 = g0 + lane;
+            item[b + k].ne = (uint32_t)(e1 - g0 - lane);
+            item[b + k].c0 = fb;
           }
         }
         carry += (uint32_t)__shfl(incl, 63, 64);
       }
     }
+  }
+}
+
+__global__ __launch_bounds__(1024) void k_soft_total(int64_t items,
+                                                     const uint32_t* __restrict__ soft_pairs,
+                                                     uint64_t* __restrict__ total) {
+  __shared__ uint64_t sh[16];
+  uint64_t s = 0;
+  for (int64_t i = threadIdx.x; i < items; i += 1024) s += soft_pairs[i];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int k = 1; k < 16; ++k) s += sh[k];
+    *total = s;
   }
 }
 
@@ -624,7 +788,22 @@ __global__ void k_p2p_reduce(NearArgs a, int ls) {
   const uint32_t t0 = a.item_off[l], t1 = a.item_off[l + 1];
   const int i = j - a.info[a.leaf_node[l]].lo;
   double sx = 0.0, sy = 0.0, sz = 0.0, sp = 0.0;
-  for (uint32_t t = t0; t < t1; ++t) {
+  // eight items' loads in flight: a particle of a Plummer sphere's halo has
+  // hundreds of items, and its lane summed them one load latency at a time
+  // (309 us at 1e6)
+  uint32_t t = t0;
+  for (; t + 8 <= t1; t += 8) {
+    double2 u[8], v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const double2* q = reinterpret_cast<const double2*>(a.part + ((int64_t)(t + k) * ls + i) * 4);
+      u[k] = q[0];
+      v[k] = q[1];
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) { sx += u[k].x; sy += u[k].y; sz += v[k].x; sp += v[k].y; }
+  }
+  for (; t < t1; ++t) {
     const double* q = a.part + ((int64_t)t * ls + i) * 4;
     sx += q[0]; sy += q[1]; sz += q[2]; sp += q[3];
   }
@@ -682,8 +861,8 @@ __global__ __launch_bounds__(256) void k_momentum_final(int nb, const double* __
 
 #define WAVE_LAUNCH(LS, TG, WPE)                                           \
   do {                                                                     \
-    if (node_lists) k_p2p_wave<LS, true, TG, WPE, 1><<<nbl, 64, 0, s>>>(a); \
-    else k_p2p_wave<LS, false, TG, WPE, 1><<<nbl, 64, 0, s>>>(a);          \
+    if (node_lists) k_p2p_wave<LS, true, TG, WPE><<<nbl, 64, 0, s>>>(a); \
+    else k_p2p_wave<LS, false, TG, WPE><<<nbl, 64, 0, s>>>(a);          \
     record_mark(km.end, s);                                                \
     if (!km.skip_reduce) launch_p2p_reduce(a, LS, s);                      \
   } while (0)
@@ -703,14 +882,15 @@ void launch_p2p_items_count(bool node_lists, const NearArgs& a, uint32_t* src_to
   else k_p2p_items_count<false><<<a.nleaves, 64, 0, s>>>(a, src_total, item_cnt);
 }
 
-void launch_p2p_items_fill(bool node_lists, const NearArgs& a, int32_t* item_leaf,
-                           uint32_t* item_k, uint32_t* item_e0, uint32_t* item_c0, hipStream_t s) {
+void launch_p2p_items_fill(bool node_lists, const NearArgs& a, P2PItem* item, hipStream_t s) {
   if (a.nleaves <= 0) return;
   const unsigned nb = (unsigned)((a.nleaves + kFillLeaves - 1) / kFillLeaves);
-  if (node_lists)
-    k_p2p_items_fill<true><<<nb, 64, 0, s>>>(a, item_leaf, item_k, item_e0, item_c0);
-  else
-    k_p2p_items_fill<false><<<nb, 64, 0, s>>>(a, item_leaf, item_k, item_e0, item_c0);
+  if (node_lists) k_p2p_items_fill<true><<<nb, 64 * kFillLeaves, 0, s>>>(a, item);
+  else k_p2p_items_fill<false><<<nb, 64 * kFillLeaves, 0, s>>>(a, item);
+}
+
+void launch_soft_total(int64_t items, const uint32_t* soft_pairs, uint64_t* total, hipStream_t s) {
+  k_soft_total<<<1, 1024, 0, s>>>(items, soft_pairs, total);
 }
 
 void launch_p2p_reduce(const NearArgs& a, int ls, hipStream_t s) {
@@ -731,15 +911,18 @@ void launch_near(bool node_lists, int leaf_size, int variant, const NearArgs& a,
     if (!km.skip_reduce) launch_p2p_reduce(a, p2p_leaf_slots(leaf_size), s);
     return;
   }
-  // leaf_size <= 10: five targets per pass at four waves per SIMD; <= 16:
-  // six at four (the shapes that won on the polytrope and Plummer workloads);
-  // <= 32: eight at three
+  // The wave shape: eight targets per pass at three waves per SIMD (at leaf
+  // size 10 on the Plummer sphere and the polytrope of 1e6: 2.86 ms, with six
+  // at three 2.97, five or six at four, which spill, 2.95).  It addresses the
+  // particles by 32-bit byte offsets of 16 bytes each, so from 2^28 particles
+  // on shape 6 takes its place.
+  if (a.n >= (1 << 28) && variant != 6) variant = 6;
   if (leaf_size <= 10) {
     if (variant == 6) NEAR_LAUNCH(10, 5);
-    else WAVE_LAUNCH(10, 5, 4);
+    else WAVE_LAUNCH(10, 8, 3);
   } else if (leaf_size <= 16) {
     if (variant == 6) NEAR_LAUNCH(16, 8);
-    else WAVE_LAUNCH(16, 6, 4);
+    else WAVE_LAUNCH(16, 8, 3);
   } else if (leaf_size <= 32) {
     if (variant == 6) NEAR_LAUNCH(32, 8);
     else WAVE_LAUNCH(32, 8, 3);

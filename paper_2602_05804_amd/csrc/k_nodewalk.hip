@@ -624,9 +624,10 @@ __device__ void leaf_lists(const NodeWalkArgs& a, int l, uint32_t* stk) {
     // lists left for the second pass (none when they fit)
     a.leaf_m2l_cnt[l] = fits ? 0u : nm;
     a.leaf_p2p_cnt[l] = fits ? 0u : np + nq;
-    // P2P work items of the leaf: runs of at most kP2PItem source particles
+    // P2P work items of the leaf
     a.src_total[l] = ns;
-    const uint32_t k = (ns + kP2PItem - 1) / kP2PItem;
+    const uint32_t len = a.rule.len(vi.lo);
+    const uint32_t k = (ns + len - 1) / len;
     a.item_cnt[l] = k > 0 ? k : 1u;
   }
 }

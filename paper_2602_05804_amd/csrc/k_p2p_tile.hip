@@ -80,11 +80,9 @@ __global__ __launch_bounds__(64) void k_p2p_tile(NearArgs a) {
   const int lane = threadIdx.x;
   const uint32_t item = xcd_block(blockIdx.x, gridDim.x);
   if (item >= a.item_off[a.nleaves]) return;  // the grid is an upper bound
-  const int l = a.item_leaf[item];
-  const uint32_t kitem = a.item_k[item];
-  const int node = a.leaf_node[l];
-  const NodeInfo ti = a.info[node];
-  const int nt = uni(ti.cnt);  // 1 .. LS
+  const P2PItem it0 = a.item[item];
+  const int node = it0.node(), tlo = it0.lo;
+  const int nt = uni(it0.cnt());  // 1 .. LS
   const int ns = uni(min(64 / nt, kMaxStripes));
   const int s = lane / nt, t = lane - s * nt;
   const bool lane_ok = s < ns;
@@ -93,7 +91,7 @@ __global__ __launch_bounds__(64) void k_p2p_tile(NearArgs a) {
   // the stripe this lane reads a batch source for (lanes past the stripes
   // read stripe 0's and keep sums nobody reads: full steps need no masks)
   const int sq = lane_ok ? s : 0;
-  const int it = ti.lo + tq;
+  const int it = tlo + tq;
   const double xi = a.xs[it], yi = a.ys[it], zi = a.zs[it];
   const double hi = a.hs[it], hiinv = a.his[it];
   const double h4i = 4.0 * hi * hi;
@@ -115,8 +113,7 @@ __global__ __launch_bounds__(64) void k_p2p_tile(NearArgs a) {
   auto soft_pass = [&]() {
     const bool v = lane_ok && s < qlen;
     const int j = v ? sh.queue[tq][(qhead + s) & (kQueue - 1)] : it;
-    const double2* rj = reinterpret_cast<const double2*>(a.p4 + 4 * (int64_t)j);
-    const double2 xy = rj[0], zm = rj[1];
+    const double2 xy = a.pxy[j], zm = a.pzm[j];
     const double hj = a.hs[j], hjinv = a.his[j];
     const double dx = xi - xy.x, dy = yi - xy.y, dz = zi - zm.x;
     const double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
@@ -192,24 +189,12 @@ __global__ __launch_bounds__(64) void k_p2p_tile(NearArgs a) {
     }
   };
 
-  uint64_t e0, e1;
-  const int32_t* list;
-  if (NODE) {
-    e0 = a.node_p2p_off[node];
-    e1 = e0 + a.node_p2p_cnt[node];
-    list = reinterpret_cast<const int32_t*>(a.node_p2p_pool);
-  } else {
-    e0 = a.p2p_off[l];
-    e1 = a.p2p_off[l + 1];
-    list = a.p2p_list;
-  }
   // this item's run [f_lo, f_hi) of the leaf's flattened sources, from the
   // list entry that holds its first source
-  const uint32_t f_lo = kitem * kP2PItem;
-  const uint32_t ftot = a.src_total[l];
-  const uint32_t f_hi = f_lo + kP2PItem < ftot ? f_lo + kP2PItem : ftot;
-  uint32_t carry = 0;
-  if (kitem > 0) { e0 = a.item_e0[item]; carry = a.item_c0[item]; }
+  const uint64_t e0 = it0.e0, e1 = e0 + it0.ne;
+  const int32_t* list = NODE ? reinterpret_cast<const int32_t*>(a.node_p2p_pool) : a.p2p_list;
+  const uint32_t f_lo = it0.f0, f_hi = it0.f1;
+  uint32_t carry = it0.c0;
   for (uint64_t c0 = e0; c0 < e1; c0 += 64) {
     // 64 list entries: their particle ranges in the flattened order, clipped
     // to the run: [pre, pre + cnt) of this group's sources start at particle lo
@@ -255,10 +240,9 @@ __global__ __launch_bounds__(64) void k_p2p_tile(NearArgs a) {
       __syncthreads();
       // batches of 64 sources; the next batch's records load during the steps
       auto load_src = [&](int u0, int& j, double2& xy, double2& zm, double& hj) {
-        j = u0 + lane < wn ? (int)sh.sidx[u0 + lane] : ti.lo;
-        const double2* rj = reinterpret_cast<const double2*>(a.p4 + 4 * (int64_t)j);
-        xy = rj[0];
-        zm = rj[1];
+        j = u0 + lane < wn ? (int)sh.sidx[u0 + lane] : tlo;
+        xy = a.pxy[j];
+        zm = a.pzm[j];
         hj = a.hs[j];
       };
       int j;
@@ -319,7 +303,7 @@ __global__ __launch_bounds__(64) void k_p2p_tile(NearArgs a) {
     double* o = a.part + (item * (int64_t)LS + lane) * 4;
     o[0] = sx; o[1] = sy; o[2] = sz; o[3] = sp;
   }
-  if (lane == 0 && nsoft) atomicAdd(a.soft_pairs, (unsigned long long)nsoft);
+  if (lane == 0) a.soft_pairs[item] = nsoft;
 }
 
 }  // namespace

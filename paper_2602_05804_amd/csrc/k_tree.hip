@@ -301,7 +301,8 @@ __global__ void k_gather(int n, const uint32_t* __restrict__ perm, const double*
                          double* __restrict__ xs, double* __restrict__ ys,
                          double* __restrict__ zs, double* __restrict__ ms,
                          double* __restrict__ hs, double* __restrict__ his,
-                         double* __restrict__ p4) {
+                         double* __restrict__ h4, double2* __restrict__ pxy,
+                         double2* __restrict__ pzm) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   int64_t j = perm[i];
@@ -313,9 +314,9 @@ __global__ void k_gather(int n, const uint32_t* __restrict__ perm, const double*
   ms[i] = pm;
   hs[i] = ph;
   his[i] = phi;
-  double2* r = reinterpret_cast<double2*>(p4 + 4 * (int64_t)i);
-  r[0] = make_double2(px, py);
-  r[1] = make_double2(pz, pm);
+  h4[i] = 4.0 * ph * ph;
+  pxy[i] = make_double2(px, py);
+  pzm[i] = make_double2(pz, pm);
 }
 
 // ---- binary radix tree (Karras 2012) ----------------------------------------
@@ -670,8 +671,10 @@ void launch_node_flags(int nn, const NodeInfo* info, const uint32_t* sys, uint8_
 
 void launch_gather(int n, const uint32_t* perm, const double* x, const double* m,
                    const double* h, double* xs, double* ys, double* zs, double* ms,
-                   double* hs, double* his, double* p4, hipStream_t s) {
-  k_gather<<<blocks_for(n, 256), 256, 0, s>>>(n, perm, x, m, h, xs, ys, zs, ms, hs, his, p4);
+                   double* hs, double* his, double* h4, double2* pxy, double2* pzm,
+                   hipStream_t s) {
+  k_gather<<<blocks_for(n, 256), 256, 0, s>>>(n, perm, x, m, h, xs, ys, zs, ms, hs, his, h4, pxy,
+                                             pzm);
 }
 
 void launch_karras(int n, const uint64_t* key, const uint32_t* sys, const int32_t* sys_start,

@@ -27,7 +27,7 @@ struct DevBuf {
 enum BufId {
   B_BOXPART, B_BOX, B_STATUS, B_SMALL,
   B_KEY0, B_KEY1, B_VAL0, B_VAL1, B_HIST, B_SCANTMP,
-  B_XS, B_YS, B_ZS, B_MS, B_HS, B_HIS, B_P4,
+  B_XS, B_YS, B_ZS, B_MS, B_HS, B_HIS, B_H4, B_P4,
   B_KFIRST, B_KLAST, B_KLEFT, B_KRIGHT, B_KPAR, B_KSIDE, B_KEPT,
   B_LFLAG, B_LAT, B_INFO, B_REC, B_L2BITS, B_CHUNK,
   B_LEAFNODE, B_LEAFDEPTH, B_PLEAF,
@@ -38,14 +38,14 @@ enum BufId {
   B_M2LPOOL, B_NEXP, B_P2PPOOL, B_WALKTOT,
   B_REC32, B_PF32, B_PH32,
   B_SYSOFF, B_BOXES, B_SYS, B_SYSS, B_SYSSTART, B_SKEY0, B_SKEY1, B_SPOS0, B_SPOS1, B_NFLAG,
-  B_LN, B_ITEMCNT, B_ITEMOFF, B_ITEMLEAF, B_ITEMK, B_PART, B_SRCTOT, B_SOFTCNT, B_ITEME0, B_ITEMC0, B_EXTMAP,
+  B_LN, B_ITEMCNT, B_ITEMOFF, B_ITEM, B_PART, B_SRCTOT, B_SOFTCNT, B_EXTMAP,
   B_LWM2LCNT, B_LWP2PCNT, B_LWM2LOFF, B_LWP2POFF, B_DIRPART, B_OVFLEAF, B_BIGPLAIN,
   B_COUNT
 };
 
 // small device scalars (B_SMALL, u64 slots)
 enum SmallId { S_NKEPT = 0, S_NLEAVES, S_MAXDEPTH, S_NITEMS, S_M2LTOT, S_P2PTOT, S_PAIRTOT,
-               S_DOFFTOT, S_SORTTOT, S_L2LTOT, S_COUNT };
+               S_DOFFTOT, S_SORTTOT, S_L2LTOT, S_SOFTTOT, S_COUNT };
 
 }  // namespace
 
@@ -83,6 +83,7 @@ struct sfmm_ctx {
   std::vector<uint32_t> level_off;
   std::vector<uint32_t> level_int;  // end of each level's internal nodes
   uint64_t m2l_cap = 0, p2p_cap = 0;
+  int64_t soft_items = 0;       // items whose softened pairs the last solve counted
   int64_t items_from_walk = 0;  // P2P work items counted by the level walk
   uint32_t stack_cap = 0;
   // per-leaf list slots of the level walk (entries; doubled, up to kSlotMax,
@@ -239,7 +240,7 @@ int do_build(sfmm_ctx* ctx, int64_t n64, const double* x, const double* m, const
       {B_SCANTMP, sizeof(uint64_t) * scan_tmp_elems(std::max<int64_t>(256 * (int64_t)radix_blocks(n), 2 * (int64_t)n + 2))},
       {B_XS, sizeof(double) * n}, {B_YS, sizeof(double) * n}, {B_ZS, sizeof(double) * n},
       {B_MS, sizeof(double) * n}, {B_HS, sizeof(double) * n}, {B_HIS, sizeof(double) * n},
-      {B_P4, sizeof(double) * 4 * n},
+      {B_H4, sizeof(double) * n}, {B_P4, sizeof(double) * 4 * n},
       {B_KFIRST, sizeof(int32_t) * n}, {B_KLAST, sizeof(int32_t) * n},
       {B_KLEFT, sizeof(int32_t) * n}, {B_KRIGHT, sizeof(int32_t) * n},
       {B_KPAR, sizeof(int32_t) * n}, {B_KSIDE, sizeof(int32_t) * n},
@@ -310,7 +311,7 @@ int do_build(sfmm_ctx* ctx, int64_t n64, const double* x, const double* m, const
   const uint32_t* perm = P<uint32_t>(ctx, B_VAL0);
   launch_gather(n, perm, x, m, h, P<double>(ctx, B_XS), P<double>(ctx, B_YS), P<double>(ctx, B_ZS),
                 P<double>(ctx, B_MS), P<double>(ctx, B_HS), P<double>(ctx, B_HIS),
-                P<double>(ctx, B_P4), s);
+                P<double>(ctx, B_H4), P<double2>(ctx, B_P4), P<double2>(ctx, B_P4) + n, s);
   NodeInfo* info = P<NodeInfo>(ctx, B_INFO);
   int32_t* leaf_node = P<int32_t>(ctx, B_LEAFNODE);
   // ---- topology
@@ -419,6 +420,17 @@ int do_build(sfmm_ctx* ctx, int64_t n64, const double* x, const double* m, const
   HIPCHK(hipGetLastError());
   ctx->have_tree = true;
   return SFMM_OK;
+}
+
+// the lengths of the P2P work items of the last build's leaves
+P2PItemRule item_rule(sfmm_ctx* ctx) {
+  P2PItemRule r{};
+  r.n = (int)ctx->n;
+  if (ctx->nsys > 1) {
+    r.sys = P<uint32_t>(ctx, B_SYSS);
+    r.sys_off = P<int64_t>(ctx, B_SYSOFF);
+  }
+  return r;
 }
 
 // Algorithm 1 per leaf: count pass, list sizes to the host, fill pass
@@ -599,6 +611,7 @@ int walk_levels(sfmm_ctx* ctx, double theta) {
     a.src_total = P<uint32_t>(ctx, B_SRCTOT);
     a.item_cnt = P<uint32_t>(ctx, B_ITEMCNT);
     a.item_off = P<uint32_t>(ctx, B_ITEMOFF);
+    a.rule = item_rule(ctx);
     // internal nodes level by level, then every leaf
     uint32_t rank0 = 0;
     for (int k = 0; k <= ctx->maxdepth; ++k) {
@@ -805,7 +818,9 @@ int do_walk_and_eval(sfmm_ctx* ctx, double theta, int precision, const double* m
   a.ms = P<double>(ctx, B_MS);
   a.hs = P<double>(ctx, B_HS);
   a.his = P<double>(ctx, B_HIS);
-  a.p4 = P<double>(ctx, B_P4);
+  a.h4 = P<double>(ctx, B_H4);
+  a.pxy = P<double2>(ctx, B_P4);
+  a.pzm = a.pxy + n;
   a.far = f.far;
   a.rec = f.rec;
   a.rec_stride = rec_stride(ctx->order);
@@ -814,10 +829,7 @@ int do_walk_and_eval(sfmm_ctx* ctx, double theta, int precision, const double* m
   a.include_self = ctx->cfg.include_self_potential;
   a.acc = acc;
   a.pot = pot;
-  if ((rc = ensure(ctx, B_SOFTCNT, sizeof(unsigned long long)))) return rc;
-  a.soft_pairs = P<unsigned long long>(ctx, B_SOFTCNT);
-  // P2P work items: runs of at most kP2PItem flattened source particles of
-  // one leaf; their number is read back to size the partial sums
+  // P2P work items: runs of flattened source particles of one leaf; their number is read back to size the partial sums
   int64_t items = 0;
   if (ctx->cfg.leaf_size <= 32) {
     // P2P work items: the level walk has counted them (and read their total
@@ -826,6 +838,7 @@ int do_walk_and_eval(sfmm_ctx* ctx, double theta, int precision, const double* m
     uint32_t* item_off = P<uint32_t>(ctx, B_ITEMOFF);
     a.src_total = P<uint32_t>(ctx, B_SRCTOT);
     a.item_off = item_off;
+    a.rule = item_rule(ctx);
     if (level) {
       items = ctx->items_from_walk;
     } else {
@@ -840,17 +853,16 @@ int do_walk_and_eval(sfmm_ctx* ctx, double theta, int precision, const double* m
     }
     const int ls = p2p_leaf_slots(ctx->cfg.leaf_size);
     struct { int id; size_t bytes; } need5[] = {
-        {B_ITEMLEAF, sizeof(int32_t) * (size_t)items}, {B_ITEMK, sizeof(uint32_t) * (size_t)items},
-        {B_ITEME0, sizeof(uint32_t) * (size_t)items}, {B_ITEMC0, sizeof(uint32_t) * (size_t)items},
+        {B_ITEM, sizeof(P2PItem) * (size_t)items}, {B_SOFTCNT, sizeof(uint32_t) * (size_t)items},
         {B_PART, sizeof(double) * 4 * (size_t)ls * (size_t)items}};
     for (auto& q : need5)
       if ((rc = ensure(ctx, q.id, q.bytes))) return rc;
-    a.item_leaf = P<int32_t>(ctx, B_ITEMLEAF);
-    a.item_k = P<uint32_t>(ctx, B_ITEMK);
+    a.item = P<P2PItem>(ctx, B_ITEM);
     a.part = P<double>(ctx, B_PART);
-    a.item_e0 = P<uint32_t>(ctx, B_ITEME0);
-    a.item_c0 = P<uint32_t>(ctx, B_ITEMC0);
+    a.soft_pairs = P<uint32_t>(ctx, B_SOFTCNT);
   }
+  // (the particle-per-thread shape counts no softened pairs)
+  ctx->soft_items = ctx->near_variant == 1 ? 0 : items;
   // the P2P kernel runs beside the far field when it writes only item partial
   // sums: the reduction, which adds the far field, then waits for both
   const bool overlap = ctx->overlap != 0 && ctx->cfg.leaf_size <= 32 && ctx->near_variant != 1;
@@ -864,10 +876,8 @@ int do_walk_and_eval(sfmm_ctx* ctx, double theta, int precision, const double* m
   km.end = phase_event(ctx, 6, 1);
   km.skip_reduce = overlap;
   auto near_field = [&](hipStream_t ns) -> int {
-    HIPCHK(hipMemsetAsync(a.soft_pairs, 0, sizeof(unsigned long long), ns));
     if (ctx->cfg.leaf_size <= 32)
-      launch_p2p_items_fill(level, a, P<int32_t>(ctx, B_ITEMLEAF), P<uint32_t>(ctx, B_ITEMK),
-                            P<uint32_t>(ctx, B_ITEME0), P<uint32_t>(ctx, B_ITEMC0), ns);
+      launch_p2p_items_fill(level, a, P<P2PItem>(ctx, B_ITEM), ns);
     if (f32) launch_near32(ctx->order, level, ctx->cfg.leaf_size, ctx->near_variant, a,
                           P<float4>(ctx, B_PF32), P<float2>(ctx, B_PH32), items, ns, km);
     else launch_near(level, ctx->cfg.leaf_size, ctx->near_variant, a, items, ns, km);
@@ -1223,12 +1233,15 @@ int sfmm_get_stats(sfmm_ctx* ctx, sfmm_stats* out) {
     out->n_p2p_leaf_pairs = (int64_t)ctx->p2p_total;
     out->n_p2p_pairs = (int64_t)ctx->pair_total;
     out->n_m2l_unique = (int64_t)ctx->m2l_unique;
-    unsigned long long soft = 0;
-    if (ctx->buf[B_SOFTCNT].p &&
-        (hipMemcpyAsync(&soft, ctx->buf[B_SOFTCNT].p, sizeof(soft), hipMemcpyDeviceToHost,
-                        ctx->stream) != hipSuccess ||
-         hipStreamSynchronize(ctx->stream) != hipSuccess))
-      return fail(ctx, SFMM_EDEVICE, "statistics copy failed");
+    uint64_t soft = 0;
+    if (ctx->soft_items > 0) {
+      uint64_t* total = P<uint64_t>(ctx, B_SMALL) + S_SOFTTOT;
+      launch_soft_total(ctx->soft_items, P<uint32_t>(ctx, B_SOFTCNT), total, ctx->stream);
+      if (hipMemcpyAsync(&soft, total, sizeof(soft), hipMemcpyDeviceToHost, ctx->stream) !=
+              hipSuccess ||
+          hipStreamSynchronize(ctx->stream) != hipSuccess)
+        return fail(ctx, SFMM_EDEVICE, "statistics copy failed");
+    }
     out->n_p2p_soft_pairs = (int64_t)soft;
   }
   if (ctx->have_mom && ctx->n > 0) {

@@ -109,11 +109,12 @@ void radix_sort(int n, uint64_t* key0, uint32_t* val0, uint64_t* key1, uint32_t*
 void radix_pass(int n, const uint64_t* kin, const uint32_t* vin, uint64_t* kout, uint32_t* vout,
                 int shift, uint32_t* hist, uint32_t* hist_tmp, uint32_t* scratch_total,
                 hipStream_t s);
-// sorted particle data: separate arrays and one 32-byte record per particle
-// (p4: x, y, z, m)
+// sorted particle data: separate arrays and two of 16 bytes per particle
+// (pxy: x, y; pzm: z, m)
 void launch_gather(int n, const uint32_t* perm, const double* x, const double* m,
                    const double* h, double* xs, double* ys, double* zs, double* ms,
-                   double* hs, double* his, double* p4, hipStream_t s);
+                   double* hs, double* his, double* h4, double2* pxy, double2* pzm,
+                   hipStream_t s);
 // sys / sys_start: system of each sorted position and first position of each
 // system (nullptr for a single system)
 void launch_karras(int n, const uint64_t* key, const uint32_t* sys, const int32_t* sys_start,
@@ -178,6 +179,45 @@ struct WalkArgs {
 void launch_walk(const WalkArgs& a, int maxdepth, bool fill, hipStream_t s);
 void launch_leaf_doff(int nleaves, const int32_t* leaf_depth, uint64_t* out, hipStream_t s);
 
+// ---- P2P work items ----------------------------------------------------------
+// A leaf's flattened P2P sources are cut into runs of at most this many.  Long
+// runs amortise an item's set-up (its targets, its list scan, the reduction of
+// its sums) over many sources; a small system has too few leaves to fill the
+// chip with them, so its runs are shorter.  The near field at runs of 256 / 512
+// / 1024 / 2048: Plummer sphere of 1e3 43 / 61 / 95 / 94 us, of 1e4 114 / 126 /
+// 156 / 228 us, polytrope of 1e5 246 / 221 / 200 / 203 us, Plummer sphere of
+// 1e6 5.27 / 4.00 / 3.46 / 3.12 ms.  The length follows from the size of the
+// leaf's own system alone, so that a system solved together with others is
+// summed in the same order as alone.
+constexpr uint32_t kP2PItem = 2048;  // the longest run
+// One work item, all a P2P wave needs to begin (one load instead of a chain
+// of five through the leaf, its node and its list)
+struct P2PItem {
+  uint64_t e0;   // list entry holding the run's first source
+  uint32_t ne;   // list entries from there on
+  uint32_t c0;   // that entry's start in the leaf's flattened sources
+  uint32_t f0;   // the run [f0, f1) of the flattened sources
+  uint32_t f1;
+  int32_t lo;    // the leaf's first particle
+  uint32_t nd;   // its node (kSrcBits bits) and its particle count above
+  __device__ __forceinline__ int node() const { return (int)(nd & kSrcMask); }
+  __device__ __forceinline__ int cnt() const { return (int)(nd >> kSrcBits); }
+};
+static_assert(sizeof(P2PItem) == 32, "two 16-byte loads");
+struct P2PItemRule {
+  int n;                    // particles, for a single system
+  const uint32_t* sys;      // several systems: the system of each sorted particle
+  const int64_t* sys_off;   // and their offsets (nullptr for a single system)
+  __device__ __forceinline__ uint32_t len(int lo) const {
+    int64_t k = n;
+    if (sys) {
+      const uint32_t s = sys[lo];
+      k = sys_off[s + 1] - sys_off[s];
+    }
+    return k <= 2048 ? 256u : k <= 16384 ? 512u : k <= 131072 ? 1024u : kP2PItem;
+  }
+};
+
 // ---- level-synchronous node walk -------------------------------------------------
 struct NodeWalkArgs {
   const NodeInfo* info;
@@ -230,6 +270,7 @@ struct NodeWalkArgs {
   // per leaf: particles over its P2P entries, P2P work items and their offsets
   // ([nleaves + 1], the last entry the total)
   uint32_t *src_total, *item_cnt, *item_off;
+  P2PItemRule rule;
   uint32_t stack_cap;  // LDS lowering stack, entries
   int* status;
 };
@@ -324,7 +365,8 @@ struct NearArgs {
   const int32_t* leaf_node;  // (node lists)
   const uint32_t *node_p2p_off, *node_p2p_cnt, *node_p2p_pool;
   const double *xs, *ys, *zs, *ms, *hs, *his;  // his = 1/h
-  const double* p4;  // [n][4] x, y, z, m (one record per particle)
+  const double* h4;            // 4 h^2
+  const double2 *pxy, *pzm;  // [n] x, y and z, m (16-byte loads, contiguous over a run)
   const double* far;
   const double* rec;  // node records (leaf centres, FP32C; leaf spheres)
   int rec_stride;     // doubles per node record
@@ -335,27 +377,25 @@ struct NearArgs {
   double* pot;  // caller order [n]
   // work items (leaf_size <= 32): a leaf's P2P sources, flattened over its
   // list entries (leaves, or whole subtrees), are cut into runs of at most
-  // kP2PItem source particles, one wave per run; each item writes partial
+  // p2p_item_len source particles, one wave per run; each item writes partial
   // sums for the leaf's targets, which a second kernel adds in item order
   const uint32_t* src_total;  // per leaf: particles over its P2P list entries
   const uint32_t* item_off;  // [nleaves + 1] first item of each leaf; [nleaves] = total
-  const int32_t* item_leaf;  // [items] leaf of each item
-  const uint32_t* item_k;    // [items] index of the item within its leaf
-  const uint32_t* item_e0;   // [items] (k > 0) list entry holding the item's first source
-  const uint32_t* item_c0;   // [items] (k > 0) that entry's start in the flattened order
+  const P2PItem* item;       // [items]
+  P2PItemRule rule;
   double* part;              // [items][LS][4] partial field (x, y, z) and potential
-  unsigned long long* soft_pairs;  // count of pairs inside a kernel (queueing shape)
+  // [items] pairs of each item inside a kernel (summed when the statistics are
+  // asked for: one total for all items, added atomically, took 4 ns an item)
+  uint32_t* soft_pairs;
 };
-constexpr uint32_t kP2PItem = 2048;
 // particles over each leaf's P2P entries (src_total) and the number of
 // items of each leaf (item_cnt), nleaves entries each; one wave per leaf
 void launch_p2p_items_count(bool node_lists, const NearArgs& a, uint32_t* src_total,
                             uint32_t* item_cnt, hipStream_t s);
-// item_leaf / item_k from the scanned item offsets
-// item_leaf / item_k of every item; item_e0 / item_c0 of the items after a
-// leaf's first (one wave per leaf)
-void launch_p2p_items_fill(bool node_lists, const NearArgs& a, int32_t* item_leaf,
-                           uint32_t* item_k, uint32_t* item_e0, uint32_t* item_c0, hipStream_t s);
+// sum of the items' softened pairs into *total
+void launch_soft_total(int64_t items, const uint32_t* soft_pairs, uint64_t* total, hipStream_t s);
+// the items from their scanned offsets
+void launch_p2p_items_fill(bool node_lists, const NearArgs& a, P2PItem* item, hipStream_t s);
 // target slots per P2P work item: the kernels are built for leaves of at most
 // 10, 16 and 32 particles
 inline int p2p_leaf_slots(int leaf_size) { return leaf_size <= 10 ? 10 : leaf_size <= 16 ? 16 : 32; }
