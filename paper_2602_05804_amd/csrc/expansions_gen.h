@@ -1,6 +1,7 @@
 // Generated by gen_expansions.py -- do not edit.
 // Cartesian expansion kernels for orders 0..4 (see the generator's docstring).
 #pragma once
+#include "softening.h"
 namespace sfmm {
 template <int P> struct Exp;
 template <> struct Exp<0> {
@@ -47,9 +48,9 @@ template <> struct Exp<0> {
     }
   }
   static constexpr int FLOPS_M2L = 24;  // + one rsqrt
-  __device__ __forceinline__ static void m2l_add_f32(const float* r, const float* Q, double* local) {
+  __device__ __forceinline__ static void m2l_add_f32(const float* r, const float* Q, double* local, bool ok = true) {
     const float r2 = r[0] * r[0] + r[1] * r[1] + r[2] * r[2];
-    const float rinv = __frsqrt_rn(r2);
+    const float rinv = ok ? __frsqrt_rn(r2) : 0.0f;
     const float rinv2 = rinv * rinv;
     float D[4];
     D[0] = rinv;
@@ -57,22 +58,58 @@ template <> struct Exp<0> {
     D[1] = (1.0f * r[0] * D[0]) * sn1;
     D[2] = (1.0f * r[1] * D[0]) * sn1;
     D[3] = (1.0f * r[2] * D[0]) * sn1;
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[1] * Q[0];
       local[0] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[2] * Q[0];
       local[1] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[3] * Q[0];
       local[2] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[0] * Q[0];
       local[3] += (double)s;
     }
+  }
+  static constexpr int NQR = 1;   // independent moments
+  static constexpr int NLR = 4;  // S then X
+  __device__ __forceinline__ static void reduce(const double* Q, double* Qr) {
+    Qr[0] = Q[0];
+  }
+  __device__ __forceinline__ static void m2l_h(const double* r, const double* Qr, double* lr, bool ok) {
+    const double r2 = fma(r[0], r[0], fma(r[1], r[1], r[2] * r[2]));
+    const double ri = rsqrt_refined(r2);
+    const double rinv = ok ? ri : 0.0;
+    const double s = rinv * rinv;
+    const double R0_000 = rinv;
+    const double R1_000 = R0_000 * (-1.0 * s);
+    lr[0] = fma(R0_000, Qr[0], lr[0]);
+    const double R0_100 = r[0] * R1_000;
+    lr[1] = fma(R0_100, Qr[0], lr[1]);
+    const double R0_010 = r[1] * R1_000;
+    lr[2] = fma(R0_010, Qr[0], lr[2]);
+    const double R0_001 = r[2] * R1_000;
+    lr[3] = fma(R0_001, Qr[0], lr[3]);
+  }
+  static constexpr int FLOPS_M2L_H = 18;  // + one refined rsqrt
+  __device__ __forceinline__ static void expand(const double* lr, double* local) {
+    double t[4];
+    t[0] = lr[0];
+    local[3] = t[0];
+    t[1] = lr[1];
+    local[0] = t[1];
+    t[2] = lr[2];
+    local[1] = t[2];
+    t[3] = lr[3];
+    local[2] = t[3];
   }
   __device__ __forceinline__ static void m2l_pair(const double* r, const double* QS,
                                                     const double* QTs, double* local,
@@ -241,9 +278,9 @@ template <> struct Exp<1> {
     }
   }
   static constexpr int FLOPS_M2L = 97;  // + one rsqrt
-  __device__ __forceinline__ static void m2l_add_f32(const float* r, const float* Q, double* local) {
+  __device__ __forceinline__ static void m2l_add_f32(const float* r, const float* Q, double* local, bool ok = true) {
     const float r2 = r[0] * r[0] + r[1] * r[1] + r[2] * r[2];
-    const float rinv = __frsqrt_rn(r2);
+    const float rinv = ok ? __frsqrt_rn(r2) : 0.0f;
     const float rinv2 = rinv * rinv;
     float D[10];
     D[0] = rinv;
@@ -258,6 +295,7 @@ template <> struct Exp<1> {
     D[7] = (6.0f * r[1] * D[2] + 2.0f * D[0]) * sn2;
     D[8] = (3.0f * r[1] * D[3] + 3.0f * r[2] * D[2]) * sn2;
     D[9] = (6.0f * r[2] * D[3] + 2.0f * D[0]) * sn2;
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[1] * Q[0];
       local[10] -= (double)s;
@@ -266,6 +304,7 @@ template <> struct Exp<1> {
       s = fmaf(D[6], Q[3], s);
       local[0] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[2] * Q[0];
       local[11] -= (double)s;
@@ -274,6 +313,7 @@ template <> struct Exp<1> {
       s = fmaf(D[8], Q[3], s);
       local[1] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[3] * Q[0];
       local[12] -= (double)s;
@@ -282,30 +322,37 @@ template <> struct Exp<1> {
       s = fmaf(D[9], Q[3], s);
       local[2] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[4] * Q[0];
       local[3] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[5] * Q[0];
       local[4] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[6] * Q[0];
       local[5] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[7] * Q[0];
       local[6] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[8] * Q[0];
       local[7] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[9] * Q[0];
       local[8] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[0] * Q[0];
       s = fmaf(D[1], Q[1], s);
@@ -313,6 +360,86 @@ template <> struct Exp<1> {
       s = fmaf(D[3], Q[3], s);
       local[9] += (double)s;
     }
+  }
+  static constexpr int NQR = 4;   // independent moments
+  static constexpr int NLR = 12;  // S then X
+  __device__ __forceinline__ static void reduce(const double* Q, double* Qr) {
+    Qr[0] = Q[0];
+    Qr[1] = Q[1];
+    Qr[2] = Q[2];
+    Qr[3] = Q[3];
+  }
+  __device__ __forceinline__ static void m2l_h(const double* r, const double* Qr, double* lr, bool ok) {
+    const double r2 = fma(r[0], r[0], fma(r[1], r[1], r[2] * r[2]));
+    const double ri = rsqrt_refined(r2);
+    const double rinv = ok ? ri : 0.0;
+    const double s = rinv * rinv;
+    const double R0_000 = rinv;
+    const double R1_000 = R0_000 * (-1.0 * s);
+    const double R2_000 = R1_000 * (-3.0 * s);
+    lr[0] = fma(R0_000, Qr[0], lr[0]);
+    const double R0_100 = r[0] * R1_000;
+    lr[0] = fma(R0_100, Qr[1], lr[0]);
+    lr[1] = fma(R0_100, Qr[0], lr[1]);
+    const double R0_010 = r[1] * R1_000;
+    lr[0] = fma(R0_010, Qr[2], lr[0]);
+    lr[2] = fma(R0_010, Qr[0], lr[2]);
+    const double R0_001 = r[2] * R1_000;
+    lr[0] = fma(R0_001, Qr[3], lr[0]);
+    lr[3] = fma(R0_001, Qr[0], lr[3]);
+    const double R1_100 = r[0] * R2_000;
+    const double R0_200 = fma(r[0], R1_100, R1_000);
+    lr[4] = fma(R0_200, Qr[1], lr[4]);
+    lr[7] = fma(R0_200, Qr[0], lr[7]);
+    const double R1_010 = r[1] * R2_000;
+    const double R0_110 = r[0] * R1_010;
+    lr[4] = fma(R0_110, Qr[2], lr[4]);
+    lr[5] = fma(R0_110, Qr[1], lr[5]);
+    lr[8] = fma(R0_110, Qr[0], lr[8]);
+    __builtin_amdgcn_sched_barrier(0);
+    const double R0_101 = r[2] * R1_100;
+    lr[4] = fma(R0_101, Qr[3], lr[4]);
+    lr[6] = fma(R0_101, Qr[1], lr[6]);
+    lr[9] = fma(R0_101, Qr[0], lr[9]);
+    const double R0_020 = fma(r[1], R1_010, R1_000);
+    lr[5] = fma(R0_020, Qr[2], lr[5]);
+    lr[10] = fma(R0_020, Qr[0], lr[10]);
+    const double R0_011 = r[2] * R1_010;
+    lr[5] = fma(R0_011, Qr[3], lr[5]);
+    lr[6] = fma(R0_011, Qr[2], lr[6]);
+    lr[11] = fma(R0_011, Qr[0], lr[11]);
+    const double R0_002 = -(R0_200 + R0_020);
+    lr[6] = fma(R0_002, Qr[3], lr[6]);
+  }
+  static constexpr int FLOPS_M2L_H = 64;  // + one refined rsqrt
+  __device__ __forceinline__ static void expand(const double* lr, double* local) {
+    double t[10];
+    t[0] = lr[0];
+    local[9] = t[0];
+    t[1] = -lr[1];
+    local[10] = t[1];
+    t[2] = -lr[2];
+    local[11] = t[2];
+    t[3] = -lr[3];
+    local[12] = t[3];
+    t[1] = (lr[1] + lr[4]);
+    local[0] = t[1];
+    t[2] = (lr[2] + lr[5]);
+    local[1] = t[2];
+    t[3] = (lr[3] + lr[6]);
+    local[2] = t[3];
+    t[4] = -lr[7];
+    local[3] = t[4];
+    t[5] = -lr[8];
+    local[4] = t[5];
+    t[6] = -lr[9];
+    local[5] = t[6];
+    t[7] = -lr[10];
+    local[6] = t[7];
+    t[8] = -lr[11];
+    local[7] = t[8];
+    t[9] = -(t[4] + t[7]);
+    local[8] = t[9];
   }
   __device__ __forceinline__ static void m2l_pair(const double* r, const double* QS,
                                                     const double* QTs, double* local,
@@ -704,9 +831,9 @@ template <> struct Exp<2> {
     }
   }
   static constexpr int FLOPS_M2L = 280;  // + one rsqrt
-  __device__ __forceinline__ static void m2l_add_f32(const float* r, const float* Q, double* local) {
+  __device__ __forceinline__ static void m2l_add_f32(const float* r, const float* Q, double* local, bool ok = true) {
     const float r2 = r[0] * r[0] + r[1] * r[1] + r[2] * r[2];
-    const float rinv = __frsqrt_rn(r2);
+    const float rinv = ok ? __frsqrt_rn(r2) : 0.0f;
     const float rinv2 = rinv * rinv;
     float D[20];
     D[0] = rinv;
@@ -732,6 +859,7 @@ template <> struct Exp<2> {
     D[17] = (10.0f * r[1] * D[8] + 4.0f * D[3] + 5.0f * r[2] * D[7]) * sn3;
     D[18] = (5.0f * r[1] * D[9] + 10.0f * r[2] * D[8] + 4.0f * D[2]) * sn3;
     D[19] = (15.0f * r[2] * D[9] + 12.0f * D[3]) * sn3;
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[1] * Q[0];
       s = fmaf(D[4], Q[1], s);
@@ -746,6 +874,7 @@ template <> struct Exp<2> {
       s = fmaf(D[15], Q[9], s);
       local[0] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[2] * Q[0];
       s = fmaf(D[5], Q[1], s);
@@ -760,6 +889,7 @@ template <> struct Exp<2> {
       s = fmaf(D[18], Q[9], s);
       local[1] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[3] * Q[0];
       s = fmaf(D[6], Q[1], s);
@@ -774,6 +904,7 @@ template <> struct Exp<2> {
       s = fmaf(D[19], Q[9], s);
       local[2] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[4] * Q[0];
       local[23] += (double)s;
@@ -782,6 +913,7 @@ template <> struct Exp<2> {
       s = fmaf(D[12], Q[3], s);
       local[3] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[5] * Q[0];
       local[24] += (double)s;
@@ -790,6 +922,7 @@ template <> struct Exp<2> {
       s = fmaf(D[14], Q[3], s);
       local[4] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[6] * Q[0];
       local[25] += (double)s;
@@ -798,6 +931,7 @@ template <> struct Exp<2> {
       s = fmaf(D[15], Q[3], s);
       local[5] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[7] * Q[0];
       local[26] += (double)s;
@@ -806,6 +940,7 @@ template <> struct Exp<2> {
       s = fmaf(D[17], Q[3], s);
       local[6] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[8] * Q[0];
       local[27] += (double)s;
@@ -814,6 +949,7 @@ template <> struct Exp<2> {
       s = fmaf(D[18], Q[3], s);
       local[7] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[9] * Q[0];
       local[28] += (double)s;
@@ -822,46 +958,57 @@ template <> struct Exp<2> {
       s = fmaf(D[19], Q[3], s);
       local[8] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[10] * Q[0];
       local[9] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[11] * Q[0];
       local[10] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[12] * Q[0];
       local[11] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[13] * Q[0];
       local[12] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[14] * Q[0];
       local[13] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[15] * Q[0];
       local[14] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[16] * Q[0];
       local[15] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[17] * Q[0];
       local[16] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[18] * Q[0];
       local[17] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[19] * Q[0];
       local[18] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[0] * Q[0];
       s = fmaf(D[1], Q[1], s);
@@ -875,6 +1022,183 @@ template <> struct Exp<2> {
       s = fmaf(D[9], Q[9], s);
       local[19] += (double)s;
     }
+  }
+  static constexpr int NQR = 9;   // independent moments
+  static constexpr int NLR = 24;  // S then X
+  __device__ __forceinline__ static void reduce(const double* Q, double* Qr) {
+    Qr[0] = Q[0];
+    Qr[1] = Q[1];
+    Qr[2] = Q[2];
+    Qr[3] = Q[3];
+    Qr[4] = Q[4] - Q[9];
+    Qr[5] = Q[5];
+    Qr[6] = Q[6];
+    Qr[7] = Q[7] - Q[9];
+    Qr[8] = Q[8];
+  }
+  __device__ __forceinline__ static void m2l_h(const double* r, const double* Qr, double* lr, bool ok) {
+    const double r2 = fma(r[0], r[0], fma(r[1], r[1], r[2] * r[2]));
+    const double ri = rsqrt_refined(r2);
+    const double rinv = ok ? ri : 0.0;
+    const double s = rinv * rinv;
+    const double R0_000 = rinv;
+    const double R1_000 = R0_000 * (-1.0 * s);
+    const double R2_000 = R1_000 * (-3.0 * s);
+    const double R3_000 = R2_000 * (-5.0 * s);
+    lr[0] = fma(R0_000, Qr[0], lr[0]);
+    const double R0_100 = r[0] * R1_000;
+    lr[0] = fma(R0_100, Qr[1], lr[0]);
+    lr[1] = fma(R0_100, Qr[0], lr[1]);
+    const double R0_010 = r[1] * R1_000;
+    lr[0] = fma(R0_010, Qr[2], lr[0]);
+    lr[2] = fma(R0_010, Qr[0], lr[2]);
+    const double R0_001 = r[2] * R1_000;
+    lr[0] = fma(R0_001, Qr[3], lr[0]);
+    lr[3] = fma(R0_001, Qr[0], lr[3]);
+    const double R1_100 = r[0] * R2_000;
+    const double R0_200 = fma(r[0], R1_100, R1_000);
+    lr[0] = fma(R0_200, Qr[4], lr[0]);
+    lr[1] = fma(R0_200, Qr[1], lr[1]);
+    lr[4] = fma(R0_200, Qr[0], lr[4]);
+    const double R1_010 = r[1] * R2_000;
+    const double R0_110 = r[0] * R1_010;
+    lr[0] = fma(R0_110, Qr[5], lr[0]);
+    lr[1] = fma(R0_110, Qr[2], lr[1]);
+    lr[2] = fma(R0_110, Qr[1], lr[2]);
+    lr[5] = fma(R0_110, Qr[0], lr[5]);
+    __builtin_amdgcn_sched_barrier(0);
+    const double R0_101 = r[2] * R1_100;
+    lr[0] = fma(R0_101, Qr[6], lr[0]);
+    lr[1] = fma(R0_101, Qr[3], lr[1]);
+    lr[3] = fma(R0_101, Qr[1], lr[3]);
+    lr[6] = fma(R0_101, Qr[0], lr[6]);
+    const double R0_020 = fma(r[1], R1_010, R1_000);
+    lr[0] = fma(R0_020, Qr[7], lr[0]);
+    lr[2] = fma(R0_020, Qr[2], lr[2]);
+    lr[7] = fma(R0_020, Qr[0], lr[7]);
+    const double R0_011 = r[2] * R1_010;
+    lr[0] = fma(R0_011, Qr[8], lr[0]);
+    lr[2] = fma(R0_011, Qr[3], lr[2]);
+    lr[3] = fma(R0_011, Qr[2], lr[3]);
+    lr[8] = fma(R0_011, Qr[0], lr[8]);
+    const double R0_002 = -(R0_200 + R0_020);
+    lr[3] = fma(R0_002, Qr[3], lr[3]);
+    __builtin_amdgcn_sched_barrier(0);
+    const double R2_100 = r[0] * R3_000;
+    const double R1_200 = fma(r[0], R2_100, R2_000);
+    const double R0_300 = fma(r[0], R1_200, 2.0 * R1_100);
+    lr[9] = fma(R0_300, Qr[4], lr[9]);
+    lr[12] = fma(R0_300, Qr[1], lr[12]);
+    lr[17] = fma(R0_300, Qr[0], lr[17]);
+    const double R2_010 = r[1] * R3_000;
+    const double R1_110 = r[0] * R2_010;
+    const double R0_210 = fma(r[0], R1_110, R1_010);
+    lr[9] = fma(R0_210, Qr[5], lr[9]);
+    lr[10] = fma(R0_210, Qr[4], lr[10]);
+    lr[12] = fma(R0_210, Qr[2], lr[12]);
+    lr[13] = fma(R0_210, Qr[1], lr[13]);
+    lr[18] = fma(R0_210, Qr[0], lr[18]);
+    const double R0_201 = r[2] * R1_200;
+    lr[9] = fma(R0_201, Qr[6], lr[9]);
+    lr[11] = fma(R0_201, Qr[4], lr[11]);
+    lr[12] = fma(R0_201, Qr[3], lr[12]);
+    lr[14] = fma(R0_201, Qr[1], lr[14]);
+    lr[19] = fma(R0_201, Qr[0], lr[19]);
+    __builtin_amdgcn_sched_barrier(0);
+    const double R0_120 = fma(r[1], R1_110, R1_100);
+    lr[9] = fma(R0_120, Qr[7], lr[9]);
+    lr[10] = fma(R0_120, Qr[5], lr[10]);
+    lr[13] = fma(R0_120, Qr[2], lr[13]);
+    lr[15] = fma(R0_120, Qr[1], lr[15]);
+    lr[20] = fma(R0_120, Qr[0], lr[20]);
+    const double R0_111 = r[2] * R1_110;
+    lr[9] = fma(R0_111, Qr[8], lr[9]);
+    lr[10] = fma(R0_111, Qr[6], lr[10]);
+    lr[11] = fma(R0_111, Qr[5], lr[11]);
+    lr[13] = fma(R0_111, Qr[3], lr[13]);
+    lr[14] = fma(R0_111, Qr[2], lr[14]);
+    lr[16] = fma(R0_111, Qr[1], lr[16]);
+    lr[21] = fma(R0_111, Qr[0], lr[21]);
+    __builtin_amdgcn_sched_barrier(0);
+    const double R0_102 = -(R0_300 + R0_120);
+    lr[11] = fma(R0_102, Qr[6], lr[11]);
+    lr[14] = fma(R0_102, Qr[3], lr[14]);
+    const double R1_020 = fma(r[1], R2_010, R2_000);
+    const double R0_030 = fma(r[1], R1_020, 2.0 * R1_010);
+    lr[10] = fma(R0_030, Qr[7], lr[10]);
+    lr[15] = fma(R0_030, Qr[2], lr[15]);
+    lr[22] = fma(R0_030, Qr[0], lr[22]);
+    const double R0_021 = r[2] * R1_020;
+    lr[10] = fma(R0_021, Qr[8], lr[10]);
+    lr[11] = fma(R0_021, Qr[7], lr[11]);
+    lr[15] = fma(R0_021, Qr[3], lr[15]);
+    lr[16] = fma(R0_021, Qr[2], lr[16]);
+    lr[23] = fma(R0_021, Qr[0], lr[23]);
+    const double R0_012 = -(R0_210 + R0_030);
+    lr[11] = fma(R0_012, Qr[8], lr[11]);
+    lr[16] = fma(R0_012, Qr[3], lr[16]);
+  }
+  static constexpr int FLOPS_M2L_H = 172;  // + one refined rsqrt
+  __device__ __forceinline__ static void expand(const double* lr, double* local) {
+    double t[20];
+    t[0] = lr[0];
+    local[19] = t[0];
+    t[1] = -lr[1];
+    local[20] = t[1];
+    t[2] = -lr[2];
+    local[21] = t[2];
+    t[3] = -lr[3];
+    local[22] = t[3];
+    t[4] = lr[4];
+    local[23] = t[4];
+    t[5] = lr[5];
+    local[24] = t[5];
+    t[6] = lr[6];
+    local[25] = t[6];
+    t[7] = lr[7];
+    local[26] = t[7];
+    t[8] = lr[8];
+    local[27] = t[8];
+    t[9] = -(t[4] + t[7]);
+    local[28] = t[9];
+    t[1] = (lr[1] + lr[9]);
+    local[0] = t[1];
+    t[2] = (lr[2] + lr[10]);
+    local[1] = t[2];
+    t[3] = (lr[3] + lr[11]);
+    local[2] = t[3];
+    t[4] = -(lr[4] + lr[12]);
+    local[3] = t[4];
+    t[5] = -(lr[5] + lr[13]);
+    local[4] = t[5];
+    t[6] = -(lr[6] + lr[14]);
+    local[5] = t[6];
+    t[7] = -(lr[7] + lr[15]);
+    local[6] = t[7];
+    t[8] = -(lr[8] + lr[16]);
+    local[7] = t[8];
+    t[9] = -(t[4] + t[7]);
+    local[8] = t[9];
+    t[10] = lr[17];
+    local[9] = t[10];
+    t[11] = lr[18];
+    local[10] = t[11];
+    t[12] = lr[19];
+    local[11] = t[12];
+    t[13] = lr[20];
+    local[12] = t[13];
+    t[14] = lr[21];
+    local[13] = t[14];
+    t[15] = -(t[10] + t[13]);
+    local[14] = t[15];
+    t[16] = lr[22];
+    local[15] = t[16];
+    t[17] = lr[23];
+    local[16] = t[17];
+    t[18] = -(t[11] + t[16]);
+    local[17] = t[18];
+    t[19] = -(t[12] + t[17]);
+    local[18] = t[19];
   }
   __device__ __forceinline__ static void m2l_pair(const double* r, const double* QS,
                                                     const double* QTs, double* local,
@@ -1713,9 +2037,9 @@ template <> struct Exp<3> {
     }
   }
   static constexpr int FLOPS_M2L = 659;  // + one rsqrt
-  __device__ __forceinline__ static void m2l_add_f32(const float* r, const float* Q, double* local) {
+  __device__ __forceinline__ static void m2l_add_f32(const float* r, const float* Q, double* local, bool ok = true) {
     const float r2 = r[0] * r[0] + r[1] * r[1] + r[2] * r[2];
-    const float rinv = __frsqrt_rn(r2);
+    const float rinv = ok ? __frsqrt_rn(r2) : 0.0f;
     const float rinv2 = rinv * rinv;
     float D[35];
     D[0] = rinv;
@@ -1757,6 +2081,7 @@ template <> struct Exp<3> {
     D[32] = (14.0f * r[1] * D[18] + 6.0f * D[9] + 14.0f * r[2] * D[17] + 6.0f * D[7]) * sn4;
     D[33] = (7.0f * r[1] * D[19] + 21.0f * r[2] * D[18] + 18.0f * D[8]) * sn4;
     D[34] = (28.0f * r[2] * D[19] + 36.0f * D[9]) * sn4;
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[1] * Q[0];
       s = fmaf(D[4], Q[1], s);
@@ -1781,6 +2106,7 @@ template <> struct Exp<3> {
       s = fmaf(D[29], Q[19], s);
       local[0] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[2] * Q[0];
       s = fmaf(D[5], Q[1], s);
@@ -1805,6 +2131,7 @@ template <> struct Exp<3> {
       s = fmaf(D[33], Q[19], s);
       local[1] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[3] * Q[0];
       s = fmaf(D[6], Q[1], s);
@@ -1829,6 +2156,7 @@ template <> struct Exp<3> {
       s = fmaf(D[34], Q[19], s);
       local[2] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[4] * Q[0];
       s = fmaf(D[10], Q[1], s);
@@ -1843,6 +2171,7 @@ template <> struct Exp<3> {
       s = fmaf(D[25], Q[9], s);
       local[3] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[5] * Q[0];
       s = fmaf(D[11], Q[1], s);
@@ -1857,6 +2186,7 @@ template <> struct Exp<3> {
       s = fmaf(D[28], Q[9], s);
       local[4] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[6] * Q[0];
       s = fmaf(D[12], Q[1], s);
@@ -1871,6 +2201,7 @@ template <> struct Exp<3> {
       s = fmaf(D[29], Q[9], s);
       local[5] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[7] * Q[0];
       s = fmaf(D[13], Q[1], s);
@@ -1885,6 +2216,7 @@ template <> struct Exp<3> {
       s = fmaf(D[32], Q[9], s);
       local[6] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[8] * Q[0];
       s = fmaf(D[14], Q[1], s);
@@ -1899,6 +2231,7 @@ template <> struct Exp<3> {
       s = fmaf(D[33], Q[9], s);
       local[7] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[9] * Q[0];
       s = fmaf(D[15], Q[1], s);
@@ -1913,6 +2246,7 @@ template <> struct Exp<3> {
       s = fmaf(D[34], Q[9], s);
       local[8] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[10] * Q[0];
       local[44] -= (double)s;
@@ -1921,6 +2255,7 @@ template <> struct Exp<3> {
       s = fmaf(D[22], Q[3], s);
       local[9] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[11] * Q[0];
       local[45] -= (double)s;
@@ -1929,6 +2264,7 @@ template <> struct Exp<3> {
       s = fmaf(D[24], Q[3], s);
       local[10] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[12] * Q[0];
       local[46] -= (double)s;
@@ -1937,6 +2273,7 @@ template <> struct Exp<3> {
       s = fmaf(D[25], Q[3], s);
       local[11] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[13] * Q[0];
       local[47] -= (double)s;
@@ -1945,6 +2282,7 @@ template <> struct Exp<3> {
       s = fmaf(D[27], Q[3], s);
       local[12] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[14] * Q[0];
       local[48] -= (double)s;
@@ -1953,6 +2291,7 @@ template <> struct Exp<3> {
       s = fmaf(D[28], Q[3], s);
       local[13] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[15] * Q[0];
       local[49] -= (double)s;
@@ -1961,6 +2300,7 @@ template <> struct Exp<3> {
       s = fmaf(D[29], Q[3], s);
       local[14] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[16] * Q[0];
       local[50] -= (double)s;
@@ -1969,6 +2309,7 @@ template <> struct Exp<3> {
       s = fmaf(D[31], Q[3], s);
       local[15] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[17] * Q[0];
       local[51] -= (double)s;
@@ -1977,6 +2318,7 @@ template <> struct Exp<3> {
       s = fmaf(D[32], Q[3], s);
       local[16] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[18] * Q[0];
       local[52] -= (double)s;
@@ -1985,6 +2327,7 @@ template <> struct Exp<3> {
       s = fmaf(D[33], Q[3], s);
       local[17] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[19] * Q[0];
       local[53] -= (double)s;
@@ -1993,66 +2336,82 @@ template <> struct Exp<3> {
       s = fmaf(D[34], Q[3], s);
       local[18] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[20] * Q[0];
       local[19] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[21] * Q[0];
       local[20] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[22] * Q[0];
       local[21] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[23] * Q[0];
       local[22] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[24] * Q[0];
       local[23] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[25] * Q[0];
       local[24] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[26] * Q[0];
       local[25] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[27] * Q[0];
       local[26] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[28] * Q[0];
       local[27] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[29] * Q[0];
       local[28] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[30] * Q[0];
       local[29] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[31] * Q[0];
       local[30] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[32] * Q[0];
       local[31] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[33] * Q[0];
       local[32] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[34] * Q[0];
       local[33] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[0] * Q[0];
       s = fmaf(D[1], Q[1], s);
@@ -2076,6 +2435,351 @@ template <> struct Exp<3> {
       s = fmaf(D[19], Q[19], s);
       local[34] += (double)s;
     }
+  }
+  static constexpr int NQR = 16;   // independent moments
+  static constexpr int NLR = 40;  // S then X
+  __device__ __forceinline__ static void reduce(const double* Q, double* Qr) {
+    Qr[0] = Q[0];
+    Qr[1] = Q[1];
+    Qr[2] = Q[2];
+    Qr[3] = Q[3];
+    Qr[4] = Q[4] - Q[9];
+    Qr[5] = Q[5];
+    Qr[6] = Q[6];
+    Qr[7] = Q[7] - Q[9];
+    Qr[8] = Q[8];
+    Qr[9] = Q[10] - Q[15];
+    Qr[10] = Q[11] - Q[18];
+    Qr[11] = Q[12] - Q[19];
+    Qr[12] = Q[13] - Q[15];
+    Qr[13] = Q[14];
+    Qr[14] = Q[16] - Q[18];
+    Qr[15] = Q[17] - Q[19];
+  }
+  __device__ __forceinline__ static void m2l_h(const double* r, const double* Qr, double* lr, bool ok) {
+    const double r2 = fma(r[0], r[0], fma(r[1], r[1], r[2] * r[2]));
+    const double ri = rsqrt_refined(r2);
+    const double rinv = ok ? ri : 0.0;
+    const double s = rinv * rinv;
+    const double R0_000 = rinv;
+    const double R1_000 = R0_000 * (-1.0 * s);
+    const double R2_000 = R1_000 * (-3.0 * s);
+    const double R3_000 = R2_000 * (-5.0 * s);
+    const double R4_000 = R3_000 * (-7.0 * s);
+    lr[0] = fma(R0_000, Qr[0], lr[0]);
+    const double R0_100 = r[0] * R1_000;
+    lr[0] = fma(R0_100, Qr[1], lr[0]);
+    lr[1] = fma(R0_100, Qr[0], lr[1]);
+    const double R0_010 = r[1] * R1_000;
+    lr[0] = fma(R0_010, Qr[2], lr[0]);
+    lr[2] = fma(R0_010, Qr[0], lr[2]);
+    const double R0_001 = r[2] * R1_000;
+    lr[0] = fma(R0_001, Qr[3], lr[0]);
+    lr[3] = fma(R0_001, Qr[0], lr[3]);
+    const double R1_100 = r[0] * R2_000;
+    const double R0_200 = fma(r[0], R1_100, R1_000);
+    lr[0] = fma(R0_200, Qr[4], lr[0]);
+    lr[1] = fma(R0_200, Qr[1], lr[1]);
+    lr[4] = fma(R0_200, Qr[0], lr[4]);
+    const double R1_010 = r[1] * R2_000;
+    const double R0_110 = r[0] * R1_010;
+    lr[0] = fma(R0_110, Qr[5], lr[0]);
+    lr[1] = fma(R0_110, Qr[2], lr[1]);
+    lr[2] = fma(R0_110, Qr[1], lr[2]);
+    lr[5] = fma(R0_110, Qr[0], lr[5]);
+    __builtin_amdgcn_sched_barrier(0);
+    const double R0_101 = r[2] * R1_100;
+    lr[0] = fma(R0_101, Qr[6], lr[0]);
+    lr[1] = fma(R0_101, Qr[3], lr[1]);
+    lr[3] = fma(R0_101, Qr[1], lr[3]);
+    lr[6] = fma(R0_101, Qr[0], lr[6]);
+    const double R0_020 = fma(r[1], R1_010, R1_000);
+    lr[0] = fma(R0_020, Qr[7], lr[0]);
+    lr[2] = fma(R0_020, Qr[2], lr[2]);
+    lr[7] = fma(R0_020, Qr[0], lr[7]);
+    const double R0_011 = r[2] * R1_010;
+    lr[0] = fma(R0_011, Qr[8], lr[0]);
+    lr[2] = fma(R0_011, Qr[3], lr[2]);
+    lr[3] = fma(R0_011, Qr[2], lr[3]);
+    lr[8] = fma(R0_011, Qr[0], lr[8]);
+    const double R0_002 = -(R0_200 + R0_020);
+    lr[3] = fma(R0_002, Qr[3], lr[3]);
+    __builtin_amdgcn_sched_barrier(0);
+    const double R2_100 = r[0] * R3_000;
+    const double R1_200 = fma(r[0], R2_100, R2_000);
+    const double R0_300 = fma(r[0], R1_200, 2.0 * R1_100);
+    lr[0] = fma(R0_300, Qr[9], lr[0]);
+    lr[1] = fma(R0_300, Qr[4], lr[1]);
+    lr[4] = fma(R0_300, Qr[1], lr[4]);
+    lr[9] = fma(R0_300, Qr[0], lr[9]);
+    const double R2_010 = r[1] * R3_000;
+    const double R1_110 = r[0] * R2_010;
+    const double R0_210 = fma(r[0], R1_110, R1_010);
+    lr[0] = fma(R0_210, Qr[10], lr[0]);
+    lr[1] = fma(R0_210, Qr[5], lr[1]);
+    lr[2] = fma(R0_210, Qr[4], lr[2]);
+    lr[4] = fma(R0_210, Qr[2], lr[4]);
+    lr[5] = fma(R0_210, Qr[1], lr[5]);
+    lr[10] = fma(R0_210, Qr[0], lr[10]);
+    const double R0_201 = r[2] * R1_200;
+    lr[0] = fma(R0_201, Qr[11], lr[0]);
+    lr[1] = fma(R0_201, Qr[6], lr[1]);
+    lr[3] = fma(R0_201, Qr[4], lr[3]);
+    lr[4] = fma(R0_201, Qr[3], lr[4]);
+    lr[6] = fma(R0_201, Qr[1], lr[6]);
+    lr[11] = fma(R0_201, Qr[0], lr[11]);
+    __builtin_amdgcn_sched_barrier(0);
+    const double R0_120 = fma(r[1], R1_110, R1_100);
+    lr[0] = fma(R0_120, Qr[12], lr[0]);
+    lr[1] = fma(R0_120, Qr[7], lr[1]);
+    lr[2] = fma(R0_120, Qr[5], lr[2]);
+    lr[5] = fma(R0_120, Qr[2], lr[5]);
+    lr[7] = fma(R0_120, Qr[1], lr[7]);
+    lr[12] = fma(R0_120, Qr[0], lr[12]);
+    const double R0_111 = r[2] * R1_110;
+    lr[0] = fma(R0_111, Qr[13], lr[0]);
+    lr[1] = fma(R0_111, Qr[8], lr[1]);
+    lr[2] = fma(R0_111, Qr[6], lr[2]);
+    lr[3] = fma(R0_111, Qr[5], lr[3]);
+    lr[5] = fma(R0_111, Qr[3], lr[5]);
+    lr[6] = fma(R0_111, Qr[2], lr[6]);
+    lr[8] = fma(R0_111, Qr[1], lr[8]);
+    lr[13] = fma(R0_111, Qr[0], lr[13]);
+    __builtin_amdgcn_sched_barrier(0);
+    const double R0_102 = -(R0_300 + R0_120);
+    lr[3] = fma(R0_102, Qr[6], lr[3]);
+    lr[6] = fma(R0_102, Qr[3], lr[6]);
+    const double R1_020 = fma(r[1], R2_010, R2_000);
+    const double R0_030 = fma(r[1], R1_020, 2.0 * R1_010);
+    lr[0] = fma(R0_030, Qr[14], lr[0]);
+    lr[2] = fma(R0_030, Qr[7], lr[2]);
+    lr[7] = fma(R0_030, Qr[2], lr[7]);
+    lr[14] = fma(R0_030, Qr[0], lr[14]);
+    const double R0_021 = r[2] * R1_020;
+    lr[0] = fma(R0_021, Qr[15], lr[0]);
+    lr[2] = fma(R0_021, Qr[8], lr[2]);
+    lr[3] = fma(R0_021, Qr[7], lr[3]);
+    lr[7] = fma(R0_021, Qr[3], lr[7]);
+    lr[8] = fma(R0_021, Qr[2], lr[8]);
+    lr[15] = fma(R0_021, Qr[0], lr[15]);
+    __builtin_amdgcn_sched_barrier(0);
+    const double R0_012 = -(R0_210 + R0_030);
+    lr[3] = fma(R0_012, Qr[8], lr[3]);
+    lr[8] = fma(R0_012, Qr[3], lr[8]);
+    const double R3_100 = r[0] * R4_000;
+    const double R2_200 = fma(r[0], R3_100, R3_000);
+    const double R1_300 = fma(r[0], R2_200, 2.0 * R2_100);
+    const double R0_400 = fma(r[0], R1_300, 3.0 * R1_200);
+    lr[16] = fma(R0_400, Qr[9], lr[16]);
+    lr[19] = fma(R0_400, Qr[4], lr[19]);
+    lr[24] = fma(R0_400, Qr[1], lr[24]);
+    lr[31] = fma(R0_400, Qr[0], lr[31]);
+    const double R3_010 = r[1] * R4_000;
+    const double R2_110 = r[0] * R3_010;
+    const double R1_210 = fma(r[0], R2_110, R2_010);
+    const double R0_310 = fma(r[0], R1_210, 2.0 * R1_110);
+    lr[16] = fma(R0_310, Qr[10], lr[16]);
+    lr[17] = fma(R0_310, Qr[9], lr[17]);
+    lr[19] = fma(R0_310, Qr[5], lr[19]);
+    lr[20] = fma(R0_310, Qr[4], lr[20]);
+    lr[24] = fma(R0_310, Qr[2], lr[24]);
+    lr[25] = fma(R0_310, Qr[1], lr[25]);
+    lr[32] = fma(R0_310, Qr[0], lr[32]);
+    __builtin_amdgcn_sched_barrier(0);
+    const double R0_301 = r[2] * R1_300;
+    lr[16] = fma(R0_301, Qr[11], lr[16]);
+    lr[18] = fma(R0_301, Qr[9], lr[18]);
+    lr[19] = fma(R0_301, Qr[6], lr[19]);
+    lr[21] = fma(R0_301, Qr[4], lr[21]);
+    lr[24] = fma(R0_301, Qr[3], lr[24]);
+    lr[26] = fma(R0_301, Qr[1], lr[26]);
+    lr[33] = fma(R0_301, Qr[0], lr[33]);
+    const double R1_120 = fma(r[1], R2_110, R2_100);
+    const double R0_220 = fma(r[0], R1_120, R1_020);
+    lr[16] = fma(R0_220, Qr[12], lr[16]);
+    lr[17] = fma(R0_220, Qr[10], lr[17]);
+    lr[19] = fma(R0_220, Qr[7], lr[19]);
+    lr[20] = fma(R0_220, Qr[5], lr[20]);
+    lr[22] = fma(R0_220, Qr[4], lr[22]);
+    lr[25] = fma(R0_220, Qr[2], lr[25]);
+    lr[27] = fma(R0_220, Qr[1], lr[27]);
+    lr[34] = fma(R0_220, Qr[0], lr[34]);
+    __builtin_amdgcn_sched_barrier(0);
+    const double R0_211 = r[2] * R1_210;
+    lr[16] = fma(R0_211, Qr[13], lr[16]);
+    lr[17] = fma(R0_211, Qr[11], lr[17]);
+    lr[18] = fma(R0_211, Qr[10], lr[18]);
+    lr[19] = fma(R0_211, Qr[8], lr[19]);
+    lr[20] = fma(R0_211, Qr[6], lr[20]);
+    lr[21] = fma(R0_211, Qr[5], lr[21]);
+    lr[23] = fma(R0_211, Qr[4], lr[23]);
+    lr[25] = fma(R0_211, Qr[3], lr[25]);
+    lr[26] = fma(R0_211, Qr[2], lr[26]);
+    lr[28] = fma(R0_211, Qr[1], lr[28]);
+    lr[35] = fma(R0_211, Qr[0], lr[35]);
+    const double R0_202 = -(R0_400 + R0_220);
+    lr[18] = fma(R0_202, Qr[11], lr[18]);
+    lr[21] = fma(R0_202, Qr[6], lr[21]);
+    lr[26] = fma(R0_202, Qr[3], lr[26]);
+    __builtin_amdgcn_sched_barrier(0);
+    const double R0_130 = fma(r[1], R1_120, 2.0 * R1_110);
+    lr[16] = fma(R0_130, Qr[14], lr[16]);
+    lr[17] = fma(R0_130, Qr[12], lr[17]);
+    lr[20] = fma(R0_130, Qr[7], lr[20]);
+    lr[22] = fma(R0_130, Qr[5], lr[22]);
+    lr[27] = fma(R0_130, Qr[2], lr[27]);
+    lr[29] = fma(R0_130, Qr[1], lr[29]);
+    lr[36] = fma(R0_130, Qr[0], lr[36]);
+    const double R0_121 = r[2] * R1_120;
+    lr[16] = fma(R0_121, Qr[15], lr[16]);
+    lr[17] = fma(R0_121, Qr[13], lr[17]);
+    lr[18] = fma(R0_121, Qr[12], lr[18]);
+    lr[20] = fma(R0_121, Qr[8], lr[20]);
+    lr[21] = fma(R0_121, Qr[7], lr[21]);
+    lr[22] = fma(R0_121, Qr[6], lr[22]);
+    lr[23] = fma(R0_121, Qr[5], lr[23]);
+    lr[27] = fma(R0_121, Qr[3], lr[27]);
+    lr[28] = fma(R0_121, Qr[2], lr[28]);
+    lr[30] = fma(R0_121, Qr[1], lr[30]);
+    lr[37] = fma(R0_121, Qr[0], lr[37]);
+    __builtin_amdgcn_sched_barrier(0);
+    const double R0_112 = -(R0_310 + R0_130);
+    lr[18] = fma(R0_112, Qr[13], lr[18]);
+    lr[21] = fma(R0_112, Qr[8], lr[21]);
+    lr[23] = fma(R0_112, Qr[6], lr[23]);
+    lr[28] = fma(R0_112, Qr[3], lr[28]);
+    const double R2_020 = fma(r[1], R3_010, R3_000);
+    const double R1_030 = fma(r[1], R2_020, 2.0 * R2_010);
+    const double R0_040 = fma(r[1], R1_030, 3.0 * R1_020);
+    lr[17] = fma(R0_040, Qr[14], lr[17]);
+    lr[22] = fma(R0_040, Qr[7], lr[22]);
+    lr[29] = fma(R0_040, Qr[2], lr[29]);
+    lr[38] = fma(R0_040, Qr[0], lr[38]);
+    const double R0_031 = r[2] * R1_030;
+    lr[17] = fma(R0_031, Qr[15], lr[17]);
+    lr[18] = fma(R0_031, Qr[14], lr[18]);
+    lr[22] = fma(R0_031, Qr[8], lr[22]);
+    lr[23] = fma(R0_031, Qr[7], lr[23]);
+    lr[29] = fma(R0_031, Qr[3], lr[29]);
+    lr[30] = fma(R0_031, Qr[2], lr[30]);
+    lr[39] = fma(R0_031, Qr[0], lr[39]);
+    __builtin_amdgcn_sched_barrier(0);
+    const double R0_022 = -(R0_220 + R0_040);
+    lr[18] = fma(R0_022, Qr[15], lr[18]);
+    lr[23] = fma(R0_022, Qr[8], lr[23]);
+    lr[30] = fma(R0_022, Qr[3], lr[30]);
+  }
+  static constexpr int FLOPS_M2L_H = 378;  // + one refined rsqrt
+  __device__ __forceinline__ static void expand(const double* lr, double* local) {
+    double t[35];
+    t[0] = lr[0];
+    local[34] = t[0];
+    t[1] = -lr[1];
+    local[35] = t[1];
+    t[2] = -lr[2];
+    local[36] = t[2];
+    t[3] = -lr[3];
+    local[37] = t[3];
+    t[4] = lr[4];
+    local[38] = t[4];
+    t[5] = lr[5];
+    local[39] = t[5];
+    t[6] = lr[6];
+    local[40] = t[6];
+    t[7] = lr[7];
+    local[41] = t[7];
+    t[8] = lr[8];
+    local[42] = t[8];
+    t[9] = -(t[4] + t[7]);
+    local[43] = t[9];
+    t[10] = -lr[9];
+    local[44] = t[10];
+    t[11] = -lr[10];
+    local[45] = t[11];
+    t[12] = -lr[11];
+    local[46] = t[12];
+    t[13] = -lr[12];
+    local[47] = t[13];
+    t[14] = -lr[13];
+    local[48] = t[14];
+    t[15] = -(t[10] + t[13]);
+    local[49] = t[15];
+    t[16] = -lr[14];
+    local[50] = t[16];
+    t[17] = -lr[15];
+    local[51] = t[17];
+    t[18] = -(t[11] + t[16]);
+    local[52] = t[18];
+    t[19] = -(t[12] + t[17]);
+    local[53] = t[19];
+    t[1] = (lr[1] + lr[16]);
+    local[0] = t[1];
+    t[2] = (lr[2] + lr[17]);
+    local[1] = t[2];
+    t[3] = (lr[3] + lr[18]);
+    local[2] = t[3];
+    t[4] = -(lr[4] + lr[19]);
+    local[3] = t[4];
+    t[5] = -(lr[5] + lr[20]);
+    local[4] = t[5];
+    t[6] = -(lr[6] + lr[21]);
+    local[5] = t[6];
+    t[7] = -(lr[7] + lr[22]);
+    local[6] = t[7];
+    t[8] = -(lr[8] + lr[23]);
+    local[7] = t[8];
+    t[9] = -(t[4] + t[7]);
+    local[8] = t[9];
+    t[10] = (lr[9] + lr[24]);
+    local[9] = t[10];
+    t[11] = (lr[10] + lr[25]);
+    local[10] = t[11];
+    t[12] = (lr[11] + lr[26]);
+    local[11] = t[12];
+    t[13] = (lr[12] + lr[27]);
+    local[12] = t[13];
+    t[14] = (lr[13] + lr[28]);
+    local[13] = t[14];
+    t[15] = -(t[10] + t[13]);
+    local[14] = t[15];
+    t[16] = (lr[14] + lr[29]);
+    local[15] = t[16];
+    t[17] = (lr[15] + lr[30]);
+    local[16] = t[17];
+    t[18] = -(t[11] + t[16]);
+    local[17] = t[18];
+    t[19] = -(t[12] + t[17]);
+    local[18] = t[19];
+    t[20] = -lr[31];
+    local[19] = t[20];
+    t[21] = -lr[32];
+    local[20] = t[21];
+    t[22] = -lr[33];
+    local[21] = t[22];
+    t[23] = -lr[34];
+    local[22] = t[23];
+    t[24] = -lr[35];
+    local[23] = t[24];
+    t[25] = -(t[20] + t[23]);
+    local[24] = t[25];
+    t[26] = -lr[36];
+    local[25] = t[26];
+    t[27] = -lr[37];
+    local[26] = t[27];
+    t[28] = -(t[21] + t[26]);
+    local[27] = t[28];
+    t[29] = -(t[22] + t[27]);
+    local[28] = t[29];
+    t[30] = -lr[38];
+    local[29] = t[30];
+    t[31] = -lr[39];
+    local[30] = t[31];
+    t[32] = -(t[23] + t[30]);
+    local[31] = t[32];
+    t[33] = -(t[24] + t[31]);
+    local[32] = t[33];
+    t[34] = -(t[25] + t[32]);
+    local[33] = t[34];
   }
   __device__ __forceinline__ static void m2l_pair(const double* r, const double* QS,
                                                     const double* QTs, double* local,
@@ -3733,9 +4437,9 @@ template <> struct Exp<4> {
     }
   }
   static constexpr int FLOPS_M2L = 1362;  // + one rsqrt
-  __device__ __forceinline__ static void m2l_add_f32(const float* r, const float* Q, double* local) {
+  __device__ __forceinline__ static void m2l_add_f32(const float* r, const float* Q, double* local, bool ok = true) {
     const float r2 = r[0] * r[0] + r[1] * r[1] + r[2] * r[2];
-    const float rinv = __frsqrt_rn(r2);
+    const float rinv = ok ? __frsqrt_rn(r2) : 0.0f;
     const float rinv2 = rinv * rinv;
     float D[56];
     D[0] = rinv;
@@ -3799,6 +4503,7 @@ template <> struct Exp<4> {
     D[53] = (18.0f * r[1] * D[33] + 8.0f * D[19] + 27.0f * r[2] * D[32] + 24.0f * D[17]) * sn5;
     D[54] = (9.0f * r[1] * D[34] + 36.0f * r[2] * D[33] + 48.0f * D[18]) * sn5;
     D[55] = (45.0f * r[2] * D[34] + 80.0f * D[19]) * sn5;
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[1] * Q[0];
       s = fmaf(D[4], Q[1], s);
@@ -3838,6 +4543,7 @@ template <> struct Exp<4> {
       s = fmaf(D[49], Q[34], s);
       local[0] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[2] * Q[0];
       s = fmaf(D[5], Q[1], s);
@@ -3877,6 +4583,7 @@ template <> struct Exp<4> {
       s = fmaf(D[54], Q[34], s);
       local[1] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[3] * Q[0];
       s = fmaf(D[6], Q[1], s);
@@ -3916,6 +4623,7 @@ template <> struct Exp<4> {
       s = fmaf(D[55], Q[34], s);
       local[2] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[4] * Q[0];
       s = fmaf(D[10], Q[1], s);
@@ -3940,6 +4648,7 @@ template <> struct Exp<4> {
       s = fmaf(D[44], Q[19], s);
       local[3] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[5] * Q[0];
       s = fmaf(D[11], Q[1], s);
@@ -3964,6 +4673,7 @@ template <> struct Exp<4> {
       s = fmaf(D[48], Q[19], s);
       local[4] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[6] * Q[0];
       s = fmaf(D[12], Q[1], s);
@@ -3988,6 +4698,7 @@ template <> struct Exp<4> {
       s = fmaf(D[49], Q[19], s);
       local[5] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[7] * Q[0];
       s = fmaf(D[13], Q[1], s);
@@ -4012,6 +4723,7 @@ template <> struct Exp<4> {
       s = fmaf(D[53], Q[19], s);
       local[6] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[8] * Q[0];
       s = fmaf(D[14], Q[1], s);
@@ -4036,6 +4748,7 @@ template <> struct Exp<4> {
       s = fmaf(D[54], Q[19], s);
       local[7] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[9] * Q[0];
       s = fmaf(D[15], Q[1], s);
@@ -4060,6 +4773,7 @@ template <> struct Exp<4> {
       s = fmaf(D[55], Q[19], s);
       local[8] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[10] * Q[0];
       s = fmaf(D[20], Q[1], s);
@@ -4074,6 +4788,7 @@ template <> struct Exp<4> {
       s = fmaf(D[40], Q[9], s);
       local[9] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[11] * Q[0];
       s = fmaf(D[21], Q[1], s);
@@ -4088,6 +4803,7 @@ template <> struct Exp<4> {
       s = fmaf(D[43], Q[9], s);
       local[10] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[12] * Q[0];
       s = fmaf(D[22], Q[1], s);
@@ -4102,6 +4818,7 @@ template <> struct Exp<4> {
       s = fmaf(D[44], Q[9], s);
       local[11] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[13] * Q[0];
       s = fmaf(D[23], Q[1], s);
@@ -4116,6 +4833,7 @@ template <> struct Exp<4> {
       s = fmaf(D[47], Q[9], s);
       local[12] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[14] * Q[0];
       s = fmaf(D[24], Q[1], s);
@@ -4130,6 +4848,7 @@ template <> struct Exp<4> {
       s = fmaf(D[48], Q[9], s);
       local[13] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[15] * Q[0];
       s = fmaf(D[25], Q[1], s);
@@ -4144,6 +4863,7 @@ template <> struct Exp<4> {
       s = fmaf(D[49], Q[9], s);
       local[14] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[16] * Q[0];
       s = fmaf(D[26], Q[1], s);
@@ -4158,6 +4878,7 @@ template <> struct Exp<4> {
       s = fmaf(D[52], Q[9], s);
       local[15] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[17] * Q[0];
       s = fmaf(D[27], Q[1], s);
@@ -4172,6 +4893,7 @@ template <> struct Exp<4> {
       s = fmaf(D[53], Q[9], s);
       local[16] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[18] * Q[0];
       s = fmaf(D[28], Q[1], s);
@@ -4186,6 +4908,7 @@ template <> struct Exp<4> {
       s = fmaf(D[54], Q[9], s);
       local[17] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[19] * Q[0];
       s = fmaf(D[29], Q[1], s);
@@ -4200,6 +4923,7 @@ template <> struct Exp<4> {
       s = fmaf(D[55], Q[9], s);
       local[18] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[20] * Q[0];
       local[75] += (double)s;
@@ -4208,6 +4932,7 @@ template <> struct Exp<4> {
       s = fmaf(D[37], Q[3], s);
       local[19] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[21] * Q[0];
       local[76] += (double)s;
@@ -4216,6 +4941,7 @@ template <> struct Exp<4> {
       s = fmaf(D[39], Q[3], s);
       local[20] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[22] * Q[0];
       local[77] += (double)s;
@@ -4224,6 +4950,7 @@ template <> struct Exp<4> {
       s = fmaf(D[40], Q[3], s);
       local[21] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[23] * Q[0];
       local[78] += (double)s;
@@ -4232,6 +4959,7 @@ template <> struct Exp<4> {
       s = fmaf(D[42], Q[3], s);
       local[22] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[24] * Q[0];
       local[79] += (double)s;
@@ -4240,6 +4968,7 @@ template <> struct Exp<4> {
       s = fmaf(D[43], Q[3], s);
       local[23] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[25] * Q[0];
       local[80] += (double)s;
@@ -4248,6 +4977,7 @@ template <> struct Exp<4> {
       s = fmaf(D[44], Q[3], s);
       local[24] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[26] * Q[0];
       local[81] += (double)s;
@@ -4256,6 +4986,7 @@ template <> struct Exp<4> {
       s = fmaf(D[46], Q[3], s);
       local[25] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[27] * Q[0];
       local[82] += (double)s;
@@ -4264,6 +4995,7 @@ template <> struct Exp<4> {
       s = fmaf(D[47], Q[3], s);
       local[26] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[28] * Q[0];
       local[83] += (double)s;
@@ -4272,6 +5004,7 @@ template <> struct Exp<4> {
       s = fmaf(D[48], Q[3], s);
       local[27] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[29] * Q[0];
       local[84] += (double)s;
@@ -4280,6 +5013,7 @@ template <> struct Exp<4> {
       s = fmaf(D[49], Q[3], s);
       local[28] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[30] * Q[0];
       local[85] += (double)s;
@@ -4288,6 +5022,7 @@ template <> struct Exp<4> {
       s = fmaf(D[51], Q[3], s);
       local[29] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[31] * Q[0];
       local[86] += (double)s;
@@ -4296,6 +5031,7 @@ template <> struct Exp<4> {
       s = fmaf(D[52], Q[3], s);
       local[30] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[32] * Q[0];
       local[87] += (double)s;
@@ -4304,6 +5040,7 @@ template <> struct Exp<4> {
       s = fmaf(D[53], Q[3], s);
       local[31] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[33] * Q[0];
       local[88] += (double)s;
@@ -4312,6 +5049,7 @@ template <> struct Exp<4> {
       s = fmaf(D[54], Q[3], s);
       local[32] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[34] * Q[0];
       local[89] += (double)s;
@@ -4320,90 +5058,112 @@ template <> struct Exp<4> {
       s = fmaf(D[55], Q[3], s);
       local[33] -= (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[35] * Q[0];
       local[34] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[36] * Q[0];
       local[35] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[37] * Q[0];
       local[36] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[38] * Q[0];
       local[37] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[39] * Q[0];
       local[38] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[40] * Q[0];
       local[39] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[41] * Q[0];
       local[40] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[42] * Q[0];
       local[41] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[43] * Q[0];
       local[42] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[44] * Q[0];
       local[43] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[45] * Q[0];
       local[44] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[46] * Q[0];
       local[45] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[47] * Q[0];
       local[46] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[48] * Q[0];
       local[47] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[49] * Q[0];
       local[48] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[50] * Q[0];
       local[49] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[51] * Q[0];
       local[50] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[52] * Q[0];
       local[51] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[53] * Q[0];
       local[52] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[54] * Q[0];
       local[53] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[55] * Q[0];
       local[54] += (double)s;
     }
+    __builtin_amdgcn_sched_barrier(0);
     {
       float s = D[0] * Q[0];
       s = fmaf(D[1], Q[1], s);
@@ -4442,6 +5202,614 @@ template <> struct Exp<4> {
       s = fmaf(D[34], Q[34], s);
       local[55] += (double)s;
     }
+  }
+  static constexpr int NQR = 25;   // independent moments
+  static constexpr int NLR = 60;  // S then X
+  __device__ __forceinline__ static void reduce(const double* Q, double* Qr) {
+    Qr[0] = Q[0];
+    Qr[1] = Q[1];
+    Qr[2] = Q[2];
+    Qr[3] = Q[3];
+    Qr[4] = Q[4] - Q[9];
+    Qr[5] = Q[5];
+    Qr[6] = Q[6];
+    Qr[7] = Q[7] - Q[9];
+    Qr[8] = Q[8];
+    Qr[9] = Q[10] - Q[15];
+    Qr[10] = Q[11] - Q[18];
+    Qr[11] = Q[12] - Q[19];
+    Qr[12] = Q[13] - Q[15];
+    Qr[13] = Q[14];
+    Qr[14] = Q[16] - Q[18];
+    Qr[15] = Q[17] - Q[19];
+    Qr[16] = Q[20] - Q[25] + Q[34];
+    Qr[17] = Q[21] - Q[28];
+    Qr[18] = Q[22] - Q[29];
+    Qr[19] = Q[23] - Q[25] + 2.0 * Q[34] - Q[32];
+    Qr[20] = Q[24] - Q[33];
+    Qr[21] = Q[26] - Q[28];
+    Qr[22] = Q[27] - Q[29];
+    Qr[23] = Q[30] - Q[32] + Q[34];
+    Qr[24] = Q[31] - Q[33];
+  }
+  __device__ __forceinline__ static void m2l_h(const double* r, const double* Qr, double* lr, bool ok) {
+    const double r2 = fma(r[0], r[0], fma(r[1], r[1], r[2] * r[2]));
+    const double ri = rsqrt_refined(r2);
+    const double rinv = ok ? ri : 0.0;
+    const double s = rinv * rinv;
+    const double R0_000 = rinv;
+    const double R1_000 = R0_000 * (-1.0 * s);
+    const double R2_000 = R1_000 * (-3.0 * s);
+    const double R3_000 = R2_000 * (-5.0 * s);
+    const double R4_000 = R3_000 * (-7.0 * s);
+    const double R5_000 = R4_000 * (-9.0 * s);
+    lr[0] = fma(R0_000, Qr[0], lr[0]);
+    const double R0_100 = r[0] * R1_000;
+    lr[0] = fma(R0_100, Qr[1], lr[0]);
+    lr[1] = fma(R0_100, Qr[0], lr[1]);
+    const double R0_010 = r[1] * R1_000;
+    lr[0] = fma(R0_010, Qr[2], lr[0]);
+    lr[2] = fma(R0_010, Qr[0], lr[2]);
+    const double R0_001 = r[2] * R1_000;
+    lr[0] = fma(R0_001, Qr[3], lr[0]);
+    lr[3] = fma(R0_001, Qr[0], lr[3]);
+    const double R1_100 = r[0] * R2_000;
+    const double R0_200 = fma(r[0], R1_100, R1_000);
+    lr[0] = fma(R0_200, Qr[4], lr[0]);
+    lr[1] = fma(R0_200, Qr[1], lr[1]);
+    lr[4] = fma(R0_200, Qr[0], lr[4]);
+    const double R1_010 = r[1] * R2_000;
+    const double R0_110 = r[0] * R1_010;
+    lr[0] = fma(R0_110, Qr[5], lr[0]);
+    lr[1] = fma(R0_110, Qr[2], lr[1]);
+    lr[2] = fma(R0_110, Qr[1], lr[2]);
+    lr[5] = fma(R0_110, Qr[0], lr[5]);
+    __builtin_amdgcn_sched_barrier(0);
+    const double R0_101 = r[2] * R1_100;
+    lr[0] = fma(R0_101, Qr[6], lr[0]);
+    lr[1] = fma(R0_101, Qr[3], lr[1]);
+    lr[3] = fma(R0_101, Qr[1], lr[3]);
+    lr[6] = fma(R0_101, Qr[0], lr[6]);
+    const double R0_020 = fma(r[1], R1_010, R1_000);
+    lr[0] = fma(R0_020, Qr[7], lr[0]);
+    lr[2] = fma(R0_020, Qr[2], lr[2]);
+    lr[7] = fma(R0_020, Qr[0], lr[7]);
+    const double R0_011 = r[2] * R1_010;
+    lr[0] = fma(R0_011, Qr[8], lr[0]);
+    lr[2] = fma(R0_011, Qr[3], lr[2]);
+    lr[3] = fma(R0_011, Qr[2], lr[3]);
+    lr[8] = fma(R0_011, Qr[0], lr[8]);
+    const double R0_002 = -(R0_200 + R0_020);
+    lr[3] = fma(R0_002, Qr[3], lr[3]);
+    __builtin_amdgcn_sched_barrier(0);
+    const double R2_100 = r[0] * R3_000;
+    const double R1_200 = fma(r[0], R2_100, R2_000);
+    const double R0_300 = fma(r[0], R1_200, 2.0 * R1_100);
+    lr[0] = fma(R0_300, Qr[9], lr[0]);
+    lr[1] = fma(R0_300, Qr[4], lr[1]);
+    lr[4] = fma(R0_300, Qr[1], lr[4]);
+    lr[9] = fma(R0_300, Qr[0], lr[9]);
+    const double R2_010 = r[1] * R3_000;
+    const double R1_110 = r[0] * R2_010;
+    const double R0_210 = fma(r[0], R1_110, R1_010);
+    lr[0] = fma(R0_210, Qr[10], lr[0]);
+    lr[1] = fma(R0_210, Qr[5], lr[1]);
+    lr[2] = fma(R0_210, Qr[4], lr[2]);
+    lr[4] = fma(R0_210, Qr[2], lr[4]);
+    lr[5] = fma(R0_210, Qr[1], lr[5]);
+    lr[10] = fma(R0_210, Qr[0], lr[10]);
+    const double R0_201 = r[2] * R1_200;
+    lr[0] = fma(R0_201, Qr[11], lr[0]);
+    lr[1] = fma(R0_201, Qr[6], lr[1]);
+    lr[3] = fma(R0_201, Qr[4], lr[3]);
+    lr[4] = fma(R0_201, Qr[3], lr[4]);
+    lr[6] = fma(R0_201, Qr[1], lr[6]);
+    lr[11] = fma(R0_201, Qr[0], lr[11]);
+    __builtin_amdgcn_sched_barrier(0);
+    const double R0_120 = fma(r[1], R1_110, R1_100);
+    lr[0] = fma(R0_120, Qr[12], lr[0]);
+    lr[1] = fma(R0_120, Qr[7], lr[1]);
+    lr[2] = fma(R0_120, Qr[5], lr[2]);
+    lr[5] = fma(R0_120, Qr[2], lr[5]);
+    lr[7] = fma(R0_120, Qr[1], lr[7]);
+    lr[12] = fma(R0_120, Qr[0], lr[12]);
+    const double R0_111 = r[2] * R1_110;
+    lr[0] = fma(R0_111, Qr[13], lr[0]);
+    lr[1] = fma(R0_111, Qr[8], lr[1]);
+    lr[2] = fma(R0_111, Qr[6], lr[2]);
+    lr[3] = fma(R0_111, Qr[5], lr[3]);
+    lr[5] = fma(R0_111, Qr[3], lr[5]);
+    lr[6] = fma(R0_111, Qr[2], lr[6]);
+    lr[8] = fma(R0_111, Qr[1], lr[8]);
+    lr[13] = fma(R0_111, Qr[0], lr[13]);
+    __builtin_amdgcn_sched_barrier(0);
+    const double R0_102 = -(R0_300 + R0_120);
+    lr[3] = fma(R0_102, Qr[6], lr[3]);
+    lr[6] = fma(R0_102, Qr[3], lr[6]);
+    const double R1_020 = fma(r[1], R2_010, R2_000);
+    const double R0_030 = fma(r[1], R1_020, 2.0 * R1_010);
+    lr[0] = fma(R0_030, Qr[14], lr[0]);
+    lr[2] = fma(R0_030, Qr[7], lr[2]);
+    lr[7] = fma(R0_030, Qr[2], lr[7]);
+    lr[14] = fma(R0_030, Qr[0], lr[14]);
+    const double R0_021 = r[2] * R1_020;
+    lr[0] = fma(R0_021, Qr[15], lr[0]);
+    lr[2] = fma(R0_021, Qr[8], lr[2]);
+    lr[3] = fma(R0_021, Qr[7], lr[3]);
+    lr[7] = fma(R0_021, Qr[3], lr[7]);
+    lr[8] = fma(R0_021, Qr[2], lr[8]);
+    lr[15] = fma(R0_021, Qr[0], lr[15]);
+    __builtin_amdgcn_sched_barrier(0);
+    const double R0_012 = -(R0_210 + R0_030);
+    lr[3] = fma(R0_012, Qr[8], lr[3]);
+    lr[8] = fma(R0_012, Qr[3], lr[8]);
+    const double R3_100 = r[0] * R4_000;
+    const double R2_200 = fma(r[0], R3_100, R3_000);
+    const double R1_300 = fma(r[0], R2_200, 2.0 * R2_100);
+    const double R0_400 = fma(r[0], R1_300, 3.0 * R1_200);
+    lr[0] = fma(R0_400, Qr[16], lr[0]);
+    lr[1] = fma(R0_400, Qr[9], lr[1]);
+    lr[4] = fma(R0_400, Qr[4], lr[4]);
+    lr[9] = fma(R0_400, Qr[1], lr[9]);
+    lr[16] = fma(R0_400, Qr[0], lr[16]);
+    const double R3_010 = r[1] * R4_000;
+    const double R2_110 = r[0] * R3_010;
+    const double R1_210 = fma(r[0], R2_110, R2_010);
+    const double R0_310 = fma(r[0], R1_210, 2.0 * R1_110);
+    lr[0] = fma(R0_310, Qr[17], lr[0]);
+    lr[1] = fma(R0_310, Qr[10], lr[1]);
+    lr[2] = fma(R0_310, Qr[9], lr[2]);
+    lr[4] = fma(R0_310, Qr[5], lr[4]);
+    lr[5] = fma(R0_310, Qr[4], lr[5]);
+    lr[9] = fma(R0_310, Qr[2], lr[9]);
+    lr[10] = fma(R0_310, Qr[1], lr[10]);
+    lr[17] = fma(R0_310, Qr[0], lr[17]);
+    __builtin_amdgcn_sched_barrier(0);
+    const double R0_301 = r[2] * R1_300;
+    lr[0] = fma(R0_301, Qr[18], lr[0]);
+    lr[1] = fma(R0_301, Qr[11], lr[1]);
+    lr[3] = fma(R0_301, Qr[9], lr[3]);
+    lr[4] = fma(R0_301, Qr[6], lr[4]);
+    lr[6] = fma(R0_301, Qr[4], lr[6]);
+    lr[9] = fma(R0_301, Qr[3], lr[9]);
+    lr[11] = fma(R0_301, Qr[1], lr[11]);
+    lr[18] = fma(R0_301, Qr[0], lr[18]);
+    const double R1_120 = fma(r[1], R2_110, R2_100);
+    const double R0_220 = fma(r[0], R1_120, R1_020);
+    lr[0] = fma(R0_220, Qr[19], lr[0]);
+    lr[1] = fma(R0_220, Qr[12], lr[1]);
+    lr[2] = fma(R0_220, Qr[10], lr[2]);
+    lr[4] = fma(R0_220, Qr[7], lr[4]);
+    lr[5] = fma(R0_220, Qr[5], lr[5]);
+    lr[7] = fma(R0_220, Qr[4], lr[7]);
+    lr[10] = fma(R0_220, Qr[2], lr[10]);
+    lr[12] = fma(R0_220, Qr[1], lr[12]);
+    lr[19] = fma(R0_220, Qr[0], lr[19]);
+    __builtin_amdgcn_sched_barrier(0);
+    const double R0_211 = r[2] * R1_210;
+    lr[0] = fma(R0_211, Qr[20], lr[0]);
+    lr[1] = fma(R0_211, Qr[13], lr[1]);
+    lr[2] = fma(R0_211, Qr[11], lr[2]);
+    lr[3] = fma(R0_211, Qr[10], lr[3]);
+    lr[4] = fma(R0_211, Qr[8], lr[4]);
+    lr[5] = fma(R0_211, Qr[6], lr[5]);
+    lr[6] = fma(R0_211, Qr[5], lr[6]);
+    lr[8] = fma(R0_211, Qr[4], lr[8]);
+    lr[10] = fma(R0_211, Qr[3], lr[10]);
+    lr[11] = fma(R0_211, Qr[2], lr[11]);
+    lr[13] = fma(R0_211, Qr[1], lr[13]);
+    lr[20] = fma(R0_211, Qr[0], lr[20]);
+    __builtin_amdgcn_sched_barrier(0);
+    const double R0_202 = -(R0_400 + R0_220);
+    lr[3] = fma(R0_202, Qr[11], lr[3]);
+    lr[6] = fma(R0_202, Qr[6], lr[6]);
+    lr[11] = fma(R0_202, Qr[3], lr[11]);
+    const double R0_130 = fma(r[1], R1_120, 2.0 * R1_110);
+    lr[0] = fma(R0_130, Qr[21], lr[0]);
+    lr[1] = fma(R0_130, Qr[14], lr[1]);
+    lr[2] = fma(R0_130, Qr[12], lr[2]);
+    lr[5] = fma(R0_130, Qr[7], lr[5]);
+    lr[7] = fma(R0_130, Qr[5], lr[7]);
+    lr[12] = fma(R0_130, Qr[2], lr[12]);
+    lr[14] = fma(R0_130, Qr[1], lr[14]);
+    lr[21] = fma(R0_130, Qr[0], lr[21]);
+    const double R0_121 = r[2] * R1_120;
+    lr[0] = fma(R0_121, Qr[22], lr[0]);
+    lr[1] = fma(R0_121, Qr[15], lr[1]);
+    lr[2] = fma(R0_121, Qr[13], lr[2]);
+    lr[3] = fma(R0_121, Qr[12], lr[3]);
+    lr[5] = fma(R0_121, Qr[8], lr[5]);
+    lr[6] = fma(R0_121, Qr[7], lr[6]);
+    lr[7] = fma(R0_121, Qr[6], lr[7]);
+    lr[8] = fma(R0_121, Qr[5], lr[8]);
+    lr[12] = fma(R0_121, Qr[3], lr[12]);
+    lr[13] = fma(R0_121, Qr[2], lr[13]);
+    lr[15] = fma(R0_121, Qr[1], lr[15]);
+    lr[22] = fma(R0_121, Qr[0], lr[22]);
+    __builtin_amdgcn_sched_barrier(0);
+    const double R0_112 = -(R0_310 + R0_130);
+    lr[3] = fma(R0_112, Qr[13], lr[3]);
+    lr[6] = fma(R0_112, Qr[8], lr[6]);
+    lr[8] = fma(R0_112, Qr[6], lr[8]);
+    lr[13] = fma(R0_112, Qr[3], lr[13]);
+    const double R2_020 = fma(r[1], R3_010, R3_000);
+    const double R1_030 = fma(r[1], R2_020, 2.0 * R2_010);
+    const double R0_040 = fma(r[1], R1_030, 3.0 * R1_020);
+    lr[0] = fma(R0_040, Qr[23], lr[0]);
+    lr[2] = fma(R0_040, Qr[14], lr[2]);
+    lr[7] = fma(R0_040, Qr[7], lr[7]);
+    lr[14] = fma(R0_040, Qr[2], lr[14]);
+    lr[23] = fma(R0_040, Qr[0], lr[23]);
+    const double R0_031 = r[2] * R1_030;
+    lr[0] = fma(R0_031, Qr[24], lr[0]);
+    lr[2] = fma(R0_031, Qr[15], lr[2]);
+    lr[3] = fma(R0_031, Qr[14], lr[3]);
+    lr[7] = fma(R0_031, Qr[8], lr[7]);
+    lr[8] = fma(R0_031, Qr[7], lr[8]);
+    lr[14] = fma(R0_031, Qr[3], lr[14]);
+    lr[15] = fma(R0_031, Qr[2], lr[15]);
+    lr[24] = fma(R0_031, Qr[0], lr[24]);
+    __builtin_amdgcn_sched_barrier(0);
+    const double R0_022 = -(R0_220 + R0_040);
+    lr[3] = fma(R0_022, Qr[15], lr[3]);
+    lr[8] = fma(R0_022, Qr[8], lr[8]);
+    lr[15] = fma(R0_022, Qr[3], lr[15]);
+    const double R4_100 = r[0] * R5_000;
+    const double R3_200 = fma(r[0], R4_100, R4_000);
+    const double R2_300 = fma(r[0], R3_200, 2.0 * R3_100);
+    const double R1_400 = fma(r[0], R2_300, 3.0 * R2_200);
+    const double R0_500 = fma(r[0], R1_400, 4.0 * R1_300);
+    lr[25] = fma(R0_500, Qr[16], lr[25]);
+    lr[28] = fma(R0_500, Qr[9], lr[28]);
+    lr[33] = fma(R0_500, Qr[4], lr[33]);
+    lr[40] = fma(R0_500, Qr[1], lr[40]);
+    lr[49] = fma(R0_500, Qr[0], lr[49]);
+    const double R4_010 = r[1] * R5_000;
+    const double R3_110 = r[0] * R4_010;
+    const double R2_210 = fma(r[0], R3_110, R3_010);
+    const double R1_310 = fma(r[0], R2_210, 2.0 * R2_110);
+    const double R0_410 = fma(r[0], R1_310, 3.0 * R1_210);
+    lr[25] = fma(R0_410, Qr[17], lr[25]);
+    lr[26] = fma(R0_410, Qr[16], lr[26]);
+    lr[28] = fma(R0_410, Qr[10], lr[28]);
+    lr[29] = fma(R0_410, Qr[9], lr[29]);
+    lr[33] = fma(R0_410, Qr[5], lr[33]);
+    lr[34] = fma(R0_410, Qr[4], lr[34]);
+    lr[40] = fma(R0_410, Qr[2], lr[40]);
+    lr[41] = fma(R0_410, Qr[1], lr[41]);
+    lr[50] = fma(R0_410, Qr[0], lr[50]);
+    __builtin_amdgcn_sched_barrier(0);
+    const double R0_401 = r[2] * R1_400;
+    lr[25] = fma(R0_401, Qr[18], lr[25]);
+    lr[27] = fma(R0_401, Qr[16], lr[27]);
+    lr[28] = fma(R0_401, Qr[11], lr[28]);
+    lr[30] = fma(R0_401, Qr[9], lr[30]);
+    lr[33] = fma(R0_401, Qr[6], lr[33]);
+    lr[35] = fma(R0_401, Qr[4], lr[35]);
+    lr[40] = fma(R0_401, Qr[3], lr[40]);
+    lr[42] = fma(R0_401, Qr[1], lr[42]);
+    lr[51] = fma(R0_401, Qr[0], lr[51]);
+    const double R2_120 = fma(r[1], R3_110, R3_100);
+    const double R1_220 = fma(r[0], R2_120, R2_020);
+    const double R0_320 = fma(r[0], R1_220, 2.0 * R1_120);
+    lr[25] = fma(R0_320, Qr[19], lr[25]);
+    lr[26] = fma(R0_320, Qr[17], lr[26]);
+    lr[28] = fma(R0_320, Qr[12], lr[28]);
+    lr[29] = fma(R0_320, Qr[10], lr[29]);
+    lr[31] = fma(R0_320, Qr[9], lr[31]);
+    lr[33] = fma(R0_320, Qr[7], lr[33]);
+    lr[34] = fma(R0_320, Qr[5], lr[34]);
+    lr[36] = fma(R0_320, Qr[4], lr[36]);
+    lr[41] = fma(R0_320, Qr[2], lr[41]);
+    lr[43] = fma(R0_320, Qr[1], lr[43]);
+    lr[52] = fma(R0_320, Qr[0], lr[52]);
+    __builtin_amdgcn_sched_barrier(0);
+    const double R0_311 = r[2] * R1_310;
+    lr[25] = fma(R0_311, Qr[20], lr[25]);
+    lr[26] = fma(R0_311, Qr[18], lr[26]);
+    lr[27] = fma(R0_311, Qr[17], lr[27]);
+    lr[28] = fma(R0_311, Qr[13], lr[28]);
+    lr[29] = fma(R0_311, Qr[11], lr[29]);
+    lr[30] = fma(R0_311, Qr[10], lr[30]);
+    lr[32] = fma(R0_311, Qr[9], lr[32]);
+    lr[33] = fma(R0_311, Qr[8], lr[33]);
+    lr[34] = fma(R0_311, Qr[6], lr[34]);
+    lr[35] = fma(R0_311, Qr[5], lr[35]);
+    lr[37] = fma(R0_311, Qr[4], lr[37]);
+    lr[41] = fma(R0_311, Qr[3], lr[41]);
+    lr[42] = fma(R0_311, Qr[2], lr[42]);
+    lr[44] = fma(R0_311, Qr[1], lr[44]);
+    lr[53] = fma(R0_311, Qr[0], lr[53]);
+    __builtin_amdgcn_sched_barrier(0);
+    const double R0_302 = -(R0_500 + R0_320);
+    lr[27] = fma(R0_302, Qr[18], lr[27]);
+    lr[30] = fma(R0_302, Qr[11], lr[30]);
+    lr[35] = fma(R0_302, Qr[6], lr[35]);
+    lr[42] = fma(R0_302, Qr[3], lr[42]);
+    const double R0_230 = fma(r[1], R1_220, 2.0 * R1_210);
+    lr[25] = fma(R0_230, Qr[21], lr[25]);
+    lr[26] = fma(R0_230, Qr[19], lr[26]);
+    lr[28] = fma(R0_230, Qr[14], lr[28]);
+    lr[29] = fma(R0_230, Qr[12], lr[29]);
+    lr[31] = fma(R0_230, Qr[10], lr[31]);
+    lr[34] = fma(R0_230, Qr[7], lr[34]);
+    lr[36] = fma(R0_230, Qr[5], lr[36]);
+    lr[38] = fma(R0_230, Qr[4], lr[38]);
+    lr[43] = fma(R0_230, Qr[2], lr[43]);
+    lr[45] = fma(R0_230, Qr[1], lr[45]);
+    lr[54] = fma(R0_230, Qr[0], lr[54]);
+    __builtin_amdgcn_sched_barrier(0);
+    const double R0_221 = r[2] * R1_220;
+    lr[25] = fma(R0_221, Qr[22], lr[25]);
+    lr[26] = fma(R0_221, Qr[20], lr[26]);
+    lr[27] = fma(R0_221, Qr[19], lr[27]);
+    lr[28] = fma(R0_221, Qr[15], lr[28]);
+    lr[29] = fma(R0_221, Qr[13], lr[29]);
+    lr[30] = fma(R0_221, Qr[12], lr[30]);
+    lr[31] = fma(R0_221, Qr[11], lr[31]);
+    lr[32] = fma(R0_221, Qr[10], lr[32]);
+    lr[34] = fma(R0_221, Qr[8], lr[34]);
+    lr[35] = fma(R0_221, Qr[7], lr[35]);
+    lr[36] = fma(R0_221, Qr[6], lr[36]);
+    lr[37] = fma(R0_221, Qr[5], lr[37]);
+    lr[39] = fma(R0_221, Qr[4], lr[39]);
+    lr[43] = fma(R0_221, Qr[3], lr[43]);
+    lr[44] = fma(R0_221, Qr[2], lr[44]);
+    lr[46] = fma(R0_221, Qr[1], lr[46]);
+    lr[55] = fma(R0_221, Qr[0], lr[55]);
+    __builtin_amdgcn_sched_barrier(0);
+    const double R0_212 = -(R0_410 + R0_230);
+    lr[27] = fma(R0_212, Qr[20], lr[27]);
+    lr[30] = fma(R0_212, Qr[13], lr[30]);
+    lr[32] = fma(R0_212, Qr[11], lr[32]);
+    lr[35] = fma(R0_212, Qr[8], lr[35]);
+    lr[37] = fma(R0_212, Qr[6], lr[37]);
+    lr[44] = fma(R0_212, Qr[3], lr[44]);
+    const double R1_130 = fma(r[1], R2_120, 2.0 * R2_110);
+    const double R0_140 = fma(r[1], R1_130, 3.0 * R1_120);
+    lr[25] = fma(R0_140, Qr[23], lr[25]);
+    lr[26] = fma(R0_140, Qr[21], lr[26]);
+    lr[29] = fma(R0_140, Qr[14], lr[29]);
+    lr[31] = fma(R0_140, Qr[12], lr[31]);
+    lr[36] = fma(R0_140, Qr[7], lr[36]);
+    lr[38] = fma(R0_140, Qr[5], lr[38]);
+    lr[45] = fma(R0_140, Qr[2], lr[45]);
+    lr[47] = fma(R0_140, Qr[1], lr[47]);
+    lr[56] = fma(R0_140, Qr[0], lr[56]);
+    __builtin_amdgcn_sched_barrier(0);
+    const double R0_131 = r[2] * R1_130;
+    lr[25] = fma(R0_131, Qr[24], lr[25]);
+    lr[26] = fma(R0_131, Qr[22], lr[26]);
+    lr[27] = fma(R0_131, Qr[21], lr[27]);
+    lr[29] = fma(R0_131, Qr[15], lr[29]);
+    lr[30] = fma(R0_131, Qr[14], lr[30]);
+    lr[31] = fma(R0_131, Qr[13], lr[31]);
+    lr[32] = fma(R0_131, Qr[12], lr[32]);
+    lr[36] = fma(R0_131, Qr[8], lr[36]);
+    lr[37] = fma(R0_131, Qr[7], lr[37]);
+    lr[38] = fma(R0_131, Qr[6], lr[38]);
+    lr[39] = fma(R0_131, Qr[5], lr[39]);
+    lr[45] = fma(R0_131, Qr[3], lr[45]);
+    lr[46] = fma(R0_131, Qr[2], lr[46]);
+    lr[48] = fma(R0_131, Qr[1], lr[48]);
+    lr[57] = fma(R0_131, Qr[0], lr[57]);
+    __builtin_amdgcn_sched_barrier(0);
+    const double R0_122 = -(R0_320 + R0_140);
+    lr[27] = fma(R0_122, Qr[22], lr[27]);
+    lr[30] = fma(R0_122, Qr[15], lr[30]);
+    lr[32] = fma(R0_122, Qr[13], lr[32]);
+    lr[37] = fma(R0_122, Qr[8], lr[37]);
+    lr[39] = fma(R0_122, Qr[6], lr[39]);
+    lr[46] = fma(R0_122, Qr[3], lr[46]);
+    const double R3_020 = fma(r[1], R4_010, R4_000);
+    const double R2_030 = fma(r[1], R3_020, 2.0 * R3_010);
+    const double R1_040 = fma(r[1], R2_030, 3.0 * R2_020);
+    const double R0_050 = fma(r[1], R1_040, 4.0 * R1_030);
+    lr[26] = fma(R0_050, Qr[23], lr[26]);
+    lr[31] = fma(R0_050, Qr[14], lr[31]);
+    lr[38] = fma(R0_050, Qr[7], lr[38]);
+    lr[47] = fma(R0_050, Qr[2], lr[47]);
+    lr[58] = fma(R0_050, Qr[0], lr[58]);
+    const double R0_041 = r[2] * R1_040;
+    lr[26] = fma(R0_041, Qr[24], lr[26]);
+    lr[27] = fma(R0_041, Qr[23], lr[27]);
+    lr[31] = fma(R0_041, Qr[15], lr[31]);
+    lr[32] = fma(R0_041, Qr[14], lr[32]);
+    lr[38] = fma(R0_041, Qr[8], lr[38]);
+    lr[39] = fma(R0_041, Qr[7], lr[39]);
+    lr[47] = fma(R0_041, Qr[3], lr[47]);
+    lr[48] = fma(R0_041, Qr[2], lr[48]);
+    lr[59] = fma(R0_041, Qr[0], lr[59]);
+    __builtin_amdgcn_sched_barrier(0);
+    const double R0_032 = -(R0_230 + R0_050);
+    lr[27] = fma(R0_032, Qr[24], lr[27]);
+    lr[32] = fma(R0_032, Qr[15], lr[32]);
+    lr[39] = fma(R0_032, Qr[8], lr[39]);
+    lr[48] = fma(R0_032, Qr[3], lr[48]);
+  }
+  static constexpr int FLOPS_M2L_H = 726;  // + one refined rsqrt
+  __device__ __forceinline__ static void expand(const double* lr, double* local) {
+    double t[56];
+    t[0] = lr[0];
+    local[55] = t[0];
+    t[1] = -lr[1];
+    local[56] = t[1];
+    t[2] = -lr[2];
+    local[57] = t[2];
+    t[3] = -lr[3];
+    local[58] = t[3];
+    t[4] = lr[4];
+    local[59] = t[4];
+    t[5] = lr[5];
+    local[60] = t[5];
+    t[6] = lr[6];
+    local[61] = t[6];
+    t[7] = lr[7];
+    local[62] = t[7];
+    t[8] = lr[8];
+    local[63] = t[8];
+    t[9] = -(t[4] + t[7]);
+    local[64] = t[9];
+    t[10] = -lr[9];
+    local[65] = t[10];
+    t[11] = -lr[10];
+    local[66] = t[11];
+    t[12] = -lr[11];
+    local[67] = t[12];
+    t[13] = -lr[12];
+    local[68] = t[13];
+    t[14] = -lr[13];
+    local[69] = t[14];
+    t[15] = -(t[10] + t[13]);
+    local[70] = t[15];
+    t[16] = -lr[14];
+    local[71] = t[16];
+    t[17] = -lr[15];
+    local[72] = t[17];
+    t[18] = -(t[11] + t[16]);
+    local[73] = t[18];
+    t[19] = -(t[12] + t[17]);
+    local[74] = t[19];
+    t[20] = lr[16];
+    local[75] = t[20];
+    t[21] = lr[17];
+    local[76] = t[21];
+    t[22] = lr[18];
+    local[77] = t[22];
+    t[23] = lr[19];
+    local[78] = t[23];
+    t[24] = lr[20];
+    local[79] = t[24];
+    t[25] = -(t[20] + t[23]);
+    local[80] = t[25];
+    t[26] = lr[21];
+    local[81] = t[26];
+    t[27] = lr[22];
+    local[82] = t[27];
+    t[28] = -(t[21] + t[26]);
+    local[83] = t[28];
+    t[29] = -(t[22] + t[27]);
+    local[84] = t[29];
+    t[30] = lr[23];
+    local[85] = t[30];
+    t[31] = lr[24];
+    local[86] = t[31];
+    t[32] = -(t[23] + t[30]);
+    local[87] = t[32];
+    t[33] = -(t[24] + t[31]);
+    local[88] = t[33];
+    t[34] = -(t[25] + t[32]);
+    local[89] = t[34];
+    t[1] = (lr[1] + lr[25]);
+    local[0] = t[1];
+    t[2] = (lr[2] + lr[26]);
+    local[1] = t[2];
+    t[3] = (lr[3] + lr[27]);
+    local[2] = t[3];
+    t[4] = -(lr[4] + lr[28]);
+    local[3] = t[4];
+    t[5] = -(lr[5] + lr[29]);
+    local[4] = t[5];
+    t[6] = -(lr[6] + lr[30]);
+    local[5] = t[6];
+    t[7] = -(lr[7] + lr[31]);
+    local[6] = t[7];
+    t[8] = -(lr[8] + lr[32]);
+    local[7] = t[8];
+    t[9] = -(t[4] + t[7]);
+    local[8] = t[9];
+    t[10] = (lr[9] + lr[33]);
+    local[9] = t[10];
+    t[11] = (lr[10] + lr[34]);
+    local[10] = t[11];
+    t[12] = (lr[11] + lr[35]);
+    local[11] = t[12];
+    t[13] = (lr[12] + lr[36]);
+    local[12] = t[13];
+    t[14] = (lr[13] + lr[37]);
+    local[13] = t[14];
+    t[15] = -(t[10] + t[13]);
+    local[14] = t[15];
+    t[16] = (lr[14] + lr[38]);
+    local[15] = t[16];
+    t[17] = (lr[15] + lr[39]);
+    local[16] = t[17];
+    t[18] = -(t[11] + t[16]);
+    local[17] = t[18];
+    t[19] = -(t[12] + t[17]);
+    local[18] = t[19];
+    t[20] = -(lr[16] + lr[40]);
+    local[19] = t[20];
+    t[21] = -(lr[17] + lr[41]);
+    local[20] = t[21];
+    t[22] = -(lr[18] + lr[42]);
+    local[21] = t[22];
+    t[23] = -(lr[19] + lr[43]);
+    local[22] = t[23];
+    t[24] = -(lr[20] + lr[44]);
+    local[23] = t[24];
+    t[25] = -(t[20] + t[23]);
+    local[24] = t[25];
+    t[26] = -(lr[21] + lr[45]);
+    local[25] = t[26];
+    t[27] = -(lr[22] + lr[46]);
+    local[26] = t[27];
+    t[28] = -(t[21] + t[26]);
+    local[27] = t[28];
+    t[29] = -(t[22] + t[27]);
+    local[28] = t[29];
+    t[30] = -(lr[23] + lr[47]);
+    local[29] = t[30];
+    t[31] = -(lr[24] + lr[48]);
+    local[30] = t[31];
+    t[32] = -(t[23] + t[30]);
+    local[31] = t[32];
+    t[33] = -(t[24] + t[31]);
+    local[32] = t[33];
+    t[34] = -(t[25] + t[32]);
+    local[33] = t[34];
+    t[35] = lr[49];
+    local[34] = t[35];
+    t[36] = lr[50];
+    local[35] = t[36];
+    t[37] = lr[51];
+    local[36] = t[37];
+    t[38] = lr[52];
+    local[37] = t[38];
+    t[39] = lr[53];
+    local[38] = t[39];
+    t[40] = -(t[35] + t[38]);
+    local[39] = t[40];
+    t[41] = lr[54];
+    local[40] = t[41];
+    t[42] = lr[55];
+    local[41] = t[42];
+    t[43] = -(t[36] + t[41]);
+    local[42] = t[43];
+    t[44] = -(t[37] + t[42]);
+    local[43] = t[44];
+    t[45] = lr[56];
+    local[44] = t[45];
+    t[46] = lr[57];
+    local[45] = t[46];
+    t[47] = -(t[38] + t[45]);
+    local[46] = t[47];
+    t[48] = -(t[39] + t[46]);
+    local[47] = t[48];
+    t[49] = -(t[40] + t[47]);
+    local[48] = t[49];
+    t[50] = lr[58];
+    local[49] = t[50];
+    t[51] = lr[59];
+    local[50] = t[51];
+    t[52] = -(t[41] + t[50]);
+    local[51] = t[52];
+    t[53] = -(t[42] + t[51]);
+    local[52] = t[53];
+    t[54] = -(t[43] + t[52]);
+    local[53] = t[54];
+    t[55] = -(t[44] + t[53]);
+    local[54] = t[55];
   }
   __device__ __forceinline__ static void m2l_pair(const double* r, const double* QS,
                                                     const double* QTs, double* local,

@@ -9,6 +9,7 @@ coefficient lives in a register:
   p2m_add  Q_a += m b^a / a!                      (Sect. 2.1, Eq. massmom)
   m2m_add  Q_a += sum_{b<=a} Qc_b g^(a-b)/(a-b)!  (Appendix A.1, Eq. massmomtrans)
   m2l_add  local += M2L(r = s_src - s_tgt, Q)     (Sect. 2.2, Eq. dmkdeffmm; M_k)
+  m2l_h    the same M2L in reduced components, and what goes with it (below)
   l2l      local re-centred by h                  (Appendix A.2, Eq. gravmtranslat)
   l2p      field and potential polynomials at a  (Sect. 2.2)
 
@@ -21,7 +22,27 @@ stored as local[0 .. NH-2] = H (slots 1..NH-1) followed by local[NH-1 ..] = P.
 The field at offset a from the centre is F_c = sum_b H_(b+e_c) a^b/b! and the
 potential sum_b P_b a^b/b!; the caller multiplies both by -G.
 
-D_a comes from the Laplace-kernel recurrence written for D itself:
+The reduced form (the shared far field in FP64).  1/|r| is harmonic, so every
+degree of D is trace-free, D_(g+2x) + D_(g+2y) + D_(g+2z) = 0, and so are the
+sums over a whole degree of Q~ that make up a local expansion.  A degree n has
+2n + 1 independent components, here those with z exponent 0 or 1:
+  reduce   Qr from Q~: a moment with z exponent >= 2 is taken off its two
+           partners, Qr_(a-2z+2x) -= Q~_a and Qr_(a-2z+2y) -= Q~_a
+  m2l_h    S_g += sum_{|a| <= P-|g|} D_(a+g) Qr_a    for |g| <= P
+           X_g += sum_{|a| = P+1-|g|} D_(a+g) Qr_a   for 1 <= |g| <= P+1
+           over the independent components of g and a
+  expand   H_g = (-1)^(|g|+1) (S_g + X_g), P_g = (-1)^|g| S_g, the other
+           components from the traces
+At P = 3 that is 146 multiply-adds and 40 sums a node pair where the full
+components take 175, 54 additions and 54 sums.  m2l_h takes D from
+  R^m_0 = (-1)^m (2m-1)!! / r^(2m+1),  D_a = R^0_a,
+  R^m_(a+e) = r_e R^(m+1)_a + a_e R^(m+1)_(a-e),
+one multiply-add or two a component, instead of the recurrence in |r|^2.
+With ok false m2l_h and m2l_add_f32 add nothing (1/r = 0, so every D is 0): a
+lane without an entry then needs no branch, behind which the compiler would
+hold every sum twice.
+
+D_a otherwise comes from the Laplace-kernel recurrence written for D itself:
   n |r|^2 D_a = -(2n-1) sum_c a_c r_c D_(a-e_c) - (n-1) sum_c a_c (a_c-1) D_(a-2e_c).
 For |g| <= P the potential sum of P_g is a prefix of the field sum of H_g, so
 both come out of one pass over a.
@@ -31,6 +52,8 @@ import os
 import sys
 
 PMAX = 4
+# multiply-adds between two scheduling barriers of m2l_h
+SCHED_EVERY = 12
 
 
 def multi(n_max):
@@ -89,6 +112,136 @@ def monomial_code(name, vec, deg, idx, lines, cnt, over_fact=True):
         else:
             lines.append(f"    {name}[{k}] = {name}[{pk}] * {vec}[{c}];")
             cnt.mul += 1
+
+
+def reduced(n_max, n_min=0):
+    """The independent components, graded order: z exponent 0 or 1."""
+    return [a for a in multi(n_max) if a[2] <= 1 and sum(a) >= n_min]
+
+
+def gen_reduced(P):
+    """reduce, m2l_h and expand (see the docstring)."""
+    ms = multi(P + 1)
+    idx = {a: k for k, a in enumerate(ms)}
+    NH, NQ = ncoef(P + 1), ncoef(P)
+    rq = reduced(P)                 # moments and S
+    rx = reduced(P + 1, 1)          # X
+    qi = {a: k for k, a in enumerate(rq)}
+    si = qi
+    xi = {a: len(rq) + k for k, a in enumerate(rx)}
+    out = [f"  static constexpr int NQR = {len(rq)};   // independent moments",
+           f"  static constexpr int NLR = {len(rq) + len(rx)};  // S then X"]
+    # reduce: from the largest z exponent down
+    L = ["  __device__ __forceinline__ static void reduce(const double* Q, double* Qr) {"]
+    var = {a: f"Q[{idx[a]}]" for a in multi(P)}
+    terms = {a: [(1, a)] for a in multi(P)}  # kept: signed sums of full moments
+    for a in sorted(multi(P), key=lambda t: -t[2]):
+        if a[2] < 2:
+            continue
+        for e in ((2, 0, -2), (0, 2, -2)):
+            b = add(a, e)
+            terms[b] = terms[b] + [(-s, t) for s, t in terms[a]]
+        terms[a] = []
+    for a in rq:
+        merged = {}
+        for sg, t in terms[a]:
+            merged[t] = merged.get(t, 0) + sg
+        expr = ""
+        for t, cf in merged.items():
+            if cf == 0:
+                continue
+            body = var[t] if abs(cf) == 1 else f"{lit(abs(cf))} * {var[t]}"
+            expr += (" + " if cf > 0 else " - ") + body if expr else ("" if cf > 0 else "-") + body
+        L.append(f"    Qr[{qi[a]}] = {expr};")
+    L.append("  }")
+    out += L
+    # m2l_h
+    c = Counter()
+    L = ["  __device__ __forceinline__ static void m2l_h(const double* r, const double* Qr, double* lr, bool ok) {",
+         "    const double r2 = fma(r[0], r[0], fma(r[1], r[1], r[2] * r[2]));",
+         "    const double ri = rsqrt_refined(r2);",
+         "    const double rinv = ok ? ri : 0.0;",
+         "    const double s = rinv * rinv;",
+         "    const double R0_000 = rinv;"]
+    c.fma += 2; c.mul += 2
+    for m in range(1, P + 2):
+        L.append(f"    const double R{m}_000 = R{m - 1}_000 * ({lit(-(2 * m - 1))} * s);")
+        c.mul += 1 if m == 1 else 2
+    done = {(m, (0, 0, 0)) for m in range(P + 2)}
+
+    def name(m, a):
+        return f"R{m}_{a[0]}{a[1]}{a[2]}"
+
+    def need(m, a):
+        if (m, a) in done:
+            return
+        if m == 0 and a[2] >= 2:  # trace (z exponent 2)
+            b1, b2 = add(a, (2, 0, -2)), add(a, (0, 2, -2))
+            need(0, b1); need(0, b2)
+            L.append(f"    const double {name(0, a)} = -({name(0, b1)} + {name(0, b2)});")
+            c.add += 1
+            done.add((m, a))
+            return
+        e = 2 if a[2] > 0 else (0 if a[0] >= a[1] else 1)
+        b = list(a); b[e] -= 1; b = tuple(b)
+        need(m + 1, b)
+        if b[e] == 0:
+            L.append(f"    const double {name(m, a)} = r[{e}] * {name(m + 1, b)};")
+            c.mul += 1
+        else:
+            d = list(b); d[e] -= 1; d = tuple(d)
+            need(m + 1, d)
+            if b[e] == 1:
+                L.append(f"    const double {name(m, a)} = fma(r[{e}], {name(m + 1, b)}, {name(m + 1, d)});")
+                c.fma += 1
+            else:
+                L.append(f"    const double {name(m, a)} = fma(r[{e}], {name(m + 1, b)}, {lit(b[e])} * {name(m + 1, d)});")
+                c.fma += 1; c.mul += 1
+        done.add((m, a))
+
+    # one component of D after the other, each used as soon as it is known and
+    # the compiler kept from moving code across every few of them: what is held
+    # at once then fits three waves per SIMD at P = 3
+    todo = 0
+    for n in range(P + 2):
+        for d in [t for t in ms if sum(t) == n and t[2] <= 2]:
+            if todo >= SCHED_EVERY:
+                L.append("    __builtin_amdgcn_sched_barrier(0);")
+                todo = 0
+            need(0, d)
+            for g in reduced(P + 1):
+                a = sub(d, g)
+                if min(a) < 0 or a[2] > 1 or sum(a) > P:
+                    continue
+                k = si[g] if n <= P else xi[g]
+                L.append(f"    lr[{k}] = fma({name(0, d)}, Qr[{qi[a]}], lr[{k}]);")
+                c.fma += 1
+                todo += 1
+    L.append("  }")
+    out += L
+    out.append(f"  static constexpr int FLOPS_M2L_H = {c.flops()};  // + one refined rsqrt")
+    # expand
+    L = ["  __device__ __forceinline__ static void expand(const double* lr, double* local) {",
+         f"    double t[{NH}];"]
+    for which in ("P", "H"):
+        for g in ms:
+            ng = sum(g)
+            if (which == "P" and ng > P) or (which == "H" and ng == 0):
+                continue
+            if g[2] <= 1:
+                if which == "P":
+                    v = f"lr[{si[g]}]"
+                else:
+                    v = f"lr[{xi[g]}]" if ng > P else f"(lr[{si[g]}] + lr[{xi[g]}])"
+                sign = ng % 2 if which == "P" else (ng + 1) % 2
+                L.append(f"    t[{idx[g]}] = {'-' if sign else ''}{v};")
+            else:
+                b1, b2 = add(g, (2, 0, -2)), add(g, (0, 2, -2))
+                L.append(f"    t[{idx[g]}] = -(t[{idx[b1]}] + t[{idx[b2]}]);")
+            L.append(f"    local[{(NH - 1 + idx[g]) if which == 'P' else idx[g] - 1}] = t[{idx[g]}];")
+    L.append("  }")
+    out += L
+    return out
 
 
 def gen(P):
@@ -227,16 +380,21 @@ def gen(P):
     Lm = []
     for line in L:
         line = line.replace("static void m2l_add(const double* r, const double* Q, double* local)",
-                            "static void m2l_add_f32(const float* r, const float* Q, double* local)")
+                            "static void m2l_add_f32(const float* r, const float* Q, double* local, bool ok = true)")
+        if line == "    {":  # (bounds the registers: two waves per SIMD)
+            Lm.append("    __builtin_amdgcn_sched_barrier(0);")
         line = line.replace("const double ", "const float ").replace("double D[", "float D[")
         line = line.replace("double s = ", "float s = ")
-        line = line.replace("rsqrt(r2)", "__frsqrt_rn(r2)")
+        line = line.replace("rsqrt(r2)", "ok ? __frsqrt_rn(r2) : 0.0f")
         line = line.replace("fma(", "fmaf(")
         import re as _re
         line = _re.sub(r"(-?\d+\.\d+(e-?\d+)?)", r"\1f", line) if ("D[" in line and "=" in line and "local" not in line) or "sn" in line else line
         line = line.replace("local[", "local[").replace("] += s;", "] += (double)s;").replace("] -= s;", "] -= (double)s;")
         Lm.append(line)
     out += Lm
+
+    # ---- the reduced form
+    out += gen_reduced(P)
 
     # ---- M2L of one node pair in both directions (the one-sided symmetric
     # form): D(r) once for r = s_S - s_T; the target side as m2l_add; the
@@ -380,6 +538,7 @@ def main(path):
         "// Generated by gen_expansions.py -- do not edit.",
         "// Cartesian expansion kernels for orders 0..%d (see the generator's docstring)." % PMAX,
         "#pragma once",
+        "#include \"softening.h\"",
         "namespace sfmm {",
         "template <int P> struct Exp;",
     ]

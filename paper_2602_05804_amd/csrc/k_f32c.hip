@@ -20,16 +20,17 @@ namespace {
 
 template <int P>
 __global__ void k_prep_nodes32(int nn, const double* __restrict__ rec,
-                               const int32_t* __restrict__ node_depth, float* __restrict__ rec32) {
+                               float* __restrict__ rec32) {
   constexpr int NQ = Exp<P>::NQ;
   constexpr int RS = rec_stride(P), RS32 = rec32_stride(P);
   const int v = blockIdx.x * blockDim.x + threadIdx.x;
   if (v >= nn) return;
   const double* r = rec + (int64_t)v * RS;
   float* o = rec32 + (int64_t)v * RS32;
+  double* c = reinterpret_cast<double*>(o);
+  c[0] = r[0]; c[1] = r[1]; c[2] = r[2];
 #pragma unroll
-  for (int k = 0; k < NQ; ++k) o[k] = (float)r[8 + k];
-  o[NQ] = __int_as_float(node_depth[v]);
+  for (int k = 0; k < NQ; ++k) o[6 + k] = (float)r[8 + k];
 }
 
 template <int RS>
@@ -95,7 +96,7 @@ __global__ __launch_bounds__(64) void k_far32(FarArgs a, const float* __restrict
     const uint32_t s = ent & kSrcMask;
     const double* rs = rec + (int64_t)s * RS;
     sd[0] = rs[0]; sd[1] = rs[1]; sd[2] = rs[2];
-    const float* r32 = rec32 + (int64_t)s * RS32;
+    const float* r32 = rec32 + (int64_t)s * RS32 + 6;
 #pragma unroll
     for (int q = 0; q < NQ; ++q) qd[q] = r32[q];
   };
@@ -625,16 +626,16 @@ void p2p32(bool node_lists, int variant, const NearArgs& a, const float4* pf, co
 }  // namespace
 
 void launch_prep32(int order, int nn, int nleaves, const int32_t* leaf_node, const NodeInfo* info,
-                   const double* rec, const int32_t* node_depth, const double* xs, const double* ys,
-                   const double* zs, const double* ms, const double* hs, float* rec32, float4* pf,
-                   float2* ph, hipStream_t s) {
+                   const double* rec, const double* xs, const double* ys, const double* zs,
+                   const double* ms, const double* hs, float* rec32, float4* pf, float2* ph,
+                   hipStream_t s) {
   const unsigned nb = (unsigned)((nn + 255) / 256);
   switch (order) {
-    case 0: k_prep_nodes32<0><<<nb, 256, 0, s>>>(nn, rec, node_depth, rec32); break;
-    case 1: k_prep_nodes32<1><<<nb, 256, 0, s>>>(nn, rec, node_depth, rec32); break;
-    case 2: k_prep_nodes32<2><<<nb, 256, 0, s>>>(nn, rec, node_depth, rec32); break;
-    case 3: k_prep_nodes32<3><<<nb, 256, 0, s>>>(nn, rec, node_depth, rec32); break;
-    case 4: k_prep_nodes32<4><<<nb, 256, 0, s>>>(nn, rec, node_depth, rec32); break;
+    case 0: k_prep_nodes32<0><<<nb, 256, 0, s>>>(nn, rec, rec32); break;
+    case 1: k_prep_nodes32<1><<<nb, 256, 0, s>>>(nn, rec, rec32); break;
+    case 2: k_prep_nodes32<2><<<nb, 256, 0, s>>>(nn, rec, rec32); break;
+    case 3: k_prep_nodes32<3><<<nb, 256, 0, s>>>(nn, rec, rec32); break;
+    case 4: k_prep_nodes32<4><<<nb, 256, 0, s>>>(nn, rec, rec32); break;
   }
   switch (rec_stride(order)) {
     case 16: prep_particles<16>(nleaves, leaf_node, info, rec, xs, ys, zs, ms, hs, pf, ph, s); break;

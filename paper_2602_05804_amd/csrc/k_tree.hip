@@ -457,7 +457,8 @@ __device__ __forceinline__ void geom_node(int v, const NodeInfo* __restrict__ in
                                           const double* __restrict__ ys,
                                           const double* __restrict__ zs,
                                           const double* __restrict__ ms,
-                                          const double* __restrict__ hs, double* rec) {
+                                          const double* __restrict__ hs, double* rec,
+                                          double* recq) {
   using E = Exp<P>;
   constexpr int NQ = E::NQ;
   constexpr int RS = rec_stride(P);
@@ -510,6 +511,14 @@ __device__ __forceinline__ void geom_node(int v, const NodeInfo* __restrict__ in
   }
 #pragma unroll
   for (int k = 0; k < NQ; ++k) r[8 + k] = Q[k];
+  if (recq) {
+    double* q = recq + (int64_t)v * recq_stride(P);
+    double Qr[E::NQR];
+    E::reduce(Q, Qr);
+    q[0] = r[0]; q[1] = r[1]; q[2] = r[2];
+#pragma unroll
+    for (int k = 0; k < E::NQR; ++k) q[3 + k] = Qr[k];
+  }
 }
 
 // one level, a thread per node
@@ -518,10 +527,10 @@ __global__ void k_geom_level(const int32_t* __restrict__ level_nodes, uint32_t b
                              const NodeInfo* __restrict__ info, const double* __restrict__ xs,
                              const double* __restrict__ ys, const double* __restrict__ zs,
                              const double* __restrict__ ms, const double* __restrict__ hs,
-                             double* __restrict__ rec) {
+                             double* __restrict__ rec, double* __restrict__ recq) {
   const uint32_t idx = beg + blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= end) return;
-  geom_node<P>(level_nodes[idx], info, xs, ys, zs, ms, hs, rec);
+  geom_node<P>(level_nodes[idx], info, xs, ys, zs, ms, hs, rec, recq);
 }
 
 // a run of small levels, deepest first, in one block: a barrier between
@@ -533,11 +542,11 @@ __global__ __launch_bounds__(GEOM_RUN_THREADS) void k_geom_run(
     const int32_t* __restrict__ level_nodes, const uint32_t* __restrict__ level_off, int kdeep,
     int ktop, const NodeInfo* __restrict__ info, const double* __restrict__ xs,
     const double* __restrict__ ys, const double* __restrict__ zs, const double* __restrict__ ms,
-    const double* __restrict__ hs, double* rec) {
+    const double* __restrict__ hs, double* rec, double* recq) {
   for (int k = kdeep; k >= ktop; --k) {
     const uint32_t beg = level_off[k], end = level_off[k + 1];
     for (uint32_t idx = beg + threadIdx.x; idx < end; idx += GEOM_RUN_THREADS)
-      geom_node<P>(level_nodes[idx], info, xs, ys, zs, ms, hs, rec);
+      geom_node<P>(level_nodes[idx], info, xs, ys, zs, ms, hs, rec, recq);
     __syncthreads();
   }
 }
@@ -712,7 +721,7 @@ template <int P>
 void geometry_order(int maxdepth, const uint32_t* off_h, const uint32_t* off_d,
                     const int32_t* level_nodes, const NodeInfo* info, const double* xs,
                     const double* ys, const double* zs, const double* ms, const double* hs,
-                    double* rec, hipStream_t s) {
+                    double* rec, double* recq, hipStream_t s) {
   // runs of four or more consecutive levels of at most GEOM_RUN_MAX nodes
   // (the top of the tree) go to one block, the others one launch each
   int k = maxdepth;
@@ -725,14 +734,14 @@ void geometry_order(int maxdepth, const uint32_t* off_h, const uint32_t* off_d,
       // about two thirds of a launch of its own)
       if (k - top >= 3) {
         k_geom_run<P><<<1, GEOM_RUN_THREADS, 0, s>>>(level_nodes, off_d, k, top, info, xs, ys,
-                                                     zs, ms, hs, rec);
+                                                     zs, ms, hs, rec, recq);
         k = top - 1;
         continue;
       }
     }
     if (size > 0)
       k_geom_level<P><<<blocks_for(size, 128), 128, 0, s>>>(level_nodes, off_h[k], off_h[k + 1],
-                                                             info, xs, ys, zs, ms, hs, rec);
+                                                             info, xs, ys, zs, ms, hs, rec, recq);
     --k;
   }
 }
@@ -740,12 +749,13 @@ void geometry_order(int maxdepth, const uint32_t* off_h, const uint32_t* off_d,
 void launch_geometry(int order, int maxdepth, const uint32_t* level_off_host,
                      const uint32_t* level_off_dev, const int32_t* level_nodes,
                      const NodeInfo* info, const double* xs, const double* ys, const double* zs,
-                     const double* ms, const double* hs, double* rec, hipStream_t s) {
+                     const double* ms, const double* hs, double* rec, double* recq,
+                     hipStream_t s) {
   switch (order) {
 #define GEOM_CASE(P)                                                                         \
   case P:                                                                                    \
     geometry_order<P>(maxdepth, level_off_host, level_off_dev, level_nodes, info, xs, ys, zs, \
-                      ms, hs, rec, s);                                                       \
+                      ms, hs, rec, recq, s);                                                 \
     break;
     GEOM_CASE(0) GEOM_CASE(1) GEOM_CASE(2) GEOM_CASE(3) GEOM_CASE(4)
 #undef GEOM_CASE

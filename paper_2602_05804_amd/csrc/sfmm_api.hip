@@ -29,7 +29,7 @@ enum BufId {
   B_KEY0, B_KEY1, B_VAL0, B_VAL1, B_HIST, B_SCANTMP,
   B_XS, B_YS, B_ZS, B_MS, B_HS, B_HIS, B_H4, B_P4,
   B_KFIRST, B_KLAST, B_KLEFT, B_KRIGHT, B_KPAR, B_KSIDE, B_KEPT,
-  B_LFLAG, B_LAT, B_INFO, B_REC, B_L2BITS, B_CHUNK,
+  B_LFLAG, B_LAT, B_INFO, B_REC, B_RECQ, B_L2BITS, B_CHUNK,
   B_LEAFNODE, B_LEAFDEPTH, B_PLEAF,
   B_LDOFF, B_DEPTHCNT, B_M2LCNT, B_P2PCNT, B_PAIRCNT, B_M2L, B_P2P,
   B_FAR, B_MOMPART, B_MOM, B_L2LCNT,
@@ -256,6 +256,10 @@ int do_build(sfmm_ctx* ctx, int64_t n64, const double* x, const double* m, const
     if ((rc = ensure(ctx, q.id, q.bytes))) return rc;
   int* status = P<int>(ctx, B_STATUS);
   uint64_t* small = P<uint64_t>(ctx, B_SMALL);
+  // (the shared far field reads its sources from records of their own)
+  const bool recq = ctx->cfg.far_mode == SFMM_FAR_SHARED && ctx->cfg.walk_mode == SFMM_WALK_LEVEL;
+  if (recq && (rc = ensure(ctx, B_RECQ, sizeof(double) * recq_stride(order) * (size_t)nmax_nodes)))
+    return rc;
   phase_mark(ctx, 0, 0);
   HIPCHK(hipMemsetAsync(status, 0, sizeof(int) * 4, s));
   HIPCHK(hipMemsetAsync(small, 0, sizeof(uint64_t) * S_COUNT, s));
@@ -405,7 +409,8 @@ int do_build(sfmm_ctx* ctx, int64_t n64, const double* x, const double* m, const
   launch_geometry(order, ctx->maxdepth, ctx->level_off.data(), P<uint32_t>(ctx, B_LEVOFF),
                   reinterpret_cast<const int32_t*>(P<uint32_t>(ctx, B_LEVNODES)), info,
                   P<double>(ctx, B_XS), P<double>(ctx, B_YS), P<double>(ctx, B_ZS),
-                  P<double>(ctx, B_MS), P<double>(ctx, B_HS), P<double>(ctx, B_REC), s);
+                  P<double>(ctx, B_MS), P<double>(ctx, B_HS), P<double>(ctx, B_REC),
+                  recq ? P<double>(ctx, B_RECQ) : nullptr, s);
   if (nn > 1) {
     const int nitems = (int)(hsmall[S_NITEMS] & 0xffffffffu);
     if ((rc = ensure(ctx, B_EXTMAP, sizeof(uint32_t) * (size_t)std::max(nitems, 1)))) return rc;
@@ -762,7 +767,7 @@ int do_walk_and_eval(sfmm_ctx* ctx, double theta, int precision, const double* m
     return fail(ctx, SFMM_EUNSUPPORTED, "SFMM_FAR_MUTUAL is FP64 only");
   if (shared && (rc = ensure(ctx, B_LN, sizeof(double) * local_count(ctx->order) * (size_t)ctx->nn)))
     return rc;
-  if (shared && !mutual && (rc = ensure(ctx, B_M2LORD, sizeof(uint32_t) * (size_t)ctx->nn)))
+  if (shared && !mutual && (rc = ensure(ctx, B_M2LORD, sizeof(uint32_t) * 2 * (size_t)ctx->nn)))
     return rc;
   if (!level) ctx->m2l_unique = 0;
   phase_mark(ctx, 1, 0);
@@ -894,7 +899,10 @@ int do_walk_and_eval(sfmm_ctx* ctx, double theta, int precision, const double* m
       sa.pool = f.node_m2l_pool;
       sa.rec = f.rec;
       sa.rec32 = f32 ? P<float>(ctx, B_REC32) : nullptr;
+      sa.recq = P<double>(ctx, B_RECQ);
       sa.top = ctx->cfg.fp64_top_depth;
+      // (the order puts the targets above the top depth first)
+      sa.n64 = f32 ? (int)ctx->level_off[std::min(sa.top, kMaxDepthCap + 1)] : 0;
       sa.ln = P<double>(ctx, B_LN);
       if (mutual) {
         launch_far_mutual(ctx->order, f, sa, s);
@@ -906,9 +914,11 @@ int do_walk_and_eval(sfmm_ctx* ctx, double theta, int precision, const double* m
         ob.key1 = P<uint64_t>(ctx, B_LEVKEY1);
         ob.ids0 = P<uint32_t>(ctx, B_LEVIDS);
         ob.ids1 = P<uint32_t>(ctx, B_M2LORD);
+        ob.ids2 = ob.ids1 + ctx->nn;
         ob.hist = P<uint32_t>(ctx, B_HIST);
         ob.hist_tmp = P<uint32_t>(ctx, B_SCANTMP);
         ob.total = reinterpret_cast<uint32_t*>(small + S_SORTTOT);
+        m2l_windows(sa, ctx->m2l_unique);
         launch_m2l_order(sa, f32, ob, s);
         sa.level_nodes = reinterpret_cast<const int32_t*>(ob.ids1);
         launch_far_shared(ctx->order, f, sa, f32, s);
@@ -921,7 +931,7 @@ int do_walk_and_eval(sfmm_ctx* ctx, double theta, int precision, const double* m
   };
   phase_mark(ctx, 3, 0);
   if (f32) {
-    launch_prep32(ctx->order, (int)ctx->nn, nl, f.leaf_node, f.info, f.rec, P<int32_t>(ctx, B_NDEPTH),
+    launch_prep32(ctx->order, (int)ctx->nn, nl, f.leaf_node, f.info, f.rec,
                   f.xs, f.ys, f.zs, P<double>(ctx, B_MS), P<double>(ctx, B_HS),
                   P<float>(ctx, B_REC32), P<float4>(ctx, B_PF32), P<float2>(ctx, B_PH32), s);
   }

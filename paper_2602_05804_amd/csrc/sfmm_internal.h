@@ -60,8 +60,11 @@ __device__ __forceinline__ unsigned xcd_block(unsigned b, unsigned nb) {
 
 // local (field) coefficients: H_g for 1 <= |g| <= p+1, then P_b for |b| <= p
 __host__ __device__ constexpr int local_count(int p) { return ncoef(p + 1) - 1 + ncoef(p); }
-// FP32 copy of the moments (SFMM_FP32C): ncoef floats, then the node depth
-__host__ __device__ constexpr int rec32_stride(int p) { return ((ncoef(p) + 1 + 7) / 8) * 8; }
+// M2L source records, 16-byte multiples.  FP64: the centre, then the
+// independent moments ((p + 1)^2 of them, Exp<P>::reduce); FP32 (SFMM_FP32C):
+// the centre in FP64 (6 words), then all moments in FP32.
+__host__ __device__ constexpr int recq_stride(int p) { return (3 + (p + 1) * (p + 1) + 1) / 2 * 2; }
+__host__ __device__ constexpr int rec32_stride(int p) { return (6 + ncoef(p) + 3) / 4 * 4; }
 
 // ---- status bits written by kernels --------------------------------------
 // ST_BADLIST: after a walk, a list a consumer would read lies outside the
@@ -143,11 +146,13 @@ void launch_leaf_depth(int nleaves, const int32_t* leaf_node, const NodeInfo* in
                        const int32_t* node_depth, int32_t* leaf_depth, int32_t* p_leaf,
                        int* maxdepth, hipStream_t s);
 // geometry and moments, deepest level first (level offsets: a host copy for
-// the launch sizes and the device array for runs of small levels)
+// the launch sizes and the device array for runs of small levels); recq: the
+// M2L source records as well (may be null)
 void launch_geometry(int order, int maxdepth, const uint32_t* level_off_host,
                      const uint32_t* level_off_dev, const int32_t* level_nodes,
                      const NodeInfo* info, const double* xs, const double* ys, const double* zs,
-                     const double* ms, const double* hs, double* rec, hipStream_t s);
+                     const double* ms, const double* hs, double* rec, double* recq,
+                     hipStream_t s);
 void launch_extent_count(int nn, const NodeInfo* info, uint32_t* chunks, hipStream_t s);
 void launch_extent(int order, int nn, int nitems, const NodeInfo* info,
                    const uint32_t* chunk_off, uint32_t* item_node, const double* xs,
@@ -333,22 +338,34 @@ struct SharedFarArgs {
   const int32_t* depth;        // node depth
   const uint32_t *m2l_off, *m2l_cnt, *pool;  // per-node M2L lists
   const double* rec;
-  const float* rec32;  // FP32 moments (FP32C)
+  const double* recq;  // M2L source records (FP64)
+  const float* rec32;  // M2L source records (FP32C)
+  int n64;             // FP32C: targets contracted in FP64, the first n64 of the order
+  // the order's windows: nodes whose lists take more than `longer` steps of 8
+  // entries come before them (*nlong of them, 0 without the key sort)
+  int window;
+  uint32_t longer;
+  const uint32_t* nlong;
+  uint64_t steps;  // bound on the steps of all lists, and with it on
+  int maxlong;     // the number of long ones
   int top;             // FP32C: targets at depth < top in FP64
   double* ln;          // [nn][NL] per-node local expansions (written where cnt > 0)
 };
 void launch_far_shared(int order, const FarArgs& f, const SharedFarArgs& a, bool f32,
                        hipStream_t s);
-// node order for the shared M2L (k_m2l_nodes): nodes grouped by the number of
-// steps their lists take, longest first, stable over level order; result in
-// ids1 (key0/ids0 and key1 are scratch of nn entries, hist/hist_tmp/total as
-// for radix_pass)
+// The node order of the shared M2L (result in ids1, the other buffers are
+// scratch of nn entries, hist/hist_tmp/total as for radix_pass): the FP64
+// targets of FP32C, then nodes of long lists, longest first, then the others
+// in windows of a.window nodes that follow each other in level order, each
+// sorted by list length
 struct M2LOrderBufs {
   uint64_t *key0, *key1;
-  uint32_t *ids0, *ids1;
+  uint32_t *ids0, *ids1, *ids2;
   uint32_t *hist, *hist_tmp, *total;
 };
-void launch_m2l_order(const SharedFarArgs& a, bool f32, const M2LOrderBufs& b, hipStream_t s);
+// sets up a's windows for lists of m2l_total entries over all nodes
+void m2l_windows(SharedFarArgs& a, uint64_t m2l_total);
+void launch_m2l_order(SharedFarArgs& a, bool f32, const M2LOrderBufs& b, hipStream_t s);
 // the one-sided symmetric form of the shared far field: each unordered node
 // pair once (one D(r) for both nodes, the partner's side added atomically),
 // then the per-leaf L2L chain and L2P (FP64 only)
@@ -423,11 +440,11 @@ void launch_p2p_tile(bool node_lists, int ls, const NearArgs& a, int64_t items, 
 void launch_p2p_reduce(const NearArgs& a, int ls, hipStream_t s);
 
 // ---- FP32-compensated form ------------------------------------------------------
-// FP32 moments per node and FP32 leaf-relative particle offsets (+ mass, h, 1/h)
+// FP32 M2L records per node and FP32 leaf-relative particle offsets (+ mass, h, 1/h)
 void launch_prep32(int order, int nn, int nleaves, const int32_t* leaf_node, const NodeInfo* info,
-                   const double* rec, const int32_t* node_depth, const double* xs, const double* ys,
-                   const double* zs, const double* ms, const double* hs, float* rec32, float4* pf,
-                   float2* ph, hipStream_t s);
+                   const double* rec, const double* xs, const double* ys, const double* zs,
+                   const double* ms, const double* hs, float* rec32, float4* pf, float2* ph,
+                   hipStream_t s);
 void launch_far32(int order, bool node_lists, const FarArgs& a, const float* rec32, int top,
                   hipStream_t s);
 // false when leaf_size > 16 (not built)
