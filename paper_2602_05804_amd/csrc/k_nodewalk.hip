@@ -68,7 +68,7 @@ __device__ __forceinline__ uint32_t wave_prefix(uint32_t c, uint32_t& total) {
 }
 
 __global__ void k_node_depth(int nn, const NodeInfo* __restrict__ info, int32_t* __restrict__ depth,
-                             uint64_t* __restrict__ key, uint32_t* __restrict__ ids) {
+                             uint64_t* __restrict__ key) {
   const int v = blockIdx.x * blockDim.x + threadIdx.x;
   if (v >= nn) return;
   int d = 0;
@@ -76,17 +76,16 @@ __global__ void k_node_depth(int nn, const NodeInfo* __restrict__ info, int32_t*
   depth[v] = d;
   // grouped by depth, and within a depth the internal nodes first
   key[v] = (uint64_t)min(2 * d + (info[v].child < 0 ? 1 : 0), 255);
-  ids[v] = (uint32_t)v;
 }
 
 // level k spans [level_off[k], level_off[k + 1]), its internal nodes
-// [level_off[k], level_int[k]) (the scanned histogram of the sort keys)
-__global__ void k_level_offsets(int nlev, int nb, int nn, const uint32_t* __restrict__ hist,
+// [level_off[k], level_int[k]) (the first places of the sort keys)
+__global__ void k_level_offsets(int nlev, int nn, const uint32_t* __restrict__ base,
                                 uint32_t* __restrict__ level_off, uint32_t* __restrict__ level_int) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k > nlev) return;
-  level_off[k] = k < nlev ? hist[(int64_t)(2 * k) * nb] : (uint32_t)nn;
-  level_int[k] = k < nlev ? hist[(int64_t)(2 * k + 1) * nb] : (uint32_t)nn;
+  level_off[k] = k < nlev ? base[2 * k] : (uint32_t)nn;
+  level_int[k] = k < nlev ? base[2 * k + 1] : (uint32_t)nn;
 }
 
 // ---- one level -----------------------------------------------------------------
@@ -754,14 +753,13 @@ void launch_leaf_stats(const LeafStatArgs& a, hipStream_t s) {
 }
 
 void launch_node_depth(int nn, const NodeInfo* info, int32_t* depth, uint64_t* key,
-                       uint32_t* ids, hipStream_t s) {
-  k_node_depth<<<(nn + 255) / 256, 256, 0, s>>>(nn, info, depth, key, ids);
+                       hipStream_t s) {
+  k_node_depth<<<(nn + 255) / 256, 256, 0, s>>>(nn, info, depth, key);
 }
 
-void launch_level_offsets(int nlev, int nb, int nn, const uint32_t* hist_scanned,
-                          uint32_t* level_off, uint32_t* level_int, hipStream_t s) {
-  k_level_offsets<<<(nlev + 1 + 255) / 256, 256, 0, s>>>(nlev, nb, nn, hist_scanned, level_off,
-                                                          level_int);
+void launch_level_offsets(int nlev, int nn, const uint32_t* base, uint32_t* level_off,
+                          uint32_t* level_int, hipStream_t s) {
+  k_level_offsets<<<(nlev + 1 + 255) / 256, 256, 0, s>>>(nlev, nn, base, level_off, level_int);
 }
 
 void launch_nodewalk_level(const NodeWalkArgs& a, int level, int nodes_in_level, uint32_t rank0,

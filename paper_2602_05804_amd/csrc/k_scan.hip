@@ -1,5 +1,5 @@
 // k_scan.hip -- exclusive prefix sums (u32, u64) used to size and place the
-// tree's nodes, the radix-sort digits and the per-leaf interaction lists.
+// tree's nodes and the per-leaf interaction lists.
 // Two passes: tile totals, then the tile scan, each block first adding up the
 // totals of the tiles before its own (a few hundred at most for the sizes
 // here, so this costs less than a launch of its own).  Deterministic (integer

@@ -1,7 +1,8 @@
 // k_tree.hip -- tree construction on the GPU.
 //
-//   bbox + Morton keys  cubic box, 21-bit cells per axis, x > y > z interleave
-//   radix sort          stable LSD sort of (key, caller index), 8-bit digits
+//   bbox                corners of the cubic box (keys: 21-bit cells per axis,
+//                       x > y > z interleave)
+//   (the radix sorts are in k_sort.hip)
 //   binary radix tree   Karras-style parallel build on the sorted keys; equal
 //                       keys split on the bits of their sorted positions
 //   leaf collapse       a node with <= leaf_size particles is a leaf
@@ -13,15 +14,15 @@
 // The whole library is compiled with -ffp-contract=off: the centres of mass,
 // sizes and the acceptance test below round exactly as written, so every
 // node-pair decision matches a CPU evaluation of the same formulas.
+#include <algorithm>
+
+#include "morton.h"
 #include "sfmm_internal.h"
 
 namespace sfmm {
 namespace {
 
 constexpr int BBOX_THREADS = 256;
-constexpr int RS_THREADS = 256;
-constexpr int RS_ITEMS = 16;
-constexpr int RS_TILE = RS_THREADS * RS_ITEMS;
 
 __device__ __forceinline__ double wave_min(double v) {
   for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, 64));
@@ -65,50 +66,21 @@ __global__ __launch_bounds__(BBOX_THREADS) void k_bbox_partial(int n, const doub
   }
 }
 
-// box[0..2] = min corner, box[3] = cube extent, box[4] = 2^21 / extent (0 if flat)
-__global__ __launch_bounds__(256) void k_bbox_final(int nb, const double* __restrict__ part,
-                                                    double* __restrict__ box) {
-  double mn[3] = {INFINITY, INFINITY, INFINITY}, mx[3] = {-INFINITY, -INFINITY, -INFINITY};
-  for (int b = threadIdx.x; b < nb; b += 256)
-    for (int d = 0; d < 3; ++d) {
-      mn[d] = fmin(mn[d], part[6 * b + d]);
-      mx[d] = fmax(mx[d], part[6 * b + 3 + d]);
-    }
-  __shared__ double sh[6][4];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  for (int d = 0; d < 3; ++d) {
-    const double a = wave_min(mn[d]), c = wave_max(mx[d]);
-    if (lane == 0) { sh[d][w] = a; sh[3 + d][w] = c; }
-  }
-  __syncthreads();
-  if (threadIdx.x != 0) return;
-  for (int d = 0; d < 3; ++d) {
-    mn[d] = fmin(fmin(sh[d][0], sh[d][1]), fmin(sh[d][2], sh[d][3]));
-    mx[d] = fmax(fmax(sh[3 + d][0], sh[3 + d][1]), fmax(sh[3 + d][2], sh[3 + d][3]));
-  }
-  double ext = 0.0;
-  for (int d = 0; d < 3; ++d) {
-    double e = mx[d] - mn[d];
-    if (e > ext) ext = e;
-  }
-  for (int d = 0; d < 3; ++d) box[d] = mn[d];
-  box[3] = ext;
-  box[4] = ext > 0.0 ? 2097152.0 / ext : 0.0;
-}
-
 // ---- several systems (forest) -----------------------------------------------
-// box of system s: one block per system; same box[] layout as k_bbox_final
-__global__ __launch_bounds__(256) void k_bbox_sys(const int64_t* __restrict__ off,
+// box of system s: its particles in parts (one block a system took 327 us for
+// 24 systems of up to 2e5 particles: a chain of loads), then one wave joins them.
+// box[0..2] = min corner, box[3] = cube extent, box[4] = 2^21 / extent (0 if flat)
+__global__ __launch_bounds__(256) void k_bbox_sys(const int64_t* __restrict__ off, int parts,
                                                   const double* __restrict__ x,
                                                   const double* __restrict__ m,
                                                   const double* __restrict__ h,
-                                                  double* __restrict__ boxes, int* status,
+                                                  double* __restrict__ part, int* status,
                                                   int check) {
-  const int sidx = blockIdx.x;
-  const int64_t b = off[sidx], e = off[sidx + 1];
+  const int sidx = blockIdx.x / parts, q = blockIdx.x % parts;
+  const int64_t e = off[sidx + 1];
   double mn[3] = {INFINITY, INFINITY, INFINITY}, mx[3] = {-INFINITY, -INFINITY, -INFINITY};
   int bad = 0;
-  for (int64_t i = b + threadIdx.x; i < e; i += 256) {
+  for (int64_t i = off[sidx] + q * 256 + threadIdx.x; i < e; i += 256 * parts) {
     for (int d = 0; d < 3; ++d) {
       const double v = x[3 * i + d];
       mn[d] = fmin(mn[d], v);
@@ -125,26 +97,37 @@ __global__ __launch_bounds__(256) void k_bbox_sys(const int64_t* __restrict__ of
     if (lane == 0) { sh[d][w] = a; sh[3 + d][w] = c; }
   }
   __syncthreads();
-  if (threadIdx.x != 0) return;
+  const int d = threadIdx.x;
+  if (d < 3) part[6 * (int64_t)blockIdx.x + d] = fmin(fmin(sh[d][0], sh[d][1]), fmin(sh[d][2], sh[d][3]));
+  else if (d < 6) part[6 * (int64_t)blockIdx.x + d] = fmax(fmax(sh[d][0], sh[d][1]), fmax(sh[d][2], sh[d][3]));
+}
+
+__global__ __launch_bounds__(256) void k_bbox_sys_join(int nsys, int parts,
+                                                       const double* __restrict__ part,
+                                                       double* __restrict__ boxes) {
+  const int sidx = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (sidx >= nsys) return;
+  double mn[3] = {INFINITY, INFINITY, INFINITY}, mx[3] = {-INFINITY, -INFINITY, -INFINITY};
+  for (int q = lane; q < parts; q += 64)
+    for (int d = 0; d < 3; ++d) {
+      mn[d] = fmin(mn[d], part[6 * ((int64_t)sidx * parts + q) + d]);
+      mx[d] = fmax(mx[d], part[6 * ((int64_t)sidx * parts + q) + 3 + d]);
+    }
   double ext = 0.0;
   double* box = boxes + 8 * sidx;
   for (int d = 0; d < 3; ++d) {
-    const double lo = fmin(fmin(sh[d][0], sh[d][1]), fmin(sh[d][2], sh[d][3]));
-    const double hi = fmax(fmax(sh[3 + d][0], sh[3 + d][1]), fmax(sh[3 + d][2], sh[3 + d][3]));
-    box[d] = lo;
+    const double lo = wave_min(mn[d]), hi = wave_max(mx[d]);
+    if (lane == 0) box[d] = lo;
     if (hi - lo > ext) ext = hi - lo;
   }
+  if (lane != 0) return;
   box[3] = ext;
   box[4] = ext > 0.0 ? 2097152.0 / ext : 0.0;
 }
 
-__device__ __forceinline__ uint64_t spread3(uint64_t v);
-
-// Morton key of each particle in its own system's box; sys[i] = its system
 __global__ void k_keys_sys(int n, int nsys, const int64_t* __restrict__ off,
                            const double* __restrict__ x, const double* __restrict__ boxes,
-                           uint64_t* __restrict__ key, uint32_t* __restrict__ idx,
-                           uint32_t* __restrict__ sys) {
+                           uint64_t* __restrict__ key, uint32_t* __restrict__ sys) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   int lo = 0, hi = nsys - 1;  // last s with off[s] <= i
@@ -152,27 +135,16 @@ __global__ void k_keys_sys(int n, int nsys, const int64_t* __restrict__ off,
     const int mid = (lo + hi + 1) >> 1;
     if (off[mid] <= i) lo = mid; else hi = mid - 1;
   }
-  const double* box = boxes + 8 * lo;
-  uint64_t c[3] = {0, 0, 0};
-  if (box[3] > 0.0) {
-    for (int d = 0; d < 3; ++d) {
-      const double f = floor((x[3 * (int64_t)i + d] - box[d]) * box[4]);
-      c[d] = f > 2097151.0 ? 2097151ull : (uint64_t)f;
-    }
-  }
-  key[i] = (spread3(c[0]) << 2) | (spread3(c[1]) << 1) | spread3(c[2]);
-  idx[i] = (uint32_t)i;
+  key[i] = morton(x + 3 * (int64_t)i, boxes + 8 * lo);
   sys[i] = (uint32_t)lo;
 }
 
 // after the key sort: the system of each key-sorted position, as a sort key
 __global__ void k_sys_sortkey(int n, const uint32_t* __restrict__ perm1,
-                              const uint32_t* __restrict__ sys, uint64_t* __restrict__ skey,
-                              uint32_t* __restrict__ pos) {
+                              const uint32_t* __restrict__ sys, uint64_t* __restrict__ skey) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   skey[i] = sys[perm1[i]];
-  pos[i] = (uint32_t)i;
 }
 
 // final order = (system, key, caller index): gather permutation, keys, systems
@@ -207,93 +179,6 @@ __global__ void k_node_flags(int nn, const NodeInfo* __restrict__ info,
     root = sys[pi.lo] != sys[pi.lo + pi.cnt - 1];
   }
   flag[v] = !within ? 0 : (root ? 1 : 2);
-}
-
-__device__ __forceinline__ uint64_t spread3(uint64_t v) {
-  v &= 0x1fffffull;
-  v = (v | (v << 32)) & 0x1f00000000ffffull;
-  v = (v | (v << 16)) & 0x1f0000ff0000ffull;
-  v = (v | (v << 8)) & 0x100f00f00f00f00full;
-  v = (v | (v << 4)) & 0x10c30c30c30c30c3ull;
-  v = (v | (v << 2)) & 0x1249249249249249ull;
-  return v;
-}
-
-__global__ void k_keys(int n, const double* __restrict__ x, const double* __restrict__ box,
-                       uint64_t* __restrict__ key, uint32_t* __restrict__ idx) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const double scale = box[4];
-  uint64_t c[3] = {0, 0, 0};
-  if (box[3] > 0.0) {
-    for (int d = 0; d < 3; ++d) {
-      double f = floor((x[3 * (int64_t)i + d] - box[d]) * scale);
-      c[d] = f > 2097151.0 ? 2097151ull : (uint64_t)f;
-    }
-  }
-  key[i] = (spread3(c[0]) << 2) | (spread3(c[1]) << 1) | spread3(c[2]);
-  idx[i] = (uint32_t)i;
-}
-
-// ---- radix sort -----------------------------------------------------------
-__global__ __launch_bounds__(RS_THREADS) void k_radix_hist(int n, const uint64_t* __restrict__ key,
-                                                           int shift, uint32_t* __restrict__ hist,
-                                                           int nb) {
-  __shared__ uint32_t cnt[256];
-  cnt[threadIdx.x] = 0;
-  __syncthreads();
-  const int64_t base = (int64_t)blockIdx.x * RS_TILE;
-  for (int r = 0; r < RS_ITEMS; ++r) {
-    int64_t i = base + r * RS_THREADS + threadIdx.x;
-    if (i < n) atomicAdd(&cnt[(key[i] >> shift) & 255u], 1u);
-  }
-  __syncthreads();
-  hist[(int64_t)threadIdx.x * nb + blockIdx.x] = cnt[threadIdx.x];
-}
-
-// Stable scatter: elements of the tile are ranked in their original order;
-// equal digits inside a wave are found with eight ballots.
-__global__ __launch_bounds__(RS_THREADS) void k_radix_scatter(
-    int n, const uint64_t* __restrict__ kin, const uint32_t* __restrict__ vin,
-    uint64_t* __restrict__ kout, uint32_t* __restrict__ vout, int shift,
-    const uint32_t* __restrict__ offs, int nb) {
-  __shared__ uint32_t run[256];
-  __shared__ uint32_t base[256];
-  __shared__ uint32_t wc[RS_THREADS / 64][256];
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  run[t] = 0;
-  base[t] = offs[(int64_t)t * nb + blockIdx.x];
-  const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  for (int r = 0; r < RS_ITEMS; ++r) {
-    for (int q = 0; q < RS_THREADS / 64; ++q) wc[q][t] = 0;
-    __syncthreads();
-    const int64_t i = (int64_t)blockIdx.x * RS_TILE + r * RS_THREADS + t;
-    const bool valid = i < n;
-    uint64_t k = valid ? kin[i] : 0ull;
-    uint32_t v = valid ? vin[i] : 0u;
-    uint32_t d = (uint32_t)((k >> shift) & 255u);
-    uint64_t peers = __ballot(valid);
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      const bool bit = (d >> b) & 1u;
-      uint64_t bb = __ballot(bit);
-      peers &= bit ? bb : ~bb;
-    }
-    const uint32_t rank = (uint32_t)__popcll(peers & lt);
-    if (valid && rank == 0) wc[w][d] = (uint32_t)__popcll(peers);
-    __syncthreads();
-    if (valid) {
-      uint32_t pos = base[d] + run[d] + rank;
-      for (int q = 0; q < w; ++q) pos += wc[q][d];
-      kout[pos] = k;
-      vout[pos] = v;
-    }
-    __syncthreads();
-    uint32_t add = 0;
-    for (int q = 0; q < RS_THREADS / 64; ++q) add += wc[q][t];
-    run[t] += add;
-    __syncthreads();
-  }
 }
 
 __global__ void k_gather(int n, const uint32_t* __restrict__ perm, const double* __restrict__ x,
@@ -613,58 +498,34 @@ __global__ void k_extent_final(int nn, const NodeInfo* __restrict__ info,
 int bbox_blocks(int64_t n) {
   int64_t b = (n + BBOX_THREADS * 8 - 1) / (BBOX_THREADS * 8);
   if (b < 1) b = 1;
-  if (b > 1024) b = 1024;
+  if (b > 512) b = 512;  // (every block of the key kernel reads them all)
   return (int)b;
 }
 
 void launch_bbox(int n, const double* x, const double* m, const double* h, double* part,
-                 double* box, int* status, int check, hipStream_t s) {
-  int nb = bbox_blocks(n);
-  k_bbox_partial<<<nb, BBOX_THREADS, 0, s>>>(n, x, m, h, part, status, check);
-  k_bbox_final<<<1, 256, 0, s>>>(nb, part, box);
+                 int* status, int check, hipStream_t s) {
+  k_bbox_partial<<<bbox_blocks(n), BBOX_THREADS, 0, s>>>(n, x, m, h, part, status, check);
 }
 
-void launch_keys(int n, const double* x, const double* box, uint64_t* key, uint32_t* idx,
-                 hipStream_t s) {
-  k_keys<<<blocks_for(n, 256), 256, 0, s>>>(n, x, box, key, idx);
+// two loads of a thread in the largest system, within 2048 blocks
+int bbox_sys_parts(int nsys, const int64_t* off_host) {
+  int64_t most = 0;
+  for (int k = 0; k < nsys; ++k) most = std::max(most, off_host[k + 1] - off_host[k]);
+  return (int)std::max<int64_t>(1, std::min<int64_t>((most + 511) / 512, 2048 / nsys));
 }
 
-int radix_blocks(int64_t n) { return (int)((n + RS_TILE - 1) / RS_TILE); }
-
-void radix_pass(int n, const uint64_t* kin, const uint32_t* vin, uint64_t* kout, uint32_t* vout,
-                int shift, uint32_t* hist, uint32_t* hist_tmp, uint32_t* scratch_total,
-                hipStream_t s) {
-  const int nb = radix_blocks(n);
-  k_radix_hist<<<nb, RS_THREADS, 0, s>>>(n, kin, shift, hist, nb);
-  scan_u32(hist, hist, (int64_t)256 * nb, scratch_total, hist_tmp, s);
-  k_radix_scatter<<<nb, RS_THREADS, 0, s>>>(n, kin, vin, kout, vout, shift, hist, nb);
-}
-
-void radix_sort(int n, uint64_t* key0, uint32_t* val0, uint64_t* key1, uint32_t* val1,
-                uint32_t* hist, uint32_t* hist_tmp, uint32_t* scratch_total, hipStream_t s) {
-  const int nb = radix_blocks(n);
-  uint64_t *kin = key0, *kout = key1;
-  uint32_t *vin = val0, *vout = val1;
-  for (int shift = 0; shift < 64; shift += 8) {  // 8 passes: result lands in key0/val0
-    k_radix_hist<<<nb, RS_THREADS, 0, s>>>(n, kin, shift, hist, nb);
-    scan_u32(hist, hist, (int64_t)256 * nb, scratch_total, hist_tmp, s);
-    k_radix_scatter<<<nb, RS_THREADS, 0, s>>>(n, kin, vin, kout, vout, shift, hist, nb);
-    std::swap(kin, kout);
-    std::swap(vin, vout);
-  }
-}
-
-void launch_sys_keys(int n, int nsys, const int64_t* off, const double* x, const double* m,
-                     const double* h, double* boxes, int* status, int check, uint64_t* key,
-                     uint32_t* idx, uint32_t* sys, int32_t* sys_start, hipStream_t s) {
-  k_bbox_sys<<<nsys, 256, 0, s>>>(off, x, m, h, boxes, status, check);
-  k_keys_sys<<<blocks_for(n, 256), 256, 0, s>>>(n, nsys, off, x, boxes, key, idx, sys);
+void launch_sys_keys(int n, int nsys, const int64_t* off, int parts, const double* x,
+                     const double* m, const double* h, double* part, double* boxes, int* status,
+                     int check, uint64_t* key, uint32_t* sys, int32_t* sys_start, hipStream_t s) {
+  k_bbox_sys<<<(unsigned)nsys * parts, 256, 0, s>>>(off, parts, x, m, h, part, status, check);
+  k_bbox_sys_join<<<blocks_for(nsys, 4), 256, 0, s>>>(nsys, parts, part, boxes);
+  k_keys_sys<<<blocks_for(n, 256), 256, 0, s>>>(n, nsys, off, x, boxes, key, sys);
   k_sys_start<<<blocks_for(nsys, 256), 256, 0, s>>>(nsys, off, sys_start);
 }
 
 void launch_sys_sortkey(int n, const uint32_t* perm1, const uint32_t* sys, uint64_t* skey,
-                        uint32_t* pos, hipStream_t s) {
-  k_sys_sortkey<<<blocks_for(n, 256), 256, 0, s>>>(n, perm1, sys, skey, pos);
+                        hipStream_t s) {
+  k_sys_sortkey<<<blocks_for(n, 256), 256, 0, s>>>(n, perm1, sys, skey);
 }
 
 void launch_sys_final(int n, const uint32_t* q, const uint32_t* perm1, const uint64_t* key1,

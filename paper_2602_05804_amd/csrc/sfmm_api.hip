@@ -25,8 +25,8 @@ struct DevBuf {
 
 // every device buffer of a context, grown on demand and reused
 enum BufId {
-  B_BOXPART, B_BOX, B_STATUS, B_SMALL,
-  B_KEY0, B_KEY1, B_VAL0, B_VAL1, B_HIST, B_SCANTMP,
+  B_BOXPART, B_STATUS, B_SMALL,
+  B_KEY0, B_KEY1, B_VAL0, B_VAL1, B_SORT, B_BASE, B_SCANTMP,
   B_XS, B_YS, B_ZS, B_MS, B_HS, B_HIS, B_H4, B_P4,
   B_KFIRST, B_KLAST, B_KLEFT, B_KRIGHT, B_KPAR, B_KSIDE, B_KEPT,
   B_LFLAG, B_LAT, B_INFO, B_REC, B_RECQ, B_L2BITS, B_CHUNK,
@@ -45,7 +45,7 @@ enum BufId {
 
 // small device scalars (B_SMALL, u64 slots)
 enum SmallId { S_NKEPT = 0, S_NLEAVES, S_MAXDEPTH, S_NITEMS, S_M2LTOT, S_P2PTOT, S_PAIRTOT,
-               S_DOFFTOT, S_SORTTOT, S_L2LTOT, S_SOFTTOT, S_COUNT };
+               S_DOFFTOT, S_L2LTOT, S_SOFTTOT, S_COUNT };
 
 }  // namespace
 
@@ -83,6 +83,7 @@ struct sfmm_ctx {
   std::vector<uint32_t> level_off;
   std::vector<uint32_t> level_int;  // end of each level's internal nodes
   uint64_t m2l_cap = 0, p2p_cap = 0;
+  size_t words_m2l = 0;  // sort scratch of the M2L order: place in B_SORT (cleared by the build)
   int64_t soft_items = 0;       // items whose softened pairs the last solve counted
   int64_t items_from_walk = 0;  // P2P work items counted by the level walk
   uint32_t stack_cap = 0;
@@ -230,14 +231,18 @@ int do_build(sfmm_ctx* ctx, int64_t n64, const double* x, const double* m, const
   const int leaf_size = ctx->cfg.leaf_size;
   const int RS = rec_stride(order);
   const int nmax_nodes = 2 * n;  // 1 + 2 * (kept internal) <= 2n - 1
+  int sys_passes = 0;            // digits of the system number
+  while (nsys > 1 && sys_passes < 4 && ((uint64_t)(nsys - 1) >> (8 * sys_passes)) != 0) ++sys_passes;
+  const bool small_n = nsys <= 1 && n <= kSortSmall;
   // ---- workspace
   struct { int id; size_t bytes; } need[] = {
-      {B_BOXPART, sizeof(double) * 6 * bbox_blocks(n)}, {B_BOX, sizeof(double) * 8},
+      {B_BOXPART, sizeof(double) * 6 * bbox_blocks(n)},
       {B_STATUS, sizeof(int) * 4}, {B_SMALL, sizeof(uint64_t) * S_COUNT},
       {B_KEY0, sizeof(uint64_t) * n}, {B_KEY1, sizeof(uint64_t) * n},
       {B_VAL0, sizeof(uint32_t) * n}, {B_VAL1, sizeof(uint32_t) * n},
-      {B_HIST, sizeof(uint32_t) * 256 * (size_t)radix_blocks(n)},
-      {B_SCANTMP, sizeof(uint64_t) * scan_tmp_elems(std::max<int64_t>(256 * (int64_t)radix_blocks(n), 2 * (int64_t)n + 2))},
+      {B_SORT, sizeof(uint32_t) * (sort_words(n, 8 + sys_passes) + 2 * sort_words(nmax_nodes, 1))},
+      {B_BASE, sizeof(uint32_t) * 512},
+      {B_SCANTMP, sizeof(uint64_t) * scan_tmp_elems(2 * (int64_t)n + 2)},
       {B_XS, sizeof(double) * n}, {B_YS, sizeof(double) * n}, {B_ZS, sizeof(double) * n},
       {B_MS, sizeof(double) * n}, {B_HS, sizeof(double) * n}, {B_HIS, sizeof(double) * n},
       {B_H4, sizeof(double) * n}, {B_P4, sizeof(double) * 4 * n},
@@ -266,17 +271,28 @@ int do_build(sfmm_ctx* ctx, int64_t n64, const double* x, const double* m, const
   // ---- keys, sort, gather
   const uint32_t* sys_sorted = nullptr;
   const int32_t* sys_start = nullptr;
-  if (nsys <= 1) {
-    launch_bbox(n, x, m, h, P<double>(ctx, B_BOXPART), P<double>(ctx, B_BOX), status,
-                ctx->cfg.check_inputs, s);
-    launch_keys(n, x, P<double>(ctx, B_BOX), P<uint64_t>(ctx, B_KEY0), P<uint32_t>(ctx, B_VAL0), s);
-    radix_sort(n, P<uint64_t>(ctx, B_KEY0), P<uint32_t>(ctx, B_VAL0), P<uint64_t>(ctx, B_KEY1),
-               P<uint32_t>(ctx, B_VAL1), P<uint32_t>(ctx, B_HIST), P<uint32_t>(ctx, B_SCANTMP),
-               reinterpret_cast<uint32_t*>(small + S_SORTTOT), s);
+  // scratch of the sorts: of the particles (by key, by system), then of the
+  // nodes by depth and by list length, cleared in one go
+  uint32_t* words = P<uint32_t>(ctx, B_SORT);
+  uint32_t* words_sys = words + sort_words(n, 8);
+  uint32_t* words_depth = words_sys + (sys_passes ? sort_words(n, sys_passes) : 0);
+  ctx->words_m2l = (size_t)(words_depth - words) + sort_words(nmax_nodes, 1);
+  launch_clear_words(words, ctx->words_m2l + sort_words(nmax_nodes, 1), s);
+  if (small_n) {
+    launch_small_sort(n, x, m, h, ctx->cfg.check_inputs, status, P<uint64_t>(ctx, B_KEY0),
+                      P<uint32_t>(ctx, B_VAL0), s);
+  } else if (nsys <= 1) {
+    launch_bbox(n, x, m, h, P<double>(ctx, B_BOXPART), status, ctx->cfg.check_inputs, s);
+    launch_keys(n, x, bbox_blocks(n), P<double>(ctx, B_BOXPART), P<uint64_t>(ctx, B_KEY0), words,
+                s);
+    radix_sort(n, 8, true, P<uint64_t>(ctx, B_KEY0), P<uint32_t>(ctx, B_VAL0),
+               P<uint64_t>(ctx, B_KEY1), P<uint32_t>(ctx, B_VAL1), words, s);
   } else {
     // several systems: each keyed in its own box, sorted by (system, key, index)
+    const int parts = bbox_sys_parts(nsys, offsets);
     struct { int id; size_t bytes; } need1[] = {
         {B_SYSOFF, sizeof(int64_t) * (nsys + 1)}, {B_BOXES, sizeof(double) * 8 * nsys},
+        {B_BOXPART, sizeof(double) * 6 * (size_t)nsys * parts},
         {B_SYS, sizeof(uint32_t) * n}, {B_SYSS, sizeof(uint32_t) * n},
         {B_SYSSTART, sizeof(int32_t) * nsys}, {B_SKEY0, sizeof(uint64_t) * n},
         {B_SKEY1, sizeof(uint64_t) * n}, {B_SPOS0, sizeof(uint32_t) * n},
@@ -285,19 +301,17 @@ int do_build(sfmm_ctx* ctx, int64_t n64, const double* x, const double* m, const
       if ((rc = ensure(ctx, q.id, q.bytes))) return rc;
     HIPCHK(hipMemcpyAsync(P<int64_t>(ctx, B_SYSOFF), offsets, sizeof(int64_t) * (nsys + 1),
                           hipMemcpyHostToDevice, s));
-    launch_sys_keys(n, nsys, P<int64_t>(ctx, B_SYSOFF), x, m, h, P<double>(ctx, B_BOXES), status,
-                    ctx->cfg.check_inputs, P<uint64_t>(ctx, B_KEY0), P<uint32_t>(ctx, B_VAL0),
-                    P<uint32_t>(ctx, B_SYS), P<int32_t>(ctx, B_SYSSTART), s);
-    radix_sort(n, P<uint64_t>(ctx, B_KEY0), P<uint32_t>(ctx, B_VAL0), P<uint64_t>(ctx, B_KEY1),
-               P<uint32_t>(ctx, B_VAL1), P<uint32_t>(ctx, B_HIST), P<uint32_t>(ctx, B_SCANTMP),
-               reinterpret_cast<uint32_t*>(small + S_SORTTOT), s);
-    launch_sys_sortkey(n, P<uint32_t>(ctx, B_VAL0), P<uint32_t>(ctx, B_SYS), P<uint64_t>(ctx, B_SKEY0),
-                       P<uint32_t>(ctx, B_SPOS0), s);
+    launch_sys_keys(n, nsys, P<int64_t>(ctx, B_SYSOFF), parts, x, m, h, P<double>(ctx, B_BOXPART),
+                    P<double>(ctx, B_BOXES), status, ctx->cfg.check_inputs, P<uint64_t>(ctx, B_KEY0), P<uint32_t>(ctx, B_SYS),
+                    P<int32_t>(ctx, B_SYSSTART), s);
+    radix_sort(n, 8, false, P<uint64_t>(ctx, B_KEY0), P<uint32_t>(ctx, B_VAL0),
+               P<uint64_t>(ctx, B_KEY1), P<uint32_t>(ctx, B_VAL1), words, s);
+    launch_sys_sortkey(n, P<uint32_t>(ctx, B_VAL0), P<uint32_t>(ctx, B_SYS),
+                       P<uint64_t>(ctx, B_SKEY0), s);
     uint64_t *ka = P<uint64_t>(ctx, B_SKEY0), *kb = P<uint64_t>(ctx, B_SKEY1);
     uint32_t *va = P<uint32_t>(ctx, B_SPOS0), *vb = P<uint32_t>(ctx, B_SPOS1);
-    for (int shift = 0; shift < 32 && ((uint64_t)(nsys - 1) >> shift) != 0; shift += 8) {
-      radix_pass(n, ka, va, kb, vb, shift, P<uint32_t>(ctx, B_HIST), P<uint32_t>(ctx, B_SCANTMP),
-                 reinterpret_cast<uint32_t*>(small + S_SORTTOT), s);
+    radix_sort(n, sys_passes, false, ka, va, kb, vb, words_sys, s);
+    if (sys_passes % 2) {
       std::swap(ka, kb);
       std::swap(va, vb);
     }
@@ -367,18 +381,13 @@ int do_build(sfmm_ctx* ctx, int64_t n64, const double* x, const double* m, const
         {B_NDEPTH, sizeof(int32_t) * nn}, {B_LEVNODES, sizeof(uint32_t) * nn},
         {B_LEVKEY0, sizeof(uint64_t) * nn}, {B_LEVKEY1, sizeof(uint64_t) * nn},
         {B_LEVIDS, sizeof(uint32_t) * nn}, {B_LEVOFF, sizeof(uint32_t) * (kMaxDepthCap + 2)},
-        {B_LEVINT, sizeof(uint32_t) * (kMaxDepthCap + 2)},
-        {B_HIST, sizeof(uint32_t) * 256 * (size_t)radix_blocks(nn)},
-        {B_SCANTMP, sizeof(uint64_t) * scan_tmp_elems(std::max<int64_t>(256 * (int64_t)radix_blocks(nn), 2 * (int64_t)n + 2))}};
+        {B_LEVINT, sizeof(uint32_t) * (kMaxDepthCap + 2)}};
     for (auto& q : need2)
       if ((rc = ensure(ctx, q.id, q.bytes))) return rc;
-    launch_node_depth(nn, info, P<int32_t>(ctx, B_NDEPTH), P<uint64_t>(ctx, B_LEVKEY0),
-                      P<uint32_t>(ctx, B_LEVIDS), s);
-    radix_pass(nn, P<uint64_t>(ctx, B_LEVKEY0), P<uint32_t>(ctx, B_LEVIDS),
-               P<uint64_t>(ctx, B_LEVKEY1), P<uint32_t>(ctx, B_LEVNODES), 0,
-               P<uint32_t>(ctx, B_HIST), P<uint32_t>(ctx, B_SCANTMP),
-               reinterpret_cast<uint32_t*>(small + S_SORTTOT), s);
-    launch_level_offsets(kMaxDepthCap + 1, radix_blocks(nn), nn, P<uint32_t>(ctx, B_HIST),
+    launch_node_depth(nn, info, P<int32_t>(ctx, B_NDEPTH), P<uint64_t>(ctx, B_LEVKEY0), s);
+    radix_pass(nn, P<uint64_t>(ctx, B_LEVKEY0), nullptr, P<uint64_t>(ctx, B_LEVKEY1),
+               P<uint32_t>(ctx, B_LEVNODES), P<uint32_t>(ctx, B_BASE), words_depth, s);
+    launch_level_offsets(kMaxDepthCap + 1, nn, P<uint32_t>(ctx, B_BASE),
                          P<uint32_t>(ctx, B_LEVOFF), P<uint32_t>(ctx, B_LEVINT), s);
   }
   if (nsys > 1) {
@@ -915,9 +924,8 @@ int do_walk_and_eval(sfmm_ctx* ctx, double theta, int precision, const double* m
         ob.ids0 = P<uint32_t>(ctx, B_LEVIDS);
         ob.ids1 = P<uint32_t>(ctx, B_M2LORD);
         ob.ids2 = ob.ids1 + ctx->nn;
-        ob.hist = P<uint32_t>(ctx, B_HIST);
-        ob.hist_tmp = P<uint32_t>(ctx, B_SCANTMP);
-        ob.total = reinterpret_cast<uint32_t*>(small + S_SORTTOT);
+        ob.base = P<uint32_t>(ctx, B_BASE) + 256;
+        ob.words = P<uint32_t>(ctx, B_SORT) + ctx->words_m2l;
         m2l_windows(sa, ctx->m2l_unique);
         launch_m2l_order(sa, f32, ob, s);
         sa.level_nodes = reinterpret_cast<const int32_t*>(ob.ids1);

@@ -100,18 +100,31 @@ void scan_u32_u64(const uint32_t* in, uint64_t* out, int64_t n, uint64_t* total,
 // ---- tree ------------------------------------------------------------------
 int bbox_blocks(int64_t n);
 void launch_bbox(int n, const double* x, const double* m, const double* h, double* part,
-                 double* box, int* status, int check, hipStream_t s);
-void launch_keys(int n, const double* x, const double* box, uint64_t* key, uint32_t* idx,
-                 hipStream_t s);
-int radix_blocks(int64_t n);
-// sorts (key, idx) by key, stable; returns in key0/val0 (ping-pong via key1/val1)
-void radix_sort(int n, uint64_t* key0, uint32_t* val0, uint64_t* key1, uint32_t* val1,
-                uint32_t* hist, uint32_t* hist_tmp, uint32_t* scratch_total, hipStream_t s);
-// one stable pass on the 8-bit digit at `shift`; hist holds 256 * radix_blocks(n)
-// counters and, after the pass, their exclusive scan (digit-major)
+                 int* status, int check, hipStream_t s);
+// ---- radix sorts (k_sort.hip) ------------------------------------------------
+// at most this many elements: one block sorts them in LDS (tree phase of a
+// solve at 2048: 0.23-0.25 ms against 0.27 with the tiled passes, at 4096
+// 0.27-0.30 against 0.31, at 6144 0.31 against 0.29)
+constexpr int kSortSmall = 4096;
+// words of scratch for `passes` passes over n elements, to be cleared before
+size_t sort_words(int64_t n, int passes);
+void launch_clear_words(uint32_t* p, size_t n, hipStream_t s);
+// Morton keys in the box of the blocks' corners (part) and their digit counts
+// into the words of an 8-pass sort
+void launch_keys(int n, const double* x, int nb, const double* part, uint64_t* key,
+                 uint32_t* words, hipStream_t s);
+// n <= kSortSmall particles: input check, box, keys and the sort
+void launch_small_sort(int n, const double* x, const double* m, const double* h, int check,
+                       int* status, uint64_t* key, uint32_t* val, hipStream_t s);
+// stable sort by the lowest 8 * passes bits of key0 (1 to 4 or 8 passes), the
+// values being the positions; the result is in key0/val0 when passes is even,
+// else in key1/val1; counted: the words hold the digit counts
+void radix_sort(int n, int passes, bool counted, uint64_t* key0, uint32_t* val0, uint64_t* key1,
+                uint32_t* val1, uint32_t* words, hipStream_t s);
+// one stable pass on the lowest 8 bits; vin may be null (the positions); base
+// (may be null): [256] the first place of each digit
 void radix_pass(int n, const uint64_t* kin, const uint32_t* vin, uint64_t* kout, uint32_t* vout,
-                int shift, uint32_t* hist, uint32_t* hist_tmp, uint32_t* scratch_total,
-                hipStream_t s);
+                uint32_t* base, uint32_t* words, hipStream_t s);
 // sorted particle data: separate arrays and two of 16 bytes per particle
 // (pxy: x, y; pzm: z, m)
 void launch_gather(int n, const uint32_t* perm, const double* x, const double* m,
@@ -128,11 +141,13 @@ void launch_assign(int n, int leaf_size, const uint32_t* sys, const int32_t* kfi
                    const int32_t* kpar, const int32_t* kside, const uint32_t* cidx, NodeInfo* info,
                    uint32_t* leaf_flag, int32_t* leaf_at, hipStream_t s);
 // several systems: per-system boxes and keys, then (system, key) order
-void launch_sys_keys(int n, int nsys, const int64_t* off, const double* x, const double* m,
-                     const double* h, double* boxes, int* status, int check, uint64_t* key,
-                     uint32_t* idx, uint32_t* sys, int32_t* sys_start, hipStream_t s);
+// (parts blocks a system for the boxes, part: 6 parts doubles a system)
+int bbox_sys_parts(int nsys, const int64_t* off_host);
+void launch_sys_keys(int n, int nsys, const int64_t* off, int parts, const double* x,
+                     const double* m, const double* h, double* part, double* boxes, int* status, int check, uint64_t* key,
+                     uint32_t* sys, int32_t* sys_start, hipStream_t s);
 void launch_sys_sortkey(int n, const uint32_t* perm1, const uint32_t* sys, uint64_t* skey,
-                        uint32_t* pos, hipStream_t s);
+                        hipStream_t s);
 void launch_sys_final(int n, const uint32_t* q, const uint32_t* perm1, const uint64_t* key1,
                       const uint32_t* sys, uint32_t* perm, uint64_t* key, uint32_t* sys_sorted,
                       hipStream_t s);
@@ -279,15 +294,14 @@ struct NodeWalkArgs {
   uint32_t stack_cap;  // LDS lowering stack, entries
   int* status;
 };
-// node depth as a sort key (u64) and node ids (u32) for the bucketing by depth
+// node depth, also as a sort key (u64) for the bucketing by depth
 void launch_node_depth(int nn, const NodeInfo* info, int32_t* depth, uint64_t* key,
-                       uint32_t* ids, hipStream_t s);
+                       hipStream_t s);
 // level_off[k] = first position of depth k in the depth-sorted node list
 // (sort key 2 depth + leaf: a level's internal nodes first), level_int[k] =
-// the end of its internal nodes; read from the scanned radix histogram
-// (digit-major, nb blocks)
-void launch_level_offsets(int nlev, int nb, int nn, const uint32_t* hist_scanned,
-                          uint32_t* level_off, uint32_t* level_int, hipStream_t s);
+// the end of its internal nodes; read from the pass's first places
+void launch_level_offsets(int nlev, int nn, const uint32_t* base, uint32_t* level_off,
+                          uint32_t* level_int, hipStream_t s);
 // every leaf's lists (the slot pass, scans over the leaves, the second pass
 // over leaves whose lists overflow their slots); scan_tmp holds
 // scan_tmp_elems(nleaves) words; LDS of (stack_cap + slot_p) words per wave
@@ -354,14 +368,14 @@ struct SharedFarArgs {
 void launch_far_shared(int order, const FarArgs& f, const SharedFarArgs& a, bool f32,
                        hipStream_t s);
 // The node order of the shared M2L (result in ids1, the other buffers are
-// scratch of nn entries, hist/hist_tmp/total as for radix_pass): the FP64
+// scratch of nn entries, base 256 words, words as for radix_pass): the FP64
 // targets of FP32C, then nodes of long lists, longest first, then the others
 // in windows of a.window nodes that follow each other in level order, each
 // sorted by list length
 struct M2LOrderBufs {
   uint64_t *key0, *key1;
   uint32_t *ids0, *ids1, *ids2;
-  uint32_t *hist, *hist_tmp, *total;
+  uint32_t *base, *words;
 };
 // sets up a's windows for lists of m2l_total entries over all nodes
 void m2l_windows(SharedFarArgs& a, uint64_t m2l_total);
