@@ -18,6 +18,12 @@
 // M2L lists of p_0 .. p_d plus L's P2P list (same pairs; the order inside a
 // depth differs).
 //
+// Bound by the traffic between L1 and L2 and by latency.  The sources' fields
+// are in one record of 64 bytes, a pair of children in one line, and the
+// lists name the pair (an expansion record and the node's topology apart,
+// looked up per source, took 4.5 lines a pair: 2.24 ms for the walk of a 1e6
+// Plummer sphere, now 1.48; 2.29 and 1.58 ms for 2e6 particles of a binary).
+//
 // One wave (a 64-thread block) per node; lanes take 64 sources at a time,
 // and entries are written in lane order.  An internal node's M2L and opened
 // lists together are its tested list, whose size its parent records while
@@ -34,37 +40,66 @@
 namespace sfmm {
 namespace {
 
-__device__ __forceinline__ bool accept(const double* __restrict__ rt, const double* __restrict__ rs,
-                                       double theta2, double r_kern) {
-  const double dx = rs[0] - rt[0];
-  const double dy = rs[1] - rt[1];
-  const double dz = rs[2] - rt[2];
+// an opened internal node is listed as its first child with this bit: the
+// walks of its lists read the two children at once, without a lookup
+constexpr uint32_t kOpenInternal = 0x80000000u;
+
+// centre, size and largest h, first child, particles of a node
+struct Src {
+  double x, y, z, l, h;
+  int child, cnt;
+};
+__device__ __forceinline__ Src load_src(const NodeWalkArgs& a, uint32_t s) {
+  const double2* p = reinterpret_cast<const double2*>(a.wrec + s);
+  const double2 u = p[0], v = p[1], w = p[2];
+  const uint64_t b = (uint64_t)__double_as_longlong(w.y);
+  return {u.x, u.y, v.x, v.y, w.x, (int)(uint32_t)b, (int)(uint32_t)(b >> 32)};
+}
+
+__device__ __forceinline__ bool accept(const Src& t, const Src& s, double theta2, double r_kern) {
+  const double dx = s.x - t.x;
+  const double dy = s.y - t.y;
+  const double dz = s.z - t.z;
   const double d2 = dx * dx + dy * dy + dz * dz;
-  const double lsum = rt[3] + rs[3];
-  const double hm = fmax(rt[4], rs[4]);
+  const double lsum = t.l + s.l;
+  const double hm = fmax(t.h, s.h);
   const double rsum = lsum + r_kern * hm;
   return (lsum * lsum < theta2 * d2) && (d2 >= rsum * rsum);
 }
 
-__device__ __forceinline__ uint64_t lanemask_lt() {
-  const int lane = threadIdx.x & 63;
-  return lane == 0 ? 0ull : (~0ull >> (64 - lane));
+// set bits of m below this lane, added to acc
+__device__ __forceinline__ uint32_t below(uint64_t m, uint32_t acc) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                   __builtin_amdgcn_mbcnt_lo((uint32_t)m, acc));
 }
 
-// exclusive prefix over the wave of a small non-negative count (< 8) and the
-// wave total
-__device__ __forceinline__ uint32_t wave_prefix(uint32_t c, uint32_t& total) {
-  uint32_t pre = 0;
-  total = 0;
-#pragma unroll
-  for (int b = 0; b < 3; ++b) {
-    const uint64_t m = __ballot((c >> b) & 1u);
-    // set bits of m below this lane
-    pre += __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))
-           << b;
-    total += (uint32_t)__popcll(m) << b;
-  }
-  return pre;
+// appends, in lane order, v0 of the lanes with c0 and v1 of those with c1 (a
+// lane's v0 before its v1) to a list of `run` entries with room for lim
+__device__ __forceinline__ void append(uint32_t* list, uint32_t lim, uint32_t& run, bool c0,
+                                       uint32_t v0, bool c1, uint32_t v1) {
+  const uint64_t b0 = __ballot(c0), b1 = __ballot(c1);
+  if ((b0 | b1) == 0) return;  // (uniform)
+  const uint32_t k0 = run + below(b1, below(b0, 0u)), k1 = k0 + (c0 ? 1u : 0u);
+  if (c0 && k0 < lim) list[k0] = v0;
+  if (c1 && k1 < lim) list[k1] = v1;
+  run += (uint32_t)__popcll(b0) + (uint32_t)__popcll(b1);
+}
+// the same from the end of a range of `size` entries backwards
+__device__ __forceinline__ void append_back(uint32_t* list, uint32_t size, uint32_t lim,
+                                            uint32_t& run, bool c0, uint32_t v0, bool c1,
+                                            uint32_t v1) {
+  const uint64_t b0 = __ballot(c0), b1 = __ballot(c1);
+  if ((b0 | b1) == 0) return;
+  const uint32_t r0 = run + below(b1, below(b0, 0u)), r1 = r0 + (c0 ? 1u : 0u);
+  if (c0 && r0 < size && size - 1u - r0 < lim) list[size - 1u - r0] = v0;
+  if (c1 && r1 < size && size - 1u - r1 < lim) list[size - 1u - r1] = v1;
+  run += (uint32_t)__popcll(b0) + (uint32_t)__popcll(b1);
+}
+
+// entries of a pool that may be written from `base` on, at most `want`
+__device__ __forceinline__ uint32_t pool_room(uint64_t base, uint64_t cap, uint32_t want) {
+  const uint64_t room = base < cap ? cap - base : 0;
+  return room < want ? (uint32_t)room : want;
 }
 
 __global__ void k_node_depth(int nn, const NodeInfo* __restrict__ info, int32_t* __restrict__ depth,
@@ -88,69 +123,47 @@ __global__ void k_level_offsets(int nlev, int nn, const uint32_t* __restrict__ b
   level_int[k] = k < nlev ? base[2 * k + 1] : (uint32_t)nn;
 }
 
-// ---- one level -----------------------------------------------------------------
+// ---- the lists of one node ------------------------------------------------------
 struct Emit {
-  // reserved bases (uniform, 64-bit) and running offsets
-  uint64_t m2l_base, open_base, p2p_base;
-  uint32_t m2l_run, open_run, p2p_run;
-  // leaf P2P lists: pairs that may fall inside a kernel from the front,
-  // pairs beyond both kernels (plain_run of them so far) from the back of
-  // the leaf's p2p_total entries
-  uint32_t plain_run, p2p_total;
-  // internal node: opened entries go backwards from open_base - 1 (the end
-  // of its region); exp_lane sums this lane's opened entries, an internal
-  // one counted twice
-  uint32_t exp_lane;
-  // leaf: this lane's share of the particles of the P2P entries
-  uint32_t src_lane;
-  // leaf, slot mode: the sizes of the slots written, and the entries beyond
-  // both kernels staged in LDS (in rank order) until the leaf's P2P count is
-  // known, or in global memory (plain_g) once the leaf has a large slot
+  // internal node: M2L entries from the front of its region, opened entries
+  // from the back (of `region` entries, all of which or none may be written);
+  // exp_lane sums this lane's opened entries, an internal one counted twice
+  uint32_t m2l_run, open_run, exp_lane;
+  // leaf: P2P entries that may fall inside a kernel from the front of its
+  // list, those beyond both kernels (plain_run of them so far) from the back
+  uint32_t p2p_run, plain_run;
+  uint32_t src_lane;  // this lane's share of the particles of the P2P entries
+  uint64_t m2l_base, p2p_base;  // places in the pools, entries
+  uint32_t *m2l, *p2p;          // the same as addresses
+  uint32_t room_m, room_p;      // entries that may be written there
+  // exact pass: P2P entries of the leaf.  Slot pass: the sizes of the slots,
+  // and the entries beyond both kernels staged in LDS (in rank order) until
+  // the leaf's P2P count is known, or in global memory (plain_g) once the
+  // leaf has a large slot
+  uint32_t p2p_total;
   uint32_t slot_m, slot_p;
   uint32_t* plain;
   uint32_t* plain_g;
   bool big_m, big_p;  // a large slot was asked for (M2L, P2P)
 };
 
-template <bool WRITE>
-__device__ __forceinline__ void emit_lists(const NodeWalkArgs& a, Emit& e, uint32_t s0, uint32_t s1,
-                                           uint32_t nm, uint32_t sel_m, uint32_t no,
-                                           uint32_t sel_o, bool to_p2p) {
-  // nm entries (first from s0 if sel_m & 1, then s1 if sel_m & 2) go to M2L;
-  // no entries to the opened (or P2P) list likewise
-  uint32_t tm, to;
-  const uint32_t pm = wave_prefix(nm, tm);
-  const uint32_t po = wave_prefix(no, to);
-  if (WRITE) {
-    uint64_t k = e.m2l_base + e.m2l_run + pm;
-    if (sel_m & 1u) { if (k < a.m2l_cap) a.m2l_pool[k] = s0; ++k; }
-    if (sel_m & 2u) { if (k < a.m2l_cap) a.m2l_pool[k] = s1; }
-    if (to_p2p) {
-      uint64_t q = e.p2p_base + e.p2p_run + po;
-      if (sel_o & 1u) { if (q < a.p2p_cap) a.p2p_pool[q] = s0; ++q; }
-      if (sel_o & 2u) { if (q < a.p2p_cap) a.p2p_pool[q] = s1; }
-    } else {
-      // rank from the end of the node's region (r < region <= open_base)
-      uint32_t r = e.open_run + po;
-      if (sel_o & 1u) {
-        const uint64_t q = e.open_base - 1u - r;
-        if (q < a.open_cap) a.open_pool[q] = s0;
-        ++r;
-      }
-      if (sel_o & 2u) {
-        const uint64_t q = e.open_base - 1u - r;
-        if (q < a.open_cap) a.open_pool[q] = s1;
-      }
-    }
-  }
-  e.m2l_run += tm;
-  if (to_p2p) e.p2p_run += to; else e.open_run += to;
+__device__ __forceinline__ void place_m2l(const NodeWalkArgs& a, Emit& e, uint64_t base,
+                                          uint32_t want) {
+  e.m2l_base = base;
+  e.m2l = a.m2l_pool + base;
+  e.room_m = pool_room(base, a.m2l_cap, want);
+}
+__device__ __forceinline__ void place_p2p(const NodeWalkArgs& a, Emit& e, uint64_t base,
+                                          uint32_t want) {
+  e.p2p_base = base;
+  e.p2p = a.p2p_pool + base;
+  e.room_p = pool_room(base, a.p2p_cap, want);
 }
 
-// a leaf's lists: nm M2L entries (sel_m), np P2P entries that may need
-// softening (sel_p) and nq P2P entries beyond both kernels (sel_q); the
-// latter are written from the end of the leaf's range, so the P2P kernel
-// meets the softened pairs first and the rest in whole chunks without them.
+// A leaf's lists: M2L entries, P2P entries that may need softening, and P2P
+// entries beyond both kernels, which are written from the end of the leaf's
+// range, so the P2P kernel meets the softened pairs first and the rest in
+// whole chunks without them.
 // W = kLeafExact writes at the leaf's exact offsets (its P2P count known);
 // W = kLeafSlot writes the M2L and softening entries into the leaf's fixed
 // slots as far as they fit and stages the others in LDS
@@ -167,12 +180,13 @@ __device__ __forceinline__ void promote_m2l(const NodeWalkArgs& a, Emit& e) {
   b = __builtin_amdgcn_readfirstlane(b);
   e.big_m = true;
   if (b >= a.nbig) return;
-  const uint64_t nb = a.leaf_base + (uint64_t)a.nleaves * a.slot_m + (uint64_t)b * a.big_m;
-  __threadfence();  // the wave's own slot entries, read back below
-  for (uint32_t i = lane; i < e.m2l_run; i += 64)
-    if (nb + i < a.m2l_cap && e.m2l_base + i < a.m2l_cap) a.m2l_pool[nb + i] = a.m2l_pool[e.m2l_base + i];
-  e.m2l_base = nb;
+  const uint32_t* from = e.m2l;
+  const uint32_t have = e.m2l_run < e.room_m ? e.m2l_run : e.room_m;
+  place_m2l(a, e, a.leaf_base + (uint64_t)a.nleaves * a.slot_m + (uint64_t)b * a.big_m, a.big_m);
   e.slot_m = a.big_m;
+  __threadfence();  // the wave's own slot entries, read back below
+  for (uint32_t i = lane; i < have; i += 64)
+    if (i < e.room_m) e.m2l[i] = from[i];
 }
 
 // the same for the P2P list: its entries that may need softening move to a
@@ -184,107 +198,56 @@ __device__ __forceinline__ void promote_p2p(const NodeWalkArgs& a, Emit& e) {
   b = __builtin_amdgcn_readfirstlane(b);
   e.big_p = true;
   if (b >= a.nbig) return;
-  const uint64_t nb = (uint64_t)a.nleaves * a.slot_p + (uint64_t)b * a.big_p;
+  const uint32_t* from = e.p2p;
+  const uint32_t have = e.p2p_run < e.room_p ? e.p2p_run : e.room_p;
+  place_p2p(a, e, (uint64_t)a.nleaves * a.slot_p + (uint64_t)b * a.big_p, a.big_p);
+  e.slot_p = a.big_p;
   uint32_t* g = a.big_plain + (uint64_t)b * a.big_p;
   __syncthreads();  // the staged entries (LDS)
   __threadfence();  // the wave's own slot entries
-  for (uint32_t i = lane; i < e.p2p_run; i += 64)
-    if (nb + i < a.p2p_cap && e.p2p_base + i < a.p2p_cap) a.p2p_pool[nb + i] = a.p2p_pool[e.p2p_base + i];
+  for (uint32_t i = lane; i < have; i += 64)
+    if (i < e.room_p) e.p2p[i] = from[i];
   for (uint32_t i = lane; i < e.plain_run; i += 64) g[i] = e.plain[i];
-  e.p2p_base = nb;
-  e.slot_p = a.big_p;
   e.plain_g = g;
 }
 
-template <int W>
-__device__ __forceinline__ void emit_leaf_lists(const NodeWalkArgs& a, Emit& e, uint32_t s0,
-                                                uint32_t s1, uint32_t nm, uint32_t sel_m,
-                                                uint32_t np, uint32_t sel_p, uint32_t nq,
-                                                uint32_t sel_q) {
-  uint32_t tm, tp, tq;
-  const uint32_t pm = wave_prefix(nm, tm);
-  const uint32_t pp = wave_prefix(np, tp);
-  const uint32_t pq = wave_prefix(nq, tq);
-  if (W == kLeafSlot) {
-    // (uniform tests: the wave's totals)
-    if (!e.big_m && e.m2l_run + tm > e.slot_m) promote_m2l(a, e);
-    if (!e.big_p && e.p2p_run + tp + e.plain_run + tq > e.slot_p) promote_p2p(a, e);
-    uint32_t k = e.m2l_run + pm;
-    if (sel_m & 1u) { if (k < e.slot_m && e.m2l_base + k < a.m2l_cap) a.m2l_pool[e.m2l_base + k] = s0; ++k; }
-    if (sel_m & 2u) { if (k < e.slot_m && e.m2l_base + k < a.m2l_cap) a.m2l_pool[e.m2l_base + k] = s1; }
-    uint32_t q = e.p2p_run + pp;
-    if (sel_p & 1u) { if (q < e.slot_p && e.p2p_base + q < a.p2p_cap) a.p2p_pool[e.p2p_base + q] = s0; ++q; }
-    if (sel_p & 2u) { if (q < e.slot_p && e.p2p_base + q < a.p2p_cap) a.p2p_pool[e.p2p_base + q] = s1; }
-    uint32_t r = e.plain_run + pq;
-    uint32_t* pl = e.plain_g ? e.plain_g : e.plain;
-    if (sel_q & 1u) { if (r < e.slot_p) pl[r] = s0; ++r; }
-    if (sel_q & 2u) { if (r < e.slot_p) pl[r] = s1; }
-  }
-  if (W == kLeafExact) {
-    uint64_t k = e.m2l_base + e.m2l_run + pm;
-    if (sel_m & 1u) { if (k < a.m2l_cap) a.m2l_pool[k] = s0; ++k; }
-    if (sel_m & 2u) { if (k < a.m2l_cap) a.m2l_pool[k] = s1; }
-    uint64_t q = e.p2p_base + e.p2p_run + pp;
-    if (sel_p & 1u) { if (q < a.p2p_cap) a.p2p_pool[q] = s0; ++q; }
-    if (sel_p & 2u) { if (q < a.p2p_cap) a.p2p_pool[q] = s1; }
-    uint32_t r = e.plain_run + pq;  // rank from the back
-    for (int b = 0; b < 2; ++b) {
-      if (!(sel_q & (1u << b))) continue;
-      if (r < e.p2p_total) {
-        const uint64_t t = e.p2p_base + (e.p2p_total - 1u - r);
-        if (t < a.p2p_cap) a.p2p_pool[t] = b ? s1 : s0;
-      }
-      ++r;
-    }
-  }
-  e.m2l_run += tm;
-  e.p2p_run += tp;
-  e.plain_run += tq;
-}
-
-// classification of one tested source against target v
-// returns 0 = M2L, 1 = opened (no branches: the self pair is selected out)
-__device__ __forceinline__ int classify(const NodeWalkArgs& a, int v, const double* rv, uint32_t s) {
-  const bool acc = accept(rv, a.rec + (int64_t)s * a.stride, a.theta2, a.r_kern);
-  return ((int)s != v && acc) ? 0 : 1;
-}
-
-// the same test for a leaf target, from one evaluation of d^2: 0 = M2L,
-// 1 = opened (or P2P that may need softening), 2 = opened although beyond
-// both kernels (only the opening angle failed; a P2P pair of leaves then
-// needs no softening), 3 = opened, and every node below s would fail the
-// softening test against v too: s lies inside v's own kernel reach,
-// d + l_s < l_v + R_kern h_max(v) (any node below s has its centre within
-// l_s of s's and h_max >= 0), so the lowering would end with all of s's
-// leaves as P2P sources; the margin keeps rounding in the tests the
-// lowering would make from deciding otherwise
-__device__ __forceinline__ int classify3(const NodeWalkArgs& a, int v, const double* rv,
-                                         uint32_t s) {
-  const double* rs = a.rec + (int64_t)s * a.stride;
-  const double dx = rs[0] - rv[0];
-  const double dy = rs[1] - rv[1];
-  const double dz = rs[2] - rv[2];
+// the test of a leaf target, from one evaluation of d^2.  m2l:
+// accepted; beyond: d beyond both kernels (a P2P pair of leaves then needs no
+// softening); whole: every node below s would fail the softening test against
+// v too: s lies inside v's own kernel reach, d + l_s < l_v + R_kern h_max(v)
+// (any node below s has its centre within l_s of s's and h_max >= 0), so the
+// lowering would end with all of s's leaves as P2P sources; the margin keeps
+// rounding in the tests the lowering would make from deciding otherwise
+struct LeafTest {
+  bool m2l, beyond, whole;
+};
+__device__ __forceinline__ LeafTest leaf_test(const NodeWalkArgs& a, int v, const Src& rv,
+                                              uint32_t s, const Src& rs) {
+  const double dx = rs.x - rv.x;
+  const double dy = rs.y - rv.y;
+  const double dz = rs.z - rv.z;
   const double d2 = dx * dx + dy * dy + dz * dz;
-  const double lsum = rv[3] + rs[3];
-  const double rsum = lsum + a.r_kern * fmax(rv[4], rs[4]);
-  const double reach = rv[3] + a.r_kern * rv[4] - rs[3];
-  const bool beyond = d2 >= rsum * rsum;
-  const bool whole = reach > 0.0 && d2 < reach * reach * (1.0 - 1e-9);
-  const bool mac = lsum * lsum < a.theta2 * d2;
-  const int k = beyond ? (mac ? 0 : 2) : (whole ? 3 : 1);
-  return (int)s == v ? 1 : k;  // selects, no branches
+  const double lsum = rv.l + rs.l;
+  const double rsum = lsum + a.r_kern * fmax(rv.h, rs.h);
+  const double reach = rv.l + a.r_kern * rv.h - rs.l;
+  const bool other = (int)s != v;
+  LeafTest k;
+  k.beyond = other && d2 >= rsum * rsum;
+  k.m2l = k.beyond && lsum * lsum < a.theta2 * d2;
+  k.whole = other && !k.beyond && reach > 0.0 && d2 < reach * reach * (1.0 - 1e-9);
+  return k;
 }
 
-// internal target: the tested sources, 64 * kWalkBatch at a time; every
-// load of a batch (list entries, then children, then records) is issued
-// before the classification, so a node waits for one chain of dependent
-// loads per batch instead of one per 64 sources; entries are emitted in
-// the order of the tested list
-constexpr int kWalkBatch = 4;
+// internal target: the opened list of its parent, 64 * kWalkBatch entries at a
+// time; every load of a batch (entries, then the records of the nodes they
+// stand for) is issued before the classification, so a node waits for one
+// chain of two loads per batch; entries are emitted in the order of the list
+// (a batch of one group, 50 registers: 0.62 ms for the walk at 1e6 particles of a
+// polytrope; two groups took 0.65, three 0.68: the waves in flight matter more)
+constexpr int kWalkBatch = 1;
 
-template <bool WRITE>
-__device__ void walk_internal(const NodeWalkArgs& a, int v, const double* rv, const uint32_t* src,
-                              uint32_t nsrc, Emit& e) {
+__device__ void walk_internal(const NodeWalkArgs& a, int v, const Src& rv, const uint32_t* src,
+                              uint32_t nsrc, uint32_t region, uint32_t room, Emit& e) {
   const uint32_t lane = threadIdx.x & 63;
   for (uint32_t base = 0; base < nsrc; base += 64 * kWalkBatch) {
     uint32_t sb[kWalkBatch];
@@ -295,157 +258,140 @@ __device__ void walk_internal(const NodeWalkArgs& a, int v, const double* rv, co
     }
     // invalid slots read node v (a valid index) and are masked afterwards,
     // so the loads and tests need no branches
-    int cb[kWalkBatch];
-#pragma unroll
-    for (int u = 0; u < kWalkBatch; ++u) {
-      const bool ok = sb[u] != 0xffffffffu;
-      cb[u] = a.info[ok ? sb[u] : (uint32_t)v].child;
-      if (!ok) cb[u] = -2;
-    }
-    uint32_t selm[kWalkBatch], selo[kWalkBatch], nm[kWalkBatch], no[kWalkBatch];
+    Src r0[kWalkBatch], r1[kWalkBatch];
     uint32_t t0[kWalkBatch], t1[kWalkBatch];
 #pragma unroll
     for (int u = 0; u < kWalkBatch; ++u) {
-      const bool ok = cb[u] != -2;
-      const bool two = cb[u] >= 0;
-      t0[u] = two ? (uint32_t)cb[u] : (ok ? sb[u] : (uint32_t)v);
-      t1[u] = two ? (uint32_t)cb[u] + 1u : (uint32_t)v;
-      const bool m0 = classify(a, v, rv, t0[u]) == 0;
-      const bool m1 = classify(a, v, rv, t1[u]) == 0;
-      const uint32_t v0 = ok ? 1u : 0u, v1 = two ? 1u : 0u;
-      selm[u] = (m0 ? v0 : 0u) | ((m1 ? v1 : 0u) << 1);
-      selo[u] = (m0 ? 0u : v0) | ((m1 ? 0u : v1) << 1);
-      nm[u] = (m0 ? v0 : 0u) + (m1 ? v1 : 0u);
-      no[u] = (m0 ? 0u : v0) + (m1 ? 0u : v1);
-      // the children's tested list: an opened leaf once, an internal node twice
-      const uint32_t x0 = a.info[t0[u]].child >= 0 ? 2u : 1u;
-      const uint32_t x1 = a.info[t1[u]].child >= 0 ? 2u : 1u;
-      e.exp_lane += ((selo[u] & 1u) ? x0 : 0u) + ((selo[u] & 2u) ? x1 : 0u);
+      const bool ok = sb[u] != 0xffffffffu;
+      t0[u] = ok ? sb[u] & ~kOpenInternal : (uint32_t)v;
+      t1[u] = ok && (sb[u] & kOpenInternal) ? t0[u] + 1u : (uint32_t)v;
+      r0[u] = load_src(a, t0[u]);
+      r1[u] = load_src(a, t1[u]);
     }
 #pragma unroll
     for (int u = 0; u < kWalkBatch; ++u) {
       if (base + 64u * u >= nsrc) break;  // uniform
-      emit_lists<WRITE>(a, e, t0[u], t1[u], nm[u], selm[u], no[u], selo[u], false);
+      const bool ok = sb[u] != 0xffffffffu, two = ok && (sb[u] & kOpenInternal);
+      const bool m0 = (int)t0[u] != v && accept(rv, r0[u], a.theta2, a.r_kern);
+      const bool m1 = (int)t1[u] != v && accept(rv, r1[u], a.theta2, a.r_kern);
+      const bool i0 = r0[u].child >= 0, i1 = r1[u].child >= 0;
+      const bool p0 = ok && !m0, p1 = two && !m1;
+      append(e.m2l, room, e.m2l_run, ok && m0, t0[u], two && m1, t1[u]);
+      append_back(e.m2l, region, room, e.open_run, p0,
+                  i0 ? (uint32_t)r0[u].child | kOpenInternal : t0[u], p1,
+                  i1 ? (uint32_t)r1[u].child | kOpenInternal : t1[u]);
+      // the children's tested list: an opened leaf once, an internal node twice
+      e.exp_lane += (p0 ? (i0 ? 2u : 1u) : 0u) + (p1 ? (i1 ? 2u : 1u) : 0u);
     }
   }
 }
 
-// leaf target: U groups of 64 tested sources per step (all their loads
-// issued before the classification); opened internal sources are pushed on
-// the lowering stack (in LDS), which is drained 64 entries per step after
-// each batch of the tested list, so the stack stays within a few chunks per
-// tree level.  Returns false when the stack would overflow (the walk is then
-// rerun with a larger stack).
+// leaf target: U groups of 64 entries per step (all their loads issued before
+// the tests), an entry being a leaf or the pair of children of an opened
+// node; opened internal sources push their pair on the lowering stack (in
+// LDS).  Returns false when the stack would overflow (the walk is then rerun
+// with a larger stack).
 template <int W, int U>
-__device__ __forceinline__ bool leaf_step(const NodeWalkArgs& a, int v, const double* rv,
-                                          const uint32_t (&t0)[U], const uint32_t (&t1)[U],
-                                          const int (&nt)[U], Emit& e, uint32_t* stk,
-                                          uint32_t& sp) {
-  int kk[U][2], cc[U][2], pc[U][2];
+__device__ __forceinline__ bool leaf_step(const NodeWalkArgs& a, int v, const Src& rv,
+                                          const uint32_t (&t0)[U], const int (&nt)[U], Emit& e,
+                                          uint32_t* stk, uint32_t& sp) {
+  Src r[U][2];
 #pragma unroll
-  for (int u = 0; u < U; ++u) {
+  for (int u = 0; u < U; ++u)
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const bool valid = q < nt[u];
-      const uint32_t t = valid ? (q ? t1[u] : t0[u]) : (uint32_t)v;  // a valid index
-      const int k = classify3(a, v, rv, t);
-      const NodeInfo ti = a.info[t];
-      kk[u][q] = valid ? k : -1;
-      cc[u][q] = valid ? ti.child : 0;
-      pc[u][q] = ti.cnt;
-    }
-  }
+    for (int q = 0; q < 2; ++q) r[u][q] = load_src(a, q < nt[u] ? t0[u] + q : (uint32_t)v);
   bool ok = true;
 #pragma unroll
   for (int u = 0; u < U; ++u) {
-    uint32_t selm = 0, selp = 0, selq = 0, nm = 0, np = 0, nq = 0;
-    bool open0 = false, open1 = false;
+    bool cm[2], cp[2], cq[2], open[2];
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
-      const int k = kk[u][q];
-      if (k < 0) continue;
-      if (k == 0) { selm |= 1u << q; ++nm; continue; }
-      if (cc[u][q] < 0 || k == 3) {
-        // a leaf, or a whole subtree of P2P sources kept as one entry
-        if (k == 2) { selq |= 1u << q; ++nq; }
-        else { selp |= 1u << q; ++np; }
-        e.src_lane += (uint32_t)pc[u][q];
-      } else {
-        if (q) open1 = true; else open0 = true;
-      }
+      const bool valid = q < nt[u];
+      const LeafTest k = leaf_test(a, v, rv, t0[u] + q, r[u][q]);
+      // P2P: a leaf, or a whole subtree of P2P sources kept as one entry
+      const bool direct = valid && !k.m2l && (r[u][q].child < 0 || k.whole);
+      cm[q] = valid && k.m2l;
+      cq[q] = direct && k.beyond;
+      cp[q] = direct && !k.beyond;
+      open[q] = valid && !k.m2l && !direct;
+      e.src_lane += direct ? (uint32_t)r[u][q].cnt : 0u;
     }
-    emit_leaf_lists<W>(a, e, t0[u], t1[u], nm, selm, np, selp, nq, selq);
-    const uint32_t npush = (open0 ? 2u : 0u) + (open1 ? 2u : 0u);
-    uint32_t tpush;
-    const uint32_t pp = wave_prefix(npush, tpush);
+    const uint32_t s0 = t0[u], s1 = t0[u] + 1u;
+    if (W == kLeafSlot) {
+      const uint32_t tm = (uint32_t)__popcll(__ballot(cm[0])) + (uint32_t)__popcll(__ballot(cm[1]));
+      const bool d0 = cp[0] || cq[0], d1 = cp[1] || cq[1];
+      const uint32_t td = (uint32_t)__popcll(__ballot(d0)) + (uint32_t)__popcll(__ballot(d1));
+      // (uniform tests: the wave's totals)
+      if (!e.big_m && e.m2l_run + tm > e.slot_m) promote_m2l(a, e);
+      if (!e.big_p && e.p2p_run + e.plain_run + td > e.slot_p) promote_p2p(a, e);
+    }
+    append(e.m2l, e.room_m, e.m2l_run, cm[0], s0, cm[1], s1);
+    append(e.p2p, e.room_p, e.p2p_run, cp[0], s0, cp[1], s1);
+    if (W == kLeafSlot) {
+      if (e.plain_g) append(e.plain_g, e.slot_p, e.plain_run, cq[0], s0, cq[1], s1);
+      else append(e.plain, e.slot_p, e.plain_run, cq[0], s0, cq[1], s1);
+    } else {
+      append_back(e.p2p, e.p2p_total, e.room_p, e.plain_run, cq[0], s0, cq[1], s1);
+    }
+    const uint64_t b0 = __ballot(open[0]), b1 = __ballot(open[1]);
+    const uint32_t tpush = (uint32_t)__popcll(b0) + (uint32_t)__popcll(b1);
     if (!ok || sp + tpush > a.stack_cap) { ok = false; continue; }  // uniform
-    uint32_t w = sp + pp;
-    if (open0) { stk[w] = (uint32_t)cc[u][0]; stk[w + 1] = (uint32_t)cc[u][0] + 1u; w += 2; }
-    if (open1) { stk[w] = (uint32_t)cc[u][1]; stk[w + 1] = (uint32_t)cc[u][1] + 1u; }
+    uint32_t w = sp + below(b1, below(b0, 0u));
+    if (open[0]) stk[w++] = (uint32_t)r[u][0].child;
+    if (open[1]) stk[w] = (uint32_t)r[u][1].child;
     sp += tpush;
   }
   __syncthreads();
   return ok;
 }
 
+// The stack is drained in steps of U groups while it holds as many entries
+// and has room for what they may push (2 each), one group at a time while it
+// lacks the room, and by what is left once the opened list is at its end: the
+// lanes of a step are used, and the stack stays within a few groups per level.
 template <int W>
-__device__ void walk_leaf(const NodeWalkArgs& a, int v, const double* rv, const uint32_t* src,
+__device__ void walk_leaf(const NodeWalkArgs& a, int v, const Src& rv, const uint32_t* src,
                           uint32_t nsrc, bool root, Emit& e, uint32_t* stk, int* status) {
-  // three groups of 64 tested sources per step: the leaf kernels then fit
-  // 128 registers (four waves per SIMD for this latency-bound walk; four
-  // groups took 137 and left three)
-  constexpr int U = 3;
+  // two groups a step: 1.48 ms for the walk of a 1e6 Plummer sphere (one 1.55,
+  // three 1.56)
+  constexpr int U = 2;
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t n0 = root ? 1u : nsrc;
   uint32_t sp = 0;
   bool ok = true;
   for (uint32_t base = 0; base < n0 && ok; base += 64 * U) {
-    uint32_t sb[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const uint32_t i = base + 64u * u + lane;
-      sb[u] = i < n0 ? (root ? (uint32_t)v : src[i]) : 0xffffffffu;
-    }
-    int cb[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) cb[u] = (sb[u] != 0xffffffffu && !root) ? a.info[sb[u]].child : -1;
-    uint32_t t0[U], t1[U];
+    uint32_t t0[U];
     int nt[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      t0[u] = t1[u] = 0;
-      nt[u] = 0;
-      if (sb[u] == 0xffffffffu) continue;
-      if (cb[u] < 0) { t0[u] = sb[u]; nt[u] = 1; }
-      else { t0[u] = (uint32_t)cb[u]; t1[u] = (uint32_t)cb[u] + 1u; nt[u] = 2; }
+      const uint32_t i = base + 64u * u + lane;
+      const uint32_t sb = i < n0 ? (root ? (uint32_t)v : src[i]) : 0u;
+      t0[u] = sb & ~kOpenInternal;
+      nt[u] = i < n0 ? ((sb & kOpenInternal) ? 2 : 1) : 0;
     }
-    ok = leaf_step<W, U>(a, v, rv, t0, t1, nt, e, stk, sp);
-    // the stack is drained U groups of 64 at a time while it holds more than
-    // one group and has room for what they may push (2 per entry), else one
-    // group at a time (the leaves with the longest lists lower deep stacks,
-    // and their walks set the pass's time)
-    while (ok && sp > 0) {
+    ok = leaf_step<W, U>(a, v, rv, t0, nt, e, stk, sp);
+    const bool last = base + 64 * U >= n0;
+    while (ok && (last ? sp > 0 : sp >= 64u * U)) {
       const uint32_t kw = sp < 64u * U ? sp : 64u * U;
       if (sp > 64u && sp + kw <= a.stack_cap) {  // (uniform)
-        uint32_t d0[U], d1[U];
+        uint32_t d0[U];
         int dn[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          d1[u] = 0;
-          dn[u] = 64u * u + lane < kw ? 1 : 0;
+          dn[u] = 64u * u + lane < kw ? 2 : 0;
           d0[u] = dn[u] ? stk[sp - kw + 64u * u + lane] : 0u;
         }
         __syncthreads();
         sp -= kw;
-        ok = leaf_step<W, U>(a, v, rv, d0, d1, dn, e, stk, sp);
+        ok = leaf_step<W, U>(a, v, rv, d0, dn, e, stk, sp);
       } else {
         const uint32_t k = sp < 64u ? sp : 64u;
-        uint32_t d0[1] = {0}, d1[1] = {0};
-        int dn[1] = {lane < k ? 1 : 0};
+        uint32_t d0[1] = {0};
+        int dn[1] = {lane < k ? 2 : 0};
         if (dn[0]) d0[0] = stk[sp - k + lane];
         __syncthreads();
         sp -= k;
-        ok = leaf_step<W, 1>(a, v, rv, d0, d1, dn, e, stk, sp);
+        ok = leaf_step<W, 1>(a, v, rv, d0, dn, e, stk, sp);
       }
     }
   }
@@ -481,12 +427,13 @@ __global__ __launch_bounds__(64) void k_nodewalk_internal(NodeWalkArgs a, int le
   if (vi.child < 0) return;  // (the level's internal nodes come first)
   if (lane == 0) { a.p2p_cnt[v] = 0; a.p2p_off[v] = 0; }
   const bool root = flag == 1;
-  const double* rv = a.rec + (int64_t)v * a.stride;
+  const Src rv = load_src(a, (uint32_t)v);
   const uint32_t region = root ? 1u : a.exp[vi.parent];
   Emit e{};
   bool fits = true;
+  uint64_t at;
   if (region <= a.int_slot) {
-    e.m2l_base = (uint64_t)(rank0 + b) * a.int_slot;
+    at = (uint64_t)(rank0 + b) * a.int_slot;
   } else {
     uint64_t t = 0;
     if (lane == 0) {
@@ -496,21 +443,20 @@ __global__ __launch_bounds__(64) void k_nodewalk_internal(NodeWalkArgs a, int le
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)t);
     const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(t >> 32));
     t = ((uint64_t)hi << 32) | lo;
-    e.m2l_base = (uint64_t)a.int_nodes * a.int_slot + t;
+    at = (uint64_t)a.int_nodes * a.int_slot + t;
     fits = t + region <= a.int_big;
   }
-  e.open_base = e.m2l_base + region;
   // a region that does not fit gets no offset (the walk goes on counting,
   // the host grows the pool and walks again)
-  fits = fits && e.open_base <= a.m2l_cap;
-  if (lane == 0) a.m2l_off[v] = fits ? (uint32_t)e.m2l_base : kNoList;
+  fits = fits && at + region <= a.m2l_cap;
+  if (lane == 0) a.m2l_off[v] = fits ? (uint32_t)at : kNoList;
   if (root) {
     // (root, root) is opened: both root children meet both root children
     if (lane == 0) {
-      if (fits) a.open_pool[e.m2l_base] = (uint32_t)v;
+      if (fits) a.open_pool[at] = (uint32_t)vi.child | kOpenInternal;
       a.m2l_cnt[v] = 0;
       a.open_cnt[v] = 1;
-      a.open_off[v] = fits ? (uint32_t)e.m2l_base : kNoList;
+      a.open_off[v] = fits ? (uint32_t)at : kNoList;
       a.exp[v] = 2;
     }
     return;
@@ -518,14 +464,15 @@ __global__ __launch_bounds__(64) void k_nodewalk_internal(NodeWalkArgs a, int le
   const uint32_t po = a.open_off[vi.parent];
   uint32_t nsrc = a.open_cnt[vi.parent];
   if ((uint64_t)po + nsrc > a.open_cap) nsrc = 0;  // pool too small: the walk is rerun
-  walk_internal<true>(a, v, rv, a.open_pool + po, nsrc, e);
+  e.m2l = a.m2l_pool + at;
+  walk_internal(a, v, rv, a.open_pool + po, nsrc, region, fits ? region : 0u, e);
   uint32_t ex = e.exp_lane;
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) ex += (uint32_t)__shfl_xor((int)ex, o, 64);
   if (lane == 0) {
     a.m2l_cnt[v] = e.m2l_run;
     a.open_cnt[v] = e.open_run;
-    a.open_off[v] = fits ? (uint32_t)(e.open_base - e.open_run) : kNoList;
+    a.open_off[v] = fits ? (uint32_t)(at + region - e.open_run) : kNoList;
     a.exp[v] = ex;
   }
 }
@@ -541,7 +488,7 @@ __global__ __launch_bounds__(64) void k_nodewalk_internal(NodeWalkArgs a, int le
 // pass, which writes its lists after all slots, at offsets from scans of
 // such leaves' counts.
 template <bool OVF>
-__device__ void leaf_lists(const NodeWalkArgs& a, int l, uint32_t* stk) {
+__device__ __forceinline__ void leaf_lists(const NodeWalkArgs& a, int l, uint32_t* stk) {
   const int v = a.leaf_node[l];
   const NodeInfo vi = a.info[v];
   const int flag = a.node_flag ? (int)a.node_flag[v] : (vi.parent < 0 ? 1 : 2);
@@ -556,7 +503,7 @@ __device__ void leaf_lists(const NodeWalkArgs& a, int l, uint32_t* stk) {
     return;
   }
   const bool root = flag == 1;
-  const double* rv = a.rec + (int64_t)v * a.stride;
+  const Src rv = load_src(a, (uint32_t)v);
   const uint32_t* src = nullptr;
   uint32_t nsrc = 0;
   if (!root) {
@@ -568,8 +515,9 @@ __device__ void leaf_lists(const NodeWalkArgs& a, int l, uint32_t* stk) {
   const uint64_t nl = (uint64_t)a.nleaves;
   Emit e{};
   if (OVF) {
-    e.m2l_base = a.leaf_base + nl * a.slot_m + (uint64_t)a.nbig * a.big_m + a.leaf_m2l_off[l];
-    e.p2p_base = nl * a.slot_p + (uint64_t)a.nbig * a.big_p + a.leaf_p2p_off[l];
+    place_m2l(a, e, a.leaf_base + nl * a.slot_m + (uint64_t)a.nbig * a.big_m + a.leaf_m2l_off[l],
+              0xffffffffu);
+    place_p2p(a, e, nl * a.slot_p + (uint64_t)a.nbig * a.big_p + a.leaf_p2p_off[l], 0xffffffffu);
     e.p2p_total = a.p2p_cnt[v];  // from the first pass
     if (lane == 0) {
       const bool fm = e.m2l_base + a.m2l_cnt[v] <= a.m2l_cap;
@@ -581,8 +529,8 @@ __device__ void leaf_lists(const NodeWalkArgs& a, int l, uint32_t* stk) {
     __syncthreads();  // (the stack is reused by the wave's next leaf)
     return;
   }
-  e.m2l_base = a.leaf_base + (uint64_t)l * a.slot_m;
-  e.p2p_base = (uint64_t)l * a.slot_p;
+  place_m2l(a, e, a.leaf_base + (uint64_t)l * a.slot_m, a.slot_m);
+  place_p2p(a, e, (uint64_t)l * a.slot_p, a.slot_p);
   e.slot_m = a.slot_m;
   e.slot_p = a.slot_p;
   e.plain = stk + a.stack_cap;
@@ -598,10 +546,8 @@ __device__ void leaf_lists(const NodeWalkArgs& a, int l, uint32_t* stk) {
     // the entries beyond both kernels after the others, in reverse rank
     // order (as the exact pass writes them)
     const uint32_t* pl = e.plain_g ? e.plain_g : e.plain;
-    for (uint32_t i = lane; i < nq; i += 64) {
-      const uint64_t t = e.p2p_base + np + i;
-      if (t < a.p2p_cap) a.p2p_pool[t] = pl[nq - 1u - i];
-    }
+    for (uint32_t i = lane; i < nq; i += 64)
+      if (np + i < e.room_p) e.p2p[np + i] = pl[nq - 1u - i];
   }
   if (lane == 0) {
     a.m2l_cnt[v] = nm;

@@ -483,15 +483,27 @@ __global__ __launch_bounds__(256) void k_extent(int nn, int nitems, const NodeIn
   if (lane == 0) atomicMax(&l2bits[v], (unsigned long long)__double_as_longlong(d2max));
 }
 
+// sizes of the internal nodes, and what the level walk reads of every node
 template <int RS>
 __global__ void k_extent_final(int nn, const NodeInfo* __restrict__ info,
-                               const unsigned long long* __restrict__ l2bits, double* rec) {
+                               const unsigned long long* __restrict__ l2bits, double* rec,
+                               WalkRec* __restrict__ wrec) {
   int v = blockIdx.x * blockDim.x + threadIdx.x;
   if (v >= nn) return;
-  if (info[v].child < 0) return;
-  rec[(int64_t)v * RS + 3] = sqrt(__longlong_as_double((long long)l2bits[v]));
+  double* r = rec + (int64_t)v * RS;
+  const NodeInfo ni = info[v];
+  WalkRec w{};
+  w.x = r[0]; w.y = r[1]; w.z = r[2]; w.h = r[4];
+  if (ni.child < 0) {
+    w.l = r[3];
+  } else {
+    w.l = sqrt(__longlong_as_double((long long)l2bits[v]));
+    r[3] = w.l;
+  }
+  w.child = ni.child;
+  w.cnt = ni.cnt;
+  wrec[v] = w;
 }
-
 
 }  // namespace
 
@@ -646,13 +658,14 @@ void launch_extent(int order, int nn, int nitems, const NodeInfo* info,
 }
 
 void launch_extent_final(int order, int nn, const NodeInfo* info,
-                         const unsigned long long* l2bits, double* rec, hipStream_t s) {
+                         const unsigned long long* l2bits, double* rec, WalkRec* wrec,
+                         hipStream_t s) {
   const unsigned nb = blocks_for(nn, 256);
   switch (rec_stride(order)) {
-    case 16: k_extent_final<16><<<nb, 256, 0, s>>>(nn, info, l2bits, rec); break;
-    case 24: k_extent_final<24><<<nb, 256, 0, s>>>(nn, info, l2bits, rec); break;
-    case 32: k_extent_final<32><<<nb, 256, 0, s>>>(nn, info, l2bits, rec); break;
-    case 48: k_extent_final<48><<<nb, 256, 0, s>>>(nn, info, l2bits, rec); break;
+    case 16: k_extent_final<16><<<nb, 256, 0, s>>>(nn, info, l2bits, rec, wrec); break;
+    case 24: k_extent_final<24><<<nb, 256, 0, s>>>(nn, info, l2bits, rec, wrec); break;
+    case 32: k_extent_final<32><<<nb, 256, 0, s>>>(nn, info, l2bits, rec, wrec); break;
+    case 48: k_extent_final<48><<<nb, 256, 0, s>>>(nn, info, l2bits, rec, wrec); break;
   }
 }
 

@@ -29,7 +29,7 @@ enum BufId {
   B_KEY0, B_KEY1, B_VAL0, B_VAL1, B_SORT, B_BASE, B_SCANTMP,
   B_XS, B_YS, B_ZS, B_MS, B_HS, B_HIS, B_H4, B_P4,
   B_KFIRST, B_KLAST, B_KLEFT, B_KRIGHT, B_KPAR, B_KSIDE, B_KEPT,
-  B_LFLAG, B_LAT, B_INFO, B_REC, B_RECQ, B_L2BITS, B_CHUNK,
+  B_LFLAG, B_LAT, B_INFO, B_REC, B_WREC, B_RECQ, B_L2BITS, B_CHUNK,
   B_LEAFNODE, B_LEAFDEPTH, B_PLEAF,
   B_LDOFF, B_DEPTHCNT, B_M2LCNT, B_P2PCNT, B_PAIRCNT, B_M2L, B_P2P,
   B_FAR, B_MOMPART, B_MOM, B_L2LCNT,
@@ -381,7 +381,7 @@ int do_build(sfmm_ctx* ctx, int64_t n64, const double* x, const double* m, const
         {B_NDEPTH, sizeof(int32_t) * nn}, {B_LEVNODES, sizeof(uint32_t) * nn},
         {B_LEVKEY0, sizeof(uint64_t) * nn}, {B_LEVKEY1, sizeof(uint64_t) * nn},
         {B_LEVIDS, sizeof(uint32_t) * nn}, {B_LEVOFF, sizeof(uint32_t) * (kMaxDepthCap + 2)},
-        {B_LEVINT, sizeof(uint32_t) * (kMaxDepthCap + 2)}};
+        {B_LEVINT, sizeof(uint32_t) * (kMaxDepthCap + 2)}, {B_WREC, walk_rec_bytes(nn)}};
     for (auto& q : need2)
       if ((rc = ensure(ctx, q.id, q.bytes))) return rc;
     launch_node_depth(nn, info, P<int32_t>(ctx, B_NDEPTH), P<uint64_t>(ctx, B_LEVKEY0), s);
@@ -427,9 +427,10 @@ int do_build(sfmm_ctx* ctx, int64_t n64, const double* x, const double* m, const
                   P<double>(ctx, B_XS),
                   P<double>(ctx, B_YS), P<double>(ctx, B_ZS), P<double>(ctx, B_REC),
                   reinterpret_cast<unsigned long long*>(P<uint64_t>(ctx, B_L2BITS)), s);
-    launch_extent_final(order, nn, info, reinterpret_cast<unsigned long long*>(P<uint64_t>(ctx, B_L2BITS)),
-                        P<double>(ctx, B_REC), s);
   }
+  launch_extent_final(order, nn, info,
+                      reinterpret_cast<unsigned long long*>(P<uint64_t>(ctx, B_L2BITS)),
+                      P<double>(ctx, B_REC), walk_rec(P<WalkRec>(ctx, B_WREC)), s);
   phase_mark(ctx, 0, 1);
   HIPCHK(hipGetLastError());
   ctx->have_tree = true;
@@ -556,7 +557,7 @@ int walk_levels(sfmm_ctx* ctx, double theta) {
                                                (uint64_t)ctx->nbig * ctx->big_p + 8ull * nl + 1024;
   ctx->m2l_cap = std::min(kPoolMax, std::max<uint64_t>(ctx->m2l_cap, est_m));
   ctx->p2p_cap = std::min(kPoolMax, std::max<uint64_t>(ctx->p2p_cap, est_p));
-  const uint32_t stack_min = (uint32_t)std::min(16384, 64 * (ctx->maxdepth + 4) + 256);
+  const uint32_t stack_min = (uint32_t)std::min(16384, 32 * (ctx->maxdepth + 4) + 256);
   if (ctx->stack_cap < stack_min) ctx->stack_cap = stack_min;
   for (int attempt = 0;; ++attempt) {
     // the leaf kernel's LDS (stack and staged P2P entries) stays within 64 KB
@@ -581,8 +582,7 @@ int walk_levels(sfmm_ctx* ctx, double theta) {
     }
     NodeWalkArgs a{};
     a.info = P<NodeInfo>(ctx, B_INFO);
-    a.rec = P<double>(ctx, B_REC);
-    a.stride = rec_stride(ctx->order);
+    a.wrec = walk_rec(P<WalkRec>(ctx, B_WREC));
     a.theta2 = theta * theta;
     a.r_kern = ctx->cfg.r_kern;
     a.level_nodes = P<int32_t>(ctx, B_LEVNODES);

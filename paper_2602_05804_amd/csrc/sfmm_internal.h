@@ -27,6 +27,17 @@ struct NodeInfo {
   int32_t lo, cnt, child, parent;
 };
 
+// what the level walk reads of a source: centre, size l, largest h, children
+// and particles.  Two children (2c + 1, 2c + 2) share a line of 128 bytes.
+struct alignas(64) WalkRec {
+  double x, y, z, l, h;
+  int32_t child, cnt;
+  uint64_t unused[2];
+};
+inline size_t walk_rec_bytes(int64_t nn) { return sizeof(WalkRec) * ((size_t)nn + 1); }
+// (node 0 at 64 bytes of the buffer, so that node 1 begins a line)
+inline WalkRec* walk_rec(void* buf) { return reinterpret_cast<WalkRec*>(buf) + 1; }
+
 constexpr int kDepthBits = 7;
 constexpr int kSrcBits = 25;
 constexpr uint32_t kSrcMask = (1u << kSrcBits) - 1u;
@@ -173,8 +184,10 @@ void launch_extent(int order, int nn, int nitems, const NodeInfo* info,
                    const uint32_t* chunk_off, uint32_t* item_node, const double* xs,
                    const double* ys, const double* zs, double* rec, unsigned long long* l2bits,
                    hipStream_t s);
+// (l2bits: null for a tree of one leaf)
 void launch_extent_final(int order, int nn, const NodeInfo* info,
-                         const unsigned long long* l2bits, double* rec, hipStream_t s);
+                         const unsigned long long* l2bits, double* rec, WalkRec* wrec,
+                         hipStream_t s);
 constexpr int kExtentChunk = 2048;
 
 // ---- walk (Algorithms 1 and 2) ---------------------------------------------
@@ -241,8 +254,7 @@ struct P2PItemRule {
 // ---- level-synchronous node walk -------------------------------------------------
 struct NodeWalkArgs {
   const NodeInfo* info;
-  const double* rec;
-  int stride;
+  const WalkRec* wrec;
   double theta2, r_kern;
   const int32_t* level_nodes;  // nodes grouped by depth
   const uint8_t* node_flag;    // 0 spans systems (skipped), 1 walk root, 2 other
@@ -253,6 +265,8 @@ struct NodeWalkArgs {
   // (M2L from the front, opened from the back); its size, the node's tested
   // list, is known before the node is walked: exp[parent], the parent's
   // opened sources with internal ones counted twice (their two children).
+  // An opened entry is a leaf, or the first child of an internal node, marked
+  // by kOpenInternal.
   uint32_t *m2l_off, *m2l_cnt, *open_off, *open_cnt, *p2p_off, *p2p_cnt;
   uint32_t *m2l_pool, *open_pool, *p2p_pool;  // open_pool: the M2L pool
   // pool capacities (entries, <= kPoolMax).  Every running offset and total
