@@ -654,7 +654,7 @@ void launch_m2l_order(SharedFarArgs& a, bool f32, const M2LOrderBufs& b, hipStre
   if (a.nn > 8192 || a.n64 > 0) {
     k_m2l_order_keys<<<(unsigned)((a.nn + 255) / 256), 256, 0, s>>>(
         a.nn, a.level_nodes, a.m2l_cnt, a.depth, a.top, f32 ? 1 : 0, a.longer, b.key0, b.ids0);
-    radix_pass(a.nn, b.key0, b.ids0, b.key1, b.ids2, b.base, b.words, s);
+    radix_pass(a.nn, false, b.key0, b.ids0, b.key1, b.ids2, b.base, b.words, s);
     a.maxlong = (int)std::min<uint64_t>(a.nn, a.steps / (a.longer + 1));
     a.nlong = b.base + 63;  // the first place of key 63
     in = b.ids2;

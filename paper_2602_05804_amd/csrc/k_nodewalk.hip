@@ -102,27 +102,6 @@ __device__ __forceinline__ uint32_t pool_room(uint64_t base, uint64_t cap, uint3
   return room < want ? (uint32_t)room : want;
 }
 
-__global__ void k_node_depth(int nn, const NodeInfo* __restrict__ info, int32_t* __restrict__ depth,
-                             uint64_t* __restrict__ key) {
-  const int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= nn) return;
-  int d = 0;
-  for (int u = info[v].parent; u >= 0; u = info[u].parent) ++d;
-  depth[v] = d;
-  // grouped by depth, and within a depth the internal nodes first
-  key[v] = (uint64_t)min(2 * d + (info[v].child < 0 ? 1 : 0), 255);
-}
-
-// level k spans [level_off[k], level_off[k + 1]), its internal nodes
-// [level_off[k], level_int[k]) (the first places of the sort keys)
-__global__ void k_level_offsets(int nlev, int nn, const uint32_t* __restrict__ base,
-                                uint32_t* __restrict__ level_off, uint32_t* __restrict__ level_int) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k > nlev) return;
-  level_off[k] = k < nlev ? base[2 * k] : (uint32_t)nn;
-  level_int[k] = k < nlev ? base[2 * k + 1] : (uint32_t)nn;
-}
-
 // ---- the lists of one node ------------------------------------------------------
 struct Emit {
   // internal node: M2L entries from the front of its region, opened entries
@@ -407,7 +386,7 @@ __device__ void walk_leaf(const NodeWalkArgs& a, int v, const Src& rv, const uin
 // their level (they are walked after all levels); a node over two systems
 // gets empty lists.
 __global__ __launch_bounds__(64) void k_nodewalk_internal(NodeWalkArgs a, int level, uint32_t rank0) {
-  const uint32_t beg = a.level_off[level], end = a.level_int[level];
+  const uint32_t beg = a.level_base[2 * level], end = a.level_base[2 * level + 1];
   const uint32_t b = xcd_block(blockIdx.x, gridDim.x);
   const uint32_t idx = beg + b;
   if (idx >= end) return;
@@ -629,6 +608,7 @@ __global__ void k_leaf_stats(LeafStatArgs a) {
 template <bool ENTRIES>
 __global__ __launch_bounds__(256) void k_check_lists(NodeWalkArgs a, int nn) {
   __shared__ uint64_t red[4][4];
+  if (blockIdx.x == 0 && threadIdx.x == 0) *a.items_total = a.item_off[a.nleaves];
   const uint64_t nl = (uint64_t)a.nleaves;
   const uint64_t used_m = a.leaf_base + nl * a.slot_m + (uint64_t)a.nbig * a.big_m + a.run[3];
   const uint64_t used_p = nl * a.slot_p + (uint64_t)a.nbig * a.big_p + a.run[2];
@@ -696,16 +676,6 @@ void launch_check_lists(const NodeWalkArgs& a, int nn, bool check_entries, hipSt
 void launch_leaf_stats(const LeafStatArgs& a, hipStream_t s) {
   if (a.nleaves <= 0) return;
   k_leaf_stats<<<(a.nleaves + 127) / 128, 128, 0, s>>>(a);
-}
-
-void launch_node_depth(int nn, const NodeInfo* info, int32_t* depth, uint64_t* key,
-                       hipStream_t s) {
-  k_node_depth<<<(nn + 255) / 256, 256, 0, s>>>(nn, info, depth, key);
-}
-
-void launch_level_offsets(int nlev, int nn, const uint32_t* base, uint32_t* level_off,
-                          uint32_t* level_int, hipStream_t s) {
-  k_level_offsets<<<(nlev + 1 + 255) / 256, 256, 0, s>>>(nlev, nn, base, level_off, level_int);
 }
 
 void launch_nodewalk_level(const NodeWalkArgs& a, int level, int nodes_in_level, uint32_t rank0,

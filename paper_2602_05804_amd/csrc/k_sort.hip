@@ -199,10 +199,13 @@ __global__ __launch_bounds__(SB) void k_sort_small(int n, const double* __restri
 }
 
 // ---- larger inputs --------------------------------------------------------------
-__global__ void k_clear_words(size_t n, uint32_t* __restrict__ p) {
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (size_t)gridDim.x * blockDim.x)
-    p[i] = 0u;
+__global__ void k_clear_words(size_t n, uint32_t* __restrict__ p, size_t n2,
+                              uint32_t* __restrict__ p2) {
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n + n2;
+       i += (size_t)gridDim.x * blockDim.x) {
+    if (i < n) p[i] = 0u;
+    else p2[i - n] = 0u;
+  }
 }
 
 // digit counts of NP passes from the first 8 NP bits of the keys
@@ -383,9 +386,10 @@ size_t sort_words(int64_t n, int passes) {
   return (size_t)passes * (256 + 64 + 256 * (size_t)sort_tiles(n));
 }
 
-void launch_clear_words(uint32_t* p, size_t n, hipStream_t s) {
-  if (n == 0) return;
-  k_clear_words<<<(unsigned)std::min<size_t>((n + 1023) / 1024, 2048), 256, 0, s>>>(n, p);
+void launch_clear_words(uint32_t* p, size_t n, uint32_t* p2, size_t n2, hipStream_t s) {
+  if (n + n2 == 0) return;
+  k_clear_words<<<(unsigned)std::min<size_t>((n + n2 + 1023) / 1024, 2048), 256, 0, s>>>(n, p, n2,
+                                                                                        p2);
 }
 
 void launch_keys(int n, const double* x, int nb, const double* part, uint64_t* key,
@@ -419,14 +423,14 @@ void radix_sort(int n, int passes, bool counted, uint64_t* key0, uint32_t* val0,
   }
 }
 
-void radix_pass(int n, const uint64_t* kin, const uint32_t* vin, uint64_t* kout, uint32_t* vout,
-                uint32_t* base, uint32_t* words, hipStream_t s) {
+void radix_pass(int n, bool counted, const uint64_t* kin, const uint32_t* vin, uint64_t* kout,
+                uint32_t* vout, uint32_t* base, uint32_t* words, hipStream_t s) {
   if (n <= kSortSmall && !vin) {
     k_sort_small<false><<<1, SB, 0, s>>>(n, nullptr, nullptr, nullptr, 0, nullptr, kin, 8, kout,
                                          vout, base);
     return;
   }
-  k_digit_counts<1><<<count_blocks(n), ST, 0, s>>>(n, kin, words);
+  if (!counted) k_digit_counts<1><<<count_blocks(n), ST, 0, s>>>(n, kin, words);
   pass(n, kin, vin, kout, vout, 0, words, base, words + 256, words + 320, s);
 }
 

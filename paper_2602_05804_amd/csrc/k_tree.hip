@@ -303,99 +303,136 @@ __global__ void k_assign(int n, int leaf_size, const uint32_t* __restrict__ sys,
   }
 }
 
+// leaves in order, and the leaf of every particle (a leaf begins at each flag)
 __global__ void k_leaf_fill(int n, const uint32_t* __restrict__ leaf_flag,
                             const uint32_t* __restrict__ leaf_scan,
-                            const int32_t* __restrict__ leaf_at, int32_t* __restrict__ leaf_node) {
+                            const int32_t* __restrict__ leaf_at, int32_t* __restrict__ leaf_node,
+                            int32_t* __restrict__ p_leaf) {
   int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= n) return;
-  if (leaf_flag[p]) leaf_node[leaf_scan[p]] = leaf_at[p];
+  const uint32_t f = leaf_flag[p], k = leaf_scan[p];
+  if (f) leaf_node[k] = leaf_at[p];
+  p_leaf[p] = (int32_t)(k + f) - 1;
 }
 
-__global__ void k_single_leaf(int n, NodeInfo* info, int32_t* leaf_node) {
+__global__ void k_single_leaf(int n, NodeInfo* info, int32_t* leaf_node, int32_t* p_leaf) {
   NodeInfo ni;
   ni.lo = 0; ni.cnt = n; ni.child = -1; ni.parent = -1;
   info[0] = ni;
   leaf_node[0] = 0;
+  for (int p = 0; p < n; ++p) p_leaf[p] = 0;
 }
 
-// (node_depth: every node's depth, from the level grouping)
-__global__ void k_leaf_depth(int nleaves, const int32_t* __restrict__ leaf_node,
-                             const NodeInfo* __restrict__ info,
-                             const int32_t* __restrict__ node_depth, int32_t* __restrict__ leaf_depth,
-                             int32_t* __restrict__ p_leaf, int* maxdepth) {
-  int l = blockIdx.x * blockDim.x + threadIdx.x;
-  if (l >= nleaves) return;
-  const int node = leaf_node[l];
-  const int d = node_depth[node];
-  leaf_depth[l] = d;
-  atomicMax(maxdepth, d);
-  const NodeInfo ni = info[node];
-  for (int p = ni.lo; p < ni.lo + ni.cnt; ++p) p_leaf[p] = l;
+// ---- per node, once the tree's shape is known -----------------------------------
+// Depths, the keys of the grouping by depth and their counts; the subtrees and
+// the nodes above them for the moments; the chunks of the node sizes.
+// (One launch of 8 us at 1e5 particles instead of seven of 34 us: these tables
+// are small, the launches were the cost.)
+
+// kept internal nodes in the subtree of an internal node: their numbers follow
+// the particles' order, so besides the node itself they are those of the
+// binary tree's internal nodes strictly inside its range
+__device__ __forceinline__ uint32_t kept_before(const NodeSetupArgs& a, int i) {
+  return i < a.n - 1 ? a.kept_scan[i] : a.nkept;
+}
+__device__ __forceinline__ uint32_t kept_below(const NodeSetupArgs& a, const NodeInfo& ni) {
+  return 1u + kept_before(a, ni.lo + ni.cnt - 1) - kept_before(a, ni.lo + 1);
+}
+
+constexpr int kSetupThreads = 512;
+__global__ __launch_bounds__(kSetupThreads) void k_node_setup(NodeSetupArgs a) {
+  __shared__ uint32_t hist[256];
+  __shared__ uint32_t wsum[2][kSetupThreads / 64];
+  __shared__ uint32_t sbase[2];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  if (t < 256) hist[t] = 0;
+  __syncthreads();
+  const int v = blockIdx.x * kSetupThreads + t;
+  NodeInfo ni{0, 0, -1, -1};
+  uint32_t nch = 0;
+  bool few = false;
+  if (v < a.nn) {
+    ni = a.info[v];
+    int d = 0;
+    for (int u = ni.parent; u >= 0; u = a.info[u].parent) ++d;
+    a.depth[v] = d;
+    // grouped by depth, and within a depth the internal nodes first
+    const int k = min(2 * d + (ni.child < 0 ? 1 : 0), 255);
+    a.key[v] = (uint64_t)k;
+    atomicAdd(&hist[k], 1u);
+    if (d > kMaxDepthCap) atomicMax(a.too_deep, d);
+    a.l2bits[v] = 0ull;
+    if (ni.child < 0) {
+      a.leaf_depth[a.p_leaf[ni.lo]] = d;
+    } else {
+      few = ni.cnt <= kExtentFew;
+      nch = few ? 0u : (uint32_t)((ni.cnt + kExtentChunk - 1) / kExtentChunk);
+      if (kept_below(a, ni) > a.kmax)
+        a.top[atomicAdd(a.ntop, 1u)] = (uint32_t)v | ((uint32_t)d << kSrcBits);
+      else if (ni.parent < 0 || kept_below(a, a.info[ni.parent]) > a.kmax)
+        a.roots[atomicAdd(a.nroots, 1u)] = (uint32_t)v;
+    }
+  }
+  // places of the chunks and of the nodes of few particles: one addition to
+  // each common total per block
+  const uint64_t fm = __ballot(few);
+  uint32_t incl = nch;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t u = (uint32_t)__shfl_up((int)incl, o, 64);
+    if (lane >= o) incl += u;
+  }
+  if (lane == 63) {
+    wsum[0][w] = incl;
+    wsum[1][w] = (uint32_t)__popcll(fm);
+  }
+  __syncthreads();
+  if (t < 2) {
+    uint32_t tot = 0;
+    for (int k = 0; k < kSetupThreads / 64; ++k) {
+      const uint32_t c = wsum[t][k];
+      wsum[t][k] = tot;
+      tot += c;
+    }
+    sbase[t] = tot ? atomicAdd(t == 0 ? a.nitems : a.nfew, tot) : 0u;
+  }
+  if (t < 256 && hist[t]) atomicAdd(&a.hist[t], hist[t]);
+  __syncthreads();
+  if (few)
+    a.few[sbase[1] + wsum[1][w] +
+          __builtin_amdgcn_mbcnt_hi((uint32_t)(fm >> 32),
+                                    __builtin_amdgcn_mbcnt_lo((uint32_t)fm, 0u))] = (uint32_t)v;
+  const uint32_t at = sbase[0] + wsum[0][w] + incl - nch;
+  if (nch > 0 && nch <= 4)
+    for (uint32_t c = 0; c < nch; ++c) a.items[at + c] = make_uint2((uint32_t)v, c);
+  // (the chunks of a large node by the whole wave)
+  uint64_t big = __ballot(nch > 4);
+  while (big) {
+    const int l = __ffsll((unsigned long long)big) - 1;
+    big &= big - 1;
+    const uint32_t bv = (uint32_t)__shfl(v, l, 64), bn = (uint32_t)__shfl((int)nch, l, 64);
+    const uint32_t ba = (uint32_t)__shfl((int)at, l, 64);
+    for (uint32_t c = lane; c < bn; c += 64) a.items[ba + c] = make_uint2(bv, c);
+  }
 }
 
 // ---- geometry, moments (bottom-up, one level after the other) --------------
 // A leaf sums its particles in sorted order; an internal node combines its
-// two children (children first: the deepest level comes first).
+// two children, deeper nodes first.  Three launches: all leaves; subtrees of at
+// most kmax internal nodes, a block each, level by level with a barrier
+// between levels; the nodes above them in one block, the same way.  Bound by
+// the chain of levels (loads of the children's records, a division, the
+// shifts of the moments).
+// 41 us at 1e3 particles, 51 at 1e5, 153 at 1e6; with a launch for each of the
+// larger levels and a run of the smaller ones in one block it was 92, 197, 324.
+// a node's moments, and its M2L source record (recq, may be null)
 template <int P>
-__device__ __forceinline__ void geom_node(int v, const NodeInfo* __restrict__ info,
-                                          const double* __restrict__ xs,
-                                          const double* __restrict__ ys,
-                                          const double* __restrict__ zs,
-                                          const double* __restrict__ ms,
-                                          const double* __restrict__ hs, double* rec,
-                                          double* recq) {
+__device__ __forceinline__ void store_moments(int v, const double* r, const double* Q, double* rec,
+                                              double* recq) {
   using E = Exp<P>;
-  constexpr int NQ = E::NQ;
-  constexpr int RS = rec_stride(P);
-  const NodeInfo ni = info[v];
-  double* r = rec + (int64_t)v * RS;
-  double Q[NQ];
+  double* o = rec + (int64_t)v * rec_stride(P) + 8;
 #pragma unroll
-  for (int k = 0; k < NQ; ++k) Q[k] = 0.0;
-  if (ni.child < 0) {
-    double M = 0.0, S0 = 0.0, S1 = 0.0, S2 = 0.0, hm = 0.0;
-    for (int j = ni.lo; j < ni.lo + ni.cnt; ++j) {
-      const double mj = ms[j];
-      M += mj;
-      S0 += mj * xs[j];
-      S1 += mj * ys[j];
-      S2 += mj * zs[j];
-      hm = fmax(hm, hs[j]);
-    }
-    const double s0 = S0 / M, s1 = S1 / M, s2 = S2 / M;
-    double d2max = 0.0;
-    for (int j = ni.lo; j < ni.lo + ni.cnt; ++j) {
-      const double b[3] = {xs[j] - s0, ys[j] - s1, zs[j] - s2};
-      const double d2 = b[0] * b[0] + b[1] * b[1] + b[2] * b[2];
-      d2max = fmax(d2max, d2);
-      E::p2m_add(b, ms[j], Q);
-    }
-    r[0] = s0; r[1] = s1; r[2] = s2; r[3] = sqrt(d2max); r[4] = hm; r[5] = M;
-  } else {
-    const double* rl = rec + (int64_t)ni.child * RS;
-    const double* rr = rl + RS;
-    const double ML = rl[5], MR = rr[5];
-    const double M = ML + MR;
-    double s[3];
-    for (int d = 0; d < 3; ++d) s[d] = (ML * rl[d] + MR * rr[d]) / M;
-    const double hm = fmax(rl[4], rr[4]);
-    double Qc[NQ];
-    {
-      const double g[3] = {rl[0] - s[0], rl[1] - s[1], rl[2] - s[2]};
-#pragma unroll
-      for (int k = 0; k < NQ; ++k) Qc[k] = rl[8 + k];
-      E::m2m_add(g, Qc, Q);
-    }
-    {
-      const double g[3] = {rr[0] - s[0], rr[1] - s[1], rr[2] - s[2]};
-#pragma unroll
-      for (int k = 0; k < NQ; ++k) Qc[k] = rr[8 + k];
-      E::m2m_add(g, Qc, Q);
-    }
-    r[0] = s[0]; r[1] = s[1]; r[2] = s[2]; r[4] = hm; r[5] = M;
-  }
-#pragma unroll
-  for (int k = 0; k < NQ; ++k) r[8 + k] = Q[k];
+  for (int k = 0; k < E::NQ; ++k) o[k] = Q[k];
   if (recq) {
     double* q = recq + (int64_t)v * recq_stride(P);
     double Qr[E::NQR];
@@ -406,81 +443,265 @@ __device__ __forceinline__ void geom_node(int v, const NodeInfo* __restrict__ in
   }
 }
 
-// one level, a thread per node
+// (kGeomLoads particles' loads at a time; the sums in the particles' order)
+constexpr int kGeomLoads = 4;
 template <int P>
-__global__ void k_geom_level(const int32_t* __restrict__ level_nodes, uint32_t beg, uint32_t end,
-                             const NodeInfo* __restrict__ info, const double* __restrict__ xs,
-                             const double* __restrict__ ys, const double* __restrict__ zs,
-                             const double* __restrict__ ms, const double* __restrict__ hs,
-                             double* __restrict__ rec, double* __restrict__ recq) {
-  const uint32_t idx = beg + blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= end) return;
-  geom_node<P>(level_nodes[idx], info, xs, ys, zs, ms, hs, rec, recq);
+__global__ __launch_bounds__(64) void k_geom_leaves(
+    int nleaves, const int32_t* __restrict__ leaf_node, const NodeInfo* __restrict__ info,
+    const double* __restrict__ xs, const double* __restrict__ ys, const double* __restrict__ zs,
+    const double* __restrict__ ms, const double* __restrict__ hs, double* __restrict__ rec,
+    double* __restrict__ recq) {
+  using E = Exp<P>;
+  const int l = blockIdx.x * 64 + threadIdx.x;
+  if (l >= nleaves) return;
+  const int v = leaf_node[l];
+  const NodeInfo ni = info[v];
+  double Q[E::NQ];
+#pragma unroll
+  for (int k = 0; k < E::NQ; ++k) Q[k] = 0.0;
+  const int end = ni.lo + ni.cnt;
+  double M = 0.0, S0 = 0.0, S1 = 0.0, S2 = 0.0, hm = 0.0;
+  for (int j = ni.lo; j < end; j += kGeomLoads) {
+    double m[kGeomLoads], x[kGeomLoads], y[kGeomLoads], z[kGeomLoads], h[kGeomLoads];
+#pragma unroll
+    for (int u = 0; u < kGeomLoads; ++u) {
+      const int i = min(j + u, end - 1);
+      m[u] = ms[i]; x[u] = xs[i]; y[u] = ys[i]; z[u] = zs[i]; h[u] = hs[i];
+    }
+#pragma unroll
+    for (int u = 0; u < kGeomLoads; ++u) {
+      if (j + u >= end) break;
+      M += m[u];
+      S0 += m[u] * x[u];
+      S1 += m[u] * y[u];
+      S2 += m[u] * z[u];
+      hm = fmax(hm, h[u]);
+    }
+  }
+  const double s0 = S0 / M, s1 = S1 / M, s2 = S2 / M;
+  double d2max = 0.0;
+  for (int j = ni.lo; j < end; j += kGeomLoads) {
+    double m[kGeomLoads], x[kGeomLoads], y[kGeomLoads], z[kGeomLoads];
+#pragma unroll
+    for (int u = 0; u < kGeomLoads; ++u) {
+      const int i = min(j + u, end - 1);
+      m[u] = ms[i]; x[u] = xs[i]; y[u] = ys[i]; z[u] = zs[i];
+    }
+#pragma unroll
+    for (int u = 0; u < kGeomLoads; ++u) {
+      if (j + u >= end) break;
+      const double b[3] = {x[u] - s0, y[u] - s1, z[u] - s2};
+      const double d2 = b[0] * b[0] + b[1] * b[1] + b[2] * b[2];
+      d2max = fmax(d2max, d2);
+      E::p2m_add(b, m[u], Q);
+    }
+  }
+  double* r = rec + (int64_t)v * rec_stride(P);
+  r[0] = s0; r[1] = s1; r[2] = s2; r[3] = sqrt(d2max); r[4] = hm; r[5] = M;
+  const double c[3] = {s0, s1, s2};
+  store_moments<P>(v, c, Q, rec, recq);
 }
 
-// a run of small levels, deepest first, in one block: a barrier between
-// levels makes the children's records (written by this block) visible
-constexpr int GEOM_RUN_THREADS = 512;
-constexpr uint32_t GEOM_RUN_MAX = 1024;  // nodes of a level that a run takes
 template <int P>
-__global__ __launch_bounds__(GEOM_RUN_THREADS) void k_geom_run(
-    const int32_t* __restrict__ level_nodes, const uint32_t* __restrict__ level_off, int kdeep,
-    int ktop, const NodeInfo* __restrict__ info, const double* __restrict__ xs,
-    const double* __restrict__ ys, const double* __restrict__ zs, const double* __restrict__ ms,
-    const double* __restrict__ hs, double* rec, double* recq) {
-  for (int k = kdeep; k >= ktop; --k) {
-    const uint32_t beg = level_off[k], end = level_off[k + 1];
-    for (uint32_t idx = beg + threadIdx.x; idx < end; idx += GEOM_RUN_THREADS)
-      geom_node<P>(level_nodes[idx], info, xs, ys, zs, ms, hs, rec, recq);
+__device__ __forceinline__ void geom_internal(int v, int child, double* rec, double* recq) {
+  using E = Exp<P>;
+  constexpr int NQ = E::NQ;
+  constexpr int RS = rec_stride(P);
+  double* r = rec + (int64_t)v * RS;
+  double Q[NQ];
+#pragma unroll
+  for (int k = 0; k < NQ; ++k) Q[k] = 0.0;
+  const double* rl = rec + (int64_t)child * RS;
+  const double* rr = rl + RS;
+  const double ML = rl[5], MR = rr[5];
+  const double M = ML + MR;
+  double s[3];
+  for (int d = 0; d < 3; ++d) s[d] = (ML * rl[d] + MR * rr[d]) / M;
+  const double hm = fmax(rl[4], rr[4]);
+  double Qc[NQ];
+  {
+    const double g[3] = {rl[0] - s[0], rl[1] - s[1], rl[2] - s[2]};
+#pragma unroll
+    for (int k = 0; k < NQ; ++k) Qc[k] = rl[8 + k];
+    E::m2m_add(g, Qc, Q);
+  }
+  {
+    const double g[3] = {rr[0] - s[0], rr[1] - s[1], rr[2] - s[2]};
+#pragma unroll
+    for (int k = 0; k < NQ; ++k) Qc[k] = rr[8 + k];
+    E::m2m_add(g, Qc, Q);
+  }
+  r[0] = s[0]; r[1] = s[1]; r[2] = s[2]; r[4] = hm; r[5] = M;
+  store_moments<P>(v, s, Q, rec, recq);
+}
+
+// the nodes of a list sorted by depth (off[d]: the first of depth d), deepest
+// level first; the barrier makes a level's records visible to the block.  A
+// thread's next node is read before the barrier
+template <int P>
+__device__ __forceinline__ void geom_levels(const uint32_t* lst, const uint32_t* off, int dmin,
+                                            int dmax, const NodeInfo* __restrict__ info,
+                                            double* rec, double* recq) {
+  uint32_t idx = off[dmax] + threadIdx.x;
+  int v = 0, child = 0;
+  if (idx < off[dmax + 1]) {
+    v = (int)lst[idx];
+    child = info[v].child;
+  }
+  for (int d = dmax; d >= dmin; --d) {
+    const uint32_t end = off[d + 1];
+    while (idx < end) {
+      geom_internal<P>(v, child, rec, recq);
+      idx += blockDim.x;
+      if (idx < end) {
+        v = (int)lst[idx];
+        child = info[v].child;
+      }
+    }
+    if (d > dmin) {
+      idx = off[d - 1] + threadIdx.x;
+      if (idx < off[d]) {
+        v = (int)lst[idx];
+        child = info[v].child;
+      }
+    }
     __syncthreads();
   }
 }
 
-__global__ void k_extent_count(int nn, const NodeInfo* __restrict__ info,
-                               uint32_t* __restrict__ chunks) {
-  int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= nn) return;
-  const NodeInfo ni = info[v];
-  chunks[v] = ni.child >= 0 ? (uint32_t)((ni.cnt + kExtentChunk - 1) / kExtentChunk) : 0u;
+// a list of packed nodes (id, depth above it) sorted by depth: lst gets the
+// ids, off[0 .. 128] the first of each depth; hist and off: 129 words of LDS
+template <typename Raw>
+__device__ __forceinline__ void sort_by_depth(uint32_t count, Raw raw, uint32_t* lst,
+                                              uint32_t* hist, uint32_t* off, int& dmin,
+                                              int& dmax) {
+  const uint32_t t = threadIdx.x;
+  for (uint32_t q = t; q < 129; q += blockDim.x) hist[q] = 0;
+  __syncthreads();
+  for (uint32_t q = t; q < count; q += blockDim.x) atomicAdd(&hist[raw(q) >> kSrcBits], 1u);
+  __syncthreads();
+  if (t < 64) {
+    const uint32_t a = hist[2 * t], b = hist[2 * t + 1];
+    uint32_t incl = a + b;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t u = (uint32_t)__shfl_up((int)incl, o, 64);
+      if ((int)t >= o) incl += u;
+    }
+    const uint32_t ex = incl - a - b;
+    off[2 * t] = ex;
+    off[2 * t + 1] = ex + a;
+    if (t == 63) off[128] = incl;
+    hist[2 * t] = ex;  // the places handed out below
+    hist[2 * t + 1] = ex + a;
+  }
+  __syncthreads();
+  for (uint32_t q = t; q < count; q += blockDim.x) {
+    const uint32_t p = raw(q);
+    lst[atomicAdd(&hist[p >> kSrcBits], 1u)] = p & kSrcMask;
+  }
+  __syncthreads();
+  dmin = 0;
+  while (off[dmin + 1] == 0) ++dmin;  // (count > 0)
+  dmax = dmin;
+  while (dmax < 127 && off[dmax + 1] < count) ++dmax;
 }
 
-// one wave per chunk of an internal node: largest squared distance to the
-// node's centre of mass, folded in with an integer max on the FP64 bits
-// (non-negative doubles order like their bit patterns)
-// the node of each chunk (thread per node)
-__global__ void k_extent_map(int nn, int nitems, const uint32_t* __restrict__ chunk_off,
-                             uint32_t* __restrict__ item_node) {
-  const int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= nn) return;
-  const uint32_t b = chunk_off[v], e = v + 1 < nn ? chunk_off[v + 1] : (uint32_t)nitems;
-  for (uint32_t t = b; t < e; ++t) item_node[t] = (uint32_t)v;
+constexpr int kSubThreads = 256, kTopThreads = 512;
+template <int P>
+__global__ __launch_bounds__(kSubThreads) void k_geom_subtrees(NodeSetupArgs a, double* rec,
+                                                               double* recq) {
+  __shared__ uint32_t raw[kGeomMax], lst[kGeomMax];
+  __shared__ uint32_t hist[129], off[129];
+  const uint32_t nroots = *a.nroots;
+  for (uint32_t r = blockIdx.x; r < nroots; r += gridDim.x) {
+    const NodeInfo ni = a.info[a.roots[r]];
+    const uint32_t c0 = kept_before(a, ni.lo + 1);
+    const uint32_t count = min(kept_below(a, ni), (uint32_t)kGeomMax);
+    for (uint32_t q = threadIdx.x; q < count; q += kSubThreads) {
+      // number c: the children of that internal node are 1 + 2c and 2 + 2c
+      const uint32_t child = q == 0 ? (uint32_t)ni.child : 1u + 2u * (c0 + q - 1u);
+      const uint32_t v = (uint32_t)a.info[child].parent;
+      raw[q] = v | ((uint32_t)a.depth[v] << kSrcBits);
+    }
+    __syncthreads();
+    int dmin, dmax;
+    sort_by_depth(count, [&](uint32_t q) { return raw[q]; }, lst, hist, off, dmin, dmax);
+    geom_levels<P>(lst, off, dmin, dmax, a.info, rec, recq);
+  }
 }
 
+template <int P>
+__global__ __launch_bounds__(kTopThreads) void k_geom_top(NodeSetupArgs a, double* rec,
+                                                          double* recq) {
+  __shared__ uint32_t hist[129], off[129];
+  const uint32_t count = *a.ntop;
+  if (count == 0) return;
+  int dmin, dmax;
+  sort_by_depth(count, [&](uint32_t q) { return a.top[q]; }, a.top_sorted, hist, off, dmin, dmax);
+  geom_levels<P>(a.top_sorted, off, dmin, dmax, a.info, rec, recq);
+}
+
+// The largest squared distance of a node's particles to its centre of mass:
+// chunks of the larger nodes by a wave each, folded with an integer max on the
+// FP64 bits (non-negative doubles order like their bit patterns), then the
+// nodes of few particles by 16 lanes each (at 1e6 particles a wave for every
+// node took 67 us, 16 lanes for every chunk 100: lanes that wait for the others)
 template <int RS>
-__global__ __launch_bounds__(256) void k_extent(int nn, int nitems, const NodeInfo* __restrict__ info,
-                                                const uint32_t* __restrict__ chunk_off,
-                                                const uint32_t* __restrict__ item_node,
-                                                const double* __restrict__ xs,
+__global__ __launch_bounds__(256) void k_extent(NodeSetupArgs a, const double* __restrict__ xs,
                                                 const double* __restrict__ ys,
                                                 const double* __restrict__ zs,
-                                                const double* __restrict__ rec,
-                                                unsigned long long* l2bits) {
-  const int item = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (item >= nitems) return;
-  const int v = (int)item_node[item];
-  const NodeInfo ni = info[v];
-  const int c = item - (int)chunk_off[v];
-  const int beg = ni.lo + c * kExtentChunk;
-  const int end = min(ni.lo + ni.cnt, beg + kExtentChunk);
-  const double s0 = rec[(int64_t)v * RS], s1 = rec[(int64_t)v * RS + 1], s2 = rec[(int64_t)v * RS + 2];
-  double d2max = 0.0;
-  for (int j = beg + lane; j < end; j += 64) {
-    const double dx = xs[j] - s0, dy = ys[j] - s1, dz = zs[j] - s2;
-    d2max = fmax(d2max, dx * dx + dy * dy + dz * dz);
+                                                const double* __restrict__ rec) {
+  const uint32_t nitems = *a.nitems, nfew = *a.nfew;
+  for (uint32_t i = blockIdx.x * 4 + (threadIdx.x >> 6); i < nitems; i += gridDim.x * 4) {
+    const int lane = threadIdx.x & 63;
+    const uint2 it = a.items[i];
+    const NodeInfo ni = a.info[it.x];
+    const int beg = ni.lo + (int)it.y * kExtentChunk;
+    const int end = min(ni.lo + ni.cnt, beg + kExtentChunk);
+    const double* r = rec + (int64_t)it.x * RS;
+    const double s0 = r[0], s1 = r[1], s2 = r[2];
+    double d2max = 0.0;
+    // four loads in flight (the last particle again past the end)
+    for (int j = beg; j < end; j += 256) {
+      double x[4], y[4], z[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int k = min(j + 64 * u + lane, end - 1);
+        x[u] = xs[k]; y[u] = ys[k]; z[u] = zs[k];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const double dx = x[u] - s0, dy = y[u] - s1, dz = z[u] - s2;
+        d2max = fmax(d2max, dx * dx + dy * dy + dz * dz);
+      }
+    }
+    d2max = wave_max(d2max);
+    if (lane == 0) {
+      const auto bits = (unsigned long long)__double_as_longlong(d2max);
+      auto* to = reinterpret_cast<unsigned long long*>(a.l2bits) + it.x;
+      if (ni.cnt <= kExtentChunk) *to = bits;
+      else atomicMax(to, bits);
+    }
   }
-  d2max = wave_max(d2max);
-  if (lane == 0) atomicMax(&l2bits[v], (unsigned long long)__double_as_longlong(d2max));
+  for (uint32_t i = blockIdx.x * 16 + (threadIdx.x >> 4); i < nfew; i += gridDim.x * 16) {
+    const int lane = threadIdx.x & 15;
+    const uint32_t v = a.few[i];
+    const NodeInfo ni = a.info[v];
+    const int end = ni.lo + ni.cnt;
+    const double* r = rec + (int64_t)v * RS;
+    const double s0 = r[0], s1 = r[1], s2 = r[2];
+    double d2max = 0.0;
+#pragma unroll
+    for (int u = 0; u < kExtentFew / 16; ++u) {
+      const int k = min(ni.lo + 16 * u + lane, end - 1);
+      const double dx = xs[k] - s0, dy = ys[k] - s1, dz = zs[k] - s2;
+      d2max = fmax(d2max, dx * dx + dy * dy + dz * dz);
+    }
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) d2max = fmax(d2max, __shfl_xor(d2max, o, 16));
+    if (lane == 0) a.l2bits[v] = (uint64_t)__double_as_longlong(d2max);
+  }
 }
 
 // sizes of the internal nodes, and what the level walk reads of every node
@@ -575,86 +796,53 @@ void launch_assign(int n, int leaf_size, const uint32_t* sys, const int32_t* kfi
 }
 
 void launch_leaf_fill(int n, const uint32_t* leaf_flag, const uint32_t* leaf_scan,
-                      const int32_t* leaf_at, int32_t* leaf_node, hipStream_t s) {
-  k_leaf_fill<<<blocks_for(n, 256), 256, 0, s>>>(n, leaf_flag, leaf_scan, leaf_at, leaf_node);
+                      const int32_t* leaf_at, int32_t* leaf_node, int32_t* p_leaf,
+                      hipStream_t s) {
+  k_leaf_fill<<<blocks_for(n, 256), 256, 0, s>>>(n, leaf_flag, leaf_scan, leaf_at, leaf_node,
+                                                 p_leaf);
 }
 
-void launch_single_leaf(int n, NodeInfo* info, int32_t* leaf_node, hipStream_t s) {
-  k_single_leaf<<<1, 1, 0, s>>>(n, info, leaf_node);
+void launch_single_leaf(int n, NodeInfo* info, int32_t* leaf_node, int32_t* p_leaf,
+                        hipStream_t s) {
+  k_single_leaf<<<1, 1, 0, s>>>(n, info, leaf_node, p_leaf);
 }
 
-void launch_leaf_depth(int nleaves, const int32_t* leaf_node, const NodeInfo* info,
-                       const int32_t* node_depth, int32_t* leaf_depth, int32_t* p_leaf,
-                       int* maxdepth, hipStream_t s) {
-  k_leaf_depth<<<blocks_for(nleaves, 256), 256, 0, s>>>(nleaves, leaf_node, info, node_depth,
-                                                        leaf_depth, p_leaf, maxdepth);
+// a block's share: 512 nodes (10 levels, two rounds of its threads on the
+// deepest), or more so that a level has at most 256 nodes above the subtrees,
+// which are one block's work
+uint32_t geom_kmax(uint32_t nkept) {
+  return std::min<uint32_t>(kGeomMax, std::max<uint32_t>(512, (nkept + 255) / 256));
 }
 
-template <int P>
-void geometry_order(int maxdepth, const uint32_t* off_h, const uint32_t* off_d,
-                    const int32_t* level_nodes, const NodeInfo* info, const double* xs,
-                    const double* ys, const double* zs, const double* ms, const double* hs,
-                    double* rec, double* recq, hipStream_t s) {
-  // runs of four or more consecutive levels of at most GEOM_RUN_MAX nodes
-  // (the top of the tree) go to one block, the others one launch each
-  int k = maxdepth;
-  while (k >= 0) {
-    const uint32_t size = off_h[k + 1] - off_h[k];
-    if (size <= GEOM_RUN_MAX) {
-      int top = k;
-      while (top - 1 >= 0 && off_h[top] - off_h[top - 1] <= GEOM_RUN_MAX) --top;
-      // (a run pays off from four levels on: one level in the block takes
-      // about two thirds of a launch of its own)
-      if (k - top >= 3) {
-        k_geom_run<P><<<1, GEOM_RUN_THREADS, 0, s>>>(level_nodes, off_d, k, top, info, xs, ys,
-                                                     zs, ms, hs, rec, recq);
-        k = top - 1;
-        continue;
-      }
-    }
-    if (size > 0)
-      k_geom_level<P><<<blocks_for(size, 128), 128, 0, s>>>(level_nodes, off_h[k], off_h[k + 1],
-                                                             info, xs, ys, zs, ms, hs, rec, recq);
-    --k;
-  }
+size_t extent_items(int n, uint32_t nkept) {
+  return (size_t)nkept + (size_t)n * (kMaxDepthCap + 1) / kExtentChunk + 1;
 }
 
-void launch_geometry(int order, int maxdepth, const uint32_t* level_off_host,
-                     const uint32_t* level_off_dev, const int32_t* level_nodes,
-                     const NodeInfo* info, const double* xs, const double* ys, const double* zs,
-                     const double* ms, const double* hs, double* rec, double* recq,
-                     hipStream_t s) {
+void launch_node_setup(const NodeSetupArgs& a, hipStream_t s) {
+  k_node_setup<<<blocks_for(a.nn, kSetupThreads), kSetupThreads, 0, s>>>(a);
+}
+
+void launch_geometry(int order, const NodeSetupArgs& a, int nleaves, const int32_t* leaf_node,
+                     const double* xs, const double* ys, const double* zs, const double* ms,
+                     const double* hs, double* rec, double* recq, hipStream_t s) {
+  // (the numbers of subtrees and chunks are known on the device only: grids
+  // that fill the chip take them in turn)
+  const unsigned nsub = std::min<unsigned>(a.nkept, 1024);
+  const unsigned next = (unsigned)std::min<uint32_t>((a.nkept + 3) / 4, 4096);
   switch (order) {
-#define GEOM_CASE(P)                                                                         \
-  case P:                                                                                    \
-    geometry_order<P>(maxdepth, level_off_host, level_off_dev, level_nodes, info, xs, ys, zs, \
-                      ms, hs, rec, recq, s);                                                 \
+#define GEOM_CASE(P)                                                                             \
+  case P:                                                                                        \
+    k_geom_leaves<P><<<blocks_for(nleaves, 64), 64, 0, s>>>(nleaves, leaf_node, a.info, xs, ys,  \
+                                                            zs, ms, hs, rec, recq);              \
+    if (a.nkept > 0) {                                                                           \
+      k_geom_subtrees<P><<<nsub, kSubThreads, 0, s>>>(a, rec, recq);                             \
+      if (a.nkept > a.kmax) k_geom_top<P><<<1, kTopThreads, 0, s>>>(a, rec, recq);               \
+      k_extent<rec_stride(P)><<<next, 256, 0, s>>>(a, xs, ys, zs, rec);                          \
+    }                                                                                            \
     break;
     GEOM_CASE(0) GEOM_CASE(1) GEOM_CASE(2) GEOM_CASE(3) GEOM_CASE(4)
 #undef GEOM_CASE
   }
-}
-
-void launch_extent_count(int nn, const NodeInfo* info, uint32_t* chunks, hipStream_t s) {
-  k_extent_count<<<blocks_for(nn, 256), 256, 0, s>>>(nn, info, chunks);
-}
-
-void launch_extent(int order, int nn, int nitems, const NodeInfo* info,
-                   const uint32_t* chunk_off, uint32_t* item_node, const double* xs,
-                   const double* ys, const double* zs, double* rec, unsigned long long* l2bits,
-                   hipStream_t s) {
-  if (nitems <= 0) return;
-  k_extent_map<<<blocks_for(nn, 256), 256, 0, s>>>(nn, nitems, chunk_off, item_node);
-  const unsigned nb = blocks_for(nitems, 4);
-#define SFMM_EXTENT(RS) \
-  k_extent<RS><<<nb, 256, 0, s>>>(nn, nitems, info, chunk_off, item_node, xs, ys, zs, rec, l2bits)
-  switch (rec_stride(order)) {
-    case 16: SFMM_EXTENT(16); break;
-    case 24: SFMM_EXTENT(24); break;
-    case 32: SFMM_EXTENT(32); break;
-    case 48: SFMM_EXTENT(48); break;
-  }
-#undef SFMM_EXTENT
 }
 
 void launch_extent_final(int order, int nn, const NodeInfo* info,

@@ -3,6 +3,7 @@
 #include <algorithm>
 #include <chrono>
 #include <cmath>
+#include <cstddef>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -25,17 +26,17 @@ struct DevBuf {
 
 // every device buffer of a context, grown on demand and reused
 enum BufId {
-  B_BOXPART, B_STATUS, B_SMALL,
+  B_BOXPART, B_STATUS, B_SMALL, B_GEOLIST,
   B_KEY0, B_KEY1, B_VAL0, B_VAL1, B_SORT, B_BASE, B_SCANTMP,
   B_XS, B_YS, B_ZS, B_MS, B_HS, B_HIS, B_H4, B_P4,
   B_KFIRST, B_KLAST, B_KLEFT, B_KRIGHT, B_KPAR, B_KSIDE, B_KEPT,
-  B_LFLAG, B_LAT, B_INFO, B_REC, B_WREC, B_RECQ, B_L2BITS, B_CHUNK,
+  B_LAT, B_INFO, B_REC, B_WREC, B_RECQ, B_L2BITS,
   B_LEAFNODE, B_LEAFDEPTH, B_PLEAF,
   B_LDOFF, B_DEPTHCNT, B_M2LCNT, B_P2PCNT, B_PAIRCNT, B_M2L, B_P2P,
   B_FAR, B_MOMPART, B_MOM, B_L2LCNT,
-  B_NDEPTH, B_LEVKEY0, B_LEVKEY1, B_LEVIDS, B_LEVOFF, B_LEVNODES, B_LEVINT, B_M2LORD,
+  B_NDEPTH, B_LEVKEY0, B_LEVKEY1, B_LEVIDS, B_LEVNODES, B_M2LORD,
   B_NM2LOFF, B_NM2LCNT, B_NOPENOFF, B_NOPENCNT, B_NP2POFF, B_NP2PCNT,
-  B_M2LPOOL, B_NEXP, B_P2PPOOL, B_WALKTOT,
+  B_M2LPOOL, B_NEXP, B_P2PPOOL,
   B_REC32, B_PF32, B_PH32,
   B_SYSOFF, B_BOXES, B_SYS, B_SYSS, B_SYSSTART, B_SKEY0, B_SKEY1, B_SPOS0, B_SPOS1, B_NFLAG,
   B_LN, B_ITEMCNT, B_ITEMOFF, B_ITEM, B_PART, B_SRCTOT, B_SOFTCNT, B_EXTMAP,
@@ -44,21 +45,20 @@ enum BufId {
 };
 
 // small device scalars (B_SMALL, u64 slots)
-enum SmallId { S_NKEPT = 0, S_NLEAVES, S_MAXDEPTH, S_NITEMS, S_M2LTOT, S_P2PTOT, S_PAIRTOT,
+enum SmallId { S_NKEPT = 0, S_NLEAVES, S_TOODEEP, S_NITEMS, S_NFEW, S_NROOTS, S_NTOP, S_M2LTOT, S_P2PTOT, S_PAIRTOT,
                S_DOFFTOT, S_L2LTOT, S_SOFTTOT, S_COUNT };
 
 }  // namespace
 
-// The small device values each synchronisation of a solve reads back, in one
-// pinned host block per context: the copies are then plain asynchronous
-// transfers instead of staged copies into pageable memory.
+// The small device values each synchronisation of a solve reads back: one
+// device block (B_SMALL) and its copy in pinned host memory, one per context,
+// so that a synchronisation is one plain asynchronous transfer.
 struct Readback {
   uint64_t small[S_COUNT];
+  uint32_t level_base[256];  // first places of the keys 2 depth + leaf
   int status[4];
-  uint32_t level_off[kMaxDepthCap + 2];
-  uint32_t level_int[kMaxDepthCap + 2];
   uint64_t walk_tot[11 + kXcds];
-  uint32_t items;
+  uint32_t items, unused;
 };
 
 struct sfmm_ctx {
@@ -80,8 +80,9 @@ struct sfmm_ctx {
   bool timing = false;
   hipEvent_t order_ev = nullptr;  // orders work across a stream change
   // level walk: nodes per depth (host copy) and pool capacities
-  std::vector<uint32_t> level_off;
-  std::vector<uint32_t> level_int;  // end of each level's internal nodes
+  uint32_t level_base[257] = {};  // first node of each key 2 depth + leaf, then nn
+  bool walk_clear = false;        // the walk's totals and status are zero (a new build)
+  hipEvent_t tree_event = nullptr;
   uint64_t m2l_cap = 0, p2p_cap = 0;
   size_t words_m2l = 0;  // sort scratch of the M2L order: place in B_SORT (cleared by the build)
   int64_t soft_items = 0;       // items whose softened pairs the last solve counted
@@ -139,8 +140,19 @@ hipError_t wait_stream(hipStream_t s) {
   }
 }
 
-// the context's pinned read-back block (allocated on first use; null when
-// the allocation fails)
+hipError_t wait_event(hipEvent_t ev) {
+  const auto t0 = std::chrono::steady_clock::now();
+  for (;;) {
+    const hipError_t e = hipEventQuery(ev);
+    if (e != hipErrorNotReady) return e;
+    if (std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(2))
+      return hipEventSynchronize(ev);
+  }
+}
+
+// the context's pinned read-back block, with the event of the read-back that
+// the host does not wait for at once (made on first use; null when that
+// fails)
 Readback* readback(sfmm_ctx* ctx) {
   if (!ctx->rb) {
     void* p = nullptr;
@@ -149,6 +161,12 @@ Readback* readback(sfmm_ctx* ctx) {
       return nullptr;
     }
     ctx->rb = static_cast<Readback*>(p);
+  }
+  if (!ctx->tree_event &&
+      hipEventCreateWithFlags(&ctx->tree_event, hipEventDisableTiming) != hipSuccess) {
+    (void)hipGetLastError();
+    ctx->tree_event = nullptr;
+    return nullptr;
   }
   return ctx->rb;
 }
@@ -237,11 +255,12 @@ int do_build(sfmm_ctx* ctx, int64_t n64, const double* x, const double* m, const
   // ---- workspace
   struct { int id; size_t bytes; } need[] = {
       {B_BOXPART, sizeof(double) * 6 * bbox_blocks(n)},
-      {B_STATUS, sizeof(int) * 4}, {B_SMALL, sizeof(uint64_t) * S_COUNT},
+      {B_SMALL, sizeof(Readback)},
       {B_KEY0, sizeof(uint64_t) * n}, {B_KEY1, sizeof(uint64_t) * n},
       {B_VAL0, sizeof(uint32_t) * n}, {B_VAL1, sizeof(uint32_t) * n},
-      {B_SORT, sizeof(uint32_t) * (sort_words(n, 8 + sys_passes) + 2 * sort_words(nmax_nodes, 1))},
-      {B_BASE, sizeof(uint32_t) * 512},
+      {B_SORT, sizeof(uint32_t) * (sort_words(n, 8 + sys_passes) + 2 * sort_words(nmax_nodes, 1) +
+                                   (size_t)n + 1)},
+      {B_BASE, sizeof(uint32_t) * 256},
       {B_SCANTMP, sizeof(uint64_t) * scan_tmp_elems(2 * (int64_t)n + 2)},
       {B_XS, sizeof(double) * n}, {B_YS, sizeof(double) * n}, {B_ZS, sizeof(double) * n},
       {B_MS, sizeof(double) * n}, {B_HS, sizeof(double) * n}, {B_HIS, sizeof(double) * n},
@@ -250,34 +269,36 @@ int do_build(sfmm_ctx* ctx, int64_t n64, const double* x, const double* m, const
       {B_KLEFT, sizeof(int32_t) * n}, {B_KRIGHT, sizeof(int32_t) * n},
       {B_KPAR, sizeof(int32_t) * n}, {B_KSIDE, sizeof(int32_t) * n},
       {B_KEPT, sizeof(uint32_t) * (n + 1)},
-      {B_LFLAG, sizeof(uint32_t) * (n + 1)}, {B_LAT, sizeof(int32_t) * n},
+      {B_LAT, sizeof(int32_t) * n},
       {B_INFO, sizeof(NodeInfo) * nmax_nodes}, {B_REC, sizeof(double) * RS * (size_t)nmax_nodes},
       {B_L2BITS, sizeof(uint64_t) * nmax_nodes},
-      {B_CHUNK, sizeof(uint32_t) * (nmax_nodes + 1)},
       {B_LEAFNODE, sizeof(int32_t) * n}, {B_LEAFDEPTH, sizeof(int32_t) * n},
       {B_PLEAF, sizeof(int32_t) * n},
   };
   for (auto& q : need)
     if ((rc = ensure(ctx, q.id, q.bytes))) return rc;
-  int* status = P<int>(ctx, B_STATUS);
-  uint64_t* small = P<uint64_t>(ctx, B_SMALL);
+  Readback* dev = P<Readback>(ctx, B_SMALL);
+  int* status = dev->status;
+  uint64_t* small = dev->small;
   // (the shared far field reads its sources from records of their own)
   const bool recq = ctx->cfg.far_mode == SFMM_FAR_SHARED && ctx->cfg.walk_mode == SFMM_WALK_LEVEL;
   if (recq && (rc = ensure(ctx, B_RECQ, sizeof(double) * recq_stride(order) * (size_t)nmax_nodes)))
     return rc;
   phase_mark(ctx, 0, 0);
-  HIPCHK(hipMemsetAsync(status, 0, sizeof(int) * 4, s));
-  HIPCHK(hipMemsetAsync(small, 0, sizeof(uint64_t) * S_COUNT, s));
   // ---- keys, sort, gather
   const uint32_t* sys_sorted = nullptr;
   const int32_t* sys_start = nullptr;
-  // scratch of the sorts: of the particles (by key, by system), then of the
-  // nodes by depth and by list length, cleared in one go
+  // cleared in one go: scratch of the sorts (of the particles by key and by
+  // system, of the nodes by depth and by list length), the leaf flags, and the
+  // block of small values
   uint32_t* words = P<uint32_t>(ctx, B_SORT);
   uint32_t* words_sys = words + sort_words(n, 8);
   uint32_t* words_depth = words_sys + (sys_passes ? sort_words(n, sys_passes) : 0);
   ctx->words_m2l = (size_t)(words_depth - words) + sort_words(nmax_nodes, 1);
-  launch_clear_words(words, ctx->words_m2l + sort_words(nmax_nodes, 1), s);
+  uint32_t* leaf_flag = words + ctx->words_m2l + sort_words(nmax_nodes, 1);
+  launch_clear_words(words, (size_t)(leaf_flag - words) + (size_t)n + 1,
+                     reinterpret_cast<uint32_t*>(dev), sizeof(Readback) / sizeof(uint32_t), s);
+  ctx->walk_clear = true;
   if (small_n) {
     launch_small_sort(n, x, m, h, ctx->cfg.check_inputs, status, P<uint64_t>(ctx, B_KEY0),
                       P<uint32_t>(ctx, B_VAL0), s);
@@ -334,7 +355,7 @@ int do_build(sfmm_ctx* ctx, int64_t n64, const double* x, const double* m, const
   int32_t* leaf_node = P<int32_t>(ctx, B_LEAFNODE);
   // ---- topology
   if (n <= leaf_size && nsys <= 1) {
-    launch_single_leaf(n, info, leaf_node, s);
+    launch_single_leaf(n, info, leaf_node, P<int32_t>(ctx, B_PLEAF), s);
   } else {
     launch_karras(n, key, sys_sorted, sys_start, leaf_size, P<int32_t>(ctx, B_KFIRST), P<int32_t>(ctx, B_KLAST),
                   P<int32_t>(ctx, B_KLEFT), P<int32_t>(ctx, B_KRIGHT), P<int32_t>(ctx, B_KPAR),
@@ -342,23 +363,22 @@ int do_build(sfmm_ctx* ctx, int64_t n64, const double* x, const double* m, const
     uint32_t* cidx = P<uint32_t>(ctx, B_KEPT);
     scan_u32(cidx, cidx, n - 1, reinterpret_cast<uint32_t*>(small + S_NKEPT),
              P<uint32_t>(ctx, B_SCANTMP), s);
-    HIPCHK(hipMemsetAsync(P<uint32_t>(ctx, B_LFLAG), 0, sizeof(uint32_t) * (n + 1), s));
     launch_assign(n, leaf_size, sys_sorted, P<int32_t>(ctx, B_KFIRST), P<int32_t>(ctx, B_KLAST),
                   P<int32_t>(ctx, B_KLEFT), P<int32_t>(ctx, B_KRIGHT), P<int32_t>(ctx, B_KPAR),
-                  P<int32_t>(ctx, B_KSIDE), cidx, info, P<uint32_t>(ctx, B_LFLAG),
+                  P<int32_t>(ctx, B_KSIDE), cidx, info, leaf_flag,
                   P<int32_t>(ctx, B_LAT), s);
     // leaf_flag -> leaf index (scan into KFIRST's storage, no longer needed)
     uint32_t* lscan = reinterpret_cast<uint32_t*>(P<int32_t>(ctx, B_KFIRST));
-    scan_u32(P<uint32_t>(ctx, B_LFLAG), lscan, n, reinterpret_cast<uint32_t*>(small + S_NLEAVES),
+    scan_u32(leaf_flag, lscan, n, reinterpret_cast<uint32_t*>(small + S_NLEAVES),
              P<uint32_t>(ctx, B_SCANTMP), s);
-    launch_leaf_fill(n, P<uint32_t>(ctx, B_LFLAG), lscan, P<int32_t>(ctx, B_LAT), leaf_node, s);
+    launch_leaf_fill(n, leaf_flag, lscan, P<int32_t>(ctx, B_LAT), leaf_node,
+                     P<int32_t>(ctx, B_PLEAF), s);
   }
   // ---- sizes to the host (one synchronisation)
   Readback* hb = readback(ctx);
   if (!hb) return fail(ctx, SFMM_ENOMEM, "pinned host block for read-backs");
   const uint64_t* hsmall = hb->small;
-  HIPCHK(hipMemcpyAsync(hb->small, small, sizeof(hb->small), hipMemcpyDeviceToHost, s));
-  HIPCHK(hipMemcpyAsync(hb->status, status, sizeof(hb->status), hipMemcpyDeviceToHost, s));
+  HIPCHK(hipMemcpyAsync(hb, dev, sizeof(Readback), hipMemcpyDeviceToHost, s));
   HIPCHK(wait_stream(s));
   if (hb->status[0] & ST_NONFINITE)
     return fail(ctx, SFMM_ENONFINITE, "non-finite position or non-positive m/h");
@@ -374,65 +394,64 @@ int do_build(sfmm_ctx* ctx, int64_t n64, const double* x, const double* m, const
   if (ctx->nn > (int64_t)kSrcMask + 1)
     return fail(ctx, SFMM_EUNSUPPORTED, "tree has more than 2^25 nodes");
   const int nn = (int)ctx->nn, nl = (int)ctx->nleaves;
-  // node depths and nodes grouped by depth (level walk): one stable radix
-  // pass on the depth
-  {
-    struct { int id; size_t bytes; } need2[] = {
-        {B_NDEPTH, sizeof(int32_t) * nn}, {B_LEVNODES, sizeof(uint32_t) * nn},
-        {B_LEVKEY0, sizeof(uint64_t) * nn}, {B_LEVKEY1, sizeof(uint64_t) * nn},
-        {B_LEVIDS, sizeof(uint32_t) * nn}, {B_LEVOFF, sizeof(uint32_t) * (kMaxDepthCap + 2)},
-        {B_LEVINT, sizeof(uint32_t) * (kMaxDepthCap + 2)}, {B_WREC, walk_rec_bytes(nn)}};
-    for (auto& q : need2)
-      if ((rc = ensure(ctx, q.id, q.bytes))) return rc;
-    launch_node_depth(nn, info, P<int32_t>(ctx, B_NDEPTH), P<uint64_t>(ctx, B_LEVKEY0), s);
-    radix_pass(nn, P<uint64_t>(ctx, B_LEVKEY0), nullptr, P<uint64_t>(ctx, B_LEVKEY1),
-               P<uint32_t>(ctx, B_LEVNODES), P<uint32_t>(ctx, B_BASE), words_depth, s);
-    launch_level_offsets(kMaxDepthCap + 1, nn, P<uint32_t>(ctx, B_BASE),
-                         P<uint32_t>(ctx, B_LEVOFF), P<uint32_t>(ctx, B_LEVINT), s);
-  }
+  // node depths, nodes grouped by depth (level walk): one stable radix pass
+  const uint32_t nkept = (uint32_t)(nn / 2);
+  struct { int id; size_t bytes; } need2[] = {
+      {B_NDEPTH, sizeof(int32_t) * nn}, {B_LEVNODES, sizeof(uint32_t) * nn},
+      {B_LEVKEY0, sizeof(uint64_t) * nn}, {B_LEVKEY1, sizeof(uint64_t) * nn},
+      {B_LEVIDS, sizeof(uint32_t) * nn}, {B_WREC, walk_rec_bytes(nn)},
+      {B_GEOLIST, sizeof(uint32_t) * (4 * (size_t)nkept + 1)},
+      {B_EXTMAP, sizeof(uint2) * extent_items(n, nkept)}};
+  for (auto& q : need2)
+    if ((rc = ensure(ctx, q.id, q.bytes))) return rc;
+  NodeSetupArgs ns{};
+  ns.nn = nn;
+  ns.n = n;
+  ns.nkept = nkept;
+  ns.kmax = geom_kmax(nkept);
+  ns.info = info;
+  ns.kept_scan = P<uint32_t>(ctx, B_KEPT);
+  ns.p_leaf = P<int32_t>(ctx, B_PLEAF);
+  ns.depth = P<int32_t>(ctx, B_NDEPTH);
+  ns.leaf_depth = P<int32_t>(ctx, B_LEAFDEPTH);
+  ns.key = P<uint64_t>(ctx, B_LEVKEY0);
+  ns.hist = words_depth;
+  ns.l2bits = P<uint64_t>(ctx, B_L2BITS);
+  ns.roots = P<uint32_t>(ctx, B_GEOLIST);
+  ns.top = ns.roots + nkept;
+  ns.top_sorted = ns.top + nkept;
+  ns.few = ns.top_sorted + nkept;
+  ns.items = P<uint2>(ctx, B_EXTMAP);
+  ns.nroots = reinterpret_cast<uint32_t*>(small + S_NROOTS);
+  ns.ntop = reinterpret_cast<uint32_t*>(small + S_NTOP);
+  ns.nitems = reinterpret_cast<uint32_t*>(small + S_NITEMS);
+  ns.nfew = reinterpret_cast<uint32_t*>(small + S_NFEW);
+  ns.too_deep = reinterpret_cast<int*>(small + S_TOODEEP);
+  launch_node_setup(ns, s);
+  radix_pass(nn, true, P<uint64_t>(ctx, B_LEVKEY0), nullptr, P<uint64_t>(ctx, B_LEVKEY1),
+             P<uint32_t>(ctx, B_LEVNODES), dev->level_base, words_depth, s);
   if (nsys > 1) {
     if ((rc = ensure(ctx, B_NFLAG, sizeof(uint8_t) * nn))) return rc;
     launch_node_flags(nn, info, sys_sorted, P<uint8_t>(ctx, B_NFLAG), s);
   }
-  int* maxd_dev = reinterpret_cast<int*>(small + S_MAXDEPTH);
-  launch_leaf_depth(nl, leaf_node, info, P<int32_t>(ctx, B_NDEPTH), P<int32_t>(ctx, B_LEAFDEPTH),
-                    P<int32_t>(ctx, B_PLEAF), maxd_dev, s);
-  if (nn > 1) {
-    uint32_t* chunk = P<uint32_t>(ctx, B_CHUNK);
-    launch_extent_count(nn, info, chunk, s);
-    scan_u32(chunk, chunk, nn, reinterpret_cast<uint32_t*>(small + S_NITEMS),
-             P<uint32_t>(ctx, B_SCANTMP), s);
-    HIPCHK(hipMemsetAsync(P<uint64_t>(ctx, B_L2BITS), 0, sizeof(uint64_t) * nn, s));
-  }
-  HIPCHK(hipMemcpyAsync(hb->small, small, sizeof(hb->small), hipMemcpyDeviceToHost, s));
-  HIPCHK(hipMemcpyAsync(hb->level_off, P<uint32_t>(ctx, B_LEVOFF), sizeof(hb->level_off),
-                        hipMemcpyDeviceToHost, s));
-  HIPCHK(hipMemcpyAsync(hb->level_int, P<uint32_t>(ctx, B_LEVINT), sizeof(hb->level_int),
-                        hipMemcpyDeviceToHost, s));
-  HIPCHK(wait_stream(s));
-  ctx->level_off.assign(hb->level_off, hb->level_off + kMaxDepthCap + 2);
-  ctx->level_int.assign(hb->level_int, hb->level_int + kMaxDepthCap + 2);
-  ctx->maxdepth = (int)(hsmall[S_MAXDEPTH] & 0x7fffffff);
-  if (ctx->maxdepth > kMaxDepthCap) return fail(ctx, SFMM_EUNSUPPORTED, "tree deeper than 127");
-  // ---- geometry and moments, level by level from the deepest
-  launch_geometry(order, ctx->maxdepth, ctx->level_off.data(), P<uint32_t>(ctx, B_LEVOFF),
-                  reinterpret_cast<const int32_t*>(P<uint32_t>(ctx, B_LEVNODES)), info,
-                  P<double>(ctx, B_XS), P<double>(ctx, B_YS), P<double>(ctx, B_ZS),
-                  P<double>(ctx, B_MS), P<double>(ctx, B_HS), P<double>(ctx, B_REC),
-                  recq ? P<double>(ctx, B_RECQ) : nullptr, s);
-  if (nn > 1) {
-    const int nitems = (int)(hsmall[S_NITEMS] & 0xffffffffu);
-    if ((rc = ensure(ctx, B_EXTMAP, sizeof(uint32_t) * (size_t)std::max(nitems, 1)))) return rc;
-    launch_extent(order, nn, nitems, info, P<uint32_t>(ctx, B_CHUNK), P<uint32_t>(ctx, B_EXTMAP),
-                  P<double>(ctx, B_XS),
-                  P<double>(ctx, B_YS), P<double>(ctx, B_ZS), P<double>(ctx, B_REC),
-                  reinterpret_cast<unsigned long long*>(P<uint64_t>(ctx, B_L2BITS)), s);
-  }
+  // the levels' sizes to the host, which waits for them only once the geometry
+  // is queued
+  HIPCHK(hipMemcpyAsync(hb, dev, sizeof(Readback), hipMemcpyDeviceToHost, s));
+  HIPCHK(hipEventRecord(ctx->tree_event, s));
+  launch_geometry(order, ns, nl, leaf_node, P<double>(ctx, B_XS), P<double>(ctx, B_YS),
+                  P<double>(ctx, B_ZS), P<double>(ctx, B_MS), P<double>(ctx, B_HS),
+                  P<double>(ctx, B_REC), recq ? P<double>(ctx, B_RECQ) : nullptr, s);
   launch_extent_final(order, nn, info,
                       reinterpret_cast<unsigned long long*>(P<uint64_t>(ctx, B_L2BITS)),
                       P<double>(ctx, B_REC), walk_rec(P<WalkRec>(ctx, B_WREC)), s);
   phase_mark(ctx, 0, 1);
   HIPCHK(hipGetLastError());
+  HIPCHK(wait_event(ctx->tree_event));
+  if (hsmall[S_TOODEEP] != 0) return fail(ctx, SFMM_EUNSUPPORTED, "tree deeper than 127");
+  std::copy(hb->level_base, hb->level_base + 256, ctx->level_base);
+  ctx->level_base[256] = (uint32_t)nn;
+  ctx->maxdepth = kMaxDepthCap;
+  while (ctx->level_base[2 * ctx->maxdepth] == (uint32_t)nn) --ctx->maxdepth;
   ctx->have_tree = true;
   return SFMM_OK;
 }
@@ -453,8 +472,8 @@ int walk_per_leaf(sfmm_ctx* ctx, double theta) {
   int rc;
   const hipStream_t s = ctx->stream;
   const int nl = (int)ctx->nleaves;
-  uint64_t* small = P<uint64_t>(ctx, B_SMALL);
-  int* status = P<int>(ctx, B_STATUS);
+  uint64_t* small = P<Readback>(ctx, B_SMALL)->small;
+  int* status = P<Readback>(ctx, B_SMALL)->status;
   uint64_t* ldoff = P<uint64_t>(ctx, B_LDOFF);
   launch_leaf_doff(nl, P<int32_t>(ctx, B_LEAFDEPTH), ldoff, s);
   scan_u64(ldoff, ldoff, nl, small + S_DOFFTOT, P<uint64_t>(ctx, B_SCANTMP), s);
@@ -491,8 +510,7 @@ int walk_per_leaf(sfmm_ctx* ctx, double theta) {
   Readback* hb = readback(ctx);
   if (!hb) return fail(ctx, SFMM_ENOMEM, "pinned host block for read-backs");
   const uint64_t* hsmall = hb->small;
-  HIPCHK(hipMemcpyAsync(hb->small, small, sizeof(hb->small), hipMemcpyDeviceToHost, s));
-  HIPCHK(hipMemcpyAsync(hb->status, status, sizeof(hb->status), hipMemcpyDeviceToHost, s));
+  HIPCHK(hipMemcpyAsync(hb, P<Readback>(ctx, B_SMALL), sizeof(Readback), hipMemcpyDeviceToHost, s));
   HIPCHK(wait_stream(s));
   if (hb->status[0] & (ST_DEPTH | ST_OVERFLOW))
     return fail(ctx, SFMM_EDEVICE, "walk stack overflow (tree depth)");
@@ -526,13 +544,12 @@ int walk_levels(sfmm_ctx* ctx, double theta) {
   int rc;
   const hipStream_t s = ctx->stream;
   const int nn = (int)ctx->nn, nl = (int)ctx->nleaves;
-  uint64_t* small = P<uint64_t>(ctx, B_SMALL);
-  int* status = P<int>(ctx, B_STATUS);
+  uint64_t* small = P<Readback>(ctx, B_SMALL)->small;
+  int* status = P<Readback>(ctx, B_SMALL)->status;
   const int node_arrays[] = {B_NM2LOFF, B_NM2LCNT, B_NOPENOFF, B_NOPENCNT, B_NP2POFF, B_NP2PCNT,
                              B_NEXP};
   for (int id : node_arrays)
     if ((rc = ensure(ctx, id, sizeof(uint32_t) * nn))) return rc;
-  if ((rc = ensure(ctx, B_WALKTOT, sizeof(uint64_t) * (11 + kXcds)))) return rc;
   if ((rc = ensure_item_buffers(ctx))) return rc;
   for (int id : {B_LWM2LCNT, B_LWP2PCNT, B_OVFLEAF})
     if ((rc = ensure(ctx, id, sizeof(uint32_t) * std::max(nl, 1)))) return rc;
@@ -571,9 +588,14 @@ int walk_levels(sfmm_ctx* ctx, double theta) {
     ctx->walk_attempts = attempt + 1;
     if ((rc = ensure(ctx, B_M2LPOOL, sizeof(uint32_t) * ctx->m2l_cap))) return rc;
     if ((rc = ensure(ctx, B_P2PPOOL, sizeof(uint32_t) * ctx->p2p_cap))) return rc;
-    uint64_t* tot = P<uint64_t>(ctx, B_WALKTOT);
-    HIPCHK(hipMemsetAsync(tot, 0, sizeof(uint64_t) * (11 + kXcds), s));
-    HIPCHK(hipMemsetAsync(status, 0, sizeof(int), s));
+    Readback* dev = P<Readback>(ctx, B_SMALL);
+    uint64_t* tot = dev->walk_tot;
+    // (zero after a build)
+    if (!ctx->walk_clear)
+      launch_clear_words(reinterpret_cast<uint32_t*>(dev->status),
+                         (sizeof(Readback) - offsetof(Readback, status)) / sizeof(uint32_t),
+                         nullptr, 0, s);
+    ctx->walk_clear = false;
     if (ctx->check_pools) {
       // every entry a consumer reads must then come from this walk: clear
       // the pools to a value no node id takes (checked after the walk)
@@ -587,8 +609,8 @@ int walk_levels(sfmm_ctx* ctx, double theta) {
     a.r_kern = ctx->cfg.r_kern;
     a.level_nodes = P<int32_t>(ctx, B_LEVNODES);
     a.node_flag = ctx->nsys > 1 ? P<uint8_t>(ctx, B_NFLAG) : nullptr;
-    a.level_off = P<uint32_t>(ctx, B_LEVOFF);
-    a.level_int = P<uint32_t>(ctx, B_LEVINT);
+    a.level_base = dev->level_base;
+    a.items_total = &dev->items;
     a.m2l_off = P<uint32_t>(ctx, B_NM2LOFF);
     a.m2l_cnt = P<uint32_t>(ctx, B_NM2LCNT);
     a.open_off = P<uint32_t>(ctx, B_NOPENOFF);
@@ -629,7 +651,7 @@ int walk_levels(sfmm_ctx* ctx, double theta) {
     // internal nodes level by level, then every leaf
     uint32_t rank0 = 0;
     for (int k = 0; k <= ctx->maxdepth; ++k) {
-      const uint32_t nk = ctx->level_int[k] - ctx->level_off[k];
+      const uint32_t nk = ctx->level_base[2 * k + 1] - ctx->level_base[2 * k];
       launch_nodewalk_level(a, k, (int)nk, rank0, s);
       rank0 += nk;
     }
@@ -643,12 +665,7 @@ int walk_levels(sfmm_ctx* ctx, double theta) {
     if (!hb) return fail(ctx, SFMM_ENOMEM, "pinned host block for read-backs");
     const uint64_t* htot = hb->walk_tot;
     const int* hstatus = hb->status;
-    hb->items = 0;
-    HIPCHK(hipMemcpyAsync(hb->walk_tot, tot, sizeof(hb->walk_tot), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipMemcpyAsync(hb->status, status, sizeof(hb->status), hipMemcpyDeviceToHost, s));
-    if (nl > 0)
-      HIPCHK(hipMemcpyAsync(&hb->items, a.item_off + nl, sizeof(uint32_t), hipMemcpyDeviceToHost,
-                            s));
+    HIPCHK(hipMemcpyAsync(hb, dev, sizeof(Readback), hipMemcpyDeviceToHost, s));
     HIPCHK(wait_stream(s));
     ctx->items_from_walk = hb->items;
     // 64-bit totals: internal regions, the leaves' slots, then the lists that
@@ -754,7 +771,7 @@ int do_walk_and_eval(sfmm_ctx* ctx, double theta, int precision, const double* m
   int rc;
   const hipStream_t s = ctx->stream;
   const int n = (int)ctx->n, nl = (int)ctx->nleaves;
-  uint64_t* small = P<uint64_t>(ctx, B_SMALL);
+  uint64_t* small = P<Readback>(ctx, B_SMALL)->small;
   struct { int id; size_t bytes; } need[] = {
       {B_LDOFF, sizeof(uint64_t) * (nl + 1)}, {B_M2LCNT, sizeof(uint64_t) * (nl + 1)},
       {B_P2PCNT, sizeof(uint64_t) * (nl + 1)}, {B_PAIRCNT, sizeof(uint64_t) * (nl + 1)},
@@ -911,7 +928,7 @@ int do_walk_and_eval(sfmm_ctx* ctx, double theta, int precision, const double* m
       sa.recq = P<double>(ctx, B_RECQ);
       sa.top = ctx->cfg.fp64_top_depth;
       // (the order puts the targets above the top depth first)
-      sa.n64 = f32 ? (int)ctx->level_off[std::min(sa.top, kMaxDepthCap + 1)] : 0;
+      sa.n64 = f32 ? (int)ctx->level_base[2 * std::min(sa.top, kMaxDepthCap + 1)] : 0;
       sa.ln = P<double>(ctx, B_LN);
       if (mutual) {
         launch_far_mutual(ctx->order, f, sa, s);
@@ -924,7 +941,7 @@ int do_walk_and_eval(sfmm_ctx* ctx, double theta, int precision, const double* m
         ob.ids0 = P<uint32_t>(ctx, B_LEVIDS);
         ob.ids1 = P<uint32_t>(ctx, B_M2LORD);
         ob.ids2 = ob.ids1 + ctx->nn;
-        ob.base = P<uint32_t>(ctx, B_BASE) + 256;
+        ob.base = P<uint32_t>(ctx, B_BASE);
         ob.words = P<uint32_t>(ctx, B_SORT) + ctx->words_m2l;
         m2l_windows(sa, ctx->m2l_unique);
         launch_m2l_order(sa, f32, ob, s);
@@ -1136,6 +1153,7 @@ int sfmm_destroy(sfmm_ctx* ctx) {
   for (auto& b : ctx->buf)
     if (b.p) (void)hipFree(b.p);
   if (ctx->rb) (void)hipHostFree(ctx->rb);
+  if (ctx->tree_event) (void)hipEventDestroy(ctx->tree_event);
   delete ctx;
   return SFMM_OK;
 }
@@ -1218,7 +1236,7 @@ int sfmm_get_stats(sfmm_ctx* ctx, sfmm_stats* out) {
     // the level walk's per-leaf totals are only computed when asked for
     const int nl = (int)ctx->nleaves;
     const hipStream_t s = ctx->stream;
-    uint64_t* small = P<uint64_t>(ctx, B_SMALL);
+    uint64_t* small = P<Readback>(ctx, B_SMALL)->small;
     LeafStatArgs ls{};
     ls.nleaves = nl;
     ls.leaf_node = P<int32_t>(ctx, B_LEAFNODE);

@@ -119,7 +119,8 @@ void launch_bbox(int n, const double* x, const double* m, const double* h, doubl
 constexpr int kSortSmall = 4096;
 // words of scratch for `passes` passes over n elements, to be cleared before
 size_t sort_words(int64_t n, int passes);
-void launch_clear_words(uint32_t* p, size_t n, hipStream_t s);
+// zeroes two ranges of words
+void launch_clear_words(uint32_t* p, size_t n, uint32_t* p2, size_t n2, hipStream_t s);
 // Morton keys in the box of the blocks' corners (part) and their digit counts
 // into the words of an 8-pass sort
 void launch_keys(int n, const double* x, int nb, const double* part, uint64_t* key,
@@ -133,9 +134,10 @@ void launch_small_sort(int n, const double* x, const double* m, const double* h,
 void radix_sort(int n, int passes, bool counted, uint64_t* key0, uint32_t* val0, uint64_t* key1,
                 uint32_t* val1, uint32_t* words, hipStream_t s);
 // one stable pass on the lowest 8 bits; vin may be null (the positions); base
-// (may be null): [256] the first place of each digit
-void radix_pass(int n, const uint64_t* kin, const uint32_t* vin, uint64_t* kout, uint32_t* vout,
-                uint32_t* base, uint32_t* words, hipStream_t s);
+// (may be null): [256] the first place of each digit; counted: the words hold
+// the digit counts
+void radix_pass(int n, bool counted, const uint64_t* kin, const uint32_t* vin, uint64_t* kout,
+                uint32_t* vout, uint32_t* base, uint32_t* words, hipStream_t s);
 // sorted particle data: separate arrays and two of 16 bytes per particle
 // (pxy: x, y; pzm: z, m)
 void launch_gather(int n, const uint32_t* perm, const double* x, const double* m,
@@ -166,29 +168,43 @@ void launch_sys_final(int n, const uint32_t* q, const uint32_t* perm1, const uin
 void launch_node_flags(int nn, const NodeInfo* info, const uint32_t* sys, uint8_t* flag,
                        hipStream_t s);
 void launch_leaf_fill(int n, const uint32_t* leaf_flag, const uint32_t* leaf_scan,
-                      const int32_t* leaf_at, int32_t* leaf_node, hipStream_t s);
-void launch_single_leaf(int n, NodeInfo* info, int32_t* leaf_node, hipStream_t s);
-void launch_leaf_depth(int nleaves, const int32_t* leaf_node, const NodeInfo* info,
-                       const int32_t* node_depth, int32_t* leaf_depth, int32_t* p_leaf,
-                       int* maxdepth, hipStream_t s);
-// geometry and moments, deepest level first (level offsets: a host copy for
-// the launch sizes and the device array for runs of small levels); recq: the
-// M2L source records as well (may be null)
-void launch_geometry(int order, int maxdepth, const uint32_t* level_off_host,
-                     const uint32_t* level_off_dev, const int32_t* level_nodes,
-                     const NodeInfo* info, const double* xs, const double* ys, const double* zs,
-                     const double* ms, const double* hs, double* rec, double* recq,
-                     hipStream_t s);
-void launch_extent_count(int nn, const NodeInfo* info, uint32_t* chunks, hipStream_t s);
-void launch_extent(int order, int nn, int nitems, const NodeInfo* info,
-                   const uint32_t* chunk_off, uint32_t* item_node, const double* xs,
-                   const double* ys, const double* zs, double* rec, unsigned long long* l2bits,
-                   hipStream_t s);
+                      const int32_t* leaf_at, int32_t* leaf_node, int32_t* p_leaf,
+                      hipStream_t s);
+void launch_single_leaf(int n, NodeInfo* info, int32_t* leaf_node, int32_t* p_leaf,
+                        hipStream_t s);
+// per node, once the shape of the tree is known
+struct NodeSetupArgs {
+  int nn, n;
+  uint32_t nkept, kmax;       // internal nodes; those of a subtree for one block
+  const NodeInfo* info;
+  const uint32_t* kept_scan;  // [n - 1] numbers of the binary tree's kept nodes
+  const int32_t* p_leaf;
+  int32_t *depth, *leaf_depth;
+  uint64_t* key;              // 2 depth + leaf, and its counts (256)
+  uint32_t* hist;
+  uint64_t* l2bits;
+  // the subtrees' roots, the nodes above (id and depth; sorted: room for them
+  // by depth), the chunks (node, chunk of its particles), and their numbers
+  uint32_t *roots, *top, *top_sorted;
+  uint2* items;
+  uint32_t* few;              // nodes of at most kExtentFew particles
+  uint32_t *nroots, *ntop, *nitems, *nfew;
+  int* too_deep;              // set to a depth beyond kMaxDepthCap
+};
+constexpr int kGeomMax = 4096;      // largest kmax
+constexpr int kExtentChunk = 2048, kExtentFew = 64;  // particles
+uint32_t geom_kmax(uint32_t nkept);
+size_t extent_items(int n, uint32_t nkept);  // at most
+void launch_node_setup(const NodeSetupArgs& a, hipStream_t s);
+// geometry and moments, and the squared sizes of the internal nodes (l2bits);
+// recq: the M2L source records as well (may be null)
+void launch_geometry(int order, const NodeSetupArgs& a, int nleaves, const int32_t* leaf_node,
+                     const double* xs, const double* ys, const double* zs, const double* ms,
+                     const double* hs, double* rec, double* recq, hipStream_t s);
 // (l2bits: null for a tree of one leaf)
 void launch_extent_final(int order, int nn, const NodeInfo* info,
                          const unsigned long long* l2bits, double* rec, WalkRec* wrec,
                          hipStream_t s);
-constexpr int kExtentChunk = 2048;
 
 // ---- walk (Algorithms 1 and 2) ---------------------------------------------
 struct WalkArgs {
@@ -258,8 +274,8 @@ struct NodeWalkArgs {
   double theta2, r_kern;
   const int32_t* level_nodes;  // nodes grouped by depth
   const uint8_t* node_flag;    // 0 spans systems (skipped), 1 walk root, 2 other
-  const uint32_t* level_off;   // [levels + 1]
-  const uint32_t* level_int;   // [levels] end of each level's internal nodes
+  const uint32_t* level_base;  // [256] a level's nodes begin at [2 level], its leaves
+                               // at [2 level + 1] (the internal nodes first)
   // per node (node-indexed): M2L list, opened list (internal), P2P list (leaf).
   // An internal node's M2L and opened lists share one region of the M2L pool
   // (M2L from the front, opened from the back); its size, the node's tested
@@ -307,15 +323,8 @@ struct NodeWalkArgs {
   P2PItemRule rule;
   uint32_t stack_cap;  // LDS lowering stack, entries
   int* status;
+  uint32_t* items_total;  // set to item_off[nleaves] with the totals
 };
-// node depth, also as a sort key (u64) for the bucketing by depth
-void launch_node_depth(int nn, const NodeInfo* info, int32_t* depth, uint64_t* key,
-                       hipStream_t s);
-// level_off[k] = first position of depth k in the depth-sorted node list
-// (sort key 2 depth + leaf: a level's internal nodes first), level_int[k] =
-// the end of its internal nodes; read from the pass's first places
-void launch_level_offsets(int nlev, int nn, const uint32_t* base, uint32_t* level_off,
-                          uint32_t* level_int, hipStream_t s);
 // every leaf's lists (the slot pass, scans over the leaves, the second pass
 // over leaves whose lists overflow their slots); scan_tmp holds
 // scan_tmp_elems(nleaves) words; LDS of (stack_cap + slot_p) words per wave
