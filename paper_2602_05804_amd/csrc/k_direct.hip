@@ -3,83 +3,203 @@
 // approximates (accuracy sweeps against the opening angle, the paper's
 // Plummer and homogeneous-sphere tests).
 //
-// One thread per target, the sources split into chunks: block (b, c) sums
-// chunk c of the sources for targets b * 256 .. b * 256 + 255, streaming them
-// through LDS in tiles of 256 (x, y, z, m, h, 1/h) read back as broadcasts,
-// and writes its partial sums to a buffer [chunk][target][4]; a second kernel
-// adds each target's partials in chunk order.  Pairs with j == i are skipped;
-// unequal h are averaged as in P2P.  The summation order is fixed, so the
-// result is reproducible.  With few targets the chunks keep the chip busy.
+// A wave takes 64 targets and a chunk of the sources: block (b, c) sums chunk
+// c for the targets of group b and writes its partial sums to a buffer
+// [chunk][target][4]; a second kernel adds each target's partials in chunk
+// order.  Pairs with j == i are skipped; unequal h are averaged as in P2P.
+// The summation order is fixed, so the result is reproducible.
+//
+// Bound by FP64 issue.  The sources are the same for all lanes: they come
+// through scalar loads, four at a time, and stay in scalar registers.  A pair
+// beyond both kernels costs 24 FP64 operations and one estimate of 1/sqrt; the
+// others are queued and evaluated 64 at a time.  All pairs of 1e5 particles of a
+// Plummer sphere (softening lengths over four decades): 8.9 ms; 16.2 with the
+// sources in LDS (six reads a pair), a full 1/sqrt, and the softened pair in
+// place, which nearly a tenth of the steps took for one lane; 14.6 with only that
+// left.  A polytrope of 1e5: 8.5 ms, 12.5 before.
 #include "sfmm_internal.h"
 #include "softening.h"
 
 namespace sfmm {
 namespace {
 
-constexpr int kDirTile = 256;
+constexpr int kDirTile = 64;    // chunks are whole numbers of this many sources
+constexpr int kDirGroup = 4;    // sources loaded at a time
 
-__global__ __launch_bounds__(kDirTile) void k_direct_part(int64_t n, const double* __restrict__ x,
-                                                          const double* __restrict__ m,
-                                                          const double* __restrict__ h,
-                                                          int64_t nt,
-                                                          const int64_t* __restrict__ targets,
-                                                          int64_t chunk, double* __restrict__ part,
-                                                          int* status) {
-  __shared__ double sx[kDirTile], sy[kDirTile], sz[kDirTile], sm[kDirTile], sh[kDirTile],
-      shi[kDirTile];
-  const int64_t t = (int64_t)blockIdx.x * kDirTile + threadIdx.x;
+constexpr int kDirQueue = 64 * (kDirGroup + 1);
+
+// a wave's pairs that may lie within a kernel, kept until 64 of them fill the
+// lanes: (source within the chunk, target lane).  A few targets with a large h
+// have a pair there with every source: in place, all lanes would go through
+// the softened pair for the sake of one.
+struct DirLds {
+  SoftCoef coef[3];
+  double t[5][64];    // the targets' x, y, z, h, 1/h
+  double acc[4][64];  // their softened sums
+  unsigned long long mask[64];
+  uint32_t first[64], last[64];
+  uint32_t qj[kDirQueue], sj[64];
+  uint8_t ql[kDirQueue], sl[64];
+};
+
+// one softened pair a lane, the queue's last `count` (<= 64) entries from `at`
+// on: put in the order of their targets, evaluated, and summed over runs of
+// one target, whose last lane adds the sum to the target's.  The order of the
+// sums depends on the queue alone.
+__device__ __forceinline__ void direct_flush(DirLds& sh, uint32_t at, uint32_t count, int64_t j0,
+                                             int64_t i0, const int64_t* __restrict__ targets,
+                                             const double* __restrict__ x,
+                                             const double* __restrict__ m,
+                                             const double* __restrict__ h) {
+  const uint32_t lane = threadIdx.x;
+  const bool on = lane < count;
+  sh.mask[lane] = 0ull;
+  __syncthreads();
+  const uint32_t lq = on ? sh.ql[at + lane] : 0u, jq = on ? sh.qj[at + lane] : 0u;
+  if (on) atomicOr(&sh.mask[lq], 1ull << lane);
+  __syncthreads();
+  const uint32_t own = (uint32_t)__popcll(sh.mask[lane]);
+  uint32_t incl = own;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t u = (uint32_t)__shfl_up((int)incl, o, 64);
+    if ((int)lane >= o) incl += u;
+  }
+  sh.first[lane] = incl - own;
+  sh.last[lane] = incl - 1u;
+  __syncthreads();
+  if (on) {
+    const uint32_t pos =
+        sh.first[lq] + (uint32_t)__popcll(sh.mask[lq] & ((1ull << lane) - 1ull));
+    sh.sj[pos] = jq;
+    sh.sl[pos] = (uint8_t)lq;
+  }
+  __syncthreads();
+  const uint32_t l = on ? sh.sl[lane] : 0u;
+  const int64_t j = j0 + (on ? sh.sj[lane] : 0u);
+  const int64_t i = targets ? targets[i0 + l] : i0 + l;
+  const uint32_t first = on ? sh.first[l] : lane;
+  const double tx = sh.t[0][l], ty = sh.t[1][l], tz = sh.t[2][l], hi = sh.t[3][l],
+               hiinv = sh.t[4][l];
+  const double hj = h[j], hjinv = 1.0 / hj;
+  const double w = on && j != i ? m[j] : 0.0;
+  const double dx = tx - x[3 * j], dy = ty - x[3 * j + 1], dz = tz - x[3 * j + 2];
+  const double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
+  const double rinv = r2 > 0.0 ? rsqrt(r2) : 0.0;
+  const double r = r2 * rinv;
+  double g1, p1, g2, p2;
+  soft_piece(sh.coef, r * hiinv, hi * rinv, hiinv, g1, p1);
+  soft_piece(sh.coef, r * hjinv, hj * rinv, hjinv, g2, p2);
+  const bool inside = (r2 * (hiinv * hiinv) < 4.0) || (r2 * (hjinv * hjinv) < 4.0);
+  const double mg = w * (inside ? 0.5 * (g1 + g2) : rinv * rinv * rinv);
+  double v[4] = {mg * dx, mg * dy, mg * dz, w * (inside ? 0.5 * (p1 + p2) : rinv)};
+  for (int o = 1; o < 64 && __ballot((int)own > o); o <<= 1) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const double u = __shfl_up(v[k], o, 64);
+      if ((int)lane - o >= (int)first) v[k] += u;
+    }
+  }
+  if (on && lane == sh.last[l]) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) sh.acc[k][l] += v[k];
+  }
+  __syncthreads();
+}
+
+__global__ __launch_bounds__(64) void k_direct_part(int64_t n, const double* __restrict__ x,
+                                                    const double* __restrict__ m,
+                                                    const double* __restrict__ h, int64_t nt,
+                                                    const int64_t* __restrict__ targets,
+                                                    int64_t chunk, double* __restrict__ part,
+                                                    int* status) {
+  __shared__ DirLds sh;
+  const uint32_t lane = threadIdx.x;
+  if (lane < sizeof(kSoftCoef) / sizeof(double))
+    reinterpret_cast<double*>(sh.coef)[lane] = reinterpret_cast<const double*>(kSoftCoef)[lane];
+  const int64_t i0 = (int64_t)blockIdx.x * 64;
+  const int64_t t = i0 + lane;
   const int64_t it = t < nt ? (targets ? targets[t] : t) : 0;
   const bool valid = it >= 0 && it < n;  // a bad index is reported, never read
   if (t < nt && !valid && blockIdx.y == 0) atomicOr(status, ST_OVERFLOW);
   const int64_t i = valid ? it : 0;
-  const double xi = x[3 * i], yi = x[3 * i + 1], zi = x[3 * i + 2];
-  const double hinv_i = 1.0 / h[i];
-  const double h_i = h[i];
+  const bool on = t < nt && valid;
+  const double xi = x[3 * i], yi = x[3 * i + 1], zi = x[3 * i + 2], hi = h[i];
+  const double h4 = 4.0 * hi * hi;
+  sh.t[0][lane] = xi;
+  sh.t[1][lane] = yi;
+  sh.t[2][lane] = zi;
+  sh.t[3][lane] = hi;
+  sh.t[4][lane] = 1.0 / hi;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) sh.acc[k][lane] = 0.0;
+  __syncthreads();
   double ax = 0.0, ay = 0.0, az = 0.0, ph = 0.0;
+  uint32_t nq = 0;  // (uniform)
+  const uint64_t on_mask = __ballot(on);
   const int64_t j0 = (int64_t)blockIdx.y * chunk;
   const int64_t j1 = j0 + chunk < n ? j0 + chunk : n;
-  for (int64_t base = j0; base < j1; base += kDirTile) {
-    const int64_t j = base + threadIdx.x;
-    if (j < j1) {
-      sx[threadIdx.x] = x[3 * j];
-      sy[threadIdx.x] = x[3 * j + 1];
-      sz[threadIdx.x] = x[3 * j + 2];
-      sm[threadIdx.x] = m[j];
-      sh[threadIdx.x] = h[j];
-      shi[threadIdx.x] = 1.0 / h[j];
-    }
-    __syncthreads();
-    const int cnt = (int)((j1 - base) < kDirTile ? (j1 - base) : kDirTile);
-    for (int k = 0; k < cnt; ++k) {
-      const double w = (base + k == i) ? 0.0 : sm[k];
-      const double dx = xi - sx[k], dy = yi - sy[k], dz = zi - sz[k];
-      const double r2 = dx * dx + dy * dy + dz * dz;
-      const double rinv = r2 > 0.0 ? rsqrt(r2) : 0.0;
-      const double rinv3 = rinv * rinv * rinv;
-      double gs = rinv3, ps = rinv;
-      const double hj = sh[k], hjinv = shi[k];
-      const bool inside = (r2 * (hinv_i * hinv_i) < 4.0) || (r2 * (hjinv * hjinv) < 4.0);
-      if (__ballot(inside)) {
-        const double r = r2 * rinv;
-        double g1, p1, g2, p2;
-        soft_sel(r * hinv_i, hinv_i, h_i * rinv, rinv, rinv3, g1, p1);
-        soft_sel(r * hjinv, hjinv, hj * rinv, rinv, rinv3, g2, p2);
-        if (inside) {
-          gs = 0.5 * (g1 + g2);
-          ps = 0.5 * (p1 + p2);
-        }
+
+  // one source (j, sx .. sm the same for all lanes); r^2 beyond far2 lies
+  // outside both kernels
+  auto source = [&](int64_t j, double far2, double sx, double sy, double sz, double sm) {
+    const double dx = xi - sx, dy = yi - sy, dz = zi - sz;
+    const double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
+    const bool near = !(r2 > far2);  // (also when the comparison fails for a NaN)
+    const double y = rsqrt_refined(r2);
+    double mr = sm * y;
+    double mg = mr * (y * y);
+    const uint64_t nb = __ballot(near) & on_mask;
+    if (nb != 0) {
+      const uint32_t k = nq + __builtin_amdgcn_mbcnt_hi(
+                                  (uint32_t)(nb >> 32),
+                                  __builtin_amdgcn_mbcnt_lo((uint32_t)nb, 0u));
+      mr = near ? 0.0 : mr;
+      mg = near ? 0.0 : mg;
+      if ((nb >> lane) & 1u) {
+        sh.qj[k] = (uint32_t)(j - j0);
+        sh.ql[k] = (uint8_t)lane;
       }
-      const double mg = w * gs;
-      ax = fma(mg, dx, ax);
-      ay = fma(mg, dy, ay);
-      az = fma(mg, dz, az);
-      ph = fma(w, ps, ph);
+      nq += (uint32_t)__popcll(nb);
     }
-    __syncthreads();
+    ax = fma(mg, dx, ax);
+    ay = fma(mg, dy, ay);
+    az = fma(mg, dz, az);
+    ph += mr;
+    // (sums made here, not kept for later: twice the registers otherwise)
+    asm volatile("" : "+v"(ax), "+v"(ay), "+v"(az), "+v"(ph));
+  };
+
+  for (int64_t j = j0; j < j1; j += kDirGroup) {
+    if (j + kDirGroup <= j1) {
+      double s[3 * kDirGroup], sm[kDirGroup], sj[kDirGroup];
+#pragma unroll
+      for (int k = 0; k < 3 * kDirGroup; ++k) s[k] = x[3 * j + k];
+#pragma unroll
+      for (int k = 0; k < kDirGroup; ++k) sm[k] = m[j + k];
+#pragma unroll
+      for (int k = 0; k < kDirGroup; ++k) sj[k] = h[j + k];
+#pragma unroll
+      for (int k = 0; k < kDirGroup; ++k)
+        source(j + k, fmax(h4, 4.0 * sj[k] * sj[k]), s[3 * k], s[3 * k + 1], s[3 * k + 2], sm[k]);
+    } else {
+      for (int64_t k = j; k < j1; ++k)
+        source(k, fmax(h4, 4.0 * h[k] * h[k]), x[3 * k], x[3 * k + 1], x[3 * k + 2], m[k]);
+    }
+    const bool last = j + kDirGroup >= j1;
+    while (nq >= 64 || (last && nq > 0)) {
+      const uint32_t c = nq < 64 ? nq : 64;
+      nq -= c;
+      __syncthreads();
+      direct_flush(sh, nq, c, j0, i0, targets, x, m, h);
+    }
   }
   if (t >= nt) return;
   double* o = part + ((int64_t)blockIdx.y * nt + t) * 4;
-  o[0] = ax; o[1] = ay; o[2] = az; o[3] = ph;
+  o[0] = ax + sh.acc[0][lane];
+  o[1] = ay + sh.acc[1][lane];
+  o[2] = az + sh.acc[2][lane];
+  o[3] = ph + sh.acc[3][lane];
 }
 
 // per target: the chunks' partial sums in chunk order, the self term, -G
@@ -93,9 +213,20 @@ __global__ void k_direct_final(int64_t n, const double* __restrict__ m,
   const int64_t it = targets ? targets[t] : t;
   if (it < 0 || it >= n) return;  // reported by the first kernel
   double ax = 0.0, ay = 0.0, az = 0.0, ph = 0.0;
-  for (int c = 0; c < nchunk; ++c) {
-    const double* q = part + ((int64_t)c * nt + t) * 4;
-    ax += q[0]; ay += q[1]; az += q[2]; ph += q[3];
+  // eight partials' loads at a time, added one after the other
+  for (int c = 0; c < nchunk; c += 8) {
+    double v[8][4];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const double* q = part + ((int64_t)min(c + u, nchunk - 1) * nt + t) * 4;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[u][k] = q[k];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      if (c + u >= nchunk) break;
+      ax += v[u][0]; ay += v[u][1]; az += v[u][2]; ph += v[u][3];
+    }
   }
   if (include_self) ph = fma(m[it], 1.4 * (1.0 / h[it]), ph);
   acc[3 * t] = -G * ax;
@@ -110,8 +241,10 @@ __global__ void k_clear_int(int* p) { *p = 0; }
 
 int direct_chunks(int64_t n, int64_t nt, uint64_t max_part_bytes) {
   if (n <= 0 || nt <= 0) return 1;
-  const int64_t nb = (nt + kDirTile - 1) / kDirTile;
-  int64_t c = (4096 + nb - 1) / nb;                      // about 4096 blocks in all
+  const int64_t nb = (nt + 63) / 64;
+  int64_t c = (49152 + nb - 1) / nb;                     // about 49152 waves in all: waves
+  // with a far-reaching target take longer (1e5 targets: 10.1 ms with 16384, 9.2
+  // with 32768, 8.9 with 49152 and with 65536)
   const int64_t tiles = (n + kDirTile - 1) / kDirTile;   // at least one tile per chunk
   if (c > tiles) c = tiles;
   const int64_t fit = (int64_t)(max_part_bytes / ((uint64_t)nt * 4 * sizeof(double)));
@@ -129,8 +262,8 @@ void launch_direct(int64_t n, const double* x, const double* m, const double* h,
   const int64_t tiles = (n + kDirTile - 1) / kDirTile;
   const int64_t chunk = ((tiles + nchunk - 1) / nchunk) * kDirTile;
   const int nc = (int)((n + chunk - 1) / chunk);
-  const dim3 grid((unsigned)((nt + kDirTile - 1) / kDirTile), (unsigned)nc);
-  k_direct_part<<<grid, kDirTile, 0, s>>>(n, x, m, h, nt, targets, chunk, part, status);
+  const dim3 grid((unsigned)((nt + 63) / 64), (unsigned)nc);
+  k_direct_part<<<grid, 64, 0, s>>>(n, x, m, h, nt, targets, chunk, part, status);
   k_direct_final<<<(unsigned)((nt + 255) / 256), 256, 0, s>>>(n, m, h, nt, targets, nc, part, G,
                                                                include_self, acc, pot);
 }

@@ -76,4 +76,31 @@ __device__ __forceinline__ void soft_sel(double q, double hinv, double qi, doubl
   psi = q >= 2.0 ? rinv : (q < 1.0 ? pA : pB);
 }
 
+// One piece of the cubic spline of softening.h: with q = r / h
+//   g   = (c0 + q (c1 + q (c2 + q c3)) - cr / q^3) / h^3
+//   psi = (d0 + q^2 (d2 + q (d3 + q (d4 + q d5))) - dr / q) / h
+// for q < 1, 1 <= q < 2 and q >= 2 (outside: 1/r^3 and 1/r).  A lane reads
+// its piece from LDS, which takes 24 instructions a kernel where evaluating
+// the pieces and selecting takes 38.
+struct alignas(16) SoftCoef {
+  double c0, c1, c2, c3, cr, d0, d2, d3, d4, d5, dr, pad;
+};
+[[maybe_unused]] static __constant__ const SoftCoef kSoftCoef[3] = {
+    {4.0 / 3.0, 0.0, -1.2, 0.5, 0.0, 1.4, -2.0 / 3.0, 0.0, 0.3, -0.1, 0.0, 0.0},
+    {8.0 / 3.0, -3.0, 1.2, -1.0 / 6.0, 1.0 / 15.0, 1.6, -4.0 / 3.0, 1.0, -0.3, 1.0 / 30.0,
+     1.0 / 15.0, 0.0},
+    {0.0, 0.0, 0.0, 0.0, -1.0, 0.0, 0.0, 0.0, 0.0, 0.0, -1.0, 0.0}};
+
+// g = f(q) / (q h^3) and psi(q) / h at q = r hinv, qi = h / r
+__device__ __forceinline__ void soft_piece(const SoftCoef* coef, double q, double qi, double hinv,
+                                           double& g, double& psi) {
+  const SoftCoef& k = coef[q < 1.0 ? 0 : q < 2.0 ? 1 : 2];
+  const double qr = q < 1.0 ? 0.0 : qi;  // (1/q^3 may overflow there; its coefficient is 0)
+  const double q2 = q * q;
+  const double gp = fma(q, fma(q, fma(q, k.c3, k.c2), k.c1), k.c0);
+  const double pp = fma(q2, fma(q, fma(q, fma(q, k.d5, k.d4), k.d3), k.d2), k.d0);
+  g = hinv * hinv * hinv * fma(-k.cr, qr * qr * qr, gp);
+  psi = hinv * fma(-k.dr, qr, pp);
+}
+
 }  // namespace sfmm
