@@ -13,6 +13,7 @@
 //        (i in A, j in B) uses d = fl32(c_A - c_B) + (o_i - o_j), which is
 //        exactly minus the separation seen from j, so each pair force is
 //        antisymmetric.
+#include "p2p_wave.h"
 #include "sfmm_internal.h"
 
 namespace sfmm {
@@ -33,23 +34,22 @@ __global__ void k_prep_nodes32(int nn, const double* __restrict__ rec,
   for (int k = 0; k < NQ; ++k) o[6 + k] = (float)r[8 + k];
 }
 
+// (a thread per particle: one per leaf took 123 us at 2e6 particles)
 template <int RS>
-__global__ void k_prep_particles32(int nleaves, const int32_t* __restrict__ leaf_node,
-                                   const NodeInfo* __restrict__ info, const double* __restrict__ rec,
-                                   const double* __restrict__ xs, const double* __restrict__ ys,
-                                   const double* __restrict__ zs, const double* __restrict__ ms,
-                                   const double* __restrict__ hs, float4* __restrict__ pf,
-                                   float2* __restrict__ ph) {
-  const int l = blockIdx.x * blockDim.x + threadIdx.x;
-  if (l >= nleaves) return;
-  const int v = leaf_node[l];
-  const NodeInfo ni = info[v];
-  const double* r = rec + (int64_t)v * RS;
-  for (int j = ni.lo; j < ni.lo + ni.cnt; ++j) {
-    pf[j] = make_float4((float)(xs[j] - r[0]), (float)(ys[j] - r[1]), (float)(zs[j] - r[2]),
-                        (float)ms[j]);
-    ph[j] = make_float2((float)hs[j], (float)(1.0 / hs[j]));
-  }
+__global__ void k_prep_particles32(int n, const int32_t* __restrict__ p_leaf,
+                                   const int32_t* __restrict__ leaf_node,
+                                   const double* __restrict__ rec, const double* __restrict__ xs,
+                                   const double* __restrict__ ys, const double* __restrict__ zs,
+                                   const double* __restrict__ ms, const double* __restrict__ hs,
+                                   Part32 p) {
+  const int j = blockIdx.x * blockDim.x + threadIdx.x;
+  if (j >= n) return;
+  const double* r = rec + (int64_t)leaf_node[p_leaf[j]] * RS;
+  const double c0 = r[0], c1 = r[1], c2 = r[2];
+  p.off[j] = make_float4((float)(xs[j] - c0), (float)(ys[j] - c1), (float)(zs[j] - c2),
+                         (float)ms[j]);
+  p.cxy[j] = make_double2(c0, c1);
+  p.czh[j] = Part32Z{c2, (float)hs[j], (float)(1.0 / hs[j])};
 }
 
 // ---- far field -----------------------------------------------------------------
@@ -208,8 +208,9 @@ __device__ __forceinline__ double wave_sum64(double v) {
 // targets in passes of TG, each pass unrolled (static accumulator indices);
 // the sources are read once per pass
 template <int LS, bool NODE, int TG>
-__global__ __launch_bounds__(64) void k_p2p_leaf32(NearArgs a, const float4* __restrict__ pf,
-                                                   const float2* __restrict__ phh) {
+__global__ __launch_bounds__(64) void k_p2p_leaf32(NearArgs a, Part32 p) {
+  const float4* __restrict__ pf = p.off;
+  const Part32Z* __restrict__ phh = p.czh;
   const int RS = a.rec_stride;
   const int lane = threadIdx.x;
   const uint32_t item = blockIdx.x;
@@ -221,9 +222,9 @@ __global__ __launch_bounds__(64) void k_p2p_leaf32(NearArgs a, const float4* __r
   __shared__ float tg[LS][5];  // offset x, y, z, 1/h, h
   if (lane < nt) {
     const float4 o = pf[tlo + lane];
-    const float2 hh = phh[tlo + lane];
+    const Part32Z hh = phh[tlo + lane];
     tg[lane][0] = o.x; tg[lane][1] = o.y; tg[lane][2] = o.z;
-    tg[lane][3] = hh.y; tg[lane][4] = hh.x;
+    tg[lane][3] = hh.hinv; tg[lane][4] = hh.h;
   }
   __syncthreads();
   // this item's run [f_lo, f_hi) of the leaf's flattened sources, from the
@@ -284,8 +285,8 @@ __global__ __launch_bounds__(64) void k_p2p_leaf32(NearArgs a, const float4* __r
           cz = (float)(ct2 - rl[2]);
         }
         const float4 oj = pf[j];
-        const float2 hj = phh[j];
-        const float hj2inv = hj.y * hj.y;
+        const Part32Z hj = phh[j];
+        const float hj2inv = hj.hinv * hj.hinv;
 #pragma unroll
         for (int ii = 0; ii < TG; ++ii) {
           const int i = t0 + ii;
@@ -305,7 +306,7 @@ __global__ __launch_bounds__(64) void k_p2p_leaf32(NearArgs a, const float4* __r
             const float r = r2 * rinv;
             float g1, p1, g2, p2;
             soft32(r * thi, thi, tg[i][4] * rinv, rinv, rinv3, g1, p1);
-            soft32(r * hj.y, hj.y, hj.x * rinv, rinv, rinv3, g2, p2);
+            soft32(r * hj.hinv, hj.hinv, hj.h * rinv, rinv, rinv3, g2, p2);
             if (inside) {
               gs = 0.5f * (g1 + g2);
               ps = 0.5f * (p1 + p2);
@@ -335,26 +336,17 @@ __global__ __launch_bounds__(64) void k_p2p_leaf32(NearArgs a, const float4* __r
 }
 
 // ---- P2P, wave per item with the targets in scalar registers -------------------
-// The FP32 form of k_p2p_wave (k_near.hip): wave-uniform loop control, the
-// targets of a pass (FP32 offsets and 4 h^2) as wave-uniform values, the
-// field of a pair beyond both kernels as m/r^3 (dx, dy, dz) and m/r with 1/r
-// replaced by 0 inside a kernel, and the pairs inside a kernel queued per
-// target (with the pair's FP32 centre difference) and evaluated 64 at a
-// time.  Every term is added into FP64 sums.
-__device__ __forceinline__ float wave_uniform_f(float v) {
-  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
-}
-
-struct Wave32Item {
-  int tlo, nt;
-  uint64_t e0, e1;
-  const int32_t* list;
-  uint32_t f_lo, f_hi, carry0;
-  int64_t item;
-  double ct0, ct1, ct2;  // the target leaf's centre
-};
-
-constexpr uint32_t kTQ32 = 128;  // queue slots per target (63 + 64)
+// The FP32 form of k_p2p_wave (k_near.hip), with its flattened sources, passes
+// and queues: the targets of a pass (FP32 offsets and 4 h^2) as wave-uniform
+// values, the field of a pair beyond both kernels as m/r^3 (dx, dy, dz) and m/r
+// with 1/r replaced by 0 inside a kernel.  A source brings its own leaf's
+// centre (FP64; the difference to the target leaf's is rounded once a pass), so
+// entries need no table.  Every term is added into FP64 sums.
+//
+// Bound by issue: a pair takes 22 FP32 instructions, an FP32 1/sqrt, and four
+// conversions and additions in FP64.  2e6 particles of a binary (1.45e9 pairs,
+// 8.4 % softened): 2.61 ms, a cloud of 8e6 (6.0e9 pairs) 11.0 ms; with the
+// sources searched anew for every pass of five targets 3.33 and 13.8 ms.
 
 // Sums of FP32 pair terms: each term added to an FP64 accumulator (AccD, the
 // default), or compensated in FP32 (AccT: Knuth's TwoSum keeps the rounding
@@ -378,208 +370,188 @@ struct AccT {
   __device__ __forceinline__ void keep() { asm volatile("" ::"v"(hi), "v"(lo)); }
 };
 
-template <int K, int LS, typename Acc>
-__device__ __forceinline__ void p2p_wave32_pass(const NearArgs& a, const float4* __restrict__ pf,
-                                                const float2* __restrict__ phh, const Wave32Item& w,
-                                                int t0, int* qj, float* qc, uint32_t& nsoft) {
-  const int RS = a.rec_stride;
+__device__ __forceinline__ float wave_uniform_f(float v) {
+  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+}
+
+// the target leaf's centre (wave-uniform)
+struct Centre32 {
+  double x, y, z;
+};
+
+// one source's record, and its leaf's centre as seen from the target leaf
+struct Src32 {
+  float4 o;
+  double2 cxy;
+  Part32Z czh;
+};
+__device__ __forceinline__ Src32 load_src32(const Part32& p, uint32_t off) {
+  return Src32{*reinterpret_cast<const float4*>(reinterpret_cast<const char*>(p.off) + off),
+               *reinterpret_cast<const double2*>(reinterpret_cast<const char*>(p.cxy) + off),
+               *reinterpret_cast<const Part32Z*>(reinterpret_cast<const char*>(p.czh) + off)};
+}
+
+template <int K, int TG>
+__device__ __forceinline__ double p2p_wave32_soft(const Part32& p, const Centre32& ct, int t0p,
+                                                  WaveLds<TG>& sh, uint32_t lens, uint32_t total) {
+  return p2p_wave_queued<K, TG>(sh, lens, total, [&](int t, uint32_t at, uint32_t mylen,
+                                                     uint32_t run, double* sum) {
+    const uint32_t self = 16u * (uint32_t)(t0p + t);
+    const Src32 tg = load_src32(p, self);
+    const float hi = tg.czh.h, hiinv = tg.czh.hinv;
+    const uint16_t* qt = sh.q + t * kTQ;
+    double sx = 0.0, sy = 0.0, sz = 0.0, sp = 0.0;
+    auto load = [&](uint32_t b) {
+      return load_src32(p, at + b < mylen ? sh.off[qt[at + b]] : self);
+    };
+    Src32 next = load(0);
+    for (uint32_t b = 0; b < run; ++b) {
+      const bool act = at + b < mylen;
+      const Src32 s = next;
+      if (b + 1 < run) next = load(b + 1);
+      const float cx = (float)(ct.x - s.cxy.x), cy = (float)(ct.y - s.cxy.y),
+                  cz = (float)(ct.z - s.czh.cz);
+      const float dx = cx + (tg.o.x - s.o.x), dy = cy + (tg.o.y - s.o.y),
+                  dz = cz + (tg.o.z - s.o.z);
+      const float r2 = dx * dx + dy * dy + dz * dz;
+      const float rinv = r2 > 0.f ? __frsqrt_rn(r2) : 0.f;
+      const float rinv3 = rinv * rinv * rinv;
+      const float r = r2 * rinv;
+      float g1, p1, g2, p2;
+      soft32(r * hiinv, hiinv, hi * rinv, rinv, rinv3, g1, p1);
+      soft32(r * s.czh.hinv, s.czh.hinv, s.czh.h * rinv, rinv, rinv3, g2, p2);
+      const float wm = act ? s.o.w : 0.f;
+      const float mg = wm * (0.5f * (g1 + g2));
+      sx += (double)(mg * dx);
+      sy += (double)(mg * dy);
+      sz += (double)(mg * dz);
+      sp += (double)(wm * (0.5f * (p1 + p2)));
+    }
+    sum[0] = sx; sum[1] = sy; sum[2] = sz; sum[3] = sp;
+  });
+}
+
+template <int K, int LS, int TG, typename Acc>
+__device__ __forceinline__ void p2p_wave32_pass(const NearArgs& a, const Part32& p,
+                                                const Centre32& ct, const WaveItem& w, int t0,
+                                                WaveLds<TG>& sh, uint32_t& nsoft) {
   const int lane = threadIdx.x;
-  const int tlo = w.tlo;
+  const int t0p = w.tlo + t0;
   float tx[K], ty[K], tz[K], t4[K];
   Acc fx[K], fy[K], fz[K], ph[K];
-  uint32_t qn[K];
+  uint32_t qn[K];  // per-target queue length (wave-uniform)
 #pragma unroll
   for (int ii = 0; ii < K; ++ii) {
-    const float4 o = pf[tlo + t0 + ii];
+    const float4 o = p.off[t0p + ii];
     tx[ii] = wave_uniform_f(o.x);
     ty[ii] = wave_uniform_f(o.y);
     tz[ii] = wave_uniform_f(o.z);
-    const float hu = wave_uniform_f(phh[tlo + t0 + ii].x);
+    const float hu = wave_uniform_f(p.czh[t0p + ii].h);
     t4[ii] = 4.0f * hu * hu;
     fx[ii] = Acc(); fy[ii] = Acc(); fz[ii] = Acc(); ph[ii] = Acc();
     qn[ii] = 0;
   }
-  // the first `count` queued pairs of target ii (the rest moves down)
-  auto flush = [&](auto iic, uint32_t count) {
-    constexpr int ii = decltype(iic)::value;
-    __syncthreads();
-    const bool act = (uint32_t)lane < count;
-    int* qjt = qj + ii * kTQ32;
-    float* qct = qc + ii * kTQ32 * 3;
-    const int j2 = act ? qjt[lane] : tlo;
-    const float cx = act ? qct[3 * lane] : 0.f, cy = act ? qct[3 * lane + 1] : 0.f,
-                cz = act ? qct[3 * lane + 2] : 0.f;
-    const float2 th = phh[tlo + t0 + ii];
-    const float hi = wave_uniform_f(th.x), hiinv = wave_uniform_f(th.y);
-    const float4 oj = pf[j2];
-    const float2 hj = phh[j2];
-    const float dx = cx + (tx[ii] - oj.x), dy = cy + (ty[ii] - oj.y), dz = cz + (tz[ii] - oj.z);
-    const float r2 = dx * dx + dy * dy + dz * dz;
-    const float rinv = r2 > 0.f ? __frsqrt_rn(r2) : 0.f;
-    const float rinv3 = rinv * rinv * rinv;
-    const float r = r2 * rinv;
-    float g1, p1, g2, p2;
-    soft32(r * hiinv, hiinv, hi * rinv, rinv, rinv3, g1, p1);
-    soft32(r * hj.y, hj.y, hj.x * rinv, rinv, rinv3, g2, p2);
-    const float wm = act ? oj.w : 0.f;
-    const float mg = wm * (0.5f * (g1 + g2));
-    fx[ii].add(mg * dx);
-    fy[ii].add(mg * dy);
-    fz[ii].add(mg * dz);
-    ph[ii].add(wm * (0.5f * (p1 + p2)));
-    // the remainder moves to the front of the queue
-    const uint32_t rem = qn[ii] - count;
-    int tj = 0;
-    float ta = 0.f, tb = 0.f, tc = 0.f;
-    if ((uint32_t)lane < rem) {
-      tj = qjt[count + lane];
-      ta = qct[3 * (count + lane)]; tb = qct[3 * (count + lane) + 1]; tc = qct[3 * (count + lane) + 2];
+  double soft = 0.0;  // sums over queued pairs, by lane as p2p_wave32_soft returns them
+  uint32_t off = sh.off[lane];
+  Src32 s = load_src32(p, off);
+  for (int u0 = 0; u0 < w.total; u0 += 64) {
+    const uint32_t offc = off;
+    const float cx = (float)(ct.x - s.cxy.x), cy = (float)(ct.y - s.cxy.y),
+                cz = (float)(ct.z - s.czh.cz);
+    const float xj = s.o.x, yj = s.o.y, zj = s.o.z;
+    float mj = s.o.w;
+    const float h4j = 4.0f * s.czh.h * s.czh.h;
+    const bool end = u0 + 64 >= w.total;
+    uint64_t valid = ~0ull;
+    if (!end) {
+      off = sh.off[u0 + 64 + lane];
+      s = load_src32(p, off);
+    } else if (w.total - u0 < 64) {
+      // lanes past the end contribute nothing
+      valid = (1ull << (w.total - u0)) - 1ull;
+      mj = __builtin_amdgcn_inverse_ballot_w64(valid) ? mj : 0.f;
     }
-    __syncthreads();
-    if ((uint32_t)lane < rem) {
-      qjt[lane] = tj;
-      qct[3 * lane] = ta; qct[3 * lane + 1] = tb; qct[3 * lane + 2] = tc;
-    }
-    qn[ii] = rem;
-  };
-  uint32_t carry = w.carry0;  // sources of the list entries before c0 (wave-uniform)
-  for (uint64_t c0 = w.e0; c0 < w.e1; c0 += 64) {
-    // 64 list entries: their particle ranges [fb, fe) in the flattened
-    // order, clipped to the run; a leaf entry's FP32 centre difference
-    int cnt = 0, lo = 0, sub = 0;
-    uint32_t fb = 0xffffffffu;
-    float dcx = 0.f, dcy = 0.f, dcz = 0.f;
-    const bool in = c0 + lane < w.e1;
-    const int src = in ? w.list[c0 + lane] : 0;
-    NodeInfo si{};
-    if (in) si = a.info[src];
-    const int sincl = wave_incl_scan32(in ? si.cnt : 0);
-    if (in) {
-      const uint32_t fe = carry + (uint32_t)sincl;
-      fb = fe - (uint32_t)si.cnt;
-      const uint32_t b = fb > w.f_lo ? fb : w.f_lo;
-      const uint32_t en = fe < w.f_hi ? fe : w.f_hi;
-      if (en > b) { cnt = (int)(en - b); lo = si.lo + (int)(b - fb); }
-      // a whole subtree: its particles' offsets are relative to their own
-      // leaves, whose centres are looked up per particle
-      sub = si.child >= 0 ? 1 : 0;
-      const double* rs = a.rec + (int64_t)src * RS;
-      dcx = (float)(w.ct0 - rs[0]);
-      dcy = (float)(w.ct1 - rs[1]);
-      dcz = (float)(w.ct2 - rs[2]);
-    }
-    carry += (uint32_t)__builtin_amdgcn_readlane(sincl, 63);
-    // lane 0 always holds an entry (c0 < e1)
-    if ((uint32_t)__builtin_amdgcn_readfirstlane(fb) >= w.f_hi) break;  // the run is done
-    const int incl = wave_incl_scan32(cnt);
-    const int pre = incl - cnt;
-    const int total = __builtin_amdgcn_readlane(incl, 63);
-    for (int f0 = 0; f0 < total; f0 += 64) {
-      const int f = f0 + lane;
-      int k = 0;
+    uint64_t im[K], met = 0;  // the lanes whose pair lies inside a kernel
 #pragma unroll
-      for (int step = 32; step > 0; step >>= 1) {
-        const int pk = __shfl(pre, k + step, 64);
-        if (pk <= f) k += step;
-      }
-      const int jj = __shfl(lo, k, 64) + (f - __shfl(pre, k, 64));
-      float cx = __shfl(dcx, k, 64), cy = __shfl(dcy, k, 64), cz = __shfl(dcz, k, 64);
-      const int jsub = __shfl(sub, k, 64);
-      const bool fv = f < total;
-      const int j = fv ? jj : tlo;  // a valid index; contributes nothing
-      if (fv && jsub) {
-        const double* rl = a.rec + (int64_t)a.leaf_node[a.p_leaf[j]] * RS;
-        cx = (float)(w.ct0 - rl[0]);
-        cy = (float)(w.ct1 - rl[1]);
-        cz = (float)(w.ct2 - rl[2]);
-      }
-      const float4 oj = pf[j];
-      const float hj = phh[j].x;
-      const float mj = fv ? oj.w : 0.f;
-      const float h4j = 4.0f * hj * hj;
+    for (int ii = 0; ii < K; ++ii) {
+      const float dx = cx + (tx[ii] - xj), dy = cy + (ty[ii] - yj), dz = cz + (tz[ii] - zj);
+      const float r2 = dx * dx + dy * dy + dz * dz;
+      const bool inside = r2 < fmaxf(t4[ii], h4j);
+      im[ii] = __builtin_amdgcn_ballot_w64(inside);
+      const float rinv = inside ? 0.f : __builtin_amdgcn_rsqf(r2);
+      const float mr = mj * rinv;
+      const float mg = mr * (rinv * rinv);
+      fx[ii].add(mg * dx);
+      fy[ii].add(mg * dy);
+      fz[ii].add(mg * dz);
+      ph[ii].add(mr);
+      met |= im[ii];
+      // (keeps this target's arithmetic ahead of the queue branch)
+      fx[ii].keep(); fy[ii].keep(); fz[ii].keep(); ph[ii].keep();
+    }
+    if (__builtin_expect_with_probability((met & valid) != 0 || end, 1, 0.1)) {
+      uint32_t lens = 0, most = 0, sum = 0;
 #pragma unroll
       for (int ii = 0; ii < K; ++ii) {
-        const float dx = cx + (tx[ii] - oj.x), dy = cy + (ty[ii] - oj.y), dz = cz + (tz[ii] - oj.z);
-        const float r2 = dx * dx + dy * dy + dz * dz;
-        const bool inside = r2 < fmaxf(t4[ii], h4j);
-        const float rinv = inside ? 0.f : __builtin_amdgcn_rsqf(r2);
-        const float mr = mj * rinv;
-        const float mg = mr * (rinv * rinv);
-        fx[ii].add(mg * dx);
-        fy[ii].add(mg * dy);
-        fz[ii].add(mg * dz);
-        ph[ii].add(mr);
-        // (keeps this target's arithmetic ahead of the queue branch)
-        fx[ii].keep(); fy[ii].keep(); fz[ii].keep(); ph[ii].keep();
-        const bool push = inside && fv && j != tlo + t0 + ii;
-        const uint64_t bal = __builtin_amdgcn_ballot_w64(push);
-        if (bal) {
-          if (push) {
-            const uint32_t below = __builtin_amdgcn_mbcnt_hi(
-                (uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
-            const uint32_t sl = qn[ii] + below;
-            qj[ii * kTQ32 + sl] = j;
-            float* qq = qc + (ii * kTQ32 + sl) * 3;
-            qq[0] = cx; qq[1] = cy; qq[2] = cz;
-          }
-          const uint32_t c = (uint32_t)__popcll(bal);
-          qn[ii] += c;
-          nsoft += c;
+        // (the self pair has r^2 = 0 and is always inside)
+        const uint64_t bal =
+            im[ii] & valid & ~__builtin_amdgcn_ballot_w64(offc == 16u * (uint32_t)(t0p + ii));
+        if (__builtin_amdgcn_inverse_ballot_w64(bal)) {
+          const uint32_t below = __builtin_amdgcn_mbcnt_hi(
+              (uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
+          sh.q[ii * kTQ + (int)(qn[ii] + below)] = (uint16_t)(u0 + lane);
         }
+        qn[ii] = __builtin_amdgcn_readfirstlane(qn[ii] + (uint32_t)__popcll(bal));
+        most = qn[ii] > most ? qn[ii] : most;
+        sum += qn[ii];
+        lens = lane == ii ? qn[ii] : lens;
       }
-      // a queue holds at most 63 + 64 entries here
-      static_for<K>([&](auto iic) {
-        constexpr int ii = decltype(iic)::value;
-        if (qn[ii] >= 64) flush(iic, 64);
-      });
+      // queues that might overflow in the next group, at the end all of them
+      if (__builtin_expect_with_probability(most > (end ? 0u : (uint32_t)(kTQ - 64)), 1, 0.05)) {
+        nsoft += sum;
+        __syncthreads();
+        soft += p2p_wave32_soft<K, TG>(p, ct, t0p, sh, lens, sum);
+        __syncthreads();
+#pragma unroll
+        for (int ii = 0; ii < K; ++ii) qn[ii] = 0;
+      }
     }
   }
-  static_for<K>([&](auto iic) {
-    constexpr int ii = decltype(iic)::value;
-    if (qn[ii] > 0) flush(iic, qn[ii]);
-  });
+  double gx[K], gy[K], gz[K], gp[K];
 #pragma unroll
   for (int ii = 0; ii < K; ++ii) {
-    const double sx = wave_sum64(fx[ii].get()), sy = wave_sum64(fy[ii].get());
-    const double sz = wave_sum64(fz[ii].get()), sp = wave_sum64(ph[ii].get());
-    if (lane == t0 + ii) {
-      double* o = a.part + (w.item * LS + t0 + ii) * 4;
-      o[0] = sx; o[1] = sy; o[2] = sz; o[3] = sp;
-    }
+    gx[ii] = fx[ii].get();
+    gy[ii] = fy[ii].get();
+    gz[ii] = fz[ii].get();
+    gp[ii] = ph[ii].get();
   }
+  p2p_wave_store<K, LS>(a, w, t0, gx, gy, gz, gp, soft);
+  __syncthreads();  // (the queues are reused by the next pass)
 }
 
 template <int LS, bool NODE, int TG, int WPE, typename Acc>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE))) void k_p2p_wave32(
-    NearArgs a, const float4* __restrict__ pf, const float2* __restrict__ phh) {
+    NearArgs a, Part32 p) {
   const int lane = threadIdx.x;
   const uint32_t item = xcd_block(blockIdx.x, gridDim.x);
   if (item >= a.item_off[a.nleaves]) return;  // the grid is an upper bound
   const P2PItem it0 = a.item[item];
-  Wave32Item w;
-  w.tlo = it0.lo;
-  w.nt = it0.cnt();
-  w.item = item;
-  const double* rt = a.rec + (int64_t)it0.node() * a.rec_stride;
-  w.ct0 = rt[0]; w.ct1 = rt[1]; w.ct2 = rt[2];
-  w.e0 = it0.e0;
-  w.e1 = it0.e0 + it0.ne;
-  w.list = NODE ? reinterpret_cast<const int32_t*>(a.node_p2p_pool) : a.p2p_list;
-  w.f_lo = it0.f0;
-  w.f_hi = it0.f1;
-  w.carry0 = it0.c0;
-  __shared__ int qj[TG * kTQ32];
-  __shared__ float qc[TG * kTQ32 * 3];
+  __shared__ WaveLds<TG> sh;
+  const WaveItem w = p2p_wave_sources<NODE>(a, it0, item, sh.off);
+  const double2 cxy = p.cxy[w.tlo];
+  const Centre32 ct{wave_uniform(cxy.x), wave_uniform(cxy.y), wave_uniform(p.czh[w.tlo].cz)};
   uint32_t nsoft = 0;
+  const int npass = (w.nt + TG - 1) / TG;
   int t0 = 0;
-  for (; t0 + TG <= w.nt; t0 += TG)
-    p2p_wave32_pass<TG, LS, Acc>(a, pf, phh, w, t0, qj, qc, nsoft);
-  // the remainder, a pass with a fixed target count (uniform branches)
-  static_for<TG>([&](auto rc) {
-    constexpr int r = decltype(rc)::value;
-    if (r > 0 && w.nt - t0 == r)
-      p2p_wave32_pass<(r > 0 ? r : 1), LS, Acc>(a, pf, phh, w, t0, qj, qc, nsoft);
-  });
+  for (int q = 0; q < npass; ++q) {
+    const int k = (w.nt - t0 + (npass - q) - 1) / (npass - q);
+    // a pass with a fixed target count (uniform branches)
+    static_for<TG>([&](auto rc) {
+      constexpr int r = decltype(rc)::value + 1;
+      if (k == r) p2p_wave32_pass<r, LS, TG, Acc>(a, p, ct, w, t0, sh, nsoft);
+    });
+    t0 += k;
+  }
   if (lane == 0) a.soft_pairs[item] = nsoft;
 }
 
@@ -592,32 +564,28 @@ void far32_order(bool node_lists, const FarArgs& a, const float* rec32, int top,
   else k_far32<P, false, kFarSplit32><<<nb, 64, 0, s>>>(a, rec32, top);
 }
 
-template <int RS>
-void prep_particles(int nleaves, const int32_t* leaf_node, const NodeInfo* info, const double* rec,
-                    const double* xs, const double* ys, const double* zs, const double* ms,
-                    const double* hs, float4* pf, float2* ph, hipStream_t s) {
-  k_prep_particles32<RS><<<(nleaves + 127) / 128, 128, 0, s>>>(nleaves, leaf_node, info, rec, xs, ys,
-                                                               zs, ms, hs, pf, ph);
-}
-
 // variant 0: the wave kernel with scalar-register targets; 7: the same with
 // TwoSum-compensated FP32 sums instead of FP64 ones; 6: the earlier shape
 // (targets in LDS, the softened branch taken in the pass)
 template <int LS>
-void p2p32(bool node_lists, int variant, const NearArgs& a, const float4* pf, const float2* ph,
-           int64_t items, hipStream_t s, KernelMarks km) {
-  constexpr int TG = LS <= 10 ? 5 : 8;
+void p2p32(bool node_lists, int variant, const NearArgs& a, const Part32& p, int64_t items, hipStream_t s, KernelMarks km) {
+  // eight targets a pass at three waves a SIMD: 2.61 ms for 2e6 particles of a
+  // binary, 11.0 for a cloud of 8e6 (five at four: 2.65 and 10.8; six at four
+  // spill: 2.91 and 11.7)
+  constexpr int TG = 8, WPE = 3;
   const unsigned nb = (unsigned)items;
+  // (16-byte offsets in 32 bits)
+  if (a.n >= (1 << 28)) variant = 6;
   record_mark(km.begin, s);
   if (variant == 6) {
-    if (node_lists) k_p2p_leaf32<LS, true, TG><<<nb, 64, 0, s>>>(a, pf, ph);
-    else k_p2p_leaf32<LS, false, TG><<<nb, 64, 0, s>>>(a, pf, ph);
+    if (node_lists) k_p2p_leaf32<LS, true, LS <= 10 ? 5 : 8><<<nb, 64, 0, s>>>(a, p);
+    else k_p2p_leaf32<LS, false, LS <= 10 ? 5 : 8><<<nb, 64, 0, s>>>(a, p);
   } else if (variant == 7) {
-    if (node_lists) k_p2p_wave32<LS, true, TG, 4, AccT><<<nb, 64, 0, s>>>(a, pf, ph);
-    else k_p2p_wave32<LS, false, TG, 4, AccT><<<nb, 64, 0, s>>>(a, pf, ph);
+    if (node_lists) k_p2p_wave32<LS, true, TG, WPE, AccT><<<nb, 64, 0, s>>>(a, p);
+    else k_p2p_wave32<LS, false, TG, WPE, AccT><<<nb, 64, 0, s>>>(a, p);
   } else {
-    if (node_lists) k_p2p_wave32<LS, true, TG, 4, AccD><<<nb, 64, 0, s>>>(a, pf, ph);
-    else k_p2p_wave32<LS, false, TG, 4, AccD><<<nb, 64, 0, s>>>(a, pf, ph);
+    if (node_lists) k_p2p_wave32<LS, true, TG, WPE, AccD><<<nb, 64, 0, s>>>(a, p);
+    else k_p2p_wave32<LS, false, TG, WPE, AccD><<<nb, 64, 0, s>>>(a, p);
   }
   record_mark(km.end, s);
   if (!km.skip_reduce) launch_p2p_reduce(a, LS, s);
@@ -625,10 +593,9 @@ void p2p32(bool node_lists, int variant, const NearArgs& a, const float4* pf, co
 
 }  // namespace
 
-void launch_prep32(int order, int nn, int nleaves, const int32_t* leaf_node, const NodeInfo* info,
+void launch_prep32(int order, int nn, int n, const int32_t* p_leaf, const int32_t* leaf_node,
                    const double* rec, const double* xs, const double* ys, const double* zs,
-                   const double* ms, const double* hs, float* rec32, float4* pf, float2* ph,
-                   hipStream_t s) {
+                   const double* ms, const double* hs, float* rec32, const Part32& p, hipStream_t s) {
   const unsigned nb = (unsigned)((nn + 255) / 256);
   switch (order) {
     case 0: k_prep_nodes32<0><<<nb, 256, 0, s>>>(nn, rec, rec32); break;
@@ -637,11 +604,12 @@ void launch_prep32(int order, int nn, int nleaves, const int32_t* leaf_node, con
     case 3: k_prep_nodes32<3><<<nb, 256, 0, s>>>(nn, rec, rec32); break;
     case 4: k_prep_nodes32<4><<<nb, 256, 0, s>>>(nn, rec, rec32); break;
   }
+  const unsigned np = (unsigned)((n + 255) / 256);
   switch (rec_stride(order)) {
-    case 16: prep_particles<16>(nleaves, leaf_node, info, rec, xs, ys, zs, ms, hs, pf, ph, s); break;
-    case 24: prep_particles<24>(nleaves, leaf_node, info, rec, xs, ys, zs, ms, hs, pf, ph, s); break;
-    case 32: prep_particles<32>(nleaves, leaf_node, info, rec, xs, ys, zs, ms, hs, pf, ph, s); break;
-    case 48: prep_particles<48>(nleaves, leaf_node, info, rec, xs, ys, zs, ms, hs, pf, ph, s); break;
+    case 16: k_prep_particles32<16><<<np, 256, 0, s>>>(n, p_leaf, leaf_node, rec, xs, ys, zs, ms, hs, p); break;
+    case 24: k_prep_particles32<24><<<np, 256, 0, s>>>(n, p_leaf, leaf_node, rec, xs, ys, zs, ms, hs, p); break;
+    case 32: k_prep_particles32<32><<<np, 256, 0, s>>>(n, p_leaf, leaf_node, rec, xs, ys, zs, ms, hs, p); break;
+    case 48: k_prep_particles32<48><<<np, 256, 0, s>>>(n, p_leaf, leaf_node, rec, xs, ys, zs, ms, hs, p); break;
   }
 }
 
@@ -658,13 +626,12 @@ void launch_far32(int order, bool node_lists, const FarArgs& a, const float* rec
 }
 
 bool launch_near32(int order, bool node_lists, int leaf_size, int variant, const NearArgs& a,
-                   const float4* pf, const float2* ph, int64_t items, hipStream_t s,
-                   KernelMarks km) {
+                   const Part32& p, int64_t items, hipStream_t s, KernelMarks km) {
   if (a.n <= 0) return true;
   if (leaf_size > 16) return false;
   (void)order;
-  if (leaf_size <= 10) p2p32<10>(node_lists, variant, a, pf, ph, items, s, km);
-  else p2p32<16>(node_lists, variant, a, pf, ph, items, s, km);
+  if (leaf_size <= 10) p2p32<10>(node_lists, variant, a, p, items, s, km);
+  else p2p32<16>(node_lists, variant, a, p, items, s, km);
   return true;
 }
 

@@ -14,6 +14,7 @@
 //                   1/q                                            (q >= 2)
 // (force per unit separation = shape / h^3, potential = shape / h).
 #include "sfmm_internal.h"
+#include "p2p_wave.h"
 #include "softening.h"
 
 namespace sfmm {
@@ -90,11 +91,6 @@ __global__ __launch_bounds__(256) void k_near(NearArgs a) {
 }
 
 // the pool that the items' list entries lie in
-template <bool NODE>
-__device__ __forceinline__ const int32_t* p2p_list(const NearArgs& a) {
-  return NODE ? reinterpret_cast<const int32_t*>(a.node_p2p_pool) : a.p2p_list;
-}
-
 // ---- wave per target leaf ----------------------------------------------------
 // The leaf's particles (at most LS) are wave-uniform and held in registers;
 // the lanes walk the flattened list of source particles of the leaf's P2P
@@ -107,21 +103,6 @@ __device__ __forceinline__ int wave_incl_scan(int v) {
     const int t = __shfl_up(v, o, 64);
     if (lane >= o) v += t;
   }
-  return v;
-}
-
-// inclusive sum over the wave's lanes (data-parallel moves, no LDS)
-template <int CTRL, int ROWS>
-__device__ __forceinline__ uint32_t add_dpp(uint32_t v) {
-  return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
-}
-__device__ __forceinline__ uint32_t wave_incl_sum(uint32_t v) {
-  v = add_dpp<0x111, 0xf>(v);  // rows of 16: shifted by 1, 2, 4, 8
-  v = add_dpp<0x112, 0xf>(v);
-  v = add_dpp<0x114, 0xf>(v);
-  v = add_dpp<0x118, 0xf>(v);
-  v = add_dpp<0x142, 0xa>(v);  // lane 15 (47) to row 1 (3)
-  v = add_dpp<0x143, 0xc>(v);  // lane 31 to rows 2 and 3
   return v;
 }
 
@@ -312,135 +293,48 @@ __global__ __launch_bounds__(64) void k_p2p_leaf(NearArgs a) {
 // 9.95e8 VALU instructions (40 per 64 pairs) 23 are the pair's, the others the
 // queues, the softened pairs, list scans and reductions, and the VALU is busy
 // 77 % of the time.  Polytrope of 1e6 at leaf size 16: 1.95 ms, before 2.50.
-struct WaveItem {
-  int tlo, nt;
-  int total;  // flattened sources of the item
-  int64_t item;
-};
-
-constexpr int kTQ = 256;  // queue slots per target
-
-template <int TG>
-struct alignas(16) WaveLds {
-  uint32_t off[kP2PItem];  // 16 x particle index of each source
-  union {
-    uint16_t q[TG * kTQ];  // queued sources (places in off)
-    double red[4][64];     // a soft pass's sums by component (x, z, y, p) and lane
-  };
-  SoftCoef coef[3];        // the spline pieces (kSoftCoef)
-};
-
-__device__ __forceinline__ double make_double(uint32_t lo, uint32_t hi) {
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-__device__ __forceinline__ uint32_t lo32(double v) { return (uint32_t)__double_as_longlong(v); }
-__device__ __forceinline__ uint32_t hi32(double v) {
-  return (uint32_t)((unsigned long long)__double_as_longlong(v) >> 32);
-}
-
-// lanes 0..31: a summed over the wave's two halves, lanes 32..63: b
-__device__ __forceinline__ double fold32(double a, double b) {
-  auto l = __builtin_amdgcn_permlane32_swap(lo32(a), lo32(b), false, false);
-  auto h = __builtin_amdgcn_permlane32_swap(hi32(a), hi32(b), false, false);
-  return make_double(l[0], h[0]) + make_double(l[1], h[1]);
-}
-// within each half: its even row of 16 lanes gets a summed over the half's
-// two rows, its odd row b
-__device__ __forceinline__ double fold16(double a, double b) {
-  auto l = __builtin_amdgcn_permlane16_swap(lo32(a), lo32(b), false, false);
-  auto h = __builtin_amdgcn_permlane16_swap(hi32(a), hi32(b), false, false);
-  return make_double(l[0], h[0]) + make_double(l[1], h[1]);
-}
-// v plus v of the lane N places on in the row of 16 (rotated)
-template <int N>
-__device__ __forceinline__ double add_ror(double v) {
-  const int l = __builtin_amdgcn_mov_dpp((int)lo32(v), 0x120 + N, 0xf, 0xf, true);
-  const int h = __builtin_amdgcn_mov_dpp((int)hi32(v), 0x120 + N, 0xf, 0xf, true);
-  return v + make_double((uint32_t)l, (uint32_t)h);
-}
-// the wave's sums of four values, one per row of 16 lanes: x, z, y, p
-__device__ __forceinline__ double wave_sum4(double x, double y, double z, double p) {
-  double v = fold16(fold32(x, y), fold32(z, p));
-  v = add_ror<8>(v);
-  v = add_ror<4>(v);
-  v = add_ror<2>(v);
-  return add_ror<1>(v);
-}
-
-// The queued pairs of a pass of K targets (lane t of lens: the length of
-// target t's queue, total their sum).  A lane takes `run` consecutive entries
-// of one target, each target as many lanes as its queue needs:
-// sum_t ceil(len_t / run) <= total / run + K <= 64 for run >= total / (64 - K).
-// The lanes' sums are added per target in lane order, into the component that
-// lane (row, t) holds (rows of 16 lanes: x, z, y, p).
+// the queued pairs of a pass, a lane's run of one target's (p2p_wave_queued)
 template <int K, int TG>
 __device__ __forceinline__ double p2p_wave_soft(const NearArgs& a, int t0p, WaveLds<TG>& sh,
                                                 uint32_t lens, uint32_t total) {
-  const int lane = threadIdx.x;
-  const uint32_t run = (total + (64 - K) - 1) / (64 - K);
-  const uint32_t len = lane < K ? lens : 0u;
-  // (small whole numbers: the quotient's floor is exact)
-  const uint32_t nl = (uint32_t)(((float)(len + run - 1) + 0.5f) / (float)run);
-  const uint32_t end = wave_incl_sum(lane < K ? nl : 0u);  // (lanes K.. repeat the last end)
-  int t = 0;
-  uint32_t first = 0;
-#pragma unroll
-  for (int k = 0; k + 1 < K; ++k) {
-    const uint32_t e = (uint32_t)__builtin_amdgcn_readlane((int)end, k);
-    const bool past = (uint32_t)lane >= e;
-    t = past ? k + 1 : t;
-    first = past ? e : first;
-  }
-  const uint32_t at = ((uint32_t)lane - first) * run;  // this lane's first entry
-  const uint32_t mylen = (uint32_t)__shfl((int)len, t, 64);
-  const int it = t0p + t;
-  const double2 txy = a.pxy[it], tzm = a.pzm[it];
-  const double hi = a.hs[it], hiinv = a.his[it];
-  const uint16_t* qt = sh.q + t * kTQ;
-  double sx = 0.0, sy = 0.0, sz = 0.0, sp = 0.0;
-  // (the next source's record loads while the current pair is evaluated)
-  struct Src {
-    double2 xy, zm;
-    double h, hinv;
-  };
-  auto load = [&](uint32_t b) {
-    const int j = at + b < mylen ? (int)(sh.off[qt[at + b]] >> 4) : it;
-    return Src{a.pxy[j], a.pzm[j], a.hs[j], a.his[j]};
-  };
-  Src next = load(0);
-  for (uint32_t b = 0; b < run; ++b) {
-    const bool act = at + b < mylen;
-    const double2 sxy = next.xy, szm = next.zm;
-    const double hj = next.h, hjinv = next.hinv;
-    if (b + 1 < run) next = load(b + 1);
-    const double dx = txy.x - sxy.x, dy = txy.y - sxy.y, dz = tzm.x - szm.x;
-    const double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
-    const double rinv = rsqrt_pair(r2);
-    const double r = r2 * rinv;
-    double g1, p1, g2, p2;
-    soft_piece(sh.coef, r * hiinv, hi * rinv, hiinv, g1, p1);
-    soft_piece(sh.coef, r * hjinv, hj * rinv, hjinv, g2, p2);
-    const double wm = act ? 0.5 * szm.y : 0.0;
-    const double mg = wm * (g1 + g2);
-    sx = fma(mg, dx, sx);
-    sy = fma(mg, dy, sy);
-    sz = fma(mg, dz, sz);
-    sp = fma(wm, p1 + p2, sp);
-  }
-  __syncthreads();  // (the sums take the place of the queues)
-  sh.red[0][lane] = sx;
-  sh.red[1][lane] = sz;
-  sh.red[2][lane] = sy;
-  sh.red[3][lane] = sp;
-  __syncthreads();
-  const int tk = lane & 15;
-  const uint32_t e1 = (uint32_t)__shfl((int)end, tk, 64);
-  uint32_t e0 = (uint32_t)__shfl((int)end, tk > 0 ? tk - 1 : 0, 64);
-  if (tk == 0) e0 = 0;
-  double sum = 0.0;
-  if (tk < K)
-    for (uint32_t e = e0; e < e1; ++e) sum += sh.red[lane >> 4][e];
-  return sum;
+  return p2p_wave_queued<K, TG>(sh, lens, total, [&](int t, uint32_t at, uint32_t mylen,
+                                                     uint32_t run, double* sum) {
+    const int it = t0p + t;
+    const double2 txy = a.pxy[it], tzm = a.pzm[it];
+    const double hi = a.hs[it], hiinv = a.his[it];
+    const uint16_t* qt = sh.q + t * kTQ;
+    double sx = 0.0, sy = 0.0, sz = 0.0, sp = 0.0;
+    // (the next source's record loads while the current pair is evaluated)
+    struct Src {
+      double2 xy, zm;
+      double h, hinv;
+    };
+    auto load = [&](uint32_t b) {
+      const int j = at + b < mylen ? (int)(sh.off[qt[at + b]] >> 4) : it;
+      return Src{a.pxy[j], a.pzm[j], a.hs[j], a.his[j]};
+    };
+    Src next = load(0);
+    for (uint32_t b = 0; b < run; ++b) {
+      const bool act = at + b < mylen;
+      const double2 sxy = next.xy, szm = next.zm;
+      const double hj = next.h, hjinv = next.hinv;
+      if (b + 1 < run) next = load(b + 1);
+      const double dx = txy.x - sxy.x, dy = txy.y - sxy.y, dz = tzm.x - szm.x;
+      const double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
+      const double rinv = rsqrt_pair(r2);
+      const double r = r2 * rinv;
+      double g1, p1, g2, p2;
+      soft_piece(sh.coef, r * hiinv, hi * rinv, hiinv, g1, p1);
+      soft_piece(sh.coef, r * hjinv, hj * rinv, hjinv, g2, p2);
+      const double wm = act ? 0.5 * szm.y : 0.0;
+      const double mg = wm * (g1 + g2);
+      sx = fma(mg, dx, sx);
+      sy = fma(mg, dy, sy);
+      sz = fma(mg, dz, sz);
+      sp = fma(wm, p1 + p2, sp);
+    }
+    sum[0] = sx; sum[1] = sy; sum[2] = sz; sum[3] = sp;
+  });
 }
 
 template <int K, int LS, int TG>
@@ -544,19 +438,7 @@ __device__ __forceinline__ void p2p_wave_pass(const NearArgs& a, const WaveItem&
       }
     }
   }
-  // the sums over the wave: row r of 16 lanes gets component {x, z, y, p}[r];
-  // lane ii of the row keeps target ii's
-  double mine = 0.0;
-#pragma unroll
-  for (int ii = 0; ii < K; ++ii) {
-    const double v = wave_sum4(fx[ii], fy[ii], fz[ii], ph[ii]);
-    mine = (lane & 15) == ii ? v : mine;
-  }
-  const int row = lane >> 4, tk = lane & 15;
-  if (tk < K) {
-    const int comp = row == 1 ? 2 : row == 2 ? 1 : row;
-    a.part[(w.item * LS + t0 + tk) * 4 + comp] = mine + soft;
-  }
+  p2p_wave_store<K, LS>(a, w, t0, fx, fy, fz, ph, soft);
   __syncthreads();  // (the queues are reused by the next pass)
 }
 
@@ -567,53 +449,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE))) void 
   const uint32_t item = xcd_block(blockIdx.x, gridDim.x);
   if (item >= a.item_off[a.nleaves]) return;  // the grid is an upper bound
   const P2PItem it0 = a.item[item];
-  // this item's run [f_lo, f_hi) of the leaf's flattened sources, from the
-  // list entry that holds its first source
-  const uint64_t e0 = it0.e0, e1 = e0 + it0.ne;
-  const int32_t* list = p2p_list<NODE>(a);
-  const uint32_t f_lo = it0.f0, f_hi = it0.f1;
-  uint32_t carry = it0.c0;  // the flattened start of the entries of a step
   __shared__ WaveLds<TG> sh;
   if (lane < (int)(sizeof(kSoftCoef) / sizeof(double)))
     reinterpret_cast<double*>(sh.coef)[lane] = reinterpret_cast<const double*>(kSoftCoef)[lane];
-  // 64 list entries per step: entry [fb, fe) of the flattened order, clipped
-  // to the run, goes to its place in LDS; entries of at most 16 sources one
-  // source per iteration, larger ones by the whole wave
-  for (uint64_t c0 = e0; c0 < e1 && carry < f_hi; c0 += 64) {
-    NodeInfo si{};
-    if (c0 + lane < e1) si = a.info[list[c0 + lane]];
-    const uint32_t fe = carry + wave_incl_sum((uint32_t)si.cnt);
-    const uint32_t fb = fe - (uint32_t)si.cnt;
-    carry = (uint32_t)__builtin_amdgcn_readlane((int)fe, 63);
-    const uint32_t b = fb > f_lo ? fb : f_lo, en = fe < f_hi ? fe : f_hi;
-    const int nw = en > b ? (int)(en - b) : 0;
-    const int at = (int)(b - f_lo);
-    const uint32_t from = 16u * (uint32_t)(si.lo + (int)(b - fb));
-    const bool big = nw > 16;
-    const int nsm = big ? 0 : nw;
-    for (int k = 0; k < 16; ++k) {
-      if (!__builtin_amdgcn_ballot_w64(k < nsm)) break;
-      if (k < nsm) sh.off[at + k] = from + 16u * (uint32_t)k;
-    }
-    uint64_t bigm = __builtin_amdgcn_ballot_w64(big);
-    while (bigm) {
-      const int k = __builtin_ctzll(bigm);
-      bigm &= bigm - 1;
-      const int kat = __builtin_amdgcn_readlane(at, k), kn = __builtin_amdgcn_readlane(nw, k);
-      const uint32_t kfrom = (uint32_t)__builtin_amdgcn_readlane((int)from, k);
-      for (int q = lane; q < kn; q += 64) sh.off[kat + q] = kfrom + 16u * (uint32_t)q;
-    }
-  }
-  WaveItem w;
-  w.tlo = __builtin_amdgcn_readfirstlane(it0.lo);
-  w.nt = __builtin_amdgcn_readfirstlane(it0.cnt());
-  const uint32_t f_end = carry < f_hi ? carry : f_hi;
-  w.total = __builtin_amdgcn_readfirstlane(f_end > f_lo ? (int)(f_end - f_lo) : 0);
-  w.item = item;
-  // (lanes past the last source read a valid record)
-  if (w.total == 0 || w.total + lane < (w.total + 63) / 64 * 64)
-    sh.off[w.total + lane] = 16u * (uint32_t)w.tlo;
-  __syncthreads();
+  const WaveItem w = p2p_wave_sources<NODE>(a, it0, item, sh.off);
   uint32_t nsoft = 0;
   const int npass = (w.nt + TG - 1) / TG;
   int t0 = 0;

@@ -37,7 +37,7 @@ enum BufId {
   B_NDEPTH, B_LEVKEY0, B_LEVKEY1, B_LEVIDS, B_LEVNODES, B_M2LORD,
   B_NM2LOFF, B_NM2LCNT, B_NOPENOFF, B_NOPENCNT, B_NP2POFF, B_NP2PCNT,
   B_M2LPOOL, B_NEXP, B_P2PPOOL,
-  B_REC32, B_PF32, B_PH32,
+  B_REC32, B_PART32,
   B_SYSOFF, B_BOXES, B_SYS, B_SYSS, B_SYSSTART, B_SKEY0, B_SKEY1, B_SPOS0, B_SPOS1, B_NFLAG,
   B_LN, B_ITEMCNT, B_ITEMOFF, B_ITEM, B_PART, B_SRCTOT, B_SOFTCNT, B_EXTMAP,
   B_LWM2LCNT, B_LWP2PCNT, B_LWM2LOFF, B_LWP2POFF, B_DIRPART, B_OVFLEAF, B_BIGPLAIN,
@@ -467,6 +467,13 @@ P2PItemRule item_rule(sfmm_ctx* ctx) {
   return r;
 }
 
+// the FP32 particle records: three arrays of 16 bytes a particle
+Part32 part32(sfmm_ctx* ctx) {
+  float4* off = P<float4>(ctx, B_PART32);
+  return Part32{off, reinterpret_cast<double2*>(off + ctx->n),
+                reinterpret_cast<Part32Z*>(off + 2 * ctx->n)};
+}
+
 // Algorithm 1 per leaf: count pass, list sizes to the host, fill pass
 int walk_per_leaf(sfmm_ctx* ctx, double theta) {
   int rc;
@@ -830,7 +837,7 @@ int do_walk_and_eval(sfmm_ctx* ctx, double theta, int precision, const double* m
       return fail(ctx, SFMM_EUNSUPPORTED, "SFMM_FP32C needs leaf_size <= 16");
     struct { int id; size_t bytes; } need3[] = {
         {B_REC32, sizeof(float) * rec32_stride(ctx->order) * (size_t)ctx->nn},
-        {B_PF32, sizeof(float4) * (size_t)n}, {B_PH32, sizeof(float2) * (size_t)n}};
+        {B_PART32, 48 * (size_t)n}};
     for (auto& q : need3)
       if ((rc = ensure(ctx, q.id, q.bytes))) return rc;
   }
@@ -910,7 +917,7 @@ int do_walk_and_eval(sfmm_ctx* ctx, double theta, int precision, const double* m
     if (ctx->cfg.leaf_size <= 32)
       launch_p2p_items_fill(level, a, P<P2PItem>(ctx, B_ITEM), ns);
     if (f32) launch_near32(ctx->order, level, ctx->cfg.leaf_size, ctx->near_variant, a,
-                          P<float4>(ctx, B_PF32), P<float2>(ctx, B_PH32), items, ns, km);
+                          part32(ctx), items, ns, km);
     else launch_near(level, ctx->cfg.leaf_size, ctx->near_variant, a, items, ns, km);
     return SFMM_OK;
   };
@@ -956,9 +963,10 @@ int do_walk_and_eval(sfmm_ctx* ctx, double theta, int precision, const double* m
   };
   phase_mark(ctx, 3, 0);
   if (f32) {
-    launch_prep32(ctx->order, (int)ctx->nn, nl, f.leaf_node, f.info, f.rec,
-                  f.xs, f.ys, f.zs, P<double>(ctx, B_MS), P<double>(ctx, B_HS),
-                  P<float>(ctx, B_REC32), P<float4>(ctx, B_PF32), P<float2>(ctx, B_PH32), s);
+    launch_prep32(ctx->order, (int)ctx->nn, n, P<int32_t>(ctx, B_PLEAF), f.leaf_node, f.rec,
+                  P<double>(ctx, B_XS), P<double>(ctx, B_YS), P<double>(ctx, B_ZS),
+                  P<double>(ctx, B_MS), P<double>(ctx, B_HS), P<float>(ctx, B_REC32), part32(ctx),
+                  s);
   }
   if (overlap) {
     // phase 3 is then the far field with the P2P kernel beside it, phase 4

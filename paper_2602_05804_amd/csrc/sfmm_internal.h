@@ -477,10 +477,21 @@ void launch_p2p_tile(bool node_lists, int ls, const NearArgs& a, int64_t items, 
 void launch_p2p_reduce(const NearArgs& a, int ls, hipStream_t s);
 
 // ---- FP32-compensated form ------------------------------------------------------
-// FP32 M2L records per node and FP32 leaf-relative particle offsets (+ mass, h, 1/h)
-void launch_prep32(int order, int nn, int nleaves, const int32_t* leaf_node, const NodeInfo* info,
+// per particle: FP32 offset from its leaf's centre and mass; the centre (FP64),
+// h and 1/h
+struct alignas(16) Part32Z {
+  double cz;
+  float h, hinv;
+};
+struct Part32 {
+  float4* off;
+  double2* cxy;
+  Part32Z* czh;
+};
+// FP32 M2L records per node, and the particles' records
+void launch_prep32(int order, int nn, int n, const int32_t* p_leaf, const int32_t* leaf_node,
                    const double* rec, const double* xs, const double* ys, const double* zs,
-                   const double* ms, const double* hs, float* rec32, float4* pf, float2* ph,
+                   const double* ms, const double* hs, float* rec32, const Part32& p,
                    hipStream_t s);
 void launch_far32(int order, bool node_lists, const FarArgs& a, const float* rec32, int top,
                   hipStream_t s);
@@ -488,8 +499,7 @@ void launch_far32(int order, bool node_lists, const FarArgs& a, const float* rec
 // variant: the P2P shape (0 the wave kernel with scalar-register targets,
 // 6 the earlier one with targets in LDS; others as 0)
 bool launch_near32(int order, bool node_lists, int leaf_size, int variant, const NearArgs& a,
-                   const float4* pf, const float2* ph, int64_t items, hipStream_t s,
-                   KernelMarks km = {});
+                   const Part32& p, int64_t items, hipStream_t s, KernelMarks km = {});
 
 void launch_leapfrog(int64_t n, double* x, double* v, const double* acc, double kick, double drift,
                      hipStream_t s);
