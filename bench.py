@@ -34,12 +34,13 @@ P2P_FLOPS_SOFT = 40          # more for a pair inside a kernel: one branch of ea
 KERNELS = {
     ("fp64", "far"): ("void k_far<", ["k_far.hip", "expansions_gen.h", "sfmm_internal.h"],
                       "k_far: per-leaf M2L + L2L chain + L2P"),
-    ("fp64", "near"): ("void k_p2p_wave<", ["k_near.hip", "sfmm_internal.h", "softening.h"],
+    ("fp64", "near"): ("void k_p2p_wave<", ["k_near.hip", "p2p_wave.h", "sfmm_internal.h",
+                                            "softening.h"],
                        "k_p2p_wave: softened P2P, one wave per work item, targets in scalar "
                        "registers"),
     ("fp32c", "far"): ("void k_far32<", ["k_f32c.hip", "expansions_gen.h", "sfmm_internal.h"],
                        "k_far32: per-leaf M2L (FP32 terms, FP64 sums) + L2L + L2P"),
-    ("fp32c", "near"): ("void k_p2p_wave32<", ["k_f32c.hip", "sfmm_internal.h"],
+    ("fp32c", "near"): ("void k_p2p_wave32<", ["k_f32c.hip", "p2p_wave.h", "sfmm_internal.h"],
                         "k_p2p_wave32: softened P2P, FP32 terms, FP64 sums, one wave per "
                         "work item"),
     # the earlier P2P shapes, still selectable (near kernel 1 to 6)
@@ -47,19 +48,20 @@ KERNELS = {
                             "k_p2p_leaf: softened P2P, targets of a leaf in LDS"),
     ("fp64", "near_thread"): ("void k_near<", ["k_near.hip", "sfmm_internal.h", "softening.h"],
                               "k_near: softened P2P, one target particle per thread"),
-    ("fp64", "near_tile"): ("void k_p2p_tile<", ["k_p2p_tile.hip", "sfmm_internal.h",
+    # (near kernel 13: the same kernel)
+    ("fp64", "near_tile"): ("void k_p2p_wave<", ["k_near.hip", "p2p_wave.h", "sfmm_internal.h",
                                                  "softening.h"],
-                            "k_p2p_tile: softened P2P, targets of a leaf in lane stripes, "
-                            "sources staged in LDS"),
+                            "k_p2p_wave: softened P2P, one wave per work item, targets in scalar "
+                            "registers"),
     ("fp32c", "near_leaf"): ("void k_p2p_leaf32<", ["k_f32c.hip", "sfmm_internal.h"],
                              "k_p2p_leaf32: softened P2P, FP32 terms, FP64 sums"),
     ("mutual", "far"): (("void k_m2l_mutual<", "void k_far_shared<"),
                         ["k_far.hip", "expansions_gen.h", "sfmm_internal.h"],
                         "k_m2l_mutual + k_far_shared: each unordered node pair's M2L once for "
                         "both nodes, then per-leaf L2L + L2P"),
-    ("shared", "far"): (("void k_m2l_nodes<", "void k_far_shared<"),
+    ("shared", "far"): (("void k_m2l<", "void k_far_shared<"),
                         ["k_far.hip", "expansions_gen.h", "sfmm_internal.h"],
-                        "k_m2l_nodes + k_far_shared: per-node M2L sums, then per-leaf L2L + L2P"),
+                        "k_m2l + k_far_shared: per-node M2L sums, then per-leaf L2L + L2P"),
 }
 
 

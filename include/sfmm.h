@@ -115,14 +115,11 @@ typedef struct {
 } sfmm_config;
 /* P2P kernel shapes (same results up to summation order; sfmm_create returns
  * SFMM_EINVAL for any other value, and for far_kernel != 0):
- *   0  a wave per work item, the targets in scalar registers, wave-uniform
- *      loop control, the pairs inside a kernel queued per target and
- *      evaluated 64 at a time; passes of 5 targets at four waves per SIMD
- *      (leaf_size <= 10), of 6 at four (leaf_size <= 16) or of 8 at three
- *      (leaf_size <= 32);
- *   13 the targets of a leaf in lanes, in stripes over sources staged through
- *      LDS, source leaves split into near and far by the target leaf's sphere
- *      (leaf_size <= 32; faster on the polytrope, slower on a Plummer halo);
+ *   0  a wave per work item, the targets in scalar registers, the item's
+ *      sources flattened once in LDS, wave-uniform loop control, the pairs
+ *      inside a kernel queued per target and shared out over the lanes;
+ *      passes of 8 targets at three waves per SIMD (n < 2^28, else 6);
+ *   13 the same as 0;
  *   6  a wave per work item with the targets in LDS, passes of 5 (8 for
  *      leaf_size > 10), the queue shared by the pass; in SFMM_FP32C the same
  *      layout with the softened branch taken in the pass;
@@ -130,8 +127,8 @@ typedef struct {
  *      words instead of an FP64 accumulator (in FP64, shape 0);
  *   1  one thread per particle (also every leaf_size > 32; SFMM_FP32C needs
  *      leaf_size <= 16).
- * The far field has one shape per mode: 8 lanes per node (SFMM_FAR_SHARED,
- * two waves per SIMD in FP64, one in FP32C), 4 lanes per leaf (SFMM_FAR_LEAF). */
+ * The far field has one shape per mode: 8 lanes per node (SFMM_FAR_SHARED, two
+ * waves per SIMD), 4 lanes per leaf (SFMM_FAR_LEAF). */
 
 /* Solve statistics of the last sfmm_solve on a context (host copy). */
 typedef struct {

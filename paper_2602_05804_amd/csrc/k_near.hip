@@ -717,13 +717,10 @@ void launch_near(bool node_lists, int leaf_size, int variant, const NearArgs& a,
   record_mark(km.begin, s);
   if (variant == 1) leaf_size = 1 << 20;  // particle per thread
   // variant (the shapes are listed with sfmm_config.near_kernel)
-  if (leaf_size <= 32 && variant == 13) {
-    launch_p2p_tile(node_lists, p2p_leaf_slots(leaf_size), a, items, s);
-    record_mark(km.end, s);
-    if (!km.skip_reduce) launch_p2p_reduce(a, p2p_leaf_slots(leaf_size), s);
-    return;
-  }
-  // The wave shape: eight targets per pass at three waves per SIMD (at leaf
+  // The wave shape (numbers 0 and 13; 13 was one with the targets in lane stripes
+  // and the sources staged in LDS, which it beats on every system tried, e.g. at
+  // leaf size 16 on a polytrope of 1e6 1.87 against 1.97 ms, on a Plummer sphere
+  // at leaf size 10 2.73 against 3.51): eight targets per pass at three waves per SIMD (at leaf
   // size 10 on the Plummer sphere and the polytrope of 1e6: 2.86 ms, with six
   // at three 2.97, five or six at four, which spill, 2.95).  It addresses the
   // particles by 32-bit byte offsets of 16 bytes each, so from 2^28 particles

@@ -468,10 +468,6 @@ inline void record_mark(hipEvent_t e, hipStream_t s) {
 }
 void launch_near(bool node_lists, int leaf_size, int variant, const NearArgs& a, int64_t items,
                  hipStream_t s, KernelMarks km = {});
-// the default P2P kernel: targets of the leaf in lanes (NS stripes of nt
-// lanes), sources staged through LDS and split into far and near sources by
-// the target leaf's sphere (ls = 10 or 16: the partial-sum layout)
-void launch_p2p_tile(bool node_lists, int ls, const NearArgs& a, int64_t items, hipStream_t s);
 // sum of the item partials per target, plus the far field and the self term,
 // written in the caller's order (LS = the P2P kernel's target count)
 void launch_p2p_reduce(const NearArgs& a, int ls, hipStream_t s);
