@@ -685,16 +685,22 @@ void launch_nodewalk_level(const NodeWalkArgs& a, int level, int nodes_in_level,
   k_nodewalk_internal<<<nodes_in_level, 64, 0, s>>>(a, level, rank0);
 }
 
-void launch_nodewalk_leaves(const NodeWalkArgs& a, uint32_t* scan_tmp, hipStream_t s) {
+void launch_nodewalk_leaves(const NodeWalkArgs& a, uint64_t* scan_tmp, hipStream_t s) {
   if (a.nleaves <= 0) return;
   const size_t lds = a.stack_cap * sizeof(uint32_t);
   k_nodewalk_leaves<<<a.nleaves, 64, lds + a.slot_p * sizeof(uint32_t), s>>>(a);
-  scan_u32_u64(a.leaf_m2l_cnt, a.leaf_m2l_off, a.nleaves, a.run + 3,
-               reinterpret_cast<uint64_t*>(scan_tmp), s);
-  scan_u32_u64(a.leaf_p2p_cnt, a.leaf_p2p_off, a.nleaves, a.run + 2,
-               reinterpret_cast<uint64_t*>(scan_tmp), s);
+  ScanJobs jobs{};
+  jobs.j[0].in32 = a.leaf_m2l_cnt;
+  jobs.j[0].out64 = a.leaf_m2l_off;
+  jobs.j[0].total64 = a.run + 3;
+  jobs.j[1].in32 = a.leaf_p2p_cnt;
+  jobs.j[1].out64 = a.leaf_p2p_off;
+  jobs.j[1].total64 = a.run + 2;
   // P2P work items: item_off[nleaves] = their total (read back with the walk's)
-  scan_u32(a.item_cnt, a.item_off, a.nleaves, a.item_off + a.nleaves, scan_tmp, s);
+  jobs.j[2].in32 = a.item_cnt;
+  jobs.j[2].out32 = a.item_off;
+  jobs.j[2].total32 = a.item_off + a.nleaves;
+  scan_jobs(jobs, 3, a.nleaves, scan_tmp, s);
   const unsigned ng = std::min<unsigned>(kOvfWaves, ((unsigned)a.nleaves + kXcds - 1) / kXcds * kXcds);
   k_nodewalk_leaves_ovf<<<ng, 64, lds, s>>>(a);
 }

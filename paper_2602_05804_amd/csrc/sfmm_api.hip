@@ -362,7 +362,7 @@ int do_build(sfmm_ctx* ctx, int64_t n64, const double* x, const double* m, const
                   P<int32_t>(ctx, B_KSIDE), P<uint32_t>(ctx, B_KEPT), s);
     uint32_t* cidx = P<uint32_t>(ctx, B_KEPT);
     scan_u32(cidx, cidx, n - 1, reinterpret_cast<uint32_t*>(small + S_NKEPT),
-             P<uint32_t>(ctx, B_SCANTMP), s);
+             P<uint64_t>(ctx, B_SCANTMP), s);
     launch_assign(n, leaf_size, sys_sorted, P<int32_t>(ctx, B_KFIRST), P<int32_t>(ctx, B_KLAST),
                   P<int32_t>(ctx, B_KLEFT), P<int32_t>(ctx, B_KRIGHT), P<int32_t>(ctx, B_KPAR),
                   P<int32_t>(ctx, B_KSIDE), cidx, info, leaf_flag,
@@ -370,7 +370,7 @@ int do_build(sfmm_ctx* ctx, int64_t n64, const double* x, const double* m, const
     // leaf_flag -> leaf index (scan into KFIRST's storage, no longer needed)
     uint32_t* lscan = reinterpret_cast<uint32_t*>(P<int32_t>(ctx, B_KFIRST));
     scan_u32(leaf_flag, lscan, n, reinterpret_cast<uint32_t*>(small + S_NLEAVES),
-             P<uint32_t>(ctx, B_SCANTMP), s);
+             P<uint64_t>(ctx, B_SCANTMP), s);
     launch_leaf_fill(n, leaf_flag, lscan, P<int32_t>(ctx, B_LAT), leaf_node,
                      P<int32_t>(ctx, B_PLEAF), s);
   }
@@ -662,7 +662,7 @@ int walk_levels(sfmm_ctx* ctx, double theta) {
       launch_nodewalk_level(a, k, (int)nk, rank0, s);
       rank0 += nk;
     }
-    launch_nodewalk_leaves(a, P<uint32_t>(ctx, B_SCANTMP), s);
+    launch_nodewalk_leaves(a, P<uint64_t>(ctx, B_SCANTMP), s);
     // no consumer reads a list unless it lies in the part of its pool this
     // walk wrote (and, when checking, holds only node ids); with the totals
     // of M2L entries proper (the pool also holds the opened lists) and P2P
@@ -785,7 +785,7 @@ int do_walk_and_eval(sfmm_ctx* ctx, double theta, int precision, const double* m
       {B_L2LCNT, sizeof(uint64_t) * (nl + 1)},
       {B_FAR, sizeof(double) * 4 * (size_t)n},
       {B_MOMPART, sizeof(double) * 4 * momentum_blocks(n)}, {B_MOM, sizeof(double) * 4},
-      {B_SCANTMP, sizeof(uint64_t) * scan_tmp_elems(nl + 1)},
+      {B_SCANTMP, sizeof(uint64_t) * 3 * scan_tmp_elems(nl + 1)},
   };
   for (auto& q : need)
     if ((rc = ensure(ctx, q.id, q.bytes))) return rc;
@@ -881,7 +881,7 @@ int do_walk_and_eval(sfmm_ctx* ctx, double theta, int precision, const double* m
       items = ctx->items_from_walk;
     } else {
       launch_p2p_items_count(level, a, P<uint32_t>(ctx, B_SRCTOT), P<uint32_t>(ctx, B_ITEMCNT), s);
-      scan_u32(P<uint32_t>(ctx, B_ITEMCNT), item_off, nl, item_off + nl, P<uint32_t>(ctx, B_SCANTMP),
+      scan_u32(P<uint32_t>(ctx, B_ITEMCNT), item_off, nl, item_off + nl, P<uint64_t>(ctx, B_SCANTMP),
                s);
       Readback* hb = readback(ctx);
       if (!hb) return fail(ctx, SFMM_ENOMEM, "pinned host block for read-backs");

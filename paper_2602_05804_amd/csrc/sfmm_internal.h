@@ -98,15 +98,25 @@ constexpr uint32_t kIntSlotMax = 4096;
 
 // ---- scan ------------------------------------------------------------------
 // Exclusive prefix sum of `in` (n entries) into `out` (may alias in); the
-// grand total is written to *total.  tmp must hold scan_tmp_elems(n) T's.
+// grand total is written to *total.  tmp must hold scan_tmp_elems(n) words a job.
+struct ScanJob {  // one of each pair is set
+  const uint32_t* in32;
+  const uint64_t* in64;
+  uint32_t* out32;
+  uint64_t* out64;
+  uint32_t* total32;
+  uint64_t* total64;
+};
+struct ScanJobs {
+  ScanJob j[3];
+};
 size_t scan_tmp_elems(int64_t n);
-void scan_u32(const uint32_t* in, uint32_t* out, int64_t n, uint32_t* total, uint32_t* tmp,
+// `count` arrays of one length together
+void scan_jobs(const ScanJobs& jobs, int count, int64_t n, uint64_t* tmp, hipStream_t s);
+void scan_u32(const uint32_t* in, uint32_t* out, int64_t n, uint32_t* total, uint64_t* tmp,
               hipStream_t s);
 void scan_u64(const uint64_t* in, uint64_t* out, int64_t n, uint64_t* total, uint64_t* tmp,
               hipStream_t s);
-// u32 counts, u64 offsets and total
-void scan_u32_u64(const uint32_t* in, uint64_t* out, int64_t n, uint64_t* total, uint64_t* tmp,
-                  hipStream_t s);
 
 // ---- tree ------------------------------------------------------------------
 int bbox_blocks(int64_t n);
@@ -327,8 +337,8 @@ struct NodeWalkArgs {
 };
 // every leaf's lists (the slot pass, scans over the leaves, the second pass
 // over leaves whose lists overflow their slots); scan_tmp holds
-// scan_tmp_elems(nleaves) words; LDS of (stack_cap + slot_p) words per wave
-void launch_nodewalk_leaves(const NodeWalkArgs& a, uint32_t* scan_tmp, hipStream_t s);
+// 3 scan_tmp_elems(nleaves) words; LDS of (stack_cap + slot_p) words per wave
+void launch_nodewalk_leaves(const NodeWalkArgs& a, uint64_t* scan_tmp, hipStream_t s);
 // after a walk: every node's M2L list and every leaf's P2P list must lie in
 // the part of its pool the walk wrote (the internal regions, the leaf slots,
 // then run[3] M2L and run[2] P2P entries); with check_entries, each entry
