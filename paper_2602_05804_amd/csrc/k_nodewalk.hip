@@ -31,7 +31,7 @@
 // of the M2L pool holds both lists, M2L entries from the front and opened
 // entries from the back, and its size is known before the node is walked:
 // the region is the node's fixed slot, or a piece of an arena when larger.
-// Each level is then one launch.  The leaves come after all levels, in one
+// Each level is then one launch, or a few small levels together.  The leaves come after all levels, in one
 // pass that writes each leaf's lists into fixed per-leaf slots (or a few
 // large slots).  A second pass, at exact offsets, takes only the leaves that
 // fit neither.
@@ -102,14 +102,10 @@ __device__ __forceinline__ uint32_t pool_room(uint64_t base, uint64_t cap, uint3
   return room < want ? (uint32_t)room : want;
 }
 
-// ---- the lists of one node ------------------------------------------------------
+// ---- the lists of one leaf ------------------------------------------------------
 struct Emit {
-  // internal node: M2L entries from the front of its region, opened entries
-  // from the back (of `region` entries, all of which or none may be written);
-  // exp_lane sums this lane's opened entries, an internal one counted twice
-  uint32_t m2l_run, open_run, exp_lane;
-  // leaf: P2P entries that may fall inside a kernel from the front of its
-  // list, those beyond both kernels (plain_run of them so far) from the back
+  uint32_t m2l_run;
+  // P2P entries that may fall inside a kernel from the front of the list, those beyond both kernels (plain_run of them so far) from the back
   uint32_t p2p_run, plain_run;
   uint32_t src_lane;  // this lane's share of the particles of the P2P entries
   uint64_t m2l_base, p2p_base;  // places in the pools, entries
@@ -225,8 +221,16 @@ __device__ __forceinline__ LeafTest leaf_test(const NodeWalkArgs& a, int v, cons
 // polytrope; two groups took 0.65, three 0.68: the waves in flight matter more)
 constexpr int kWalkBatch = 1;
 
-__device__ void walk_internal(const NodeWalkArgs& a, int v, const Src& rv, const uint32_t* src,
-                              uint32_t nsrc, uint32_t region, uint32_t room, Emit& e) {
+// entries of an internal node's lists so far: M2L entries from the front of its
+// region, opened entries from the back; exp_lane sums this lane's opened entries,
+// an internal one counted twice
+struct NodeRuns {
+  uint32_t m2l = 0, open = 0, exp_lane = 0;
+};
+
+__device__ __forceinline__ void walk_internal(const NodeWalkArgs& a, int v, const Src& rv, const uint32_t* src,
+                              uint32_t nsrc, uint32_t region, uint32_t room, uint32_t* list,
+                              NodeRuns& e) {
   const uint32_t lane = threadIdx.x & 63;
   for (uint32_t base = 0; base < nsrc; base += 64 * kWalkBatch) {
     uint32_t sb[kWalkBatch];
@@ -255,8 +259,8 @@ __device__ void walk_internal(const NodeWalkArgs& a, int v, const Src& rv, const
       const bool m1 = (int)t1[u] != v && accept(rv, r1[u], a.theta2, a.r_kern);
       const bool i0 = r0[u].child >= 0, i1 = r1[u].child >= 0;
       const bool p0 = ok && !m0, p1 = two && !m1;
-      append(e.m2l, room, e.m2l_run, ok && m0, t0[u], two && m1, t1[u]);
-      append_back(e.m2l, region, room, e.open_run, p0,
+      append(list, room, e.m2l, ok && m0, t0[u], two && m1, t1[u]);
+      append_back(list, region, room, e.open, p0,
                   i0 ? (uint32_t)r0[u].child | kOpenInternal : t0[u], p1,
                   i1 ? (uint32_t)r1[u].child | kOpenInternal : t1[u]);
       // the children's tested list: an opened leaf once, an internal node twice
@@ -385,34 +389,25 @@ __device__ void walk_leaf(const NodeWalkArgs& a, int v, const Src& rv, const uin
 // (run[0] entries of it taken, by run[10] nodes).  Leaves take no room at
 // their level (they are walked after all levels); a node over two systems
 // gets empty lists.
-__global__ __launch_bounds__(64) void k_nodewalk_internal(NodeWalkArgs a, int level, uint32_t rank0) {
-  const uint32_t beg = a.level_base[2 * level], end = a.level_base[2 * level + 1];
-  const uint32_t b = xcd_block(blockIdx.x, gridDim.x);
-  const uint32_t idx = beg + b;
-  if (idx >= end) return;
-  const int v = a.level_nodes[idx];
-  const NodeInfo vi = a.info[v];
-  // a node over two systems (several systems solved together) is never
-  // walked; the walk of each system starts at its own root
-  const int flag = a.node_flag ? (int)a.node_flag[v] : (vi.parent < 0 ? 1 : 2);
+// a node's opened list, and the tested-list size of its children
+struct Opened {
+  uint32_t off, cnt, exp;
+};
+
+// one wave walks node v (internal), given its parent's opened list.  flag 0: a
+// node over two systems (several systems solved together) is never walked; the
+// walk of each system starts at its own root (flag 1)
+__device__ __forceinline__ Opened walk_node(const NodeWalkArgs& a, int v, const NodeInfo& vi,
+                                            int flag, Opened up) {
   const uint32_t lane = threadIdx.x & 63;
-  if (flag == 0) {
-    if (lane == 0) {
-      a.m2l_cnt[v] = 0; a.open_cnt[v] = 0; a.p2p_cnt[v] = 0;
-      a.m2l_off[v] = 0; a.open_off[v] = 0; a.p2p_off[v] = 0;
-    }
-    return;
-  }
-  if (vi.child < 0) return;  // (the level's internal nodes come first)
-  if (lane == 0) { a.p2p_cnt[v] = 0; a.p2p_off[v] = 0; }
-  const bool root = flag == 1;
   const Src rv = load_src(a, (uint32_t)v);
-  const uint32_t region = root ? 1u : a.exp[vi.parent];
-  Emit e{};
+  const bool root = flag == 1;
+  const uint32_t region = flag == 0 ? 0u : root ? 1u : up.exp;
   bool fits = true;
   uint64_t at;
   if (region <= a.int_slot) {
-    at = (uint64_t)(rank0 + b) * a.int_slot;
+    // (the internal nodes are numbered by their children: 1 + 2c, 2 + 2c)
+    at = (uint64_t)((uint32_t)(vi.child - 1) / 2u) * a.int_slot;
   } else {
     uint64_t t = 0;
     if (lane == 0) {
@@ -428,31 +423,83 @@ __global__ __launch_bounds__(64) void k_nodewalk_internal(NodeWalkArgs a, int le
   // a region that does not fit gets no offset (the walk goes on counting,
   // the host grows the pool and walks again)
   fits = fits && at + region <= a.m2l_cap;
-  if (lane == 0) a.m2l_off[v] = fits ? (uint32_t)at : kNoList;
-  if (root) {
-    // (root, root) is opened: both root children meet both root children
-    if (lane == 0) {
-      if (fits) a.open_pool[at] = (uint32_t)vi.child | kOpenInternal;
-      a.m2l_cnt[v] = 0;
-      a.open_cnt[v] = 1;
-      a.open_off[v] = fits ? (uint32_t)at : kNoList;
-      a.exp[v] = 2;
-    }
-    return;
-  }
-  const uint32_t po = a.open_off[vi.parent];
-  uint32_t nsrc = a.open_cnt[vi.parent];
-  if ((uint64_t)po + nsrc > a.open_cap) nsrc = 0;  // pool too small: the walk is rerun
-  e.m2l = a.m2l_pool + at;
-  walk_internal(a, v, rv, a.open_pool + po, nsrc, region, fits ? region : 0u, e);
+  NodeRuns e;
+  // (root, root) is opened: both root children meet both root children
+  if (root && lane == 0 && fits) a.open_pool[at] = (uint32_t)vi.child | kOpenInternal;
+  uint32_t nsrc = flag == 2 ? up.cnt : 0u;
+  if ((uint64_t)up.off + nsrc > a.open_cap) nsrc = 0;  // pool too small: the walk is rerun
+  walk_internal(a, v, rv, a.open_pool + up.off, nsrc, region, fits ? region : 0u,
+                a.m2l_pool + at, e);
   uint32_t ex = e.exp_lane;
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) ex += (uint32_t)__shfl_xor((int)ex, o, 64);
+  for (int k = 32; k > 0; k >>= 1) ex += (uint32_t)__shfl_xor((int)ex, k, 64);
+  const uint32_t open = root ? 1u : e.open;
+  const Opened o{fits ? (uint32_t)(at + region - open) : kNoList, open, root ? 2u : ex};
   if (lane == 0) {
-    a.m2l_cnt[v] = e.m2l_run;
-    a.open_cnt[v] = e.open_run;
-    a.open_off[v] = fits ? (uint32_t)(at + region - e.open_run) : kNoList;
-    a.exp[v] = ex;
+    a.m2l_off[v] = fits ? (uint32_t)at : kNoList;
+    a.m2l_cnt[v] = e.m2l;
+    a.open_off[v] = o.off;
+    a.open_cnt[v] = o.cnt;
+    a.exp[v] = o.exp;
+    a.p2p_cnt[v] = 0;
+    a.p2p_off[v] = 0;
+  }
+  return o;
+}
+
+__device__ __forceinline__ int walk_flag(const NodeWalkArgs& a, int v, const NodeInfo& vi) {
+  return a.node_flag ? (int)a.node_flag[v] : (vi.parent < 0 ? 1 : 2);
+}
+__device__ __forceinline__ Opened parent_opened(const NodeWalkArgs& a, const NodeInfo& vi) {
+  if (vi.parent < 0) return {0u, 0u, 0u};
+  return {a.open_off[vi.parent], a.open_cnt[vi.parent], a.exp[vi.parent]};
+}
+
+// one level, a wave per node
+__global__ __launch_bounds__(64) void k_nodewalk_internal(NodeWalkArgs a, int level) {
+  const uint32_t idx = a.level_base[2 * level] + xcd_block(blockIdx.x, gridDim.x);
+  if (idx >= a.level_base[2 * level + 1]) return;
+  const int v = a.level_nodes[idx];
+  const NodeInfo vi = a.info[v];
+  walk_node(a, v, vi, walk_flag(a, v, vi), parent_opened(a, vi));
+}
+
+// kWalkRun levels from `level` on, a block per node of the first: 1, 2, .. of
+// its waves take the node, its internal children, theirs.  Bound by the chain
+// of loads of a level; a launch a level adds the lookups of the node and of its
+// parent's list, which the block passes on in LDS.  Walk phase of 1e3 particles
+// 0.093 ms (0.122 with a launch a level), of 1e4 0.167 (0.214).
+constexpr int kWalkRun = 3;
+constexpr int kRunWaves = 1 << (kWalkRun - 1);
+__global__ __launch_bounds__(64 * kRunWaves) void k_nodewalk_run(NodeWalkArgs a, int level) {
+  __shared__ int node[kRunWaves];
+  __shared__ Opened up[kRunWaves];
+  const uint32_t idx = a.level_base[2 * level] + xcd_block(blockIdx.x, gridDim.x);
+  if (idx >= a.level_base[2 * level + 1]) return;
+  const int w = threadIdx.x >> 6;
+  int v = w == 0 ? a.level_nodes[idx] : -1;
+  Opened mine{0u, 0u, 0u};
+  if (w == 0) mine = parent_opened(a, a.info[v]);
+  for (int r = 0;; ++r) {
+    NodeInfo vi{0, 0, -1, -1};
+    if (v >= 0) {
+      vi = a.info[v];
+      mine = walk_node(a, v, vi, walk_flag(a, v, vi), mine);
+    }
+    if (r == kWalkRun - 1) break;
+    // the internal children of the round's nodes, and their parent's list
+    if (w < (1 << r) && (threadIdx.x & 63) == 0) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        node[2 * w + q] = v >= 0 && a.info[vi.child + q].child >= 0 ? vi.child + q : -1;
+        up[2 * w + q] = mine;
+      }
+    }
+    __syncthreads();  // (the lists written by a wave are read by others)
+    v = w < (2 << r) ? node[w] : -1;
+    mine = up[w];
+    v = __builtin_amdgcn_readfirstlane(v);
+    __syncthreads();
   }
 }
 
@@ -678,11 +725,28 @@ void launch_leaf_stats(const LeafStatArgs& a, hipStream_t s) {
   k_leaf_stats<<<(a.nleaves + 127) / 128, 128, 0, s>>>(a);
 }
 
-void launch_nodewalk_level(const NodeWalkArgs& a, int level, int nodes_in_level, uint32_t rank0,
-                           hipStream_t s) {
-  // (nodes_in_level: the level's internal nodes, rank0 those of the levels above)
-  if (nodes_in_level <= 0) return;
-  k_nodewalk_internal<<<nodes_in_level, 64, 0, s>>>(a, level, rank0);
+// levels of at most this many nodes are walked kWalkRun at a time (walk phase at
+// 1e5 particles 0.191 ms, with every level by itself 0.210, runs up to 512 nodes
+// 0.193; a batch of 24 systems 1.152, 1.175 and 1.154, up to 8192 1.28: idle waves
+// then take the place of busy ones; runs of four levels gain nothing more)
+constexpr uint32_t kRunMax = 2048;
+
+void launch_nodewalk_levels(const NodeWalkArgs& a, const uint32_t* level_base, int maxdepth,
+                            hipStream_t s) {
+  auto nodes = [&](int k) {
+    return k <= maxdepth ? level_base[2 * k + 1] - level_base[2 * k] : 0u;  // the internal ones
+  };
+  for (int k = 0; k <= maxdepth && nodes(k) > 0;) {
+    uint32_t most = 0;
+    for (int r = 0; r < kWalkRun; ++r) most = std::max(most, nodes(k + r));
+    if (most <= kRunMax && nodes(k + 1) > 0) {
+      k_nodewalk_run<<<nodes(k), 64 * kRunWaves, 0, s>>>(a, k);
+      k += kWalkRun;
+    } else {
+      k_nodewalk_internal<<<nodes(k), 64, 0, s>>>(a, k);
+      ++k;
+    }
+  }
 }
 
 void launch_nodewalk_leaves(const NodeWalkArgs& a, uint64_t* scan_tmp, hipStream_t s) {

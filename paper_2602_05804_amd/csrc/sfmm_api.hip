@@ -656,12 +656,7 @@ int walk_levels(sfmm_ctx* ctx, double theta) {
     a.item_off = P<uint32_t>(ctx, B_ITEMOFF);
     a.rule = item_rule(ctx);
     // internal nodes level by level, then every leaf
-    uint32_t rank0 = 0;
-    for (int k = 0; k <= ctx->maxdepth; ++k) {
-      const uint32_t nk = ctx->level_base[2 * k + 1] - ctx->level_base[2 * k];
-      launch_nodewalk_level(a, k, (int)nk, rank0, s);
-      rank0 += nk;
-    }
+    launch_nodewalk_levels(a, ctx->level_base, ctx->maxdepth, s);
     launch_nodewalk_leaves(a, P<uint64_t>(ctx, B_SCANTMP), s);
     // no consumer reads a list unless it lies in the part of its pool this
     // walk wrote (and, when checking, holds only node ids); with the totals

@@ -346,8 +346,8 @@ void launch_nodewalk_leaves(const NodeWalkArgs& a, uint64_t* scan_tmp, hipStream
 // otherwise.  Adds the walk's M2L and P2P entries to run[1] and run[4], and
 // takes the longest M2L and P2P lists of a leaf into run[6] and run[7].
 void launch_check_lists(const NodeWalkArgs& a, int nn, bool check_entries, hipStream_t s);
-void launch_nodewalk_level(const NodeWalkArgs& a, int level, int nodes_in_level, uint32_t rank0,
-                           hipStream_t s);
+void launch_nodewalk_levels(const NodeWalkArgs& a, const uint32_t* level_base, int maxdepth,
+                            hipStream_t s);
 
 // per-leaf statistics of node lists: replicated M2L count, L2L count, pairs
 struct LeafStatArgs {
