@@ -545,46 +545,59 @@ __global__ void k_zero_f64(int64_t n, double* __restrict__ p) {
     p[i] = 0.0;
 }
 
-// k_far_shared: one lane per leaf walks its branch from the root
+// k_far_shared: one lane per leaf goes down its branch from the root.  Bound by
+// the chain of loads of a branch: the branch is noted in LDS first (one load a
+// level, up the parents), so that on the way down a node's record is read while
+// its parent's is used.  20 us at 1e3 particles, 24 at 1e5, 70 at 1e6; finding
+// each child from its parent on the way down 34, 46, 95.
 template <int P>
 __global__ __launch_bounds__(64) void k_far_shared(FarArgs a, const double* __restrict__ ln) {
   using E = Exp<P>;
   constexpr int NL = E::NL;
   constexpr int RS = rec_stride(P);
-  const int l = xcd_block(blockIdx.x, gridDim.x) * 64 + threadIdx.x;
+  extern __shared__ int path[];  // [depth][64]: the leaf's ancestors, the leaf last
+  const int lane = threadIdx.x;
+  const int l = xcd_block(blockIdx.x, gridDim.x) * 64 + lane;
   if (l >= a.nleaves) return;
   const NodeInfo* __restrict__ info = a.info;
   const double* __restrict__ rec = a.rec;
   const int leaf = a.leaf_node[l];
   const int d = a.leaf_depth[l];
-  const int lo = info[leaf].lo;
-  const int cnt = info[leaf].cnt;
+  const NodeInfo li = info[leaf];
+  const int lo = li.lo, cnt = li.cnt;
+  path[d * 64 + lane] = leaf;
+  for (int k = d - 1, u = li.parent; k >= 0; --k, u = info[u].parent) path[k * 64 + lane] = u;
   double L[NL];
 #pragma unroll
   for (int q = 0; q < NL; ++q) L[q] = 0.0;
   bool have = false;
-  int v = 0;
-  double sv[3] = {rec[0], rec[1], rec[2]};
-  auto add_node = [&](int u) {
-    if (a.node_m2l_cnt[u] == 0) return;
-    const double* lu = ln + (int64_t)u * NL;
-#pragma unroll
-    for (int q = 0; q < NL; ++q) L[q] += lu[q];
-    have = true;
+  double sv[3] = {0.0, 0.0, 0.0};
+  // (the next node's centre and list length load while this one's are used)
+  struct Next {
+    int v;
+    uint32_t m2l;
+    double s[3];
   };
-  add_node(0);
-  for (int k = 0; k < d; ++k) {
-    const int c = info[v].child;
-    const int nv = (lo < info[c + 1].lo) ? c : c + 1;
-    const double* rn = rec + (int64_t)nv * RS;
-    const double sn[3] = {rn[0], rn[1], rn[2]};
+  auto load = [&](int k) {
+    const int v = path[k * 64 + lane];
+    const double* r = rec + (int64_t)v * RS;
+    return Next{v, a.node_m2l_cnt[v], {r[0], r[1], r[2]}};
+  };
+  Next next = load(0);
+  for (int k = 0; k <= d; ++k) {
+    const Next n = next;
+    if (k < d) next = load(k + 1);
+    const double* lu = ln + (int64_t)n.v * NL;
     if (have) {
-      const double hv[3] = {sn[0] - sv[0], sn[1] - sv[1], sn[2] - sv[2]};
+      const double hv[3] = {n.s[0] - sv[0], n.s[1] - sv[1], n.s[2] - sv[2]};
       E::l2l(hv, L);
     }
-    v = nv;
-    sv[0] = sn[0]; sv[1] = sn[1]; sv[2] = sn[2];
-    add_node(v);
+    if (n.m2l != 0) {
+#pragma unroll
+      for (int q = 0; q < NL; ++q) L[q] += lu[q];
+      have = true;
+    }
+    sv[0] = n.s[0]; sv[1] = n.s[1]; sv[2] = n.s[2];
   }
   for (int j = lo; j < lo + cnt; ++j) {
     const double off[3] = {a.xs[j] - sv[0], a.ys[j] - sv[1], a.zs[j] - sv[2]};
@@ -606,7 +619,7 @@ void shared_order(const FarArgs& f, const SharedFarArgs& a, bool f32, hipStream_
     if (f32) k_m2l<P, true, (P < 4 ? 2 : 1)><<<nb, 64, 0, s>>>(a);
     else k_m2l<P, false, 2><<<nb, 64, 0, s>>>(a);
   }
-  if (f.nleaves > 0) k_far_shared<P><<<(unsigned)((f.nleaves + 63) / 64), 64, 0, s>>>(f, a.ln);
+  if (f.nleaves > 0) k_far_shared<P><<<(unsigned)((f.nleaves + 63) / 64), 64, 64 * sizeof(int) * (f.maxdepth + 1), s>>>(f, a.ln);
 }
 
 template <int P>
@@ -617,7 +630,7 @@ void mutual_order(const FarArgs& f, const SharedFarArgs& a, hipStream_t s) {
     constexpr int SPLIT = 8;
     k_m2l_mutual<P, SPLIT><<<(unsigned)((a.nn + 64 / SPLIT - 1) / (64 / SPLIT)), 64, 0, s>>>(a);
   }
-  if (f.nleaves > 0) k_far_shared<P><<<(unsigned)((f.nleaves + 63) / 64), 64, 0, s>>>(f, a.ln);
+  if (f.nleaves > 0) k_far_shared<P><<<(unsigned)((f.nleaves + 63) / 64), 64, 64 * sizeof(int) * (f.maxdepth + 1), s>>>(f, a.ln);
 }
 
 }  // namespace

@@ -811,6 +811,7 @@ int do_walk_and_eval(sfmm_ctx* ctx, double theta, int precision, const double* m
   // ---- far field, near field, output
   FarArgs f{};
   f.nleaves = nl;
+  f.maxdepth = ctx->maxdepth;
   f.leaf_node = P<int32_t>(ctx, B_LEAFNODE);
   f.leaf_depth = P<int32_t>(ctx, B_LEAFDEPTH);
   f.info = P<NodeInfo>(ctx, B_INFO);

@@ -362,7 +362,7 @@ void launch_leaf_stats(const LeafStatArgs& a, hipStream_t s);
 
 // ---- far field: M2L + L2L chain + L2P ----------------------------------------
 struct FarArgs {
-  int nleaves;
+  int nleaves, maxdepth;
   const int32_t* leaf_node;
   const int32_t* leaf_depth;
   const NodeInfo* info;
