@@ -113,8 +113,9 @@ struct sfmm_ctx {
   Readback* rb = nullptr;  // pinned host block for the read-backs
   // near field beside the far field (SFMM_OVERLAP): the P2P kernel runs on a
   // second stream of the context while the far field runs on `stream`; the
-  // reduction waits for both (0 off, 1 P2P queued first, 2 far field first)
-  int overlap = 0;
+  // reduction waits for both (0 off, 1 P2P queued first, 2 far field first,
+  // -1 by the system's size)
+  int overlap = -1;
   hipStream_t aux = nullptr;
   hipEvent_t fork_ev = nullptr, join_ev = nullptr;
 };
@@ -899,7 +900,13 @@ int do_walk_and_eval(sfmm_ctx* ctx, double theta, int precision, const double* m
   ctx->soft_items = ctx->near_variant == 1 ? 0 : items;
   // the P2P kernel runs beside the far field when it writes only item partial
   // sums: the reduction, which adds the far field, then waits for both
-  const bool overlap = ctx->overlap != 0 && ctx->cfg.leaf_size <= 32 && ctx->near_variant != 1;
+  // By size: from 4096 to 2^19 particles, where neither fills the chip (solves
+  // side by side against one after the other, us: 2.0e3 particles 269-294 against
+  // 291, 4.1e3 320-336 against 349, 5e4 663 against 770, 2e5 1182 against 1364,
+  // 5.2e5 2316 against 2402; a polytrope, a Plummer sphere and a binary of 1e6 and
+  // 2e6 the same within 1 %, a batch of 24 systems of 8.5e5 in all 1 % slower)
+  const int side = ctx->overlap >= 0 ? ctx->overlap : (n >= 4096 && n <= (1 << 19)) ? 2 : 0;
+  const bool overlap = side != 0 && ctx->cfg.leaf_size <= 32 && ctx->near_variant != 1;
   if (overlap && !ctx->aux) {
     HIPCHK(hipStreamCreateWithFlags(&ctx->aux, hipStreamNonBlocking));
     HIPCHK(hipEventCreateWithFlags(&ctx->fork_ev, hipEventDisableTiming));
@@ -968,11 +975,11 @@ int do_walk_and_eval(sfmm_ctx* ctx, double theta, int precision, const double* m
     // phase 3 is then the far field with the P2P kernel beside it, phase 4
     // what is left of the near field after it, with the reduction
     HIPCHK(hipEventRecord(ctx->fork_ev, s));
-    if (ctx->overlap == 2) far_field();
+    if (side == 2) far_field();
     HIPCHK(hipStreamWaitEvent(ctx->aux, ctx->fork_ev, 0));
     if ((rc = near_field(ctx->aux))) return rc;
     HIPCHK(hipEventRecord(ctx->join_ev, ctx->aux));
-    if (ctx->overlap == 1) far_field();
+    if (side == 1) far_field();
     phase_mark(ctx, 3, 1);
     phase_mark(ctx, 4, 0);
     HIPCHK(hipStreamWaitEvent(s, ctx->join_ev, 0));

@@ -48,3 +48,27 @@ def test_order_and_record_edges(torch, P, orc, n, leaf_size, order, theta):
     assert (e / np.maximum(nb, 1e-6 * np.sqrt((nb ** 2).mean()))).max() < TOL
     assert (np.abs(pot.cpu().numpy() - op) / np.abs(op)).max() < TOL
     s.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32c"])
+@pytest.mark.parametrize("n", [4095, 4096, 20000, 1 << 19, (1 << 19) + 1])
+def test_near_beside_far_by_size(torch, P, monkeypatch, n, precision):
+    """The sizes at which the P2P kernel takes a second stream: the same sums, so
+    the same bits, as one after the other; a second solve reuses the buffers."""
+    print(f"case: near beside far n {n} {precision}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    x = torch.randn(n, 3, dtype=torch.float64, device="cuda", generator=g)
+    m = torch.rand(n, dtype=torch.float64, device="cuda", generator=g) + 0.5
+    h = torch.full((n,), 1.2 * n ** (-1.0 / 3.0), dtype=torch.float64, device="cuda")
+    got = []
+    for ov in (None, "0"):
+        if ov is None:
+            monkeypatch.delenv("SFMM_OVERLAP", raising=False)
+        else:
+            monkeypatch.setenv("SFMM_OVERLAP", ov)
+        s = P.Solver()
+        for scale in (1.0, 0.5):
+            acc, pot = s.solve(x * scale, m, h * scale, theta=0.8, precision=precision)[:2]
+            got.append((acc.clone(), pot.clone()))
+    for k in range(2):
+        assert torch.equal(got[k][0], got[2 + k][0]) and torch.equal(got[k][1], got[2 + k][1])
