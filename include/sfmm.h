@@ -169,7 +169,8 @@ int sfmm_config_default(sfmm_config* cfg);
  *   SFMM_NEAR_VARIANT=v  P2P kernel shape v instead of cfg->near_kernel;
  *   SFMM_OVERLAP=0|1|2   run the P2P kernel on a second stream of the
  *                        context beside the far field (1: P2P queued first,
- *                        2: far field first; 0, the default: one stream);
+ *                        2: far field first; 0: one stream; by default 2
+ *                        from 4096 to 2^19 particles, else 0);
  *   SFMM_LEAF_SLOTS=m,p[,i]  first per-leaf M2L / P2P list slots of the
  *                        level walk (1..1024 / 1..512) and, optionally, the
  *                        internal nodes' region slots (1..4096); later walks
@@ -254,7 +255,8 @@ int sfmm_get_leaf_lists(sfmm_ctx* ctx, int64_t leaf, int32_t* m2l_depth, int32_t
  * pass), 2 walk fill pass (SFMM_WALK_LEAF only), 3 far field (M2L + L2L +
  * L2P), 4 near field (P2P + output), 5 momentum reduction; 6 is the main
  * P2P kernel alone (inside phase 4, without the work-item set-up and the
- * reduction of the partial sums).  Between
+ * reduction of the partial sums).  Where P2P runs beside the far field (see
+ * sfmm_create) phase 3 spans both and phase 4 what is left after it.  Between
  * sfmm_timing_start and sfmm_timing_stop each solve records a pair of HIP
  * events around every phase on the context's stream (no extra
  * synchronisation).  sfmm_timing_stop synchronises, writes the durations in

@@ -907,10 +907,10 @@ int do_walk_and_eval(sfmm_ctx* ctx, double theta, int precision, const double* m
   // 2e6 the same within 1 %, a batch of 24 systems of 8.5e5 in all 1 % slower)
   const int side = ctx->overlap >= 0 ? ctx->overlap : (n >= 4096 && n <= (1 << 19)) ? 2 : 0;
   const bool overlap = side != 0 && ctx->cfg.leaf_size <= 32 && ctx->near_variant != 1;
-  if (overlap && !ctx->aux) {
-    HIPCHK(hipStreamCreateWithFlags(&ctx->aux, hipStreamNonBlocking));
-    HIPCHK(hipEventCreateWithFlags(&ctx->fork_ev, hipEventDisableTiming));
-    HIPCHK(hipEventCreateWithFlags(&ctx->join_ev, hipEventDisableTiming));
+  if (overlap) {
+    if (!ctx->fork_ev) HIPCHK(hipEventCreateWithFlags(&ctx->fork_ev, hipEventDisableTiming));
+    if (!ctx->join_ev) HIPCHK(hipEventCreateWithFlags(&ctx->join_ev, hipEventDisableTiming));
+    if (!ctx->aux) HIPCHK(hipStreamCreateWithFlags(&ctx->aux, hipStreamNonBlocking));
   }
   KernelMarks km;
   km.begin = phase_event(ctx, 6, 0);
