@@ -363,8 +363,10 @@ __global__ __launch_bounds__(ST) void k_sort_pass(int n, const uint64_t* __restr
 }
 
 // tiles of 1024 elements while they give every CU one at most, else of 4096
-// (fewer tiles to look back over, longer runs of a digit to write)
-int sort_items(int64_t n) { return n <= (1 << 18) ? 4 : 16; }
+// (fewer tiles to look back over, longer runs of a digit to write).  So the
+// number of tiles falls by a factor of four past kSmallTiles elements.
+constexpr int64_t kSmallTiles = 1 << 18;
+int sort_items(int64_t n) { return n <= kSmallTiles ? 4 : 16; }
 int64_t sort_tiles(int64_t n) { return (n + ST * sort_items(n) - 1) / (ST * sort_items(n)); }
 
 void pass(int n, const uint64_t* kin, const uint32_t* vin, uint64_t* kout, uint32_t* vout,
@@ -382,8 +384,12 @@ unsigned count_blocks(int64_t n) { return (unsigned)std::min<int64_t>((n + 1023)
 }  // namespace
 
 // per pass: 256 digit counts, a ticket (padded), the tiles' words
-size_t sort_words(int64_t n, int passes) {
-  return (size_t)passes * (256 + 64 + 256 * (size_t)sort_tiles(n));
+static size_t words_of_tiles(int64_t tiles, int passes) {
+  return (size_t)passes * (256 + 64 + 256 * (size_t)tiles);
+}
+size_t sort_words(int64_t n, int passes) { return words_of_tiles(sort_tiles(n), passes); }
+size_t sort_room(int64_t n, int passes) {
+  return words_of_tiles(std::max(sort_tiles(n), sort_tiles(std::min(n, kSmallTiles))), passes);
 }
 
 void launch_clear_words(uint32_t* p, size_t n, uint32_t* p2, size_t n2, hipStream_t s) {

@@ -259,7 +259,7 @@ int do_build(sfmm_ctx* ctx, int64_t n64, const double* x, const double* m, const
       {B_SMALL, sizeof(Readback)},
       {B_KEY0, sizeof(uint64_t) * n}, {B_KEY1, sizeof(uint64_t) * n},
       {B_VAL0, sizeof(uint32_t) * n}, {B_VAL1, sizeof(uint32_t) * n},
-      {B_SORT, sizeof(uint32_t) * (sort_words(n, 8 + sys_passes) + 2 * sort_words(nmax_nodes, 1) +
+      {B_SORT, sizeof(uint32_t) * (sort_words(n, 8 + sys_passes) + 2 * sort_room(nmax_nodes, 1) +
                                    (size_t)n + 1)},
       {B_BASE, sizeof(uint32_t) * 256},
       {B_SCANTMP, sizeof(uint64_t) * scan_tmp_elems(2 * (int64_t)n + 2)},
@@ -295,8 +295,8 @@ int do_build(sfmm_ctx* ctx, int64_t n64, const double* x, const double* m, const
   uint32_t* words = P<uint32_t>(ctx, B_SORT);
   uint32_t* words_sys = words + sort_words(n, 8);
   uint32_t* words_depth = words_sys + (sys_passes ? sort_words(n, sys_passes) : 0);
-  ctx->words_m2l = (size_t)(words_depth - words) + sort_words(nmax_nodes, 1);
-  uint32_t* leaf_flag = words + ctx->words_m2l + sort_words(nmax_nodes, 1);
+  ctx->words_m2l = (size_t)(words_depth - words) + sort_room(nmax_nodes, 1);
+  uint32_t* leaf_flag = words + ctx->words_m2l + sort_room(nmax_nodes, 1);
   launch_clear_words(words, (size_t)(leaf_flag - words) + (size_t)n + 1,
                      reinterpret_cast<uint32_t*>(dev), sizeof(Readback) / sizeof(uint32_t), s);
   ctx->walk_clear = true;

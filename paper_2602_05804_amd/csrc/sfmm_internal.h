@@ -129,6 +129,9 @@ void launch_bbox(int n, const double* x, const double* m, const double* h, doubl
 constexpr int kSortSmall = 4096;
 // words of scratch for `passes` passes over n elements, to be cleared before
 size_t sort_words(int64_t n, int passes);
+// the same for a count known later, at most n (sort_words is not monotone:
+// larger inputs are sorted in larger tiles)
+size_t sort_room(int64_t n, int passes);
 // zeroes two ranges of words
 void launch_clear_words(uint32_t* p, size_t n, uint32_t* p2, size_t n2, hipStream_t s);
 // Morton keys in the box of the blocks' corners (part) and their digit counts
