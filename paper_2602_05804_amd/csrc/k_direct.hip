@@ -34,7 +34,7 @@ constexpr int kDirQueue = 64 * (kDirGroup + 1);
 // the softened pair for the sake of one.
 struct DirLds {
   SoftCoef coef[3];
-  double t[5][64];    // the targets' x, y, z, h, 1/h
+  double t[4][64];    // the targets' x, y, z, 1/h
   double acc[4][64];  // their softened sums
   unsigned long long mask[64];
   uint32_t first[64], last[64];
@@ -79,19 +79,20 @@ __device__ __forceinline__ void direct_flush(DirLds& sh, uint32_t at, uint32_t c
   const int64_t j = j0 + (on ? sh.sj[lane] : 0u);
   const int64_t i = targets ? targets[i0 + l] : i0 + l;
   const uint32_t first = on ? sh.first[l] : lane;
-  const double tx = sh.t[0][l], ty = sh.t[1][l], tz = sh.t[2][l], hi = sh.t[3][l],
-               hiinv = sh.t[4][l];
-  const double hj = h[j], hjinv = 1.0 / hj;
-  const double w = on && j != i ? m[j] : 0.0;
+  const double tx = sh.t[0][l], ty = sh.t[1][l], tz = sh.t[2][l], hiinv = sh.t[3][l];
+  const double hjinv = 1.0 / h[j];
+  const bool use = on && j != i;
+  const double w = use ? m[j] : 0.0;
   const double dx = tx - x[3 * j], dy = ty - x[3 * j + 1], dz = tz - x[3 * j + 2];
   const double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
   const double rinv = r2 > 0.0 ? rsqrt(r2) : 0.0;
   const double r = r2 * rinv;
   double g1, p1, g2, p2;
-  soft_piece(sh.coef, r * hiinv, hi * rinv, hiinv, g1, p1);
-  soft_piece(sh.coef, r * hjinv, hj * rinv, hjinv, g2, p2);
+  soft_piece(sh.coef, r * hiinv, hiinv, rinv, g1, p1);
+  soft_piece(sh.coef, r * hjinv, hjinv, rinv, g2, p2);
   const bool inside = (r2 * (hiinv * hiinv) < 4.0) || (r2 * (hjinv * hjinv) < 4.0);
-  const double mg = w * (inside ? 0.5 * (g1 + g2) : rinv * rinv * rinv);
+  // (a pair left out has g = 0: with itself h^-3 may overflow)
+  const double mg = w * (!use ? 0.0 : inside ? 0.5 * (g1 + g2) : rinv * rinv * rinv);
   double v[4] = {mg * dx, mg * dy, mg * dz, w * (inside ? 0.5 * (p1 + p2) : rinv)};
   for (int o = 1; o < 64 && __ballot((int)own > o); o <<= 1) {
 #pragma unroll
@@ -129,8 +130,7 @@ __global__ __launch_bounds__(64) void k_direct_part(int64_t n, const double* __r
   sh.t[0][lane] = xi;
   sh.t[1][lane] = yi;
   sh.t[2][lane] = zi;
-  sh.t[3][lane] = hi;
-  sh.t[4][lane] = 1.0 / hi;
+  sh.t[3][lane] = 1.0 / hi;
 #pragma unroll
   for (int k = 0; k < 4; ++k) sh.acc[k][lane] = 0.0;
   __syncthreads();

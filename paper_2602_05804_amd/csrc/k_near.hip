@@ -301,33 +301,34 @@ __device__ __forceinline__ double p2p_wave_soft(const NearArgs& a, int t0p, Wave
                                                      uint32_t run, double* sum) {
     const int it = t0p + t;
     const double2 txy = a.pxy[it], tzm = a.pzm[it];
-    const double hi = a.hs[it], hiinv = a.his[it];
+    const double hiinv = a.his[it];
     const uint16_t* qt = sh.q + t * kTQ;
     double sx = 0.0, sy = 0.0, sz = 0.0, sp = 0.0;
     // (the next source's record loads while the current pair is evaluated)
     struct Src {
       double2 xy, zm;
-      double h, hinv;
+      double hinv;
     };
     auto load = [&](uint32_t b) {
       const int j = at + b < mylen ? (int)(sh.off[qt[at + b]] >> 4) : it;
-      return Src{a.pxy[j], a.pzm[j], a.hs[j], a.his[j]};
+      return Src{a.pxy[j], a.pzm[j], a.his[j]};
     };
     Src next = load(0);
     for (uint32_t b = 0; b < run; ++b) {
       const bool act = at + b < mylen;
       const double2 sxy = next.xy, szm = next.zm;
-      const double hj = next.h, hjinv = next.hinv;
+      const double hjinv = next.hinv;
       if (b + 1 < run) next = load(b + 1);
       const double dx = txy.x - sxy.x, dy = txy.y - sxy.y, dz = tzm.x - szm.x;
       const double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
       const double rinv = rsqrt_pair(r2);
       const double r = r2 * rinv;
       double g1, p1, g2, p2;
-      soft_piece(sh.coef, r * hiinv, hi * rinv, hiinv, g1, p1);
-      soft_piece(sh.coef, r * hjinv, hj * rinv, hjinv, g2, p2);
+      soft_piece(sh.coef, r * hiinv, hiinv, rinv, g1, p1);
+      soft_piece(sh.coef, r * hjinv, hjinv, rinv, g2, p2);
+      // (lanes past the end hold the target itself, whose h^-3 may overflow)
       const double wm = act ? 0.5 * szm.y : 0.0;
-      const double mg = wm * (g1 + g2);
+      const double mg = wm * (act ? g1 + g2 : 0.0);
       sx = fma(mg, dx, sx);
       sy = fma(mg, dy, sy);
       sz = fma(mg, dz, sz);

@@ -77,11 +77,13 @@ __device__ __forceinline__ void soft_sel(double q, double hinv, double qi, doubl
 }
 
 // One piece of the cubic spline of softening.h: with q = r / h
-//   g   = (c0 + q (c1 + q (c2 + q c3)) - cr / q^3) / h^3
-//   psi = (d0 + q^2 (d2 + q (d3 + q (d4 + q d5))) - dr / q) / h
-// for q < 1, 1 <= q < 2 and q >= 2 (outside: 1/r^3 and 1/r).  A lane reads
-// its piece from LDS, which takes 24 instructions a kernel where evaluating
-// the pieces and selecting takes 38.
+//   g   = u^3 (w^3 (c0 + q (c1 + q (c2 + q c3))) - cr)
+//   psi = u (w (d0 + q^2 (d2 + q (d3 + q (d4 + q d5)))) - dr)
+// for q < 1 (u = 1/h, w = 1), 1 <= q < 2 (u = 1/r, w = q) and q >= 2 (outside:
+// u = 1/r, all but cr and dr 0).  A lane reads its piece from LDS, which takes
+// fewer instructions than evaluating the pieces and selecting (24 against 38 a
+// kernel).  1/h counts for q < 1 only: h^-3 overflows where h is below 1e-103 (a
+// point mass inside another's kernel).
 struct alignas(16) SoftCoef {
   double c0, c1, c2, c3, cr, d0, d2, d3, d4, d5, dr, pad;
 };
@@ -91,16 +93,18 @@ struct alignas(16) SoftCoef {
      1.0 / 15.0, 0.0},
     {0.0, 0.0, 0.0, 0.0, -1.0, 0.0, 0.0, 0.0, 0.0, 0.0, -1.0, 0.0}};
 
-// g = f(q) / (q h^3) and psi(q) / h at q = r hinv, qi = h / r
-__device__ __forceinline__ void soft_piece(const SoftCoef* coef, double q, double qi, double hinv,
-                                           double& g, double& psi) {
-  const SoftCoef& k = coef[q < 1.0 ? 0 : q < 2.0 ? 1 : 2];
-  const double qr = q < 1.0 ? 0.0 : qi;  // (1/q^3 may overflow there; its coefficient is 0)
-  const double q2 = q * q;
-  const double gp = fma(q, fma(q, fma(q, k.c3, k.c2), k.c1), k.c0);
-  const double pp = fma(q2, fma(q, fma(q, fma(q, k.d5, k.d4), k.d3), k.d2), k.d0);
-  g = hinv * hinv * hinv * fma(-k.cr, qr * qr * qr, gp);
-  psi = hinv * fma(-k.dr, qr, pp);
+// g = f(q) / (q h^3) and psi(q) / h at q = r hinv, rinv = 1 / r
+__device__ __forceinline__ void soft_piece(const SoftCoef* coef, double q, double hinv,
+                                           double rinv, double& g, double& psi) {
+  const bool core = q < 1.0;
+  const SoftCoef& k = coef[core ? 0 : q < 2.0 ? 1 : 2];
+  const double qc = fmin(q, 2.0);  // (outside, it meets coefficients of 0 only)
+  const double u = core ? hinv : rinv, w = core ? 1.0 : qc;
+  const double q2 = qc * qc;
+  const double gp = fma(qc, fma(qc, fma(qc, k.c3, k.c2), k.c1), k.c0);
+  const double pp = fma(q2, fma(qc, fma(qc, fma(qc, k.d5, k.d4), k.d3), k.d2), k.d0);
+  g = u * u * u * fma(w * w * w, gp, -k.cr);
+  psi = u * fma(w, pp, -k.dr);
 }
 
 }  // namespace sfmm

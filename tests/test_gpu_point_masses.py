@@ -1,0 +1,61 @@
+"""GPU: particles whose softening length is so small that h^-2 or h^-3 overflows
+(point masses), inside the kernels of others, against the CPU oracle's direct
+sum; bar as for the FP64 solve, 1e-12 per particle.
+"""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-12
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    return torch
+
+
+@pytest.fixture(scope="module")
+def P(torch):
+    import paper_2602_05804_amd as P
+
+    return P
+
+
+def system(h):
+    g = np.random.default_rng(3)
+    n = 300
+    x = g.standard_normal((n, 3))
+    hs = np.full(n, 1.0)
+    hs[::41] = h
+    return x, g.random(n) + 0.5, hs
+
+
+def check(got, want):
+    acc, pot = (t.cpu().numpy() for t in got)
+    assert (np.linalg.norm(acc - want[0], axis=1) / np.linalg.norm(want[0], axis=1)).max() <= TOL
+    assert (np.abs(pot - want[1]) / np.abs(want[1])).max() <= TOL
+
+
+@pytest.mark.parametrize("h", [1e-100, 1e-103, 1e-110, 1e-140, 1e-158, 1e-200, 1e-300])
+def test_direct(torch, P, orc, h):
+    print(f"case: direct, point masses of h {h}", flush=True)
+    x, m, hs = system(h)
+    s = P.Solver(include_self_potential=False)
+    got = s.direct(*(torch.from_numpy(a).cuda() for a in (x, m, hs)))
+    check(got, orc.direct(x, m, hs, include_self=False))
+
+
+@pytest.mark.parametrize("near_kernel", [0, 6, 1])
+@pytest.mark.parametrize("h", [1e-100, 1e-103, 1e-110, 1e-140, 1e-158])
+def test_solve(torch, P, orc, h, near_kernel):
+    """(an opening angle at which every pair is summed directly)"""
+    print(f"case: solve, point masses of h {h}, shape {near_kernel}", flush=True)
+    x, m, hs = system(h)
+    s = P.Solver(include_self_potential=False, near_kernel=near_kernel)
+    got = s.solve(*(torch.from_numpy(a).cuda() for a in (x, m, hs)), theta=0.05)
+    check(got, orc.direct(x, m, hs, include_self=False))
