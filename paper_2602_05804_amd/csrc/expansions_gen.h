@@ -87,19 +87,20 @@ template <> struct Exp<0> {
   __device__ __forceinline__ static void m2l_h(const double* r, const double* Qr, double* lr, bool ok) {
     const double r2 = fma(r[0], r[0], fma(r[1], r[1], r[2] * r[2]));
     const double ri = rsqrt_refined(r2);
-    const double rinv = ok ? ri : 0.0;
+    const double rinv = ok && r2 < __builtin_inf() ? ri : 0.0;
     const double s = rinv * rinv;
+    const double w[3] = {r[0] * s, r[1] * s, r[2] * s};
     const double R0_000 = rinv;
-    const double R1_000 = R0_000 * (-1.0 * s);
+    const double R1_000 = -1.0 * rinv;
     lr[0] = fma(R0_000, Qr[0], lr[0]);
-    const double R0_100 = r[0] * R1_000;
+    const double R0_100 = w[0] * R1_000;
     lr[1] = fma(R0_100, Qr[0], lr[1]);
-    const double R0_010 = r[1] * R1_000;
+    const double R0_010 = w[1] * R1_000;
     lr[2] = fma(R0_010, Qr[0], lr[2]);
-    const double R0_001 = r[2] * R1_000;
+    const double R0_001 = w[2] * R1_000;
     lr[3] = fma(R0_001, Qr[0], lr[3]);
   }
-  static constexpr int FLOPS_M2L_H = 18;  // + one refined rsqrt
+  static constexpr int FLOPS_M2L_H = 21;  // + one refined rsqrt
   __device__ __forceinline__ static void expand(const double* lr, double* local) {
     double t[4];
     t[0] = lr[0];
@@ -372,46 +373,48 @@ template <> struct Exp<1> {
   __device__ __forceinline__ static void m2l_h(const double* r, const double* Qr, double* lr, bool ok) {
     const double r2 = fma(r[0], r[0], fma(r[1], r[1], r[2] * r[2]));
     const double ri = rsqrt_refined(r2);
-    const double rinv = ok ? ri : 0.0;
+    const double rinv = ok && r2 < __builtin_inf() ? ri : 0.0;
     const double s = rinv * rinv;
+    const double w[3] = {r[0] * s, r[1] * s, r[2] * s};
     const double R0_000 = rinv;
-    const double R1_000 = R0_000 * (-1.0 * s);
-    const double R2_000 = R1_000 * (-3.0 * s);
+    const double R1_000 = -1.0 * rinv;
+    const double R2_000 = 3.0 * rinv;
     lr[0] = fma(R0_000, Qr[0], lr[0]);
-    const double R0_100 = r[0] * R1_000;
+    const double R0_100 = w[0] * R1_000;
     lr[0] = fma(R0_100, Qr[1], lr[0]);
     lr[1] = fma(R0_100, Qr[0], lr[1]);
-    const double R0_010 = r[1] * R1_000;
+    const double R0_010 = w[1] * R1_000;
     lr[0] = fma(R0_010, Qr[2], lr[0]);
     lr[2] = fma(R0_010, Qr[0], lr[2]);
-    const double R0_001 = r[2] * R1_000;
+    const double R0_001 = w[2] * R1_000;
     lr[0] = fma(R0_001, Qr[3], lr[0]);
     lr[3] = fma(R0_001, Qr[0], lr[3]);
-    const double R1_100 = r[0] * R2_000;
-    const double R0_200 = fma(r[0], R1_100, R1_000);
+    const double R1_100 = w[0] * R2_000;
+    const double T1_000 = s * R1_000;
+    const double R0_200 = fma(w[0], R1_100, T1_000);
     lr[4] = fma(R0_200, Qr[1], lr[4]);
     lr[7] = fma(R0_200, Qr[0], lr[7]);
-    const double R1_010 = r[1] * R2_000;
-    const double R0_110 = r[0] * R1_010;
+    const double R1_010 = w[1] * R2_000;
+    const double R0_110 = w[0] * R1_010;
     lr[4] = fma(R0_110, Qr[2], lr[4]);
     lr[5] = fma(R0_110, Qr[1], lr[5]);
     lr[8] = fma(R0_110, Qr[0], lr[8]);
     __builtin_amdgcn_sched_barrier(0);
-    const double R0_101 = r[2] * R1_100;
+    const double R0_101 = w[2] * R1_100;
     lr[4] = fma(R0_101, Qr[3], lr[4]);
     lr[6] = fma(R0_101, Qr[1], lr[6]);
     lr[9] = fma(R0_101, Qr[0], lr[9]);
-    const double R0_020 = fma(r[1], R1_010, R1_000);
+    const double R0_020 = fma(w[1], R1_010, T1_000);
     lr[5] = fma(R0_020, Qr[2], lr[5]);
     lr[10] = fma(R0_020, Qr[0], lr[10]);
-    const double R0_011 = r[2] * R1_010;
+    const double R0_011 = w[2] * R1_010;
     lr[5] = fma(R0_011, Qr[3], lr[5]);
     lr[6] = fma(R0_011, Qr[2], lr[6]);
     lr[11] = fma(R0_011, Qr[0], lr[11]);
     const double R0_002 = -(R0_200 + R0_020);
     lr[6] = fma(R0_002, Qr[3], lr[6]);
   }
-  static constexpr int FLOPS_M2L_H = 64;  // + one refined rsqrt
+  static constexpr int FLOPS_M2L_H = 67;  // + one refined rsqrt
   __device__ __forceinline__ static void expand(const double* lr, double* local) {
     double t[10];
     t[0] = lr[0];
@@ -1039,44 +1042,46 @@ template <> struct Exp<2> {
   __device__ __forceinline__ static void m2l_h(const double* r, const double* Qr, double* lr, bool ok) {
     const double r2 = fma(r[0], r[0], fma(r[1], r[1], r[2] * r[2]));
     const double ri = rsqrt_refined(r2);
-    const double rinv = ok ? ri : 0.0;
+    const double rinv = ok && r2 < __builtin_inf() ? ri : 0.0;
     const double s = rinv * rinv;
+    const double w[3] = {r[0] * s, r[1] * s, r[2] * s};
     const double R0_000 = rinv;
-    const double R1_000 = R0_000 * (-1.0 * s);
-    const double R2_000 = R1_000 * (-3.0 * s);
-    const double R3_000 = R2_000 * (-5.0 * s);
+    const double R1_000 = -1.0 * rinv;
+    const double R2_000 = 3.0 * rinv;
+    const double R3_000 = -15.0 * rinv;
     lr[0] = fma(R0_000, Qr[0], lr[0]);
-    const double R0_100 = r[0] * R1_000;
+    const double R0_100 = w[0] * R1_000;
     lr[0] = fma(R0_100, Qr[1], lr[0]);
     lr[1] = fma(R0_100, Qr[0], lr[1]);
-    const double R0_010 = r[1] * R1_000;
+    const double R0_010 = w[1] * R1_000;
     lr[0] = fma(R0_010, Qr[2], lr[0]);
     lr[2] = fma(R0_010, Qr[0], lr[2]);
-    const double R0_001 = r[2] * R1_000;
+    const double R0_001 = w[2] * R1_000;
     lr[0] = fma(R0_001, Qr[3], lr[0]);
     lr[3] = fma(R0_001, Qr[0], lr[3]);
-    const double R1_100 = r[0] * R2_000;
-    const double R0_200 = fma(r[0], R1_100, R1_000);
+    const double R1_100 = w[0] * R2_000;
+    const double T1_000 = s * R1_000;
+    const double R0_200 = fma(w[0], R1_100, T1_000);
     lr[0] = fma(R0_200, Qr[4], lr[0]);
     lr[1] = fma(R0_200, Qr[1], lr[1]);
     lr[4] = fma(R0_200, Qr[0], lr[4]);
-    const double R1_010 = r[1] * R2_000;
-    const double R0_110 = r[0] * R1_010;
+    const double R1_010 = w[1] * R2_000;
+    const double R0_110 = w[0] * R1_010;
     lr[0] = fma(R0_110, Qr[5], lr[0]);
     lr[1] = fma(R0_110, Qr[2], lr[1]);
     lr[2] = fma(R0_110, Qr[1], lr[2]);
     lr[5] = fma(R0_110, Qr[0], lr[5]);
     __builtin_amdgcn_sched_barrier(0);
-    const double R0_101 = r[2] * R1_100;
+    const double R0_101 = w[2] * R1_100;
     lr[0] = fma(R0_101, Qr[6], lr[0]);
     lr[1] = fma(R0_101, Qr[3], lr[1]);
     lr[3] = fma(R0_101, Qr[1], lr[3]);
     lr[6] = fma(R0_101, Qr[0], lr[6]);
-    const double R0_020 = fma(r[1], R1_010, R1_000);
+    const double R0_020 = fma(w[1], R1_010, T1_000);
     lr[0] = fma(R0_020, Qr[7], lr[0]);
     lr[2] = fma(R0_020, Qr[2], lr[2]);
     lr[7] = fma(R0_020, Qr[0], lr[7]);
-    const double R0_011 = r[2] * R1_010;
+    const double R0_011 = w[2] * R1_010;
     lr[0] = fma(R0_011, Qr[8], lr[0]);
     lr[2] = fma(R0_011, Qr[3], lr[2]);
     lr[3] = fma(R0_011, Qr[2], lr[3]);
@@ -1084,34 +1089,37 @@ template <> struct Exp<2> {
     const double R0_002 = -(R0_200 + R0_020);
     lr[3] = fma(R0_002, Qr[3], lr[3]);
     __builtin_amdgcn_sched_barrier(0);
-    const double R2_100 = r[0] * R3_000;
-    const double R1_200 = fma(r[0], R2_100, R2_000);
-    const double R0_300 = fma(r[0], R1_200, 2.0 * R1_100);
+    const double R2_100 = w[0] * R3_000;
+    const double T2_000 = s * R2_000;
+    const double R1_200 = fma(w[0], R2_100, T2_000);
+    const double T1_100 = s * R1_100;
+    const double R0_300 = fma(w[0], R1_200, 2.0 * T1_100);
     lr[9] = fma(R0_300, Qr[4], lr[9]);
     lr[12] = fma(R0_300, Qr[1], lr[12]);
     lr[17] = fma(R0_300, Qr[0], lr[17]);
-    const double R2_010 = r[1] * R3_000;
-    const double R1_110 = r[0] * R2_010;
-    const double R0_210 = fma(r[0], R1_110, R1_010);
+    const double R2_010 = w[1] * R3_000;
+    const double R1_110 = w[0] * R2_010;
+    const double T1_010 = s * R1_010;
+    const double R0_210 = fma(w[0], R1_110, T1_010);
     lr[9] = fma(R0_210, Qr[5], lr[9]);
     lr[10] = fma(R0_210, Qr[4], lr[10]);
     lr[12] = fma(R0_210, Qr[2], lr[12]);
     lr[13] = fma(R0_210, Qr[1], lr[13]);
     lr[18] = fma(R0_210, Qr[0], lr[18]);
-    const double R0_201 = r[2] * R1_200;
+    const double R0_201 = w[2] * R1_200;
     lr[9] = fma(R0_201, Qr[6], lr[9]);
     lr[11] = fma(R0_201, Qr[4], lr[11]);
     lr[12] = fma(R0_201, Qr[3], lr[12]);
     lr[14] = fma(R0_201, Qr[1], lr[14]);
     lr[19] = fma(R0_201, Qr[0], lr[19]);
     __builtin_amdgcn_sched_barrier(0);
-    const double R0_120 = fma(r[1], R1_110, R1_100);
+    const double R0_120 = fma(w[1], R1_110, T1_100);
     lr[9] = fma(R0_120, Qr[7], lr[9]);
     lr[10] = fma(R0_120, Qr[5], lr[10]);
     lr[13] = fma(R0_120, Qr[2], lr[13]);
     lr[15] = fma(R0_120, Qr[1], lr[15]);
     lr[20] = fma(R0_120, Qr[0], lr[20]);
-    const double R0_111 = r[2] * R1_110;
+    const double R0_111 = w[2] * R1_110;
     lr[9] = fma(R0_111, Qr[8], lr[9]);
     lr[10] = fma(R0_111, Qr[6], lr[10]);
     lr[11] = fma(R0_111, Qr[5], lr[11]);
@@ -1123,12 +1131,12 @@ template <> struct Exp<2> {
     const double R0_102 = -(R0_300 + R0_120);
     lr[11] = fma(R0_102, Qr[6], lr[11]);
     lr[14] = fma(R0_102, Qr[3], lr[14]);
-    const double R1_020 = fma(r[1], R2_010, R2_000);
-    const double R0_030 = fma(r[1], R1_020, 2.0 * R1_010);
+    const double R1_020 = fma(w[1], R2_010, T2_000);
+    const double R0_030 = fma(w[1], R1_020, 2.0 * T1_010);
     lr[10] = fma(R0_030, Qr[7], lr[10]);
     lr[15] = fma(R0_030, Qr[2], lr[15]);
     lr[22] = fma(R0_030, Qr[0], lr[22]);
-    const double R0_021 = r[2] * R1_020;
+    const double R0_021 = w[2] * R1_020;
     lr[10] = fma(R0_021, Qr[8], lr[10]);
     lr[11] = fma(R0_021, Qr[7], lr[11]);
     lr[15] = fma(R0_021, Qr[3], lr[15]);
@@ -1138,7 +1146,7 @@ template <> struct Exp<2> {
     lr[11] = fma(R0_012, Qr[8], lr[11]);
     lr[16] = fma(R0_012, Qr[3], lr[16]);
   }
-  static constexpr int FLOPS_M2L_H = 172;  // + one refined rsqrt
+  static constexpr int FLOPS_M2L_H = 177;  // + one refined rsqrt
   __device__ __forceinline__ static void expand(const double* lr, double* local) {
     double t[20];
     t[0] = lr[0];
@@ -2459,45 +2467,47 @@ template <> struct Exp<3> {
   __device__ __forceinline__ static void m2l_h(const double* r, const double* Qr, double* lr, bool ok) {
     const double r2 = fma(r[0], r[0], fma(r[1], r[1], r[2] * r[2]));
     const double ri = rsqrt_refined(r2);
-    const double rinv = ok ? ri : 0.0;
+    const double rinv = ok && r2 < __builtin_inf() ? ri : 0.0;
     const double s = rinv * rinv;
+    const double w[3] = {r[0] * s, r[1] * s, r[2] * s};
     const double R0_000 = rinv;
-    const double R1_000 = R0_000 * (-1.0 * s);
-    const double R2_000 = R1_000 * (-3.0 * s);
-    const double R3_000 = R2_000 * (-5.0 * s);
-    const double R4_000 = R3_000 * (-7.0 * s);
+    const double R1_000 = -1.0 * rinv;
+    const double R2_000 = 3.0 * rinv;
+    const double R3_000 = -15.0 * rinv;
+    const double R4_000 = 105.0 * rinv;
     lr[0] = fma(R0_000, Qr[0], lr[0]);
-    const double R0_100 = r[0] * R1_000;
+    const double R0_100 = w[0] * R1_000;
     lr[0] = fma(R0_100, Qr[1], lr[0]);
     lr[1] = fma(R0_100, Qr[0], lr[1]);
-    const double R0_010 = r[1] * R1_000;
+    const double R0_010 = w[1] * R1_000;
     lr[0] = fma(R0_010, Qr[2], lr[0]);
     lr[2] = fma(R0_010, Qr[0], lr[2]);
-    const double R0_001 = r[2] * R1_000;
+    const double R0_001 = w[2] * R1_000;
     lr[0] = fma(R0_001, Qr[3], lr[0]);
     lr[3] = fma(R0_001, Qr[0], lr[3]);
-    const double R1_100 = r[0] * R2_000;
-    const double R0_200 = fma(r[0], R1_100, R1_000);
+    const double R1_100 = w[0] * R2_000;
+    const double T1_000 = s * R1_000;
+    const double R0_200 = fma(w[0], R1_100, T1_000);
     lr[0] = fma(R0_200, Qr[4], lr[0]);
     lr[1] = fma(R0_200, Qr[1], lr[1]);
     lr[4] = fma(R0_200, Qr[0], lr[4]);
-    const double R1_010 = r[1] * R2_000;
-    const double R0_110 = r[0] * R1_010;
+    const double R1_010 = w[1] * R2_000;
+    const double R0_110 = w[0] * R1_010;
     lr[0] = fma(R0_110, Qr[5], lr[0]);
     lr[1] = fma(R0_110, Qr[2], lr[1]);
     lr[2] = fma(R0_110, Qr[1], lr[2]);
     lr[5] = fma(R0_110, Qr[0], lr[5]);
     __builtin_amdgcn_sched_barrier(0);
-    const double R0_101 = r[2] * R1_100;
+    const double R0_101 = w[2] * R1_100;
     lr[0] = fma(R0_101, Qr[6], lr[0]);
     lr[1] = fma(R0_101, Qr[3], lr[1]);
     lr[3] = fma(R0_101, Qr[1], lr[3]);
     lr[6] = fma(R0_101, Qr[0], lr[6]);
-    const double R0_020 = fma(r[1], R1_010, R1_000);
+    const double R0_020 = fma(w[1], R1_010, T1_000);
     lr[0] = fma(R0_020, Qr[7], lr[0]);
     lr[2] = fma(R0_020, Qr[2], lr[2]);
     lr[7] = fma(R0_020, Qr[0], lr[7]);
-    const double R0_011 = r[2] * R1_010;
+    const double R0_011 = w[2] * R1_010;
     lr[0] = fma(R0_011, Qr[8], lr[0]);
     lr[2] = fma(R0_011, Qr[3], lr[2]);
     lr[3] = fma(R0_011, Qr[2], lr[3]);
@@ -2505,23 +2515,26 @@ template <> struct Exp<3> {
     const double R0_002 = -(R0_200 + R0_020);
     lr[3] = fma(R0_002, Qr[3], lr[3]);
     __builtin_amdgcn_sched_barrier(0);
-    const double R2_100 = r[0] * R3_000;
-    const double R1_200 = fma(r[0], R2_100, R2_000);
-    const double R0_300 = fma(r[0], R1_200, 2.0 * R1_100);
+    const double R2_100 = w[0] * R3_000;
+    const double T2_000 = s * R2_000;
+    const double R1_200 = fma(w[0], R2_100, T2_000);
+    const double T1_100 = s * R1_100;
+    const double R0_300 = fma(w[0], R1_200, 2.0 * T1_100);
     lr[0] = fma(R0_300, Qr[9], lr[0]);
     lr[1] = fma(R0_300, Qr[4], lr[1]);
     lr[4] = fma(R0_300, Qr[1], lr[4]);
     lr[9] = fma(R0_300, Qr[0], lr[9]);
-    const double R2_010 = r[1] * R3_000;
-    const double R1_110 = r[0] * R2_010;
-    const double R0_210 = fma(r[0], R1_110, R1_010);
+    const double R2_010 = w[1] * R3_000;
+    const double R1_110 = w[0] * R2_010;
+    const double T1_010 = s * R1_010;
+    const double R0_210 = fma(w[0], R1_110, T1_010);
     lr[0] = fma(R0_210, Qr[10], lr[0]);
     lr[1] = fma(R0_210, Qr[5], lr[1]);
     lr[2] = fma(R0_210, Qr[4], lr[2]);
     lr[4] = fma(R0_210, Qr[2], lr[4]);
     lr[5] = fma(R0_210, Qr[1], lr[5]);
     lr[10] = fma(R0_210, Qr[0], lr[10]);
-    const double R0_201 = r[2] * R1_200;
+    const double R0_201 = w[2] * R1_200;
     lr[0] = fma(R0_201, Qr[11], lr[0]);
     lr[1] = fma(R0_201, Qr[6], lr[1]);
     lr[3] = fma(R0_201, Qr[4], lr[3]);
@@ -2529,14 +2542,14 @@ template <> struct Exp<3> {
     lr[6] = fma(R0_201, Qr[1], lr[6]);
     lr[11] = fma(R0_201, Qr[0], lr[11]);
     __builtin_amdgcn_sched_barrier(0);
-    const double R0_120 = fma(r[1], R1_110, R1_100);
+    const double R0_120 = fma(w[1], R1_110, T1_100);
     lr[0] = fma(R0_120, Qr[12], lr[0]);
     lr[1] = fma(R0_120, Qr[7], lr[1]);
     lr[2] = fma(R0_120, Qr[5], lr[2]);
     lr[5] = fma(R0_120, Qr[2], lr[5]);
     lr[7] = fma(R0_120, Qr[1], lr[7]);
     lr[12] = fma(R0_120, Qr[0], lr[12]);
-    const double R0_111 = r[2] * R1_110;
+    const double R0_111 = w[2] * R1_110;
     lr[0] = fma(R0_111, Qr[13], lr[0]);
     lr[1] = fma(R0_111, Qr[8], lr[1]);
     lr[2] = fma(R0_111, Qr[6], lr[2]);
@@ -2549,13 +2562,13 @@ template <> struct Exp<3> {
     const double R0_102 = -(R0_300 + R0_120);
     lr[3] = fma(R0_102, Qr[6], lr[3]);
     lr[6] = fma(R0_102, Qr[3], lr[6]);
-    const double R1_020 = fma(r[1], R2_010, R2_000);
-    const double R0_030 = fma(r[1], R1_020, 2.0 * R1_010);
+    const double R1_020 = fma(w[1], R2_010, T2_000);
+    const double R0_030 = fma(w[1], R1_020, 2.0 * T1_010);
     lr[0] = fma(R0_030, Qr[14], lr[0]);
     lr[2] = fma(R0_030, Qr[7], lr[2]);
     lr[7] = fma(R0_030, Qr[2], lr[7]);
     lr[14] = fma(R0_030, Qr[0], lr[14]);
-    const double R0_021 = r[2] * R1_020;
+    const double R0_021 = w[2] * R1_020;
     lr[0] = fma(R0_021, Qr[15], lr[0]);
     lr[2] = fma(R0_021, Qr[8], lr[2]);
     lr[3] = fma(R0_021, Qr[7], lr[3]);
@@ -2566,18 +2579,23 @@ template <> struct Exp<3> {
     const double R0_012 = -(R0_210 + R0_030);
     lr[3] = fma(R0_012, Qr[8], lr[3]);
     lr[8] = fma(R0_012, Qr[3], lr[8]);
-    const double R3_100 = r[0] * R4_000;
-    const double R2_200 = fma(r[0], R3_100, R3_000);
-    const double R1_300 = fma(r[0], R2_200, 2.0 * R2_100);
-    const double R0_400 = fma(r[0], R1_300, 3.0 * R1_200);
+    const double R3_100 = w[0] * R4_000;
+    const double T3_000 = s * R3_000;
+    const double R2_200 = fma(w[0], R3_100, T3_000);
+    const double T2_100 = s * R2_100;
+    const double R1_300 = fma(w[0], R2_200, 2.0 * T2_100);
+    const double T1_200 = s * R1_200;
+    const double R0_400 = fma(w[0], R1_300, 3.0 * T1_200);
     lr[16] = fma(R0_400, Qr[9], lr[16]);
     lr[19] = fma(R0_400, Qr[4], lr[19]);
     lr[24] = fma(R0_400, Qr[1], lr[24]);
     lr[31] = fma(R0_400, Qr[0], lr[31]);
-    const double R3_010 = r[1] * R4_000;
-    const double R2_110 = r[0] * R3_010;
-    const double R1_210 = fma(r[0], R2_110, R2_010);
-    const double R0_310 = fma(r[0], R1_210, 2.0 * R1_110);
+    const double R3_010 = w[1] * R4_000;
+    const double R2_110 = w[0] * R3_010;
+    const double T2_010 = s * R2_010;
+    const double R1_210 = fma(w[0], R2_110, T2_010);
+    const double T1_110 = s * R1_110;
+    const double R0_310 = fma(w[0], R1_210, 2.0 * T1_110);
     lr[16] = fma(R0_310, Qr[10], lr[16]);
     lr[17] = fma(R0_310, Qr[9], lr[17]);
     lr[19] = fma(R0_310, Qr[5], lr[19]);
@@ -2586,7 +2604,7 @@ template <> struct Exp<3> {
     lr[25] = fma(R0_310, Qr[1], lr[25]);
     lr[32] = fma(R0_310, Qr[0], lr[32]);
     __builtin_amdgcn_sched_barrier(0);
-    const double R0_301 = r[2] * R1_300;
+    const double R0_301 = w[2] * R1_300;
     lr[16] = fma(R0_301, Qr[11], lr[16]);
     lr[18] = fma(R0_301, Qr[9], lr[18]);
     lr[19] = fma(R0_301, Qr[6], lr[19]);
@@ -2594,8 +2612,9 @@ template <> struct Exp<3> {
     lr[24] = fma(R0_301, Qr[3], lr[24]);
     lr[26] = fma(R0_301, Qr[1], lr[26]);
     lr[33] = fma(R0_301, Qr[0], lr[33]);
-    const double R1_120 = fma(r[1], R2_110, R2_100);
-    const double R0_220 = fma(r[0], R1_120, R1_020);
+    const double R1_120 = fma(w[1], R2_110, T2_100);
+    const double T1_020 = s * R1_020;
+    const double R0_220 = fma(w[0], R1_120, T1_020);
     lr[16] = fma(R0_220, Qr[12], lr[16]);
     lr[17] = fma(R0_220, Qr[10], lr[17]);
     lr[19] = fma(R0_220, Qr[7], lr[19]);
@@ -2605,7 +2624,7 @@ template <> struct Exp<3> {
     lr[27] = fma(R0_220, Qr[1], lr[27]);
     lr[34] = fma(R0_220, Qr[0], lr[34]);
     __builtin_amdgcn_sched_barrier(0);
-    const double R0_211 = r[2] * R1_210;
+    const double R0_211 = w[2] * R1_210;
     lr[16] = fma(R0_211, Qr[13], lr[16]);
     lr[17] = fma(R0_211, Qr[11], lr[17]);
     lr[18] = fma(R0_211, Qr[10], lr[18]);
@@ -2622,7 +2641,7 @@ template <> struct Exp<3> {
     lr[21] = fma(R0_202, Qr[6], lr[21]);
     lr[26] = fma(R0_202, Qr[3], lr[26]);
     __builtin_amdgcn_sched_barrier(0);
-    const double R0_130 = fma(r[1], R1_120, 2.0 * R1_110);
+    const double R0_130 = fma(w[1], R1_120, 2.0 * T1_110);
     lr[16] = fma(R0_130, Qr[14], lr[16]);
     lr[17] = fma(R0_130, Qr[12], lr[17]);
     lr[20] = fma(R0_130, Qr[7], lr[20]);
@@ -2630,7 +2649,7 @@ template <> struct Exp<3> {
     lr[27] = fma(R0_130, Qr[2], lr[27]);
     lr[29] = fma(R0_130, Qr[1], lr[29]);
     lr[36] = fma(R0_130, Qr[0], lr[36]);
-    const double R0_121 = r[2] * R1_120;
+    const double R0_121 = w[2] * R1_120;
     lr[16] = fma(R0_121, Qr[15], lr[16]);
     lr[17] = fma(R0_121, Qr[13], lr[17]);
     lr[18] = fma(R0_121, Qr[12], lr[18]);
@@ -2648,14 +2667,14 @@ template <> struct Exp<3> {
     lr[21] = fma(R0_112, Qr[8], lr[21]);
     lr[23] = fma(R0_112, Qr[6], lr[23]);
     lr[28] = fma(R0_112, Qr[3], lr[28]);
-    const double R2_020 = fma(r[1], R3_010, R3_000);
-    const double R1_030 = fma(r[1], R2_020, 2.0 * R2_010);
-    const double R0_040 = fma(r[1], R1_030, 3.0 * R1_020);
+    const double R2_020 = fma(w[1], R3_010, T3_000);
+    const double R1_030 = fma(w[1], R2_020, 2.0 * T2_010);
+    const double R0_040 = fma(w[1], R1_030, 3.0 * T1_020);
     lr[17] = fma(R0_040, Qr[14], lr[17]);
     lr[22] = fma(R0_040, Qr[7], lr[22]);
     lr[29] = fma(R0_040, Qr[2], lr[29]);
     lr[38] = fma(R0_040, Qr[0], lr[38]);
-    const double R0_031 = r[2] * R1_030;
+    const double R0_031 = w[2] * R1_030;
     lr[17] = fma(R0_031, Qr[15], lr[17]);
     lr[18] = fma(R0_031, Qr[14], lr[18]);
     lr[22] = fma(R0_031, Qr[8], lr[22]);
@@ -2669,7 +2688,7 @@ template <> struct Exp<3> {
     lr[23] = fma(R0_022, Qr[8], lr[23]);
     lr[30] = fma(R0_022, Qr[3], lr[30]);
   }
-  static constexpr int FLOPS_M2L_H = 378;  // + one refined rsqrt
+  static constexpr int FLOPS_M2L_H = 388;  // + one refined rsqrt
   __device__ __forceinline__ static void expand(const double* lr, double* local) {
     double t[35];
     t[0] = lr[0];
@@ -5235,46 +5254,48 @@ template <> struct Exp<4> {
   __device__ __forceinline__ static void m2l_h(const double* r, const double* Qr, double* lr, bool ok) {
     const double r2 = fma(r[0], r[0], fma(r[1], r[1], r[2] * r[2]));
     const double ri = rsqrt_refined(r2);
-    const double rinv = ok ? ri : 0.0;
+    const double rinv = ok && r2 < __builtin_inf() ? ri : 0.0;
     const double s = rinv * rinv;
+    const double w[3] = {r[0] * s, r[1] * s, r[2] * s};
     const double R0_000 = rinv;
-    const double R1_000 = R0_000 * (-1.0 * s);
-    const double R2_000 = R1_000 * (-3.0 * s);
-    const double R3_000 = R2_000 * (-5.0 * s);
-    const double R4_000 = R3_000 * (-7.0 * s);
-    const double R5_000 = R4_000 * (-9.0 * s);
+    const double R1_000 = -1.0 * rinv;
+    const double R2_000 = 3.0 * rinv;
+    const double R3_000 = -15.0 * rinv;
+    const double R4_000 = 105.0 * rinv;
+    const double R5_000 = -945.0 * rinv;
     lr[0] = fma(R0_000, Qr[0], lr[0]);
-    const double R0_100 = r[0] * R1_000;
+    const double R0_100 = w[0] * R1_000;
     lr[0] = fma(R0_100, Qr[1], lr[0]);
     lr[1] = fma(R0_100, Qr[0], lr[1]);
-    const double R0_010 = r[1] * R1_000;
+    const double R0_010 = w[1] * R1_000;
     lr[0] = fma(R0_010, Qr[2], lr[0]);
     lr[2] = fma(R0_010, Qr[0], lr[2]);
-    const double R0_001 = r[2] * R1_000;
+    const double R0_001 = w[2] * R1_000;
     lr[0] = fma(R0_001, Qr[3], lr[0]);
     lr[3] = fma(R0_001, Qr[0], lr[3]);
-    const double R1_100 = r[0] * R2_000;
-    const double R0_200 = fma(r[0], R1_100, R1_000);
+    const double R1_100 = w[0] * R2_000;
+    const double T1_000 = s * R1_000;
+    const double R0_200 = fma(w[0], R1_100, T1_000);
     lr[0] = fma(R0_200, Qr[4], lr[0]);
     lr[1] = fma(R0_200, Qr[1], lr[1]);
     lr[4] = fma(R0_200, Qr[0], lr[4]);
-    const double R1_010 = r[1] * R2_000;
-    const double R0_110 = r[0] * R1_010;
+    const double R1_010 = w[1] * R2_000;
+    const double R0_110 = w[0] * R1_010;
     lr[0] = fma(R0_110, Qr[5], lr[0]);
     lr[1] = fma(R0_110, Qr[2], lr[1]);
     lr[2] = fma(R0_110, Qr[1], lr[2]);
     lr[5] = fma(R0_110, Qr[0], lr[5]);
     __builtin_amdgcn_sched_barrier(0);
-    const double R0_101 = r[2] * R1_100;
+    const double R0_101 = w[2] * R1_100;
     lr[0] = fma(R0_101, Qr[6], lr[0]);
     lr[1] = fma(R0_101, Qr[3], lr[1]);
     lr[3] = fma(R0_101, Qr[1], lr[3]);
     lr[6] = fma(R0_101, Qr[0], lr[6]);
-    const double R0_020 = fma(r[1], R1_010, R1_000);
+    const double R0_020 = fma(w[1], R1_010, T1_000);
     lr[0] = fma(R0_020, Qr[7], lr[0]);
     lr[2] = fma(R0_020, Qr[2], lr[2]);
     lr[7] = fma(R0_020, Qr[0], lr[7]);
-    const double R0_011 = r[2] * R1_010;
+    const double R0_011 = w[2] * R1_010;
     lr[0] = fma(R0_011, Qr[8], lr[0]);
     lr[2] = fma(R0_011, Qr[3], lr[2]);
     lr[3] = fma(R0_011, Qr[2], lr[3]);
@@ -5282,23 +5303,26 @@ template <> struct Exp<4> {
     const double R0_002 = -(R0_200 + R0_020);
     lr[3] = fma(R0_002, Qr[3], lr[3]);
     __builtin_amdgcn_sched_barrier(0);
-    const double R2_100 = r[0] * R3_000;
-    const double R1_200 = fma(r[0], R2_100, R2_000);
-    const double R0_300 = fma(r[0], R1_200, 2.0 * R1_100);
+    const double R2_100 = w[0] * R3_000;
+    const double T2_000 = s * R2_000;
+    const double R1_200 = fma(w[0], R2_100, T2_000);
+    const double T1_100 = s * R1_100;
+    const double R0_300 = fma(w[0], R1_200, 2.0 * T1_100);
     lr[0] = fma(R0_300, Qr[9], lr[0]);
     lr[1] = fma(R0_300, Qr[4], lr[1]);
     lr[4] = fma(R0_300, Qr[1], lr[4]);
     lr[9] = fma(R0_300, Qr[0], lr[9]);
-    const double R2_010 = r[1] * R3_000;
-    const double R1_110 = r[0] * R2_010;
-    const double R0_210 = fma(r[0], R1_110, R1_010);
+    const double R2_010 = w[1] * R3_000;
+    const double R1_110 = w[0] * R2_010;
+    const double T1_010 = s * R1_010;
+    const double R0_210 = fma(w[0], R1_110, T1_010);
     lr[0] = fma(R0_210, Qr[10], lr[0]);
     lr[1] = fma(R0_210, Qr[5], lr[1]);
     lr[2] = fma(R0_210, Qr[4], lr[2]);
     lr[4] = fma(R0_210, Qr[2], lr[4]);
     lr[5] = fma(R0_210, Qr[1], lr[5]);
     lr[10] = fma(R0_210, Qr[0], lr[10]);
-    const double R0_201 = r[2] * R1_200;
+    const double R0_201 = w[2] * R1_200;
     lr[0] = fma(R0_201, Qr[11], lr[0]);
     lr[1] = fma(R0_201, Qr[6], lr[1]);
     lr[3] = fma(R0_201, Qr[4], lr[3]);
@@ -5306,14 +5330,14 @@ template <> struct Exp<4> {
     lr[6] = fma(R0_201, Qr[1], lr[6]);
     lr[11] = fma(R0_201, Qr[0], lr[11]);
     __builtin_amdgcn_sched_barrier(0);
-    const double R0_120 = fma(r[1], R1_110, R1_100);
+    const double R0_120 = fma(w[1], R1_110, T1_100);
     lr[0] = fma(R0_120, Qr[12], lr[0]);
     lr[1] = fma(R0_120, Qr[7], lr[1]);
     lr[2] = fma(R0_120, Qr[5], lr[2]);
     lr[5] = fma(R0_120, Qr[2], lr[5]);
     lr[7] = fma(R0_120, Qr[1], lr[7]);
     lr[12] = fma(R0_120, Qr[0], lr[12]);
-    const double R0_111 = r[2] * R1_110;
+    const double R0_111 = w[2] * R1_110;
     lr[0] = fma(R0_111, Qr[13], lr[0]);
     lr[1] = fma(R0_111, Qr[8], lr[1]);
     lr[2] = fma(R0_111, Qr[6], lr[2]);
@@ -5326,13 +5350,13 @@ template <> struct Exp<4> {
     const double R0_102 = -(R0_300 + R0_120);
     lr[3] = fma(R0_102, Qr[6], lr[3]);
     lr[6] = fma(R0_102, Qr[3], lr[6]);
-    const double R1_020 = fma(r[1], R2_010, R2_000);
-    const double R0_030 = fma(r[1], R1_020, 2.0 * R1_010);
+    const double R1_020 = fma(w[1], R2_010, T2_000);
+    const double R0_030 = fma(w[1], R1_020, 2.0 * T1_010);
     lr[0] = fma(R0_030, Qr[14], lr[0]);
     lr[2] = fma(R0_030, Qr[7], lr[2]);
     lr[7] = fma(R0_030, Qr[2], lr[7]);
     lr[14] = fma(R0_030, Qr[0], lr[14]);
-    const double R0_021 = r[2] * R1_020;
+    const double R0_021 = w[2] * R1_020;
     lr[0] = fma(R0_021, Qr[15], lr[0]);
     lr[2] = fma(R0_021, Qr[8], lr[2]);
     lr[3] = fma(R0_021, Qr[7], lr[3]);
@@ -5343,19 +5367,24 @@ template <> struct Exp<4> {
     const double R0_012 = -(R0_210 + R0_030);
     lr[3] = fma(R0_012, Qr[8], lr[3]);
     lr[8] = fma(R0_012, Qr[3], lr[8]);
-    const double R3_100 = r[0] * R4_000;
-    const double R2_200 = fma(r[0], R3_100, R3_000);
-    const double R1_300 = fma(r[0], R2_200, 2.0 * R2_100);
-    const double R0_400 = fma(r[0], R1_300, 3.0 * R1_200);
+    const double R3_100 = w[0] * R4_000;
+    const double T3_000 = s * R3_000;
+    const double R2_200 = fma(w[0], R3_100, T3_000);
+    const double T2_100 = s * R2_100;
+    const double R1_300 = fma(w[0], R2_200, 2.0 * T2_100);
+    const double T1_200 = s * R1_200;
+    const double R0_400 = fma(w[0], R1_300, 3.0 * T1_200);
     lr[0] = fma(R0_400, Qr[16], lr[0]);
     lr[1] = fma(R0_400, Qr[9], lr[1]);
     lr[4] = fma(R0_400, Qr[4], lr[4]);
     lr[9] = fma(R0_400, Qr[1], lr[9]);
     lr[16] = fma(R0_400, Qr[0], lr[16]);
-    const double R3_010 = r[1] * R4_000;
-    const double R2_110 = r[0] * R3_010;
-    const double R1_210 = fma(r[0], R2_110, R2_010);
-    const double R0_310 = fma(r[0], R1_210, 2.0 * R1_110);
+    const double R3_010 = w[1] * R4_000;
+    const double R2_110 = w[0] * R3_010;
+    const double T2_010 = s * R2_010;
+    const double R1_210 = fma(w[0], R2_110, T2_010);
+    const double T1_110 = s * R1_110;
+    const double R0_310 = fma(w[0], R1_210, 2.0 * T1_110);
     lr[0] = fma(R0_310, Qr[17], lr[0]);
     lr[1] = fma(R0_310, Qr[10], lr[1]);
     lr[2] = fma(R0_310, Qr[9], lr[2]);
@@ -5365,7 +5394,7 @@ template <> struct Exp<4> {
     lr[10] = fma(R0_310, Qr[1], lr[10]);
     lr[17] = fma(R0_310, Qr[0], lr[17]);
     __builtin_amdgcn_sched_barrier(0);
-    const double R0_301 = r[2] * R1_300;
+    const double R0_301 = w[2] * R1_300;
     lr[0] = fma(R0_301, Qr[18], lr[0]);
     lr[1] = fma(R0_301, Qr[11], lr[1]);
     lr[3] = fma(R0_301, Qr[9], lr[3]);
@@ -5374,8 +5403,9 @@ template <> struct Exp<4> {
     lr[9] = fma(R0_301, Qr[3], lr[9]);
     lr[11] = fma(R0_301, Qr[1], lr[11]);
     lr[18] = fma(R0_301, Qr[0], lr[18]);
-    const double R1_120 = fma(r[1], R2_110, R2_100);
-    const double R0_220 = fma(r[0], R1_120, R1_020);
+    const double R1_120 = fma(w[1], R2_110, T2_100);
+    const double T1_020 = s * R1_020;
+    const double R0_220 = fma(w[0], R1_120, T1_020);
     lr[0] = fma(R0_220, Qr[19], lr[0]);
     lr[1] = fma(R0_220, Qr[12], lr[1]);
     lr[2] = fma(R0_220, Qr[10], lr[2]);
@@ -5386,7 +5416,7 @@ template <> struct Exp<4> {
     lr[12] = fma(R0_220, Qr[1], lr[12]);
     lr[19] = fma(R0_220, Qr[0], lr[19]);
     __builtin_amdgcn_sched_barrier(0);
-    const double R0_211 = r[2] * R1_210;
+    const double R0_211 = w[2] * R1_210;
     lr[0] = fma(R0_211, Qr[20], lr[0]);
     lr[1] = fma(R0_211, Qr[13], lr[1]);
     lr[2] = fma(R0_211, Qr[11], lr[2]);
@@ -5404,7 +5434,7 @@ template <> struct Exp<4> {
     lr[3] = fma(R0_202, Qr[11], lr[3]);
     lr[6] = fma(R0_202, Qr[6], lr[6]);
     lr[11] = fma(R0_202, Qr[3], lr[11]);
-    const double R0_130 = fma(r[1], R1_120, 2.0 * R1_110);
+    const double R0_130 = fma(w[1], R1_120, 2.0 * T1_110);
     lr[0] = fma(R0_130, Qr[21], lr[0]);
     lr[1] = fma(R0_130, Qr[14], lr[1]);
     lr[2] = fma(R0_130, Qr[12], lr[2]);
@@ -5413,7 +5443,7 @@ template <> struct Exp<4> {
     lr[12] = fma(R0_130, Qr[2], lr[12]);
     lr[14] = fma(R0_130, Qr[1], lr[14]);
     lr[21] = fma(R0_130, Qr[0], lr[21]);
-    const double R0_121 = r[2] * R1_120;
+    const double R0_121 = w[2] * R1_120;
     lr[0] = fma(R0_121, Qr[22], lr[0]);
     lr[1] = fma(R0_121, Qr[15], lr[1]);
     lr[2] = fma(R0_121, Qr[13], lr[2]);
@@ -5432,15 +5462,15 @@ template <> struct Exp<4> {
     lr[6] = fma(R0_112, Qr[8], lr[6]);
     lr[8] = fma(R0_112, Qr[6], lr[8]);
     lr[13] = fma(R0_112, Qr[3], lr[13]);
-    const double R2_020 = fma(r[1], R3_010, R3_000);
-    const double R1_030 = fma(r[1], R2_020, 2.0 * R2_010);
-    const double R0_040 = fma(r[1], R1_030, 3.0 * R1_020);
+    const double R2_020 = fma(w[1], R3_010, T3_000);
+    const double R1_030 = fma(w[1], R2_020, 2.0 * T2_010);
+    const double R0_040 = fma(w[1], R1_030, 3.0 * T1_020);
     lr[0] = fma(R0_040, Qr[23], lr[0]);
     lr[2] = fma(R0_040, Qr[14], lr[2]);
     lr[7] = fma(R0_040, Qr[7], lr[7]);
     lr[14] = fma(R0_040, Qr[2], lr[14]);
     lr[23] = fma(R0_040, Qr[0], lr[23]);
-    const double R0_031 = r[2] * R1_030;
+    const double R0_031 = w[2] * R1_030;
     lr[0] = fma(R0_031, Qr[24], lr[0]);
     lr[2] = fma(R0_031, Qr[15], lr[2]);
     lr[3] = fma(R0_031, Qr[14], lr[3]);
@@ -5454,21 +5484,28 @@ template <> struct Exp<4> {
     lr[3] = fma(R0_022, Qr[15], lr[3]);
     lr[8] = fma(R0_022, Qr[8], lr[8]);
     lr[15] = fma(R0_022, Qr[3], lr[15]);
-    const double R4_100 = r[0] * R5_000;
-    const double R3_200 = fma(r[0], R4_100, R4_000);
-    const double R2_300 = fma(r[0], R3_200, 2.0 * R3_100);
-    const double R1_400 = fma(r[0], R2_300, 3.0 * R2_200);
-    const double R0_500 = fma(r[0], R1_400, 4.0 * R1_300);
+    const double R4_100 = w[0] * R5_000;
+    const double T4_000 = s * R4_000;
+    const double R3_200 = fma(w[0], R4_100, T4_000);
+    const double T3_100 = s * R3_100;
+    const double R2_300 = fma(w[0], R3_200, 2.0 * T3_100);
+    const double T2_200 = s * R2_200;
+    const double R1_400 = fma(w[0], R2_300, 3.0 * T2_200);
+    const double T1_300 = s * R1_300;
+    const double R0_500 = fma(w[0], R1_400, 4.0 * T1_300);
     lr[25] = fma(R0_500, Qr[16], lr[25]);
     lr[28] = fma(R0_500, Qr[9], lr[28]);
     lr[33] = fma(R0_500, Qr[4], lr[33]);
     lr[40] = fma(R0_500, Qr[1], lr[40]);
     lr[49] = fma(R0_500, Qr[0], lr[49]);
-    const double R4_010 = r[1] * R5_000;
-    const double R3_110 = r[0] * R4_010;
-    const double R2_210 = fma(r[0], R3_110, R3_010);
-    const double R1_310 = fma(r[0], R2_210, 2.0 * R2_110);
-    const double R0_410 = fma(r[0], R1_310, 3.0 * R1_210);
+    const double R4_010 = w[1] * R5_000;
+    const double R3_110 = w[0] * R4_010;
+    const double T3_010 = s * R3_010;
+    const double R2_210 = fma(w[0], R3_110, T3_010);
+    const double T2_110 = s * R2_110;
+    const double R1_310 = fma(w[0], R2_210, 2.0 * T2_110);
+    const double T1_210 = s * R1_210;
+    const double R0_410 = fma(w[0], R1_310, 3.0 * T1_210);
     lr[25] = fma(R0_410, Qr[17], lr[25]);
     lr[26] = fma(R0_410, Qr[16], lr[26]);
     lr[28] = fma(R0_410, Qr[10], lr[28]);
@@ -5479,7 +5516,7 @@ template <> struct Exp<4> {
     lr[41] = fma(R0_410, Qr[1], lr[41]);
     lr[50] = fma(R0_410, Qr[0], lr[50]);
     __builtin_amdgcn_sched_barrier(0);
-    const double R0_401 = r[2] * R1_400;
+    const double R0_401 = w[2] * R1_400;
     lr[25] = fma(R0_401, Qr[18], lr[25]);
     lr[27] = fma(R0_401, Qr[16], lr[27]);
     lr[28] = fma(R0_401, Qr[11], lr[28]);
@@ -5489,9 +5526,11 @@ template <> struct Exp<4> {
     lr[40] = fma(R0_401, Qr[3], lr[40]);
     lr[42] = fma(R0_401, Qr[1], lr[42]);
     lr[51] = fma(R0_401, Qr[0], lr[51]);
-    const double R2_120 = fma(r[1], R3_110, R3_100);
-    const double R1_220 = fma(r[0], R2_120, R2_020);
-    const double R0_320 = fma(r[0], R1_220, 2.0 * R1_120);
+    const double R2_120 = fma(w[1], R3_110, T3_100);
+    const double T2_020 = s * R2_020;
+    const double R1_220 = fma(w[0], R2_120, T2_020);
+    const double T1_120 = s * R1_120;
+    const double R0_320 = fma(w[0], R1_220, 2.0 * T1_120);
     lr[25] = fma(R0_320, Qr[19], lr[25]);
     lr[26] = fma(R0_320, Qr[17], lr[26]);
     lr[28] = fma(R0_320, Qr[12], lr[28]);
@@ -5504,7 +5543,7 @@ template <> struct Exp<4> {
     lr[43] = fma(R0_320, Qr[1], lr[43]);
     lr[52] = fma(R0_320, Qr[0], lr[52]);
     __builtin_amdgcn_sched_barrier(0);
-    const double R0_311 = r[2] * R1_310;
+    const double R0_311 = w[2] * R1_310;
     lr[25] = fma(R0_311, Qr[20], lr[25]);
     lr[26] = fma(R0_311, Qr[18], lr[26]);
     lr[27] = fma(R0_311, Qr[17], lr[27]);
@@ -5526,7 +5565,7 @@ template <> struct Exp<4> {
     lr[30] = fma(R0_302, Qr[11], lr[30]);
     lr[35] = fma(R0_302, Qr[6], lr[35]);
     lr[42] = fma(R0_302, Qr[3], lr[42]);
-    const double R0_230 = fma(r[1], R1_220, 2.0 * R1_210);
+    const double R0_230 = fma(w[1], R1_220, 2.0 * T1_210);
     lr[25] = fma(R0_230, Qr[21], lr[25]);
     lr[26] = fma(R0_230, Qr[19], lr[26]);
     lr[28] = fma(R0_230, Qr[14], lr[28]);
@@ -5539,7 +5578,7 @@ template <> struct Exp<4> {
     lr[45] = fma(R0_230, Qr[1], lr[45]);
     lr[54] = fma(R0_230, Qr[0], lr[54]);
     __builtin_amdgcn_sched_barrier(0);
-    const double R0_221 = r[2] * R1_220;
+    const double R0_221 = w[2] * R1_220;
     lr[25] = fma(R0_221, Qr[22], lr[25]);
     lr[26] = fma(R0_221, Qr[20], lr[26]);
     lr[27] = fma(R0_221, Qr[19], lr[27]);
@@ -5565,8 +5604,8 @@ template <> struct Exp<4> {
     lr[35] = fma(R0_212, Qr[8], lr[35]);
     lr[37] = fma(R0_212, Qr[6], lr[37]);
     lr[44] = fma(R0_212, Qr[3], lr[44]);
-    const double R1_130 = fma(r[1], R2_120, 2.0 * R2_110);
-    const double R0_140 = fma(r[1], R1_130, 3.0 * R1_120);
+    const double R1_130 = fma(w[1], R2_120, 2.0 * T2_110);
+    const double R0_140 = fma(w[1], R1_130, 3.0 * T1_120);
     lr[25] = fma(R0_140, Qr[23], lr[25]);
     lr[26] = fma(R0_140, Qr[21], lr[26]);
     lr[29] = fma(R0_140, Qr[14], lr[29]);
@@ -5577,7 +5616,7 @@ template <> struct Exp<4> {
     lr[47] = fma(R0_140, Qr[1], lr[47]);
     lr[56] = fma(R0_140, Qr[0], lr[56]);
     __builtin_amdgcn_sched_barrier(0);
-    const double R0_131 = r[2] * R1_130;
+    const double R0_131 = w[2] * R1_130;
     lr[25] = fma(R0_131, Qr[24], lr[25]);
     lr[26] = fma(R0_131, Qr[22], lr[26]);
     lr[27] = fma(R0_131, Qr[21], lr[27]);
@@ -5601,16 +5640,17 @@ template <> struct Exp<4> {
     lr[37] = fma(R0_122, Qr[8], lr[37]);
     lr[39] = fma(R0_122, Qr[6], lr[39]);
     lr[46] = fma(R0_122, Qr[3], lr[46]);
-    const double R3_020 = fma(r[1], R4_010, R4_000);
-    const double R2_030 = fma(r[1], R3_020, 2.0 * R3_010);
-    const double R1_040 = fma(r[1], R2_030, 3.0 * R2_020);
-    const double R0_050 = fma(r[1], R1_040, 4.0 * R1_030);
+    const double R3_020 = fma(w[1], R4_010, T4_000);
+    const double R2_030 = fma(w[1], R3_020, 2.0 * T3_010);
+    const double R1_040 = fma(w[1], R2_030, 3.0 * T2_020);
+    const double T1_030 = s * R1_030;
+    const double R0_050 = fma(w[1], R1_040, 4.0 * T1_030);
     lr[26] = fma(R0_050, Qr[23], lr[26]);
     lr[31] = fma(R0_050, Qr[14], lr[31]);
     lr[38] = fma(R0_050, Qr[7], lr[38]);
     lr[47] = fma(R0_050, Qr[2], lr[47]);
     lr[58] = fma(R0_050, Qr[0], lr[58]);
-    const double R0_041 = r[2] * R1_040;
+    const double R0_041 = w[2] * R1_040;
     lr[26] = fma(R0_041, Qr[24], lr[26]);
     lr[27] = fma(R0_041, Qr[23], lr[27]);
     lr[31] = fma(R0_041, Qr[15], lr[31]);
@@ -5627,7 +5667,7 @@ template <> struct Exp<4> {
     lr[39] = fma(R0_032, Qr[8], lr[39]);
     lr[48] = fma(R0_032, Qr[3], lr[48]);
   }
-  static constexpr int FLOPS_M2L_H = 726;  // + one refined rsqrt
+  static constexpr int FLOPS_M2L_H = 745;  // + one refined rsqrt
   __device__ __forceinline__ static void expand(const double* lr, double* local) {
     double t[56];
     t[0] = lr[0];

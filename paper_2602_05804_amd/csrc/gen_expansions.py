@@ -35,9 +35,12 @@ sums over a whole degree of Q~ that make up a local expansion.  A degree n has
            components from the traces
 At P = 3 that is 146 multiply-adds and 40 sums a node pair where the full
 components take 175, 54 additions and 54 sums.  m2l_h takes D from
-  R^m_0 = (-1)^m (2m-1)!! / r^(2m+1),  D_a = R^0_a,
-  R^m_(a+e) = r_e R^(m+1)_a + a_e R^(m+1)_(a-e),
-one multiply-add or two a component, instead of the recurrence in |r|^2.
+  R^m_0 = (-1)^m (2m-1)!! / r,  D_a = R^0_a,
+  R^m_(a+e) = (r_e / r^2) R^(m+1)_a + (a_e / r^2) R^(m+1)_(a-e),
+one multiply-add or two a component, instead of the recurrence in |r|^2.  A
+component R^m_a is of the size of r^-(|a|+1): nothing leaves the range of FP64
+before D does (with the powers of 1/r^2 in R instead, r^-(2P+3) did, at P = 4
+for |r| beyond 1e28).
 With ok false m2l_h and m2l_add_f32 add nothing (1/r = 0, so every D is 0): a
 lane without an entry then needs no branch, behind which the compiler would
 hold every sum twice.
@@ -162,12 +165,16 @@ def gen_reduced(P):
          "    const double ri = rsqrt_refined(r2);",
          "    const double rinv = ok ? ri : 0.0;",
          "    const double s = rinv * rinv;",
+         "    const double w[3] = {r[0] * s, r[1] * s, r[2] * s};",
          "    const double R0_000 = rinv;"]
-    c.fma += 2; c.mul += 2
+    c.fma += 2; c.mul += 5
+    f = 1
     for m in range(1, P + 2):
-        L.append(f"    const double R{m}_000 = R{m - 1}_000 * ({lit(-(2 * m - 1))} * s);")
-        c.mul += 1 if m == 1 else 2
+        f *= -(2 * m - 1)
+        L.append(f"    const double R{m}_000 = {lit(f)} * rinv;")
+        c.mul += 1
     done = {(m, (0, 0, 0)) for m in range(P + 2)}
+    over = set()  # T = R / r^2
 
     def name(m, a):
         return f"R{m}_{a[0]}{a[1]}{a[2]}"
@@ -186,16 +193,21 @@ def gen_reduced(P):
         b = list(a); b[e] -= 1; b = tuple(b)
         need(m + 1, b)
         if b[e] == 0:
-            L.append(f"    const double {name(m, a)} = r[{e}] * {name(m + 1, b)};")
+            L.append(f"    const double {name(m, a)} = w[{e}] * {name(m + 1, b)};")
             c.mul += 1
         else:
             d = list(b); d[e] -= 1; d = tuple(d)
             need(m + 1, d)
+            t = "T" + name(m + 1, d)[1:]
+            if t not in over:
+                L.append(f"    const double {t} = s * {name(m + 1, d)};")
+                c.mul += 1
+                over.add(t)
             if b[e] == 1:
-                L.append(f"    const double {name(m, a)} = fma(r[{e}], {name(m + 1, b)}, {name(m + 1, d)});")
+                L.append(f"    const double {name(m, a)} = fma(w[{e}], {name(m + 1, b)}, {t});")
                 c.fma += 1
             else:
-                L.append(f"    const double {name(m, a)} = fma(r[{e}], {name(m + 1, b)}, {lit(b[e])} * {name(m + 1, d)});")
+                L.append(f"    const double {name(m, a)} = fma(w[{e}], {name(m + 1, b)}, {lit(b[e])} * {t});")
                 c.fma += 1; c.mul += 1
         done.add((m, a))
 

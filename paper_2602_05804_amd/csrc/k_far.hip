@@ -141,7 +141,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WAVES))) voi
 // k_m2l: 8 lanes per node, 8 nodes per wave; each lane sums every 8th entry
 // of its node's list, the group's sums are added with row moves, and lane q of
 // the group stores the coefficients q, q + 8, ...  FP64 targets use the
-// reduced components (Exp<P>::m2l_h, 378 flops a pair at P = 3 where all
+// reduced components (Exp<P>::m2l_h, 388 flops a pair at P = 3 where all
 // components take 660), FP32 targets (FP32C, depth >= top) all of them with
 // FP32 terms and FP64 sums.
 //

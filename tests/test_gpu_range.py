@@ -1,0 +1,46 @@
+"""GPU: the range of lengths that a solve takes.
+
+Lengths (positions and softening lengths) times 2^k: every operation of the FP64
+solve is homogeneous in them and a power of two rounds nothing, so accelerations
+are 2^-2k and potentials 2^-k times those at k = 0, bit for bit, as long as
+nothing leaves the range of FP64.  The largest derivative met is of degree
+order + 1, of the size of r^-(order + 2): at order 4 and |k| = 160 about 2^960.
+"""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch
+
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    return torch
+
+
+@pytest.fixture(scope="module")
+def P(torch):
+    import paper_2602_05804_amd as P
+
+    return P
+
+
+@pytest.mark.parametrize("far", ["shared", "leaf"])
+@pytest.mark.parametrize("order", [0, 1, 2, 3, 4])
+def test_powers_of_two_in_the_lengths(torch, P, order, far):
+    print(f"case: lengths times 2^k, order {order} far {far}", flush=True)
+    g = np.random.default_rng(order)
+    n = 3000
+    x, m, h = (torch.from_numpy(a).cuda()
+               for a in (g.standard_normal((n, 3)), g.random(n) + 0.5, np.full(n, 0.05)))
+    s = P.Solver(far=far)
+    acc0, pot0 = (t.clone() for t in s.solve(x, m, h, theta=0.7, order=order))
+    assert s.stats()["n_m2l_unique"] > 1000
+    for k in (-160, -120, -100, -60, -1, 60, 100, 120, 160):
+        f = 2.0 ** k
+        acc, pot = s.solve(x * f, m, h * f, theta=0.7, order=order)
+        assert torch.equal(acc * f * f, acc0), k
+        assert torch.equal(pot * f, pot0), k
