@@ -41,7 +41,8 @@ one multiply-add or two a component, instead of the recurrence in |r|^2.  A
 component R^m_a is of the size of r^-(|a|+1): nothing leaves the range of FP64
 before D does (with the powers of 1/r^2 in R instead, r^-(2P+3) did, at P = 4
 for |r| beyond 1e28).
-With ok false m2l_h and m2l_add_f32 add nothing (1/r = 0, so every D is 0): a
+With ok false m2l_h and m2l_add_f32 add nothing (1/r = 0, so every D is 0), nor
+does m2l_h where |r|^2 overflows (1/r from the hardware's estimate would be NaN): a
 lane without an entry then needs no branch, behind which the compiler would
 hold every sum twice.
 
@@ -163,7 +164,7 @@ def gen_reduced(P):
     L = ["  __device__ __forceinline__ static void m2l_h(const double* r, const double* Qr, double* lr, bool ok) {",
          "    const double r2 = fma(r[0], r[0], fma(r[1], r[1], r[2] * r[2]));",
          "    const double ri = rsqrt_refined(r2);",
-         "    const double rinv = ok ? ri : 0.0;",
+         "    const double rinv = ok && r2 < __builtin_inf() ? ri : 0.0;",
          "    const double s = rinv * rinv;",
          "    const double w[3] = {r[0] * s, r[1] * s, r[2] * s};",
          "    const double R0_000 = rinv;"]

@@ -44,3 +44,32 @@ def test_powers_of_two_in_the_lengths(torch, P, order, far):
         acc, pot = s.solve(x * f, m, h * f, theta=0.7, order=order)
         assert torch.equal(acc * f * f, acc0), k
         assert torch.equal(pot * f, pot0), k
+
+
+def escaped(far):
+    """A small system, one particle of it so far away that it acts on nothing."""
+    g = np.random.default_rng(11)
+    n = 300
+    x = g.standard_normal((n, 3))
+    x[7] = (far, 0.0, 0.0)
+    return x, g.random(n) + 0.5, np.full(n, 0.3)
+
+
+@pytest.mark.parametrize("precision,tol", [("fp64", 1e-12), ("fp32c", 1e-4)])
+@pytest.mark.parametrize("far", [1e100, 1e150, 1e160, 1e300])
+def test_solve_with_an_escaped_particle(torch, P, orc, far, precision, tol):
+    """|r|^2 overflows from 1e154 on.  The others as without it (an opening angle
+    at which they meet each other directly); bars as in test_gpu_parity.py."""
+    print(f"case: solve, a particle at {far} {precision}", flush=True)
+    x, m, h = escaped(far)
+    keep = np.arange(len(m)) != 7
+    oa, op = orc.direct(x[keep], m[keep], h[keep])
+    for order in (0, 3, 4):
+        s = P.Solver()
+        acc, pot = (t.cpu().numpy() for t in s.solve(
+            *(torch.from_numpy(a).cuda() for a in (x, m, h)), theta=0.05, order=order,
+            precision=precision))
+        assert (np.linalg.norm(acc[keep] - oa, axis=1) / np.linalg.norm(oa, axis=1)).max() <= tol
+        assert (np.abs(pot[keep] - op) / np.abs(op)).max() <= tol
+        assert np.abs(acc[7]).max() <= 1e-190  # (its own: the others' mass / far^2 at most)
+        assert abs(pot[7] + 1.4 * m[7] / h[7]) <= 1e-12 * 1.4 * m[7] / h[7]
