@@ -42,6 +42,14 @@ struct DirLds {
   uint8_t ql[kDirQueue], sl[64];
 };
 
+// lane `lane`'s value (uniform)
+__device__ __forceinline__ double wave_lane(double v, int lane) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), lane);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
 // one softened pair a lane, the queue's last `count` (<= 64) entries from `at`
 // on: put in the order of their targets, evaluated, and summed over runs of
 // one target, whose last lane adds the sum to the target's.  The order of the
@@ -85,7 +93,8 @@ __device__ __forceinline__ void direct_flush(DirLds& sh, uint32_t at, uint32_t c
   const double w = use ? m[j] : 0.0;
   const double dx = tx - x[3 * j], dy = ty - x[3 * j + 1], dz = tz - x[3 * j + 2];
   const double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
-  const double rinv = r2 > 0.0 ? rsqrt(r2) : 0.0;
+  const double y = rsqrt_refined(r2);
+  const double rinv = r2 > 0.0 ? y : 0.0;  // (an r^2 that overflows: direct_all)
   const double r = r2 * rinv;
   double g1, p1, g2, p2;
   soft_piece(sh.coef, r * hiinv, hiinv, rinv, g1, p1);
@@ -106,6 +115,44 @@ __device__ __forceinline__ void direct_flush(DirLds& sh, uint32_t at, uint32_t c
     for (int k = 0; k < 4; ++k) sh.acc[k][l] += v[k];
   }
   __syncthreads();
+}
+
+// Every pair of a chunk as one that may lie inside a kernel, in place, and with
+// 1/r = 0 where r^2 overflows: for a chunk whose sums came out as NaN.
+__device__ __forceinline__ void direct_all(const DirLds& sh, int64_t j0, int64_t j1, int64_t i,
+                                           double xi, double yi, double zi, double hi,
+                                           const double* __restrict__ x,
+                                           const double* __restrict__ m,
+                                           const double* __restrict__ h, double& ax, double& ay,
+                                           double& az, double& ph) {
+  const uint32_t lane = threadIdx.x;
+  const double hiinv = 1.0 / hi;
+  for (int64_t b = j0; b < j1; b += 64) {
+    const double inv = 1.0 / h[b + lane < j1 ? b + lane : b];  // (a lane's share of 64 sources')
+    const int cnt = (int)(j1 - b < 64 ? j1 - b : 64);
+    for (int k = 0; k < cnt; ++k) {
+      const int64_t j = b + k;
+      const double hj = h[j];
+      const double hjinv = wave_lane(inv, k);
+      const double dx = xi - x[3 * j], dy = yi - x[3 * j + 1], dz = zi - x[3 * j + 2];
+      const double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
+      const double y = rsqrt_refined(r2);
+      const double rinv = r2 > 0.0 && r2 < INFINITY ? y : 0.0;
+      const double r = r2 * rinv, rinv3 = rinv * rinv * rinv;
+      // (one kernel's piece from LDS, the other's selected: both pipes are busy)
+      double g1, p1, g2, p2;
+      soft_piece(sh.coef, r * hiinv, hiinv, rinv, g1, p1);
+      soft_sel(r * hjinv, hjinv, hj * rinv, rinv, rinv3, g2, p2);
+      const bool inside = (r2 * (hiinv * hiinv) < 4.0) || (r2 * (hjinv * hjinv) < 4.0);
+      const bool use = j != i;
+      const double g = inside ? 0.5 * (g1 + g2) : rinv3, p = inside ? 0.5 * (p1 + p2) : rinv;
+      const double mg = m[j] * (use ? g : 0.0);
+      ax = fma(mg, dx, ax);
+      ay = fma(mg, dy, ay);
+      az = fma(mg, dz, az);
+      ph = fma(m[j], use ? p : 0.0, ph);
+    }
+  }
 }
 
 __global__ __launch_bounds__(64) void k_direct_part(int64_t n, const double* __restrict__ x,
@@ -193,6 +240,13 @@ __global__ __launch_bounds__(64) void k_direct_part(int64_t n, const double* __r
       __syncthreads();
       direct_flush(sh, nq, c, j0, i0, targets, x, m, h);
     }
+  }
+  // (the refined 1/sqrt of an r^2 that overflows is NaN, where 1/r is 0)
+  if (__ballot(on && !(fabs(ph + sh.acc[3][lane]) < INFINITY)) != 0) {
+    ax = ay = az = ph = 0.0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) sh.acc[k][lane] = 0.0;
+    direct_all(sh, j0, j1, on ? i : -1, xi, yi, zi, hi, x, m, h, ax, ay, az, ph);
   }
   if (t >= nt) return;
   double* o = part + ((int64_t)blockIdx.y * nt + t) * 4;

@@ -73,3 +73,21 @@ def test_solve_with_an_escaped_particle(torch, P, orc, far, precision, tol):
         assert (np.abs(pot[keep] - op) / np.abs(op)).max() <= tol
         assert np.abs(acc[7]).max() <= 1e-190  # (its own: the others' mass / far^2 at most)
         assert abs(pot[7] + 1.4 * m[7] / h[7]) <= 1e-12 * 1.4 * m[7] / h[7]
+
+
+@pytest.mark.parametrize("far", [1e100, 1e150, 1e160, 1e300])
+def test_direct_with_an_escaped_particle(torch, P, orc, far):
+    print(f"case: direct, a particle at {far}", flush=True)
+    x, m, h = escaped(far)
+    keep = np.arange(len(m)) != 7
+    oa, op = orc.direct(x[keep], m[keep], h[keep])
+    args = [torch.from_numpy(a).cuda() for a in (x, m, h)]
+    h_all = torch.full_like(args[2], 1e160)  # (every |r|^2 below 4 h^2, which overflows)
+    for hs, da, dp in ((args[2], oa, op), (h_all, None, None)):
+        acc, pot = (t.cpu().numpy() for t in P.Solver().direct(args[0], args[1], hs))
+        assert np.isfinite(acc).all() and np.isfinite(pot).all()
+        if da is None:
+            continue
+        assert (np.linalg.norm(acc[keep] - da, axis=1) / np.linalg.norm(da, axis=1)).max() <= 1e-12
+        assert (np.abs(pot[keep] - dp) / np.abs(dp)).max() <= 1e-12
+        assert np.abs(acc[7]).max() <= 1e-190
