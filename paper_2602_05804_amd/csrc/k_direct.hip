@@ -89,20 +89,18 @@ __device__ __forceinline__ void direct_flush(DirLds& sh, uint32_t at, uint32_t c
   const uint32_t first = on ? sh.first[l] : lane;
   const double tx = sh.t[0][l], ty = sh.t[1][l], tz = sh.t[2][l], hiinv = sh.t[3][l];
   const double hjinv = 1.0 / h[j];
-  const bool use = on && j != i;
-  const double w = use ? m[j] : 0.0;
+  const double w = on && j != i ? 0.5 * m[j] : 0.0;
   const double dx = tx - x[3 * j], dy = ty - x[3 * j + 1], dz = tz - x[3 * j + 2];
   const double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
-  const double y = rsqrt_refined(r2);
-  const double rinv = r2 > 0.0 ? y : 0.0;  // (an r^2 that overflows: direct_all)
-  const double r = r2 * rinv;
+  const double rinv = rsqrt_refined(r2);
+  const bool apart = r2 > 0.0;  // (at one place no force, where h^-3 may overflow)
+  const double r = apart ? r2 * rinv : 0.0;
+  // (outside both kernels, both pieces are 1/r^3 and 1/r)
   double g1, p1, g2, p2;
   soft_piece(sh.coef, r * hiinv, hiinv, rinv, g1, p1);
   soft_piece(sh.coef, r * hjinv, hjinv, rinv, g2, p2);
-  const bool inside = (r2 * (hiinv * hiinv) < 4.0) || (r2 * (hjinv * hjinv) < 4.0);
-  // (a pair left out has g = 0: with itself h^-3 may overflow)
-  const double mg = w * (!use ? 0.0 : inside ? 0.5 * (g1 + g2) : rinv * rinv * rinv);
-  double v[4] = {mg * dx, mg * dy, mg * dz, w * (inside ? 0.5 * (p1 + p2) : rinv)};
+  const double mg = apart ? w * (g1 + g2) : 0.0;
+  double v[4] = {mg * dx, mg * dy, mg * dz, w * (p1 + p2)};
   for (int o = 1; o < 64 && __ballot((int)own > o); o <<= 1) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -137,20 +135,20 @@ __device__ __forceinline__ void direct_all(const DirLds& sh, int64_t j0, int64_t
       const double dx = xi - x[3 * j], dy = yi - x[3 * j + 1], dz = zi - x[3 * j + 2];
       const double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
       const double y = rsqrt_refined(r2);
-      const double rinv = r2 > 0.0 && r2 < INFINITY ? y : 0.0;
-      const double r = r2 * rinv, rinv3 = rinv * rinv * rinv;
+      const bool apart = r2 > 0.0, in_range = r2 < INFINITY;
+      const double rinv = apart && in_range ? y : 0.0;
+      const double r = r2 * rinv;
       // (one kernel's piece from LDS, the other's selected: both pipes are busy)
       double g1, p1, g2, p2;
       soft_piece(sh.coef, r * hiinv, hiinv, rinv, g1, p1);
-      soft_sel(r * hjinv, hjinv, hj * rinv, rinv, rinv3, g2, p2);
-      const bool inside = (r2 * (hiinv * hiinv) < 4.0) || (r2 * (hjinv * hjinv) < 4.0);
-      const bool use = j != i;
-      const double g = inside ? 0.5 * (g1 + g2) : rinv3, p = inside ? 0.5 * (p1 + p2) : rinv;
-      const double mg = m[j] * (use ? g : 0.0);
+      soft_sel(r * hjinv, hjinv, hj * rinv, rinv, rinv * rinv * rinv, g2, p2);
+      const double w = 0.5 * m[j];
+      const double mg = apart && in_range ? w * (g1 + g2) : 0.0;
+      const double mp = in_range && j != i ? w * (p1 + p2) : 0.0;
       ax = fma(mg, dx, ax);
       ay = fma(mg, dy, ay);
       az = fma(mg, dz, az);
-      ph = fma(m[j], use ? p : 0.0, ph);
+      ph += mp;
     }
   }
 }

@@ -93,13 +93,13 @@ struct alignas(16) SoftCoef {
      1.0 / 15.0, 0.0},
     {0.0, 0.0, 0.0, 0.0, -1.0, 0.0, 0.0, 0.0, 0.0, 0.0, -1.0, 0.0}};
 
-// g = f(q) / (q h^3) and psi(q) / h at q = r hinv, rinv = 1 / r
+// g = f(q) / (q h^3) and psi(q) / h at q = r hinv, rinv = 1 / r (any value at r = 0)
 __device__ __forceinline__ void soft_piece(const SoftCoef* coef, double q, double hinv,
                                            double rinv, double& g, double& psi) {
   const bool core = q < 1.0;
   const SoftCoef& k = coef[core ? 0 : q < 2.0 ? 1 : 2];
   const double qc = fmin(q, 2.0);  // (outside, it meets coefficients of 0 only)
-  const double u = core ? hinv : rinv, w = core ? 1.0 : qc;
+  const double u = core ? hinv : rinv, w = fmax(qc, 1.0);
   const double q2 = qc * qc;
   const double gp = fma(qc, fma(qc, fma(qc, k.c3, k.c2), k.c1), k.c0);
   const double pp = fma(q2, fma(qc, fma(qc, fma(qc, k.d5, k.d4), k.d3), k.d2), k.d0);

@@ -59,3 +59,22 @@ def test_solve(torch, P, orc, h, near_kernel):
     s = P.Solver(include_self_potential=False, near_kernel=near_kernel)
     got = s.solve(*(torch.from_numpy(a).cuda() for a in (x, m, hs)), theta=0.05)
     check(got, orc.direct(x, m, hs, include_self=False))
+
+
+@pytest.mark.parametrize("h", [1e-100, 1e-110, 1e-140, 1e-158])
+def test_two_at_one_place(torch, P, orc, h):
+    """No force between them, in the direct sum and in the solve."""
+    print(f"case: point masses at one place, h {h}", flush=True)
+    x, m, hs = system(h)
+    x[41], x[82] = x[0], x[0]
+    want = orc.direct(x, m, np.where(hs < 1.0, 1e-90, hs), include_self=False)  # (h^-3 in range)
+    s = P.Solver(include_self_potential=False)
+    args = [torch.from_numpy(a).cuda() for a in (x, m, hs)]
+    one = np.ones(len(m), bool)
+    one[[0, 41, 82]] = False  # (of their potentials, their own share goes with 1/h)
+    for acc, pot in (s.direct(*args), s.solve(*args, theta=0.05)):
+        acc, pot = acc.cpu().numpy(), pot.cpu().numpy()
+        assert (np.linalg.norm(acc - want[0], axis=1) / np.linalg.norm(want[0], axis=1)).max() <= TOL
+        assert (np.abs(pot - want[1]) / np.abs(want[1]))[one].max() <= TOL
+        own = -1.4 / h * np.array([m[41] + m[82], m[0] + m[82], m[0] + m[41]])
+        assert np.abs(pot[[0, 41, 82]] / own - 1.0).max() <= TOL
