@@ -13,7 +13,7 @@
 // through scalar loads, four at a time, and stay in scalar registers.  A pair
 // beyond both kernels costs 24 FP64 operations and one estimate of 1/sqrt; the
 // others are queued and evaluated 64 at a time.  All pairs of 1e5 particles of a
-// Plummer sphere (softening lengths over four decades): 8.9 ms; 16.2 with the
+// Plummer sphere (softening lengths over four decades): 8.7 ms; 16.2 with the
 // sources in LDS (six reads a pair), a full 1/sqrt, and the softened pair in
 // place, which nearly a tenth of the steps took for one lane; 14.6 with only that
 // left.  A polytrope of 1e5: 8.5 ms, 12.5 before.
@@ -153,7 +153,8 @@ __device__ __forceinline__ void direct_all(const DirLds& sh, int64_t j0, int64_t
   }
 }
 
-__global__ __launch_bounds__(64) void k_direct_part(int64_t n, const double* __restrict__ x,
+// (five waves a SIMD: 8.7 ms for 1e5 particles, four 9.0, three 9.9)
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_direct_part(int64_t n, const double* __restrict__ x,
                                                     const double* __restrict__ m,
                                                     const double* __restrict__ h, int64_t nt,
                                                     const int64_t* __restrict__ targets,
