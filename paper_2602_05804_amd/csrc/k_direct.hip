@@ -12,11 +12,11 @@
 // Bound by FP64 issue.  The sources are the same for all lanes: they come
 // through scalar loads, four at a time, and stay in scalar registers.  A pair
 // beyond both kernels costs 24 FP64 operations and one estimate of 1/sqrt; the
-// others are queued and evaluated 64 at a time.  All pairs of 1e5 particles of a
-// Plummer sphere (softening lengths over four decades): 8.7 ms; 16.2 with the
-// sources in LDS (six reads a pair), a full 1/sqrt, and the softened pair in
-// place, which nearly a tenth of the steps took for one lane; 14.6 with only that
-// left.  A polytrope of 1e5: 8.5 ms, 12.5 before.
+// others are queued and evaluated 64 at a time, or, where most pairs lie inside a
+// kernel, all in place.  All pairs of 1e5 particles of a Plummer sphere (softening
+// lengths over four decades): 8.7 ms; 16.2 with the sources in LDS (six reads a
+// pair), a full 1/sqrt, and the softened pair in place, which nearly a tenth of
+// the steps took for one lane; 14.6 with only that left.  A polytrope of 1e5: 8.5 ms, 12.5 before.
 #include "sfmm_internal.h"
 #include "softening.h"
 
@@ -26,6 +26,11 @@ namespace {
 constexpr int kDirTile = 64;    // chunks are whole numbers of this many sources
 constexpr int kDirGroup = 4;    // sources loaded at a time
 
+// A chunk of which kDirSample sources lie inside a kernel with half of the wave's
+// targets is met in place: a queued pair costs about twice one in place.  All of 5e4
+// particles inside each other's kernels: 7.3 ms, 17.0 through the queue; a quarter of
+// the pairs inside: 5.1 ms through the queue.
+constexpr int kDirSample = 4;
 constexpr int kDirQueue = 64 * (kDirGroup + 1);
 
 // a wave's pairs that may lie within a kernel, kept until 64 of them fill the
@@ -116,7 +121,8 @@ __device__ __forceinline__ void direct_flush(DirLds& sh, uint32_t at, uint32_t c
 }
 
 // Every pair of a chunk as one that may lie inside a kernel, in place, and with
-// 1/r = 0 where r^2 overflows: for a chunk whose sums came out as NaN.
+// 1/r = 0 where r^2 overflows: for a chunk most of whose pairs lie inside one, and
+// for one whose sums came out as NaN.
 __device__ __forceinline__ void direct_all(const DirLds& sh, int64_t j0, int64_t j1, int64_t i,
                                            double xi, double yi, double zi, double hi,
                                            const double* __restrict__ x,
@@ -216,32 +222,46 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
     asm volatile("" : "+v"(ax), "+v"(ay), "+v"(az), "+v"(ph));
   };
 
-  for (int64_t j = j0; j < j1; j += kDirGroup) {
-    if (j + kDirGroup <= j1) {
-      double s[3 * kDirGroup], sm[kDirGroup], sj[kDirGroup];
+  // some of the sources: do half of their pairs lie inside a kernel?
+  uint32_t met = 0;
+  const int64_t every = (j1 - j0) / kDirSample;
 #pragma unroll
-      for (int k = 0; k < 3 * kDirGroup; ++k) s[k] = x[3 * j + k];
-#pragma unroll
-      for (int k = 0; k < kDirGroup; ++k) sm[k] = m[j + k];
-#pragma unroll
-      for (int k = 0; k < kDirGroup; ++k) sj[k] = h[j + k];
-#pragma unroll
-      for (int k = 0; k < kDirGroup; ++k)
-        source(j + k, fmax(h4, 4.0 * sj[k] * sj[k]), s[3 * k], s[3 * k + 1], s[3 * k + 2], sm[k]);
-    } else {
-      for (int64_t k = j; k < j1; ++k)
-        source(k, fmax(h4, 4.0 * h[k] * h[k]), x[3 * k], x[3 * k + 1], x[3 * k + 2], m[k]);
-    }
-    const bool last = j + kDirGroup >= j1;
-    while (nq >= 64 || (last && nq > 0)) {
-      const uint32_t c = nq < 64 ? nq : 64;
-      nq -= c;
-      __syncthreads();
-      direct_flush(sh, nq, c, j0, i0, targets, x, m, h);
-    }
+  for (int k = 0; k < kDirSample; ++k) {
+    const int64_t j = j0 + k * every;
+    const double dx = xi - x[3 * j], dy = yi - x[3 * j + 1], dz = zi - x[3 * j + 2];
+    const double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
+    met += (uint32_t)__popcll(__ballot(!(r2 > fmax(h4, 4.0 * h[j] * h[j]))));
   }
-  // (the refined 1/sqrt of an r^2 that overflows is NaN, where 1/r is 0)
-  if (__ballot(on && !(fabs(ph + sh.acc[3][lane]) < INFINITY)) != 0) {
+  bool all = met >= kDirSample * 32;
+  if (!all) {
+    for (int64_t j = j0; j < j1; j += kDirGroup) {
+      if (j + kDirGroup <= j1) {
+        double s[3 * kDirGroup], sm[kDirGroup], sj[kDirGroup];
+#pragma unroll
+        for (int k = 0; k < 3 * kDirGroup; ++k) s[k] = x[3 * j + k];
+#pragma unroll
+        for (int k = 0; k < kDirGroup; ++k) sm[k] = m[j + k];
+#pragma unroll
+        for (int k = 0; k < kDirGroup; ++k) sj[k] = h[j + k];
+#pragma unroll
+        for (int k = 0; k < kDirGroup; ++k)
+          source(j + k, fmax(h4, 4.0 * sj[k] * sj[k]), s[3 * k], s[3 * k + 1], s[3 * k + 2], sm[k]);
+      } else {
+        for (int64_t k = j; k < j1; ++k)
+          source(k, fmax(h4, 4.0 * h[k] * h[k]), x[3 * k], x[3 * k + 1], x[3 * k + 2], m[k]);
+      }
+      const bool last = j + kDirGroup >= j1;
+      while (nq >= 64 || (last && nq > 0)) {
+        const uint32_t c = nq < 64 ? nq : 64;
+        nq -= c;
+        __syncthreads();
+        direct_flush(sh, nq, c, j0, i0, targets, x, m, h);
+      }
+    }
+    // (the refined 1/sqrt of an r^2 that overflows is NaN, where 1/r is 0)
+    all = __ballot(on && !(fabs(ph + sh.acc[3][lane]) < INFINITY)) != 0;
+  }
+  if (all) {
     ax = ay = az = ph = 0.0;
 #pragma unroll
     for (int k = 0; k < 4; ++k) sh.acc[k][lane] = 0.0;

@@ -48,3 +48,28 @@ def test_direct_edges(torch, orc, n, nt, kind):
     scale = np.maximum(scale, 1e-300)
     assert (np.linalg.norm(acc - oa, axis=1) / scale).max() <= TOL
     assert (np.abs(pot - op) / np.maximum(np.abs(op), 1e-300)).max() <= TOL
+
+
+@pytest.mark.parametrize("n,nt", [(3, None), (64, None), (67, 33), (130, None), (1500, 70)])
+@pytest.mark.parametrize("first", [0, 1, 2, 3, 4])
+def test_chunks_met_in_place(torch, orc, n, nt, first):
+    """Chunks of which `first` of the four sources looked at reach every target and
+    the others few, on both sides of the share from which all are met in place."""
+    import paper_2602_05804_amd as P
+
+    print(f"case: direct in place n {n} targets {nt} first {first}", flush=True)
+    g = np.random.default_rng(n + first)
+    x = g.standard_normal((n, 3))
+    m = g.random(n) + 0.5
+    h = np.full(n, 1e-3)
+    h[np.isin(np.arange(n) % 64, [0, 16, 32, 48][:first])] = 20.0
+    h[::50] = 1e-110  # (and some point masses)
+    tg = None if nt is None else g.integers(0, n, nt)
+    s = P.Solver(include_self_potential=False)
+    acc, pot = s.direct(*(torch.from_numpy(a).cuda() for a in (x, m, h)),
+                        targets=None if tg is None else torch.from_numpy(tg).cuda())
+    ids = np.arange(n) if tg is None else tg
+    oa, op = orc.direct(x, m, h, targets=ids.astype(np.int64), include_self=False)
+    scale = np.maximum(np.linalg.norm(oa, axis=1), np.abs(op))  # (unit lengths)
+    assert (np.linalg.norm(acc.cpu().numpy() - oa, axis=1) / scale).max() <= TOL
+    assert (np.abs(pot.cpu().numpy() - op) / np.abs(op)).max() <= TOL
