@@ -25,6 +25,7 @@ namespace {
 
 constexpr int kDirTile = 64;    // chunks are whole numbers of this many sources
 constexpr int kDirGroup = 4;    // sources loaded at a time
+constexpr int64_t kDirSimds = 1024;  // of the chip (256 CUs)
 
 // A chunk of which kDirSample sources lie inside a kernel with half of the wave's
 // targets is met in place: a queued pair costs about twice one in place.  All of 5e4
@@ -159,8 +160,11 @@ __device__ __forceinline__ void direct_all(const DirLds& sh, int64_t j0, int64_t
   }
 }
 
-// (five waves a SIMD: 8.7 ms for 1e5 particles, four 9.0, three 9.9)
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_direct_part(int64_t n, const double* __restrict__ x,
+// WAVES a SIMD: five (1e5 particles: 8.7 ms, with four 9.0, with three 9.9), four
+// where no SIMD gets a fifth, whose registers need no spill (1e3 particles: 75 us
+// with four, 78 with five)
+template <int WAVES>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WAVES))) void k_direct_part(int64_t n, const double* __restrict__ x,
                                                     const double* __restrict__ m,
                                                     const double* __restrict__ h, int64_t nt,
                                                     const int64_t* __restrict__ targets,
@@ -336,7 +340,10 @@ void launch_direct(int64_t n, const double* x, const double* m, const double* h,
   const int64_t chunk = ((tiles + nchunk - 1) / nchunk) * kDirTile;
   const int nc = (int)((n + chunk - 1) / chunk);
   const dim3 grid((unsigned)((nt + 63) / 64), (unsigned)nc);
-  k_direct_part<<<grid, 64, 0, s>>>(n, x, m, h, nt, targets, chunk, part, status);
+  if ((int64_t)grid.x * grid.y <= 4 * kDirSimds)
+    k_direct_part<4><<<grid, 64, 0, s>>>(n, x, m, h, nt, targets, chunk, part, status);
+  else
+    k_direct_part<5><<<grid, 64, 0, s>>>(n, x, m, h, nt, targets, chunk, part, status);
   k_direct_final<<<(unsigned)((nt + 255) / 256), 256, 0, s>>>(n, m, h, nt, targets, nc, part, G,
                                                                include_self, acc, pot);
 }
