@@ -5,7 +5,7 @@
 //
 // A wave takes 64 targets and a chunk of the sources: block (b, c) sums chunk
 // c for the targets of group b and writes its partial sums to a buffer
-// [chunk][target][4]; a second kernel adds each target's partials in chunk
+// [chunk][target][4]; a second kernel adds each target's partials in a fixed
 // order.  Pairs with j == i are skipped; unequal h are averaged as in P2P.
 // The summation order is fixed, so the result is reproducible.
 //
@@ -279,6 +279,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WAVES))) voi
   o[3] = ph + sh.acc[3][lane];
 }
 
+// Above kDirWide chunks, which few targets have, a wave per target (the chain of
+// loads of one thread set the time: 2e5 sources and 1, 1000, 5000 targets 67, 273,
+// 995 us; with a thread per target 483, 750, 1160).
+constexpr int kDirWide = 256;
+
 // per target: the chunks' partial sums in chunk order, the self term, -G
 __global__ void k_direct_final(int64_t n, const double* __restrict__ m,
                                const double* __restrict__ h, int64_t nt,
@@ -310,6 +315,43 @@ __global__ void k_direct_final(int64_t n, const double* __restrict__ m,
   acc[3 * t + 1] = -G * ay;
   acc[3 * t + 2] = -G * az;
   pot[t] = -G * ph;
+}
+
+// the same with a wave per target, for many chunks
+__global__ __launch_bounds__(64) void k_direct_final_wide(
+    int64_t n, const double* __restrict__ m, const double* __restrict__ h, int64_t nt,
+    const int64_t* __restrict__ targets, int nchunk, const double* __restrict__ part, double G,
+    int include_self, double* __restrict__ acc, double* __restrict__ pot) {
+  const int64_t t = blockIdx.x;
+  const int64_t it = targets ? targets[t] : t;
+  if (it < 0 || it >= n) return;
+  double v[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int c = threadIdx.x; c < nchunk; c += 256) {
+    double u[4][4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const double* p = part + ((int64_t)min(c + 64 * q, nchunk - 1) * nt + t) * 4;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) u[q][k] = p[k];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (c + 64 * q >= nchunk) break;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] += u[q][k];
+    }
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] += __shfl_xor(v[k], o, 64);
+  }
+  if (threadIdx.x != 0) return;
+  if (include_self) v[3] = fma(m[it], 1.4 * (1.0 / h[it]), v[3]);
+  acc[3 * t] = -G * v[0];
+  acc[3 * t + 1] = -G * v[1];
+  acc[3 * t + 2] = -G * v[2];
+  pot[t] = -G * v[3];
 }
 
 __global__ void k_clear_int(int* p) { *p = 0; }
@@ -344,8 +386,12 @@ void launch_direct(int64_t n, const double* x, const double* m, const double* h,
     k_direct_part<4><<<grid, 64, 0, s>>>(n, x, m, h, nt, targets, chunk, part, status);
   else
     k_direct_part<5><<<grid, 64, 0, s>>>(n, x, m, h, nt, targets, chunk, part, status);
-  k_direct_final<<<(unsigned)((nt + 255) / 256), 256, 0, s>>>(n, m, h, nt, targets, nc, part, G,
-                                                               include_self, acc, pot);
+  if (nc > kDirWide)
+    k_direct_final_wide<<<(unsigned)nt, 64, 0, s>>>(n, m, h, nt, targets, nc, part, G,
+                                                    include_self, acc, pot);
+  else
+    k_direct_final<<<(unsigned)((nt + 255) / 256), 256, 0, s>>>(n, m, h, nt, targets, nc, part, G,
+                                                                 include_self, acc, pot);
 }
 
 }  // namespace sfmm

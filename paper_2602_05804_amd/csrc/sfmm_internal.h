@@ -515,14 +515,14 @@ void launch_leapfrog(int64_t n, double* x, double* v, const double* acc, double 
 
 // softened direct sum over all n sources for nt targets (targets == nullptr:
 // 0..nt-1), the sources in nchunk chunks whose partial sums go to part
-// ([nchunk][nt][4] doubles) and are added per target in chunk order; *status
+// ([nchunk][nt][4] doubles) and are added per target in a fixed order; *status
 // is cleared first (by a kernel) and an out-of-range target index sets
 // ST_OVERFLOW in it
 void launch_direct(int64_t n, const double* x, const double* m, const double* h, int64_t nt,
                    const int64_t* targets, double G, int include_self, double* acc, double* pot,
                    int* status, double* part, int nchunk, hipStream_t s);
-// source chunks for nt targets: enough blocks to fill the chip, at most one
-// per tile of 256 sources and at most what max_part_bytes of partial sums
+// source chunks for nt targets: enough waves to fill the chip, at most one chunk
+// per tile of 64 sources and at most what max_part_bytes of partial sums
 // hold (0 when not even one chunk fits)
 int direct_chunks(int64_t n, int64_t nt, uint64_t max_part_bytes);
 

@@ -73,3 +73,25 @@ def test_chunks_met_in_place(torch, orc, n, nt, first):
     scale = np.maximum(np.linalg.norm(oa, axis=1), np.abs(op))  # (unit lengths)
     assert (np.linalg.norm(acc.cpu().numpy() - oa, axis=1) / scale).max() <= TOL
     assert (np.abs(pot.cpu().numpy() - op) / np.abs(op)).max() <= TOL
+
+
+@pytest.mark.parametrize("nt", [1, 2, 65])
+@pytest.mark.parametrize("n", [64 * 256, 64 * 256 + 1, 64 * 257 + 5, 64 * 600])
+def test_few_targets(torch, orc, n, nt):
+    """256 chunks and more: one thread, then one wave a target."""
+    import paper_2602_05804_amd as P
+
+    print(f"case: direct n {n} targets {nt}", flush=True)
+    g = np.random.default_rng(n)
+    x, m, h = g.standard_normal((n, 3)), g.random(n) + 0.5, np.full(n, 0.02)
+    tg = g.integers(0, n, nt)
+    s = P.Solver()
+    args = [torch.from_numpy(a).cuda() for a in (x, m, h)]
+    acc, pot = s.direct(*args, targets=torch.from_numpy(tg).cuda())
+    again, _ = s.direct(*args, targets=torch.from_numpy(tg).cuda())
+    assert torch.equal(acc, again)
+    oa, op = orc.direct(x, m, h, targets=tg.astype(np.int64))
+    assert (np.linalg.norm(acc.cpu().numpy() - oa, axis=1) / np.linalg.norm(oa, axis=1)).max() <= TOL
+    assert (np.abs(pot.cpu().numpy() - op) / np.abs(op)).max() <= TOL
+    with pytest.raises(P.SfmmError):
+        s.direct(*args, targets=torch.tensor([n]).cuda())
