@@ -17,6 +17,20 @@
 
 using namespace sfmm;
 
+namespace sfmm {
+// Work queued on s from now on waits for what is queued on aux.  If that cannot be
+// arranged, the host waits for aux: the next solve reuses its buffers on s.
+hipError_t join_streams(hipStream_t s, hipStream_t aux, hipEvent_t ev) {
+  hipError_t e = hipEventRecord(ev, aux);
+  if (e == hipSuccess) e = hipStreamWaitEvent(s, ev, 0);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();  // (returned here, not to the caller's next HIP call)
+    (void)hipStreamSynchronize(aux);
+  }
+  return e;
+}
+}  // namespace sfmm
+
 namespace {
 
 struct DevBuf {
@@ -916,13 +930,12 @@ int do_walk_and_eval(sfmm_ctx* ctx, double theta, int precision, const double* m
   km.begin = phase_event(ctx, 6, 0);
   km.end = phase_event(ctx, 6, 1);
   km.skip_reduce = overlap;
-  auto near_field = [&](hipStream_t ns) -> int {
+  auto near_field = [&](hipStream_t ns) {
     if (ctx->cfg.leaf_size <= 32)
       launch_p2p_items_fill(level, a, P<P2PItem>(ctx, B_ITEM), ns);
     if (f32) launch_near32(ctx->order, level, ctx->cfg.leaf_size, ctx->near_variant, a,
                           part32(ctx), items, ns, km);
     else launch_near(level, ctx->cfg.leaf_size, ctx->near_variant, a, items, ns, km);
-    return SFMM_OK;
   };
   auto far_field = [&]() {
     if (shared) {
@@ -977,19 +990,19 @@ int do_walk_and_eval(sfmm_ctx* ctx, double theta, int precision, const double* m
     HIPCHK(hipEventRecord(ctx->fork_ev, s));
     if (side == 2) far_field();
     HIPCHK(hipStreamWaitEvent(ctx->aux, ctx->fork_ev, 0));
-    if ((rc = near_field(ctx->aux))) return rc;
-    HIPCHK(hipEventRecord(ctx->join_ev, ctx->aux));
+    // (no return from here to the join)
+    near_field(ctx->aux);
     if (side == 1) far_field();
     phase_mark(ctx, 3, 1);
     phase_mark(ctx, 4, 0);
-    HIPCHK(hipStreamWaitEvent(s, ctx->join_ev, 0));
+    HIPCHK(join_streams(s, ctx->aux, ctx->join_ev));
     launch_p2p_reduce(a, p2p_leaf_slots(ctx->cfg.leaf_size), s);
     phase_mark(ctx, 4, 1);
   } else {
     far_field();
     phase_mark(ctx, 3, 1);
     phase_mark(ctx, 4, 0);
-    if ((rc = near_field(s))) return rc;
+    near_field(s);
     phase_mark(ctx, 4, 1);
   }
   phase_mark(ctx, 5, 0);
