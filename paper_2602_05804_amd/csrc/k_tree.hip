@@ -199,7 +199,9 @@ __global__ void k_gather(int n, const uint32_t* __restrict__ perm, const double*
   ms[i] = pm;
   hs[i] = ph;
   his[i] = phi;
-  h4[i] = 4.0 * ph * ph;
+  // (at least the smallest normal number: r^2 = 0, a particle with itself, is then
+  // below it for every h; pairs that close are evaluated one by one anyway)
+  h4[i] = fmax(4.0 * ph * ph, 0x1p-1022);
   pxy[i] = make_double2(px, py);
   pzm[i] = make_double2(pz, pm);
 }

@@ -78,3 +78,13 @@ def test_two_at_one_place(torch, P, orc, h):
         assert (np.abs(pot - want[1]) / np.abs(want[1]))[one].max() <= TOL
         own = -1.4 / h * np.array([m[41] + m[82], m[0] + m[82], m[0] + m[41]])
         assert np.abs(pot[[0, 41, 82]] / own - 1.0).max() <= TOL
+
+
+@pytest.mark.parametrize("near_kernel", [0, 6, 1])
+@pytest.mark.parametrize("h", [1e-162, 1e-200, 1e-300])
+def test_solve_where_h_squared_underflows(torch, P, orc, h, near_kernel):
+    print(f"case: solve, point masses of h {h}, shape {near_kernel}", flush=True)
+    x, m, hs = system(h)
+    s = P.Solver(include_self_potential=False, near_kernel=near_kernel)
+    got = s.solve(*(torch.from_numpy(a).cuda() for a in (x, m, hs)), theta=0.05)
+    check(got, orc.direct(x, m, hs, include_self=False))
