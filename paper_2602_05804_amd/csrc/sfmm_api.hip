@@ -285,8 +285,7 @@ int do_build(sfmm_ctx* ctx, int64_t n64, const double* x, const double* m, const
       {B_KPAR, sizeof(int32_t) * n}, {B_KSIDE, sizeof(int32_t) * n},
       {B_KEPT, sizeof(uint32_t) * (n + 1)},
       {B_LAT, sizeof(int32_t) * n},
-      {B_INFO, sizeof(NodeInfo) * nmax_nodes}, {B_REC, sizeof(double) * RS * (size_t)nmax_nodes},
-      {B_L2BITS, sizeof(uint64_t) * nmax_nodes},
+      {B_INFO, sizeof(NodeInfo) * nmax_nodes},
       {B_LEAFNODE, sizeof(int32_t) * n}, {B_LEAFDEPTH, sizeof(int32_t) * n},
       {B_PLEAF, sizeof(int32_t) * n},
   };
@@ -295,10 +294,6 @@ int do_build(sfmm_ctx* ctx, int64_t n64, const double* x, const double* m, const
   Readback* dev = P<Readback>(ctx, B_SMALL);
   int* status = dev->status;
   uint64_t* small = dev->small;
-  // (the shared far field reads its sources from records of their own)
-  const bool recq = ctx->cfg.far_mode == SFMM_FAR_SHARED && ctx->cfg.walk_mode == SFMM_WALK_LEVEL;
-  if (recq && (rc = ensure(ctx, B_RECQ, sizeof(double) * recq_stride(order) * (size_t)nmax_nodes)))
-    return rc;
   phase_mark(ctx, 0, 0);
   // ---- keys, sort, gather
   const uint32_t* sys_sorted = nullptr;
@@ -411,7 +406,11 @@ int do_build(sfmm_ctx* ctx, int64_t n64, const double* x, const double* m, const
   const int nn = (int)ctx->nn, nl = (int)ctx->nleaves;
   // node depths, nodes grouped by depth (level walk): one stable radix pass
   const uint32_t nkept = (uint32_t)(nn / 2);
+  const bool recq = ctx->cfg.far_mode == SFMM_FAR_SHARED && ctx->cfg.walk_mode == SFMM_WALK_LEVEL;
   struct { int id; size_t bytes; } need2[] = {
+      {B_REC, sizeof(double) * RS * (size_t)nn}, {B_L2BITS, sizeof(uint64_t) * nn},
+      // (the shared far field reads its sources from records of their own)
+      {B_RECQ, recq ? sizeof(double) * recq_stride(order) * (size_t)nn : 0},
       {B_NDEPTH, sizeof(int32_t) * nn}, {B_LEVNODES, sizeof(uint32_t) * nn},
       {B_LEVKEY0, sizeof(uint64_t) * nn}, {B_LEVKEY1, sizeof(uint64_t) * nn},
       {B_LEVIDS, sizeof(uint32_t) * nn}, {B_WREC, walk_rec_bytes(nn)},
