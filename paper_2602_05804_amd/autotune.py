@@ -1,5 +1,5 @@
-"""Autotuner for the solve's free parameters: leaf size, the P2P and
-P2P kernel shape and, in the FP32-compensated form, the depth above which
+"""Autotuner for the solve's free parameters: leaf size, the P2P kernel
+shape and, in the FP32-compensated form, the depth above which
 M2L stays in FP64.
 
 A coordinate search on the caller's (or a synthetic) input: each parameter in
@@ -24,9 +24,9 @@ import time
 from typing import Dict, Optional
 
 LEAF_SIZES = (6, 8, 10, 12, 16, 24, 32)
-# the P2P shapes of sfmm_config.near_kernel worth a try per precision (the
-# far field has one shape per mode)
-NEAR_KERNELS = {"fp64": (0, 13, 6), "fp32c": (0, 6, 7)}
+# the P2P shapes of sfmm_config.near_kernel worth a try per precision (in FP64,
+# 7 and 13 are shape 0; the far field has one shape per mode)
+NEAR_KERNELS = {"fp64": (0, 6), "fp32c": (0, 6, 7)}
 TOP_DEPTHS = (4, 8, 12, 128)  # 128: every M2L in FP64
 
 

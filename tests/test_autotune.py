@@ -111,3 +111,11 @@ def test_tune_buckets_one_search_per_bucket(monkeypatch):
     assert out == {1024: {"leaf_size": 8, "near_kernel": 0},
                    4096: {"leaf_size": 8, "near_kernel": 0},
                    65536: {"leaf_size": 12, "near_kernel": 0}}
+
+
+def test_no_kernel_is_tried_twice():
+    """In FP64, shapes 7 and 13 run the kernel of shape 0; in FP32C, 13 does."""
+    same = {"fp64": {7: 0, 13: 0}, "fp32c": {13: 0}}
+    for precision, shapes in autotune.NEAR_KERNELS.items():
+        run = [same[precision].get(k, k) for k in shapes]
+        assert len(set(run)) == len(run)
