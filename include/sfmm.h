@@ -128,7 +128,7 @@ typedef struct {
  *   1  one thread per particle (also every leaf_size > 32; SFMM_FP32C needs
  *      leaf_size <= 16).
  * The far field has one shape per mode: 8 lanes per node (SFMM_FAR_SHARED, two
- * waves per SIMD), 4 lanes per leaf (SFMM_FAR_LEAF). */
+ * waves per SIMD, one at order 4), 4 lanes per leaf (SFMM_FAR_LEAF). */
 
 /* Solve statistics of the last sfmm_solve on a context (host copy). */
 typedef struct {

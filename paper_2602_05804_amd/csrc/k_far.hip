@@ -420,7 +420,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WAVES))) voi
 // set -- node v's M2L list holds s exactly when s's holds v -- is evaluated
 // once, by the node with the smaller id, with one derivative tensor D(r) for
 // both directions (Exp<P>::m2l_pair): the owner's side is summed in
-// registers as in k_m2l_nodes, the partner's side is added to the partner's
+// registers as in k_m2l, the partner's side is added to the partner's
 // local coefficients with FP64 atomic adds, and the owner adds its own sum
 // last, also atomically.  ln must hold zeros before.  The order of the
 // atomic additions is not fixed, so results agree with the directed form to
@@ -616,8 +616,11 @@ void shared_order(const FarArgs& f, const SharedFarArgs& a, bool f32, hipStream_
     const int64_t per = (int64_t)a.window * kXcds;
     const unsigned nb = (unsigned)((a.n64 + 7) / 8 + (a.maxlong + 7) / 8 +
                                    (a.nn + per - 1) / per * per / 8);
-    if (f32) k_m2l<P, true, (P < 4 ? 2 : 1)><<<nb, 64, 0, s>>>(a);
-    else k_m2l<P, false, 2><<<nb, 64, 0, s>>>(a);
+    // two waves a SIMD; at order 4 the sums alone leave no room for a second (FP64,
+    // 1e6 particles: 4.6 ms a solve, with two waves and 82 spilled registers 6.9)
+    constexpr int WAVES = P < 4 ? 2 : 1;
+    if (f32) k_m2l<P, true, WAVES><<<nb, 64, 0, s>>>(a);
+    else k_m2l<P, false, WAVES><<<nb, 64, 0, s>>>(a);
   }
   if (f.nleaves > 0) k_far_shared<P><<<(unsigned)((f.nleaves + 63) / 64), 64, 64 * sizeof(int) * (f.maxdepth + 1), s>>>(f, a.ln);
 }
