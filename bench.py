@@ -151,8 +151,7 @@ def main():
                     help="leaf size of the headline solve (16: the autotuner's pick for the 1e6 "
                          "polytrope, 5.8 ms per solve against 6.1 at 10)")
     ap.add_argument("--near-kernel", type=int, default=13,
-                    help="P2P kernel shape of the headline solve (13, targets in lanes: the "
-                         "autotuner's pick at leaf size 16)")
+                    help="P2P kernel shape of the headline solve (13: the same kernel as 0)")
     ap.add_argument("--no-same-fp32c", dest="same_fp32c", action="store_false",
                     help="skip the FP32C solve of the headline workload (same input and leaf "
                          "size, its error measured over every particle by the CPU oracle)")

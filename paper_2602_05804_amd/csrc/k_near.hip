@@ -90,12 +90,7 @@ __global__ __launch_bounds__(256) void k_near(NearArgs a) {
   a.pot[o] = -G * (fr[3] + ph);
 }
 
-// the pool that the items' list entries lie in
-// ---- wave per target leaf ----------------------------------------------------
-// The leaf's particles (at most LS) are wave-uniform and held in registers;
-// the lanes walk the flattened list of source particles of the leaf's P2P
-// sources, 64 at a time, and each lane accumulates the field of its source on
-// every target.  A butterfly reduction then gives each target its total.
+// inclusive sum over the wave's lanes
 __device__ __forceinline__ int wave_incl_scan(int v) {
   const int lane = threadIdx.x & 63;
 #pragma unroll
@@ -112,9 +107,12 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
-// Targets in LDS, in passes of TG targets each, fully unrolled (static
-// accumulator indices; nt is the same on every lane, so the guard is a scalar
-// branch); the sources are read once per pass.  Pairs inside a kernel are not
+// ---- wave per work item, targets in LDS -----------------------------------------
+// The lanes walk the item's flattened source particles, 64 at a time, and each
+// accumulates the field of its source on every target; a butterfly reduction
+// then gives each target its total.  In passes of TG targets each, fully unrolled
+// (static accumulator indices; nt is the same on every lane, so the guard is a
+// scalar branch); the sources are read once per pass.  Pairs inside a kernel are not
 // evaluated in the wave's pass over the sources (where most lanes would idle
 // through the softening branch) but queued in LDS as (target, source); every
 // 64 queued pairs are evaluated together, one per lane, and added to the same
@@ -267,19 +265,18 @@ __global__ __launch_bounds__(64) void k_p2p_leaf(NearArgs a) {
   if (lane == 0) a.soft_pairs[item] = nsoft;
 }
 
-// Wave per item, targets held in scalar registers.  The same sums as
-// k_p2p_leaf with less work per pair: the loop control is wave-uniform
-// (scalar), the targets of a pass are wave-uniform values, a pair is inside
-// a kernel when r^2 < 4 h_i^2 or r^2 < 4 h_j^2, and the field of a pair
-// beyond both kernels is m/r^3 (dx, dy, dz) and m/r, with the refined 1/r
-// replaced by 0 for pairs inside a kernel (the self pair and coincident
-// particles included: r^2 = 0 is always inside).  Pairs inside a kernel,
-// other than the self pair, go to a queue per target in LDS and are
-// evaluated 64 at a time, each batch for one target (so its data stay
-// wave-uniform), after each group of 64 sources has met the pass's targets.
-// A leaf's targets are taken in as few passes of at most TG as they need, of
-// equal size within one, each with a fixed target count (no per-target exits
-// inside the unrolled loop).
+// ---- wave per work item, targets in scalar registers ------------------------------
+// The same sums as k_p2p_leaf with less work per pair: the loop control is
+// wave-uniform (scalar), the targets of a pass are wave-uniform values, a pair is
+// inside a kernel when r^2 < 4 h_i^2 or r^2 < 4 h_j^2, and the field of a pair
+// beyond both kernels is m/r^3 (dx, dy, dz) and m/r, with the refined 1/r replaced
+// by 0 for pairs inside a kernel (the self pair and coincident particles included:
+// r^2 = 0 is always inside).  Pairs inside a kernel, other than the self pair, go
+// to a queue per target in LDS.  When a queue might overflow, and at the end, the
+// queued pairs of all targets of the pass are shared out over the lanes
+// (p2p_wave_queued).  A leaf's targets are taken in as few passes of at most TG as
+// they need, of equal size within one, each with a fixed target count (no
+// per-target exits inside the unrolled loop).
 //
 // The item's sources (at most kP2PItem) are flattened once into LDS, as byte
 // offsets into the 16-byte particle arrays (so n < 2^28), padded to whole
@@ -289,11 +286,12 @@ __global__ __launch_bounds__(64) void k_p2p_leaf(NearArgs a) {
 // Bound: FP64 issue.  A pair takes 21 FP64-rate instructions of 4 cycles a
 // wave and one v_rsq_f64 of 16 (100 cycles for 64 pairs), so 1.76e9 pairs need
 // 1.3 ms at the 2.05 GHz the chip holds under this load.  Measured (Plummer
-// sphere of 1e6, 1.76e9 pairs, 3.5 % softened): 2.83 ms, before 3.84 ms; of
+// sphere of 1e6, 1.76e9 pairs, 3.5 % softened): 2.73 ms, before 3.84 ms; of
 // 9.95e8 VALU instructions (40 per 64 pairs) 23 are the pair's, the others the
 // queues, the softened pairs, list scans and reductions, and the VALU is busy
-// 77 % of the time.  Polytrope of 1e6 at leaf size 16: 1.95 ms, before 2.50.
-// the queued pairs of a pass, a lane's run of one target's (p2p_wave_queued)
+// 77 % of the time.  Polytrope of 1e6 at leaf size 16: 1.87 ms, before 2.50.
+
+// the queued pairs of a pass, a lane's run of one target's
 template <int K, int TG>
 __device__ __forceinline__ double p2p_wave_soft(const NearArgs& a, int t0p, WaveLds<TG>& sh,
                                                 uint32_t lens, uint32_t total) {

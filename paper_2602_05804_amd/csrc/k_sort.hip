@@ -5,16 +5,16 @@
 // over all passes, and for a single system computes the box and the keys as
 // well: one launch for the whole ordering.
 //
-// Otherwise one launch a pass.  The counts of every digit are known before
-// (digits do not change from pass to pass), so a block only lacks the counts
-// of the tiles before its own, which it takes from the words those publish: a
-// block takes its tile by ticket, publishes the tile's digit counts, then
-// walks back over the earlier tiles, adding counts until it meets one whose
-// inclusive sums are known, and publishes its own.  A tile's block has
-// started before any later tile's (the tickets), and it publishes its counts
-// before it waits, so every wait ends.  A word holds flag and count together;
-// words are read and written whole, with relaxed atomic accesses of agent
-// scope, and nothing else passes between blocks of a launch.
+// Otherwise one launch a pass, with decoupled look-back (Merrill and Garland
+// 2016).  The counts of every digit are known before (digits do not change from
+// pass to pass), so a block only lacks the counts of the tiles before its own,
+// which it takes from the words those publish: a block takes its tile by ticket,
+// publishes the tile's digit counts, then walks back over the earlier tiles,
+// adding counts until it meets one whose inclusive sums are known, and publishes
+// its own.  A tile's block has started before any later tile's (the tickets), and
+// it publishes its counts before it waits, so every wait ends.  A word holds flag
+// and count together; words are read and written whole, with relaxed atomic
+// accesses of agent scope, and nothing else passes between blocks of a launch.
 //
 // Bound by latency: of the look-back in tiles of 1024 (9 us a pass at 1e5
 // particles), of the scattered writes in tiles of 4096 (20 us at 1e6, where 24 B

@@ -565,7 +565,6 @@ int walk_levels(sfmm_ctx* ctx, double theta) {
   int rc;
   const hipStream_t s = ctx->stream;
   const int nn = (int)ctx->nn, nl = (int)ctx->nleaves;
-  uint64_t* small = P<Readback>(ctx, B_SMALL)->small;
   int* status = P<Readback>(ctx, B_SMALL)->status;
   const int node_arrays[] = {B_NM2LOFF, B_NM2LCNT, B_NOPENOFF, B_NOPENCNT, B_NP2POFF, B_NP2PCNT,
                              B_NEXP};
