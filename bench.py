@@ -148,8 +148,7 @@ def main():
     ap.add_argument("--theta", type=float, default=0.5)
     ap.add_argument("--order", type=int, default=3)
     ap.add_argument("--leaf-size", type=int, default=16,
-                    help="leaf size of the headline solve (16: the autotuner's pick for the 1e6 "
-                         "polytrope, 5.8 ms per solve against 6.1 at 10)")
+                    help="leaf size of the headline solve (16 and 10 take the same time)")
     ap.add_argument("--near-kernel", type=int, default=13,
                     help="P2P kernel shape of the headline solve (13: the same kernel as 0)")
     ap.add_argument("--no-same-fp32c", dest="same_fp32c", action="store_false",
