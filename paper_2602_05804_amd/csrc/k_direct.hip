@@ -16,7 +16,7 @@
 // kernel, all in place.  All pairs of 1e5 particles of a Plummer sphere (softening
 // lengths over four decades): 8.7 ms; 16.2 with the sources in LDS (six reads a
 // pair), a full 1/sqrt, and the softened pair in place, which nearly a tenth of
-// the steps took for one lane; 14.6 with only that left.  A polytrope of 1e5: 8.5 ms, 12.5 before.
+// the steps took for one lane; 14.6 with only that left.
 #include "sfmm_internal.h"
 #include "softening.h"
 
@@ -98,9 +98,8 @@ __device__ __forceinline__ void direct_flush(DirLds& sh, uint32_t at, uint32_t c
   const double w = on && j != i ? 0.5 * m[j] : 0.0;
   const double dx = tx - x[3 * j], dy = ty - x[3 * j + 1], dz = tz - x[3 * j + 2];
   const double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
-  const double rinv = rsqrt_refined(r2);
+  const double rinv = rsqrt_pair(r2), r = r2 * rinv;
   const bool apart = r2 > 0.0;  // (at one place no force, where h^-3 may overflow)
-  const double r = apart ? r2 * rinv : 0.0;
   // (outside both kernels, both pieces are 1/r^3 and 1/r)
   double g1, p1, g2, p2;
   soft_piece(sh.coef, r * hiinv, hiinv, rinv, g1, p1);
@@ -164,12 +163,10 @@ __device__ __forceinline__ void direct_all(const DirLds& sh, int64_t j0, int64_t
 // where no SIMD gets a fifth, whose registers need no spill (1e3 particles: 75 us
 // with four, 78 with five)
 template <int WAVES>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WAVES))) void k_direct_part(int64_t n, const double* __restrict__ x,
-                                                    const double* __restrict__ m,
-                                                    const double* __restrict__ h, int64_t nt,
-                                                    const int64_t* __restrict__ targets,
-                                                    int64_t chunk, double* __restrict__ part,
-                                                    int* status) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WAVES))) void k_direct_part(
+    int64_t n, const double* __restrict__ x, const double* __restrict__ m,
+    const double* __restrict__ h, int64_t nt, const int64_t* __restrict__ targets, int64_t chunk,
+    double* __restrict__ part, int* status) {
   __shared__ DirLds sh;
   const uint32_t lane = threadIdx.x;
   if (lane < sizeof(kSoftCoef) / sizeof(double))

@@ -319,11 +319,10 @@ __device__ __forceinline__ double p2p_wave_soft(const NearArgs& a, int t0p, Wave
       if (b + 1 < run) next = load(b + 1);
       const double dx = txy.x - sxy.x, dy = txy.y - sxy.y, dz = tzm.x - szm.x;
       const double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
-      const double rinv = rsqrt_refined(r2);
-      // (at one place no force, where h^-3 may overflow: so do lanes past the end,
-      // which hold the target itself)
+      const double rinv = rsqrt_pair(r2), r = r2 * rinv;
+      // (at one place no force, where h^-3 may overflow; lanes past the end hold the
+      // target itself)
       const bool apart = r2 > 0.0;
-      const double r = apart ? r2 * rinv : 0.0;
       double g1, p1, g2, p2;
       soft_piece(sh.coef, r * hiinv, hiinv, rinv, g1, p1);
       soft_piece(sh.coef, r * hjinv, hjinv, rinv, g2, p2);

@@ -81,7 +81,7 @@ __device__ __forceinline__ void soft_sel(double q, double hinv, double qi, doubl
 //   psi = u (w (d0 + q^2 (d2 + q (d3 + q (d4 + q d5)))) - dr)
 // for q < 1 (u = 1/h, w = 1), 1 <= q < 2 (u = 1/r, w = q) and q >= 2 (outside:
 // u = 1/r, all but cr and dr 0).  A lane reads its piece from LDS, which takes
-// fewer instructions than evaluating the pieces and selecting (24 against 38 a
+// fewer instructions than evaluating the pieces and selecting (25 against 38 a
 // kernel).  1/h counts for q < 1 only: h^-3 overflows where h is below 1e-103 (a
 // point mass inside another's kernel).
 struct alignas(16) SoftCoef {
@@ -93,7 +93,7 @@ struct alignas(16) SoftCoef {
      1.0 / 15.0, 0.0},
     {0.0, 0.0, 0.0, 0.0, -1.0, 0.0, 0.0, 0.0, 0.0, 0.0, -1.0, 0.0}};
 
-// g = f(q) / (q h^3) and psi(q) / h at q = r hinv, rinv = 1 / r (any value at r = 0)
+// g = f(q) / (q h^3) and psi(q) / h at q = r hinv, rinv = 1 / r (0 at r = 0)
 __device__ __forceinline__ void soft_piece(const SoftCoef* coef, double q, double hinv,
                                            double rinv, double& g, double& psi) {
   const bool core = q < 1.0;

@@ -88,3 +88,14 @@ def test_solve_where_h_squared_underflows(torch, P, orc, h, near_kernel):
     s = P.Solver(include_self_potential=False, near_kernel=near_kernel)
     got = s.solve(*(torch.from_numpy(a).cuda() for a in (x, m, hs)), theta=0.05)
     check(got, orc.direct(x, m, hs, include_self=False))
+
+
+def test_subnormal_softening_length(torch, P, orc):
+    """1/h is infinite: the potential without the particle's own share is not."""
+    print("case: point masses of subnormal h", flush=True)
+    x, m, hs = system(1e-310)
+    want = orc.direct(x, m, np.where(hs < 1.0, 1e-100, hs), include_self=False)  # (same pairs)
+    s = P.Solver(include_self_potential=False)
+    args = [torch.from_numpy(a).cuda() for a in (x, m, hs)]
+    check(s.direct(*args), want)
+    check(s.solve(*args, theta=0.05), want)
