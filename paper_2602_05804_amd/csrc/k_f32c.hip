@@ -291,7 +291,8 @@ __global__ __launch_bounds__(64) void k_p2p_leaf32(NearArgs a, Part32 p) {
         for (int ii = 0; ii < TG; ++ii) {
           const int i = t0 + ii;
           if (i >= nt) continue;
-          const float w = (j == tlo + i) ? 0.f : oj.w;
+          const bool self = j == tlo + i;  // (whose g may be infinite)
+          const float w = self ? 0.f : oj.w;
           const float thi = tg[i][3];
           const float dx = cx + (tg[i][0] - oj.x);
           const float dy = cy + (tg[i][1] - oj.y);
@@ -308,8 +309,8 @@ __global__ __launch_bounds__(64) void k_p2p_leaf32(NearArgs a, Part32 p) {
             soft32(r * thi, thi, tg[i][4] * rinv, rinv, rinv3, g1, p1);
             soft32(r * hj.hinv, hj.hinv, hj.h * rinv, rinv, rinv3, g2, p2);
             if (inside) {
-              gs = 0.5f * (g1 + g2);
-              ps = 0.5f * (p1 + p2);
+              gs = self ? 0.f : 0.5f * (g1 + g2);
+              ps = self ? 0.f : 0.5f * (p1 + p2);
             }
           }
           const float mg = w * gs;
@@ -420,12 +421,13 @@ __device__ __forceinline__ double p2p_wave32_soft(const Part32& p, const Centre3
       float g1, p1, g2, p2;
       soft32(r * hiinv, hiinv, hi * rinv, rinv, rinv3, g1, p1);
       soft32(r * s.czh.hinv, s.czh.hinv, s.czh.h * rinv, rinv, rinv3, g2, p2);
-      const float wm = act ? s.o.w : 0.f;
-      const float mg = wm * (0.5f * (g1 + g2));
+      // (an idle lane meets its target itself, whose g may be infinite)
+      const float mg = act ? s.o.w * (0.5f * (g1 + g2)) : 0.f;
+      const float mp = act ? s.o.w * (0.5f * (p1 + p2)) : 0.f;
       sx += (double)(mg * dx);
       sy += (double)(mg * dy);
       sz += (double)(mg * dz);
-      sp += (double)(wm * (0.5f * (p1 + p2)));
+      sp += (double)mp;
     }
     sum[0] = sx; sum[1] = sy; sum[2] = sz; sum[3] = sp;
   });
@@ -447,7 +449,7 @@ __device__ __forceinline__ void p2p_wave32_pass(const NearArgs& a, const Part32&
     ty[ii] = wave_uniform_f(o.y);
     tz[ii] = wave_uniform_f(o.z);
     const float hu = wave_uniform_f(p.czh[t0p + ii].h);
-    t4[ii] = 4.0f * hu * hu;
+    t4[ii] = fmaxf(4.0f * hu * hu, 0x1p-126f);  // (above 0: the self pair is inside)
     fx[ii] = Acc(); fy[ii] = Acc(); fz[ii] = Acc(); ph[ii] = Acc();
     qn[ii] = 0;
   }

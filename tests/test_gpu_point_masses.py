@@ -99,3 +99,19 @@ def test_subnormal_softening_length(torch, P, orc):
     args = [torch.from_numpy(a).cuda() for a in (x, m, hs)]
     check(s.direct(*args), want)
     check(s.solve(*args, theta=0.05), want)
+
+
+@pytest.mark.parametrize("near_kernel", [0, 6, 7, 13])
+@pytest.mark.parametrize("h", [1e-12, 1e-13, 1e-18, 1e-22, 1e-25, 1e-40])
+def test_solve_fp32(torch, P, orc, h, near_kernel):
+    """FP32 leaves: h^-3 overflows below 3e-13, h^2 underflows below 1e-23.  Bar: a
+    pair's offsets and its force are rounded a few times each at 6e-8."""
+    print(f"case: solve in FP32, point masses of h {h}, shape {near_kernel}", flush=True)
+    x, m, hs = system(h)
+    s = P.Solver(include_self_potential=False, near_kernel=near_kernel)
+    args = [torch.from_numpy(a).cuda() for a in (x, m, hs)]
+    acc, pot = (t.cpu().numpy() for t in s.solve(*args, theta=0.05, precision="fp32c"))
+    want = orc.direct(x, m, hs, include_self=False)
+    size = np.linalg.norm(want[0], axis=1)
+    assert (np.linalg.norm(acc - want[0], axis=1) / size).max() <= 1e-5
+    assert (np.abs(pot - want[1]) / np.abs(want[1])).max() <= 1e-5
